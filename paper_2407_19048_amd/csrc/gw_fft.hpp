@@ -2,9 +2,11 @@
 // each of NT = NC/16 threads holding 16 of them in registers.
 //
 // Structure: Stockham auto-sort radix-R passes (radix 16 first, then 16s,
-// then one 2/4/8 pass when NC is not a power of 16).  Data is exchanged
-// between passes through LDS, in separate real/imaginary planes padded (see
-// pad_at) so that each pass's reads and writes are free of bank conflicts.
+// then one 2/4/8 pass when NC is not a power of 16).  Inside a thread a pass
+// is a radix-2 decimation-in-time DFT whose butterflies carry the inter-pass
+// twiddles (see dit_fft).  Data is exchanged between passes through LDS, in
+// separate real/imaginary planes padded (see pad_at) so that each pass's
+// reads and writes are free of bank conflicts.
 //
 // Register layout of a thread t:
 //   before the first pass   v[r]     = x[t + NT*r]                (r < 16)
@@ -17,6 +19,9 @@
 namespace gw {
 
 template <class T> struct cpx { T x, y; };
+
+__device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
 template <class T> __device__ __forceinline__ cpx<T> cadd(cpx<T> a, cpx<T> b) { return {a.x + b.x, a.y + b.y}; }
 template <class T> __device__ __forceinline__ cpx<T> csub(cpx<T> a, cpx<T> b) { return {a.x - b.x, a.y - b.y}; }
@@ -190,11 +195,84 @@ template <int DIR, class T> __device__ __forceinline__ void dft16(cpx<T>* a) {
   t = a[11]; a[11] = a[14]; a[14] = t;
 }
 
-template <int R, int DIR, class T> __device__ __forceinline__ void dftR(cpx<T>* a) {
-  if constexpr (R == 16) dft16<DIR>(a);
-  else if constexpr (R == 8) dft8<DIR>(a);
-  else if constexpr (R == 4) dft4<DIR>(a);
-  else dft2<DIR>(a);
+// exp(-2 pi i q / 16) for q = 1, 2, 3 as (cosine, tangent)
+template <class T> __host__ __device__ constexpr cpx<T> root16(int q) {
+  return q == 1 ? cpx<T>{T(0.92387953251128675613), T(-0.41421356237309504880)}
+       : q == 2 ? cpx<T>{T(0.70710678118654752440), T(-1)}
+                : cpx<T>{T(0.38268343236508977173), T(-2.41421356237309504880)};
+}
+
+// Butterfly e, o -> e + w o, e - w o with w = c (1 + i t) given as {c, t}
+// (DIR = +1: with its conjugate), ROT: w further multiplied by DIR i.  Six
+// fused multiply-adds: u + i v = (1 + i t) o takes two, the two outputs four.
+template <int DIR, bool ROT, class T>
+__device__ __forceinline__ void bfly(cpx<T> e, cpx<T> o, cpx<T> w, cpx<T>& s, cpx<T>& d) {
+  const T t = DIR < 0 ? w.y : -w.y;
+  const T u = fma_t(-t, o.y, o.x), v = fma_t(t, o.x, o.y);
+  if constexpr (!ROT) {
+    s = {fma_t(w.x, u, e.x), fma_t(w.x, v, e.y)};
+    d = {fma_t(-w.x, u, e.x), fma_t(-w.x, v, e.y)};
+  } else {
+    constexpr T sg = T(-DIR);
+    s = {fma_t(sg * w.x, v, e.x), fma_t(-sg * w.x, u, e.y)};
+    d = {fma_t(-sg * w.x, v, e.x), fma_t(sg * w.x, u, e.y)};
+  }
+}
+
+// Stage of DFT length LEN of the radix-R DFT below: butterflies of the pairs
+// (q, q + LEN/2) of every run of LEN elements.
+template <int R, int LEN, int DIR, bool TW, class T>
+__device__ __forceinline__ void dit_stage(cpx<T>* b, const cpx<T>* w) {
+#pragma unroll
+  for (int g = 0; g < R; g += LEN)
+#pragma unroll
+    for (int q = 0; q < LEN / 2; ++q) {
+      const bool rot = LEN >= 4 && q >= LEN / 4;  // the twiddle of q - LEN/4 times DIR i
+      const int qq = rot ? q - LEN / 4 : q;
+      const cpx<T> e = b[g + q], o = b[g + q + LEN / 2];
+      cpx<T>&s = b[g + q], &d = b[g + q + LEN / 2];
+      if constexpr (TW) {
+        const cpx<T> ww = w[LEN == 2 ? 0 : LEN / 4 + qq];
+        if (rot) bfly<DIR, true>(e, o, ww, s, d);
+        else bfly<DIR, false>(e, o, ww, s, d);
+      } else if (qq == 0) {
+        const cpx<T> r = rot ? mul_i<DIR>(o) : o;
+        s = cadd(e, r);
+        d = csub(e, r);
+      } else {
+        const cpx<T> ww = root16<T>(qq * (16 / LEN));
+        if (rot) bfly<DIR, true>(e, o, ww, s, d);
+        else bfly<DIR, false>(e, o, ww, s, d);
+      }
+    }
+}
+
+template <int R> __host__ __device__ constexpr int bit_reverse(int i) {
+  int r = 0;
+  for (int b = 1; b < R; b <<= 1) r = 2 * r + ((i & b) ? 1 : 0);
+  return r;
+}
+
+// X[q] = sum_r W^r a[r] exp(DIR 2 pi i q r / R), in place, natural order in and
+// out; W = 1 (TW false) or the pass's twiddle.  Radix-2 decimation in time:
+// the stage of length LEN needs the twiddles W^(R/LEN) exp(-2 pi i q / LEN),
+// of which those with q >= LEN/4 are -i times the others, so that a radix-R
+// pass has R/2 distinct ones: w[0] for LEN = 2, w[LEN/4 + q] above, each as
+// {cosine, tangent}.  A radix-16 pass with its twiddles is 192 fused
+// multiply-adds, against 60 for multiplying 15 inputs by their twiddles plus
+// 160 for a 4 x 4 DFT, and keeps 8 twiddles instead of 15.  Its rounding error
+// is the same (two roundings per butterfly output instead of three, against a
+// twiddle whose tangent and cosine are each rounded).
+template <int R, int DIR, bool TW, class T> __device__ __forceinline__ void dit_fft(cpx<T>* a, const cpx<T>* w) {
+  cpx<T> b[R];
+#pragma unroll
+  for (int i = 0; i < R; ++i) b[i] = a[bit_reverse<R>(i)];
+  dit_stage<R, 2, DIR, TW>(b, w);
+  if constexpr (R >= 4) dit_stage<R, 4, DIR, TW>(b, w);
+  if constexpr (R >= 8) dit_stage<R, 8, DIR, TW>(b, w);
+  if constexpr (R >= 16) dit_stage<R, 16, DIR, TW>(b, w);
+#pragma unroll
+  for (int i = 0; i < R; ++i) a[i] = b[i];
 }
 
 // Radix plan: NP16 radix-16 passes and, when NC is not a power of 16, one
@@ -246,79 +324,77 @@ template <int NC, int ORD = 0> __device__ __forceinline__ int fft_out_index(int 
   return t + NT * (e / R) + (e % R) * (NC / R);
 }
 
-// Twiddle providers: return the forward twiddle exp(-2 pi i r k / (NS R)).
-// Table form: tw[n] = exp(-2 pi i n / NC).
-template <class T, int NC, int ORD = 0> struct TableTwiddle {
-  const cpx<T>* __restrict__ tw;
-  template <int PASS> __device__ __forceinline__ cpx<T> get(int m, int r, int k) const {
-    constexpr int R = PassInfo<NC, PASS, ORD>::R, NS = PassInfo<NC, PASS, ORD>::NS;
-    return tw[(r * k) * (NC / (NS * R))];
-  }
+// Pass twiddle tables of a plan, one block per pass after the first, in pass
+// order: for k < NS, the R/2 twiddles of dit_fft for W = exp(-2 pi i k / (NS R)),
+// stored [max(R/4, 1)][NS][min(R/2, 2)] so that a wavefront, whose lanes hold
+// consecutive k, reads consecutive entries of 8 or 16 bytes.  (The table
+// W^n in n order was gathered at strides of up to 8 entries instead.)
+template <int NC, int PASS, int ORD> struct PassTw {
+  static constexpr int R = PassInfo<NC, PASS, ORD>::R, NS = PassInfo<NC, PASS, ORD>::NS, NB = 16 / R;
+  static constexpr int G = R >= 4 ? 2 : 1;      // twiddles per table entry
+  static constexpr int NG = R / 2 / G;          // entries per butterfly
+  static constexpr int size = R / 2 * NS;       // cpx of the block
+};
+template <int NC, int PASS, int ORD> __host__ __device__ constexpr int pass_tw_offset() {
+  if constexpr (PASS <= 1) return 0;
+  else return pass_tw_offset<NC, PASS - 1, ORD>() + PassTw<NC, PASS - 1, ORD>::size;
+}
+// cpx of the tables of one order; the table of order 1 follows that of order 0
+template <int NC, int ORD> struct PlanTw {
+  static constexpr int size = pass_tw_offset<NC, FftPlan<NC>::NPASS, ORD>();
+  static constexpr int offset = ORD == 0 ? 0 : PlanTw<NC, 0>::size;
 };
 
-// Table form with fewer loads: per butterfly, W, W^2, W^4 and W^8 come from
-// the table and the other powers are products of at most three of them
-// (rounding error a few ulp).  Used where twiddle loads would otherwise
-// dominate the load count and register pressure.
-// block_fft requests each pass's table values during the pass before it
-// (Base, load), so that their latency is hidden behind that pass.
-template <class T, int NC, int ORD = 0> struct PowTwiddle {
-  const cpx<T>* __restrict__ tw;
-  // table values of one pass: per butterfly m, W^(2^l) for l < NL
-  template <int PASS> struct Base {
-    static constexpr int R = PassInfo<NC, PASS, ORD>::R, NS = PassInfo<NC, PASS, ORD>::NS, NB = 16 / R;
-    static constexpr int NL = (NS == 1) ? 0 : (R >= 16) ? 4 : (R >= 8) ? 3 : (R >= 4) ? 2 : 1;
-    cpx<T> b[NB][NL > 0 ? NL : 1];
-  };
-  template <int PASS> __device__ __forceinline__ Base<PASS> load(int t) const {
-    using B = Base<PASS>;
-    constexpr int NT = NC / 16, STEP = NC / (B::NS * B::R);
-    B q;
+// The 8 twiddles of a thread's 16/R butterflies in pass PASS.
+template <class T, int NC, int ORD> struct PassTwiddle {
+  const cpx<T>* __restrict__ tab;  // tables of both orders
+  template <int PASS> struct Regs { cpx<T> w[8]; };
+  template <int PASS> __device__ __forceinline__ Regs<PASS> load(int t) const {
+    using P = PassTw<NC, PASS, ORD>;
+    constexpr int NT = NC / 16;
+    const cpx<T>* p = tab + PlanTw<NC, ORD>::offset + pass_tw_offset<NC, PASS, ORD>();
+    Regs<PASS> q;
 #pragma unroll
-    for (int m = 0; m < B::NB; ++m) {
-      const int i1 = ((t + NT * m) & (B::NS - 1)) * STEP;
+    for (int m = 0; m < P::NB; ++m) {
+      const int k = (t + NT * m) & (P::NS - 1);
 #pragma unroll
-      for (int l = 0; l < B::NL; ++l) q.b[m][l] = tw[(1 << l) * i1];
+      for (int g = 0; g < P::NG; ++g) {
+        struct alignas(sizeof(cpx<T>) * P::G) Entry { cpx<T> e[P::G]; };
+        const Entry v = reinterpret_cast<const Entry*>(p)[g * P::NS + k];
+#pragma unroll
+        for (int i = 0; i < P::G; ++i) q.w[m * (P::R / 2) + g * P::G + i] = v.e[i];
+      }
     }
     return q;
   }
-  // powers W^1 .. W^(R-1) from W, W^2, W^4, W^8
-  template <int R> __device__ static __forceinline__ void expand(const cpx<T>* b, cpx<T>* w) {
-    w[1] = b[0];
-    if constexpr (R >= 4) {
-      w[2] = b[1];
-      w[3] = cmul(w[2], w[1]);
-    }
-    if constexpr (R >= 8) {
-      w[4] = b[2];
-      w[5] = cmul(w[4], w[1]);
-      w[6] = cmul(w[4], w[2]);
-      w[7] = cmul(w[6], w[1]);
-    }
-    if constexpr (R >= 16) {
-      w[8] = b[3];
-      w[9] = cmul(w[8], w[1]);
-      w[10] = cmul(w[8], w[2]);
-      w[11] = cmul(w[10], w[1]);
-      w[12] = cmul(w[8], w[4]);
-      w[13] = cmul(w[12], w[1]);
-      w[14] = cmul(w[12], w[2]);
-      w[15] = cmul(w[14], w[1]);
-    }
-  }
 };
 
-template <class TW> struct TwiddleIsPow { static constexpr bool value = false; };
-template <class T, int NC, int ORD> struct TwiddleIsPow<PowTwiddle<T, NC, ORD>> { static constexpr bool value = true; };
+// All passes' twiddles held in registers (many transforms per thread).
+template <class T, int NC, int ORD> struct HeldTwiddle {
+  using Src = PassTwiddle<T, NC, ORD>;
+  typename Src::template Regs<1> w1;
+  typename Src::template Regs<2> w2;
+  typename Src::template Regs<FftPlan<NC>::NPASS == 4 ? 3 : 2> w3;
+  __device__ __forceinline__ void init(const cpx<T>* tab, int t) {
+    const Src s{tab};
+    w1 = s.template load<1>(t);
+    w2 = s.template load<2>(t);
+    if constexpr (FftPlan<NC>::NPASS == 4) w3 = s.template load<3>(t);
+  }
+  template <int PASS> __device__ __forceinline__ const auto& load(int) const {
+    if constexpr (PASS == 1) return w1;
+    else if constexpr (PASS == 2) return w2;
+    else return w3;
+  }
+};
 
 // One Stockham pass.  READ: take input from LDS (else registers already hold
 // it).  WRITE: scatter the output to LDS (else it stays in registers in the
 // final layout).  A barrier separates this pass's LDS reads from its writes;
 // the caller must ensure the LDS buffer is free before a pass that WRITEs
-// without READing.  pre: the pass's PowTwiddle table values, already loaded.
-template <class T, int NC, int PASS, int DIR, bool READ, bool WRITE, int ORD, class TW>
-__device__ __forceinline__ void fft_pass(cpx<T>* v, T* sre, T* sim, int t, const TW& tw,
-                                         const cpx<T>* pre = nullptr) {
+// without READing.  w: the pass's 8 twiddles (unused in pass 0).
+template <class T, int NC, int PASS, int DIR, bool READ, bool WRITE, int ORD>
+__device__ __forceinline__ void fft_pass(cpx<T>* v, T* sre, T* sim, int t, const cpx<T>* w) {
   constexpr int R = PassInfo<NC, PASS, ORD>::R, NS = PassInfo<NC, PASS, ORD>::NS;
   constexpr int NT = NC / 16, NB = 16 / R, STRIDE = NC / R;
   // layout of the buffer read: written by the previous pass, or natural order
@@ -336,22 +412,7 @@ __device__ __forceinline__ void fft_pass(cpx<T>* v, T* sre, T* sim, int t, const
     }
   }
 #pragma unroll
-  for (int m = 0; m < NB; ++m) {
-    const int j = t + NT * m;
-    if constexpr (NS > 1) {
-      const int k = j & (NS - 1);
-      if constexpr (TwiddleIsPow<TW>::value) {
-        cpx<T> w[R];
-        TW::template expand<R>(pre + m * TW::template Base<PASS>::NL, w);
-#pragma unroll
-        for (int r = 1; r < R; ++r) v[m * R + r] = twmul<DIR>(v[m * R + r], w[r]);
-      } else {
-#pragma unroll
-        for (int r = 1; r < R; ++r) v[m * R + r] = twmul<DIR>(v[m * R + r], tw.template get<PASS>(m, r, k));
-      }
-    }
-    dftR<R, DIR>(v + m * R);
-  }
+  for (int m = 0; m < NB; ++m) dit_fft<R, DIR, (NS > 1)>(v + m * R, w + m * (R / 2));
   if constexpr (WRITE) {
     if constexpr (READ) lds_barrier();
 #pragma unroll
@@ -374,32 +435,20 @@ __device__ __forceinline__ void fft_pass(cpx<T>* v, T* sre, T* sim, int t, const
 // in natural order (else v holds it: x[t + NT j] in slot fft_in_slot(j)).
 // The result stays in registers in the final layout (see fft_out_index).
 // Ends with LDS still being read by other threads: barrier before reusing it.
+// Each pass's twiddles are requested before the pass ahead of it, so that
+// their latency is hidden behind that pass.
 template <class T, int NC, int DIR, bool FIRST_FROM_LDS, int ORD = 0, class TW>
 __device__ __forceinline__ void block_fft(cpx<T>* v, T* sre, T* sim, int t, const TW& tw) {
-  using P = FftPlan<NC>;
-  if constexpr (TwiddleIsPow<TW>::value) {
-    // each pass's table values are requested before the pass ahead of it
-    const auto b1 = tw.template load<1>(t);
-    fft_pass<T, NC, 0, DIR, FIRST_FROM_LDS, true, ORD>(v, sre, sim, t, tw);
-    const auto b2 = tw.template load<2>(t);
-    fft_pass<T, NC, 1, DIR, true, true, ORD>(v, sre, sim, t, tw, &b1.b[0][0]);
-    if constexpr (P::NPASS == 3) {
-      fft_pass<T, NC, 2, DIR, true, false, ORD>(v, sre, sim, t, tw, &b2.b[0][0]);
-    } else {
-      const auto b3 = tw.template load<3>(t);
-      fft_pass<T, NC, 2, DIR, true, true, ORD>(v, sre, sim, t, tw, &b2.b[0][0]);
-      fft_pass<T, NC, 3, DIR, true, false, ORD>(v, sre, sim, t, tw, &b3.b[0][0]);
-    }
+  const auto w1 = tw.template load<1>(t);
+  fft_pass<T, NC, 0, DIR, FIRST_FROM_LDS, true, ORD>(v, sre, sim, t, w1.w);
+  const auto w2 = tw.template load<2>(t);
+  fft_pass<T, NC, 1, DIR, true, true, ORD>(v, sre, sim, t, w1.w);
+  if constexpr (FftPlan<NC>::NPASS == 3) {
+    fft_pass<T, NC, 2, DIR, true, false, ORD>(v, sre, sim, t, w2.w);
   } else {
-    fft_pass<T, NC, 0, DIR, FIRST_FROM_LDS, true, ORD>(v, sre, sim, t, tw);
-    if constexpr (P::NPASS == 3) {
-      fft_pass<T, NC, 1, DIR, true, true, ORD>(v, sre, sim, t, tw);
-      fft_pass<T, NC, 2, DIR, true, false, ORD>(v, sre, sim, t, tw);
-    } else {
-      fft_pass<T, NC, 1, DIR, true, true, ORD>(v, sre, sim, t, tw);
-      fft_pass<T, NC, 2, DIR, true, true, ORD>(v, sre, sim, t, tw);
-      fft_pass<T, NC, 3, DIR, true, false, ORD>(v, sre, sim, t, tw);
-    }
+    const auto w3 = tw.template load<3>(t);
+    fft_pass<T, NC, 2, DIR, true, true, ORD>(v, sre, sim, t, w2.w);
+    fft_pass<T, NC, 3, DIR, true, false, ORD>(v, sre, sim, t, w3.w);
   }
 }
 

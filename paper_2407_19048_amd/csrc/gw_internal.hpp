@@ -2,9 +2,12 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <functional>
 #include <string>
+#include <vector>
 
+#include "gw_fft.hpp"
 #include "gw_physics.hpp"
 #include "../../include/gwgen.h"
 
@@ -14,9 +17,9 @@ struct gw_ctx {
   double* kcbrt = nullptr;    // [F]  k^(1/3)
   double* lnk3 = nullptr;     // [F]  ln(k)/3
   double* k53 = nullptr;      // [F]  k^(-5/3) (0 at k = 0)
-  void* tw_win = nullptr;     // cpx<T>[N/2]
+  void* tw_win = nullptr;     // pass twiddle tables of the window (or row) transform, both orders
   void* twr_win = nullptr;    // cpx<T>[N/4 + 1]
-  void* tw_welch = nullptr;   // cpx<T>[L]
+  void* tw_welch = nullptr;   // pass twiddle tables of the L-point transform, both orders
   void* tw_long = nullptr;    // cpx<float>[N2][N1]: W_NC^(m1 k2), windows longer than 32768 samples
   // windows longer than 32768 samples: k^(1/3), ln(k)/3 (double[N/2] each) and
   // exp(-2 pi i k / N) (cpx<float>[N/2]) for k < N/2, stored at the position
@@ -51,4 +54,55 @@ gw_status ctx_check_launch(gw_ctx* c, const char* what);
 gw_status validate_config(const gw_config* g, DevCfg* dc, std::string* why);
 gw_status capture_graph(const std::function<gw_status(hipStream_t)>& enqueue, uint64_t* batch, uint64_t first,
                         gw_graph** out, std::string* why);
+
+// {cosine, tangent} of the angle -2 pi num / den, 0 <= num <= den / 2.  At the
+// quarter turn, where the tangent has no value, the cosine is set to 2^-28
+// (binary32) or 2^-56: a quarter of a unit in the last place of the sine, and
+// still far from overflow when a value is multiplied by the tangent.
+template <class T>
+inline cpx<T> tan_twiddle(int64_t num, int64_t den) {
+  if (4 * num == den) {
+    const T tiny = sizeof(T) == 4 ? T(0x1p-28) : T(0x1p-56);
+    return {tiny, T(-1) / tiny};
+  }
+  const double ang = -2.0 * M_PI * double(num) / double(den);
+  return {T(std::cos(ang)), T(std::tan(ang))};
+}
+
+template <class T, int NC, int ORD, int PASS>
+inline void append_pass_table(std::vector<cpx<T>>& h) {
+  if constexpr (PASS < FftPlan<NC>::NPASS) {
+    using P = PassTw<NC, PASS, ORD>;
+    const size_t at = h.size();
+    h.resize(at + P::size);
+    for (int k = 0; k < P::NS; ++k)
+      for (int len = 2; len <= P::R; len *= 2)
+        for (int q = 0; q < (len >= 4 ? len / 4 : 1); ++q) {
+          // W^(R/len) exp(-2 pi i q / len), W = exp(-2 pi i k / (NS R))
+          const int i = len == 2 ? 0 : len / 4 + q;
+          h[at + (size_t(i / P::G) * P::NS + k) * P::G + i % P::G] =
+              tan_twiddle<T>(int64_t(k) + int64_t(q) * P::NS, int64_t(P::NS) * len);
+        }
+    append_pass_table<T, NC, ORD, PASS + 1>(h);
+  }
+}
+
+// Pass twiddle tables of an nc-point transform (see PassTw), order 0 then 1.
+template <class T, int NC>
+inline std::vector<cpx<T>> plan_tables_of() {
+  std::vector<cpx<T>> h;
+  append_pass_table<T, NC, 0, 1>(h);
+  append_pass_table<T, NC, 1, 1>(h);
+  return h;
+}
+template <class T>
+inline std::vector<cpx<T>> plan_tables(int nc) {
+  switch (nc) {
+    case 1024: return plan_tables_of<T, 1024>();
+    case 2048: return plan_tables_of<T, 2048>();
+    case 4096: return plan_tables_of<T, 4096>();
+    case 8192: return plan_tables_of<T, 8192>();
+    default: return plan_tables_of<T, 16384>();
+  }
+}
 }  // namespace gw

@@ -108,7 +108,7 @@ struct WinArgs {
   const double* kcbrt;
   const double* lnk3;
   const double* k53;      // k^(-5/3) (SRC 3)
-  const void* tw;         // cpx<T>[N/2], exp(-2 pi i n / (N/2))
+  const void* tw;         // pass twiddle tables of the N/2-point transform
   const void* twr;        // cpx<T>[N/4 + 1], exp(-2 pi i k / N)
   const WfScalars* wf;    // [B] (SRC 1, 3)
   const DetScalars* dsc;  // [B][D] (SRC 1, 3)
@@ -256,7 +256,7 @@ __device__ __forceinline__ void window_item(const DevCfg& cf, const WinArgs& a, 
   constexpr int NT = NC / 16;
   static_assert(SRC >= 0 && SRC <= 5, "source");
   constexpr bool SIG = SRC == 1 || SRC == 5;  // in-register plain-model signal
-  PowTwiddle<T, NC, ORD> tw{twtab};
+  PassTwiddle<T, NC, ORD> tw{twtab};
   if constexpr (SRC == 3) {
     // the sample's node values go to LDS once (snodes: 2 x 1024 floats of
     // LDS); the barriers of the forward transform below make them visible to
@@ -437,7 +437,7 @@ __device__ __forceinline__ void window_item(const DevCfg& cf, const WinArgs& a, 
     store_pair(NC / 2, zk, zm);
   }
   lds_barrier();
-  block_fft<T, NC, +1, true, ORD>(v, sre, sim, fresh_lane(t), PowTwiddle<T, NC, ORD>{opaque(twtab)});
+  block_fft<T, NC, +1, true, ORD>(v, sre, sim, fresh_lane(t), PassTwiddle<T, NC, ORD>{opaque(twtab)});
   const T sc = T(1) / T(NC);
   if (active) {
 #pragma unroll
@@ -476,31 +476,6 @@ __device__ __forceinline__ void window_item(const DevCfg& cf, const WinArgs& a, 
   if (active && flag) atomicOr(sflag, flag);
 }
 
-__device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
-
-// Twiddles of passes 1.. kept in registers for the whole segment loop.
-template <class T, int NC, int ORD> struct RegTwiddle {
-  cpx<T> p[FftPlan<NC>::NPASS][16];
-  __device__ __forceinline__ void init(const cpx<T>* __restrict__ tab, int t) {
-    init_pass<1>(tab, t);
-    init_pass<2>(tab, t);
-    if constexpr (FftPlan<NC>::NPASS == 4) init_pass<3>(tab, t);
-  }
-  template <int PASS> __device__ __forceinline__ void init_pass(const cpx<T>* __restrict__ tab, int t) {
-    constexpr int R = PassInfo<NC, PASS, ORD>::R, NS = PassInfo<NC, PASS, ORD>::NS, NT = NC / 16;
-#pragma unroll
-    for (int m = 0; m < 16 / R; ++m) {
-      const int k = (t + NT * m) & (NS - 1);
-#pragma unroll
-      for (int r = 0; r < R; ++r) p[PASS][m * R + r] = tab[(r * k) * (NC / (NS * R))];
-    }
-  }
-  template <int PASS> __device__ __forceinline__ cpx<T> get(int m, int r, int) const {
-    return p[PASS][m * PassInfo<NC, PASS, ORD>::R + r];
-  }
-};
-
 // Welch PSD of one (sample, detector) stretch x = background + o, by the
 // NC/16 threads t of a (sub-)block: K periodic-Hann segments of L = NC samples
 // at stride L/2.  Segments 2p and 2p+1 go through ONE complex FFT as real and
@@ -525,7 +500,7 @@ __device__ __forceinline__ void welch_item(int K, double norm, int t, const floa
     const T sp = sinpi_t(T(t + NT * r) / T(NC));
     w[r] = sp * sp;
   }
-  RegTwiddle<T, NC, ORD> tw;
+  HeldTwiddle<T, NC, ORD> tw;
   tw.init(twtab, t);
   constexpr bool kWide = sizeof(ACC) > sizeof(T);
   constexpr int kWelchRun = 16;

@@ -69,7 +69,7 @@ struct LongArgs {
   WinArgs w;           // cf, tables, per-sample data, psd, status; out = the in-place buffer
   const void* twc;     // cpx<float>[N2][N1]: exp(-2 pi i m1 k2 / NC) at [k2][m1]
   const void* twr;     // cpx<float>[NC/2 + 1]: exp(-2 pi i k / N)
-  const void* tw1;     // cpx<float>[N1]: exp(-2 pi i n / N1)
+  const void* tw1;     // pass twiddle tables of the N1-point transform
   const float* x;      // real input of the forward columns (strain rows or the background)
   int NC, N2, l2n2;    // NC = N1 N2, l2n2 = log2(N2)
   // bin tables in the transposed layout (bin k at (k mod N2) N1 + k / N2):
@@ -149,7 +149,7 @@ __global__ __launch_bounds__(N1 / 16, kRowWaves) void k_long_rows(LongArgs a) {
   __shared__ float lds[2 * LS];
   const int t = threadIdx.x;
   float2* row = reinterpret_cast<float2*>(a.w.out) + int64_t(blockIdx.x) * N1;
-  PowTwiddle<float, N1, 0> tw{reinterpret_cast<const cpx<float>*>(a.tw1)};
+  PassTwiddle<float, N1, 0> tw{reinterpret_cast<const cpx<float>*>(a.tw1)};
   cpx<float> v[16];
 #pragma unroll
   for (int j = 0; j < 16; ++j) {
@@ -378,7 +378,7 @@ __global__ __launch_bounds__(N1 / 16, kRowWaves) void k_long_rowpair(LongArgs a)
   const float* psd = a.w.psd + bd * cf.Fw;
   const cpx<float>* tw1 = reinterpret_cast<const cpx<float>*>(a.tw1);
   // a fresh table pointer per transform (see opaque)
-  auto tw = [&]() { return PowTwiddle<float, N1, 0>{opaque(tw1)}; };
+  auto tw = [&]() { return PassTwiddle<float, N1, 0>{opaque(tw1)}; };
   if (t == 0) sflag = 0u;
   float cpl = 0.f, cxx = 0.f;
   double tauT = 0.0;

@@ -58,7 +58,7 @@ struct gw_ragged {
   int32_t* d_vitems = nullptr;
   double* kcbrt = nullptr;
   double* lnk3 = nullptr;
-  void* tw[4] = {nullptr, nullptr, nullptr, nullptr};   // exp(-2 pi i n / M), M = 2048 << s
+  void* tw[4] = {nullptr, nullptr, nullptr, nullptr};   // pass twiddle tables of M points, M = 2048 << s
   void* twr[4] = {nullptr, nullptr, nullptr, nullptr};  // exp(-2 pi i k / 2M), k <= M/2
   int n_cu = 256;
   int ord_win = 0, ord_welch = 0, grid_win = 1, grid_welch = 2;
@@ -643,7 +643,7 @@ gw_status gw_ragged_create(const gw_config* classes, int32_t n_classes, const in
             upload(reinterpret_cast<void**>(&r->kcbrt), hc) && upload(reinterpret_cast<void**>(&r->lnk3), hl);
   for (int k = 0; k < 4 && ok; ++k) {
     const int M = 2048 << k;
-    if (need_tw[k]) ok = upload(&r->tw[k], twiddles(M, M));
+    if (need_tw[k]) ok = upload(&r->tw[k], plan_tables<float>(M));
     if (ok && need_twr[k]) ok = upload(&r->twr[k], twiddles(M / 2 + 1, 2 * M));
   }
   if (!ok) return bail(GW_ENOMEM);

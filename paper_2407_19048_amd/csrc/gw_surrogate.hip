@@ -833,7 +833,7 @@ struct MismatchMaxArgs {
   const float* psd;                  // [F]
   int64_t B; int F; int kmin; double df;
   const double* params;              // for f_cut (IMR-form), may be NULL
-  const cpx<float>* tw;              // exp(-2 pi i n / NC)
+  const cpx<float>* tw;              // pass twiddle tables of the NC-point transform
   double* mm;
 };
 
@@ -909,7 +909,7 @@ __global__ __launch_bounds__(NC / 16) void k_mismatch_max(MismatchMaxArgs a) {
   };
   // coarse maximum over the NC integer shifts
   __syncthreads();
-  block_fft<float, NC, +1, false, 0>(v, lds, lds + LS, t, PowTwiddle<float, NC, 0>{a.tw});
+  block_fft<float, NC, +1, false, 0>(v, lds, lds + LS, t, PassTwiddle<float, NC, 0>{a.tw});
   float best = -1.f;
   int bi = 0;
 #pragma unroll

@@ -184,7 +184,7 @@ struct WelchArgs {
   int64_t L_bg;
   const int64_t* offset;
   float* psd;
-  const void* tw;  // cpx<T>[L], exp(-2 pi i n / L)
+  const void* tw;  // pass twiddle tables of the L-point transform
   double norm;     // 1 / (K fs sum w^2)
 };
 
@@ -241,7 +241,7 @@ struct FiltArgs {
   const float* psd;  // [D][Fw]
   float* filt;       // [D][NC + 1]
   int M;
-  const void* tw;    // cpx<T>[NC]
+  const void* tw;    // pass twiddle tables of the NC-point transform
   const void* twr;   // cpx<T>[NC/2 + 1]
   uint32_t* status;  // [D] GW_STATUS_* bits of each detector's PSD, or NULL
 };
@@ -257,7 +257,7 @@ __global__ __launch_bounds__(NC / 16) void k_filter(FiltArgs a) {
   const DevCfg& cf = a.cf;
   const float* psd = a.psd + int64_t(d) * cf.Fw;
   const cpx<T>* twr = reinterpret_cast<const cpx<T>*>(a.twr);
-  PowTwiddle<T, NC, 0> tw{reinterpret_cast<const cpx<T>*>(a.tw)};
+  PassTwiddle<T, NC, 0> tw{reinterpret_cast<const cpx<T>*>(a.tw)};
   uint32_t flag = 0;
   __shared__ uint32_t dflag;  // the detector's status bits (visible after the first barrier)
   if (t == 0) dflag = 0u;
@@ -458,16 +458,22 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 bool aligned4(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 3u) == 0; }
 
 template <class T>
-gw_status upload_twiddles(gw_ctx* c, void** dst, int n, int denom) {
-  std::vector<cpx<T>> h(n);
-  for (int i = 0; i < n; ++i) {
+gw_status upload_cpx(gw_ctx* c, void** dst, const std::vector<cpx<T>>& h) {
+  if (hipMalloc(dst, sizeof(cpx<T>) * h.size()) != hipSuccess) return fail(c, GW_ENOMEM, "hipMalloc twiddles");
+  if (hipMemcpy(*dst, h.data(), sizeof(cpx<T>) * h.size(), hipMemcpyHostToDevice) != hipSuccess)
+    return fail(c, GW_EHIP, "hipMemcpy twiddles");
+  return GW_OK;
+}
+
+// exp(-2 pi i n / denom), n < count
+template <class T>
+gw_status upload_twiddles(gw_ctx* c, void** dst, int count, int denom) {
+  std::vector<cpx<T>> h(count);
+  for (int i = 0; i < count; ++i) {
     const double ang = -2.0 * M_PI * double(i) / double(denom);
     h[i] = {T(std::cos(ang)), T(std::sin(ang))};
   }
-  if (hipMalloc(dst, sizeof(cpx<T>) * n) != hipSuccess) return fail(c, GW_ENOMEM, "hipMalloc twiddles");
-  if (hipMemcpy(*dst, h.data(), sizeof(cpx<T>) * n, hipMemcpyHostToDevice) != hipSuccess)
-    return fail(c, GW_EHIP, "hipMemcpy twiddles");
-  return GW_OK;
+  return upload_cpx(c, dst, h);
 }
 
 // Per-bin tables of the long-window bins pass in the transposed layout of
@@ -878,15 +884,15 @@ gw_status gw_create(const gw_config* cfg, gw_ctx** out) {
   }
   const int NC = dc.N / 2;
   if (dc.precision == 2) {
-    s = upload_twiddles<double>(c, &c->tw_win, NC, NC);
+    s = upload_cpx(c, &c->tw_win, plan_tables<double>(NC));
     if (s == GW_OK) s = upload_twiddles<double>(c, &c->twr_win, NC / 2 + 1, dc.N);
-    if (s == GW_OK) s = upload_twiddles<double>(c, &c->tw_welch, dc.L, dc.L);
+    if (s == GW_OK) s = upload_cpx(c, &c->tw_welch, plan_tables<double>(dc.L));
   } else {
     // windows longer than 32768 samples transform rows of N1 (four-step)
     const int NCt = NC > 16384 ? long_row_length(NC) : NC;
-    s = upload_twiddles<float>(c, &c->tw_win, NCt, NCt);
+    s = upload_cpx(c, &c->tw_win, plan_tables<float>(NCt));
     if (s == GW_OK) s = upload_twiddles<float>(c, &c->twr_win, NC / 2 + 1, dc.N);
-    if (s == GW_OK) s = upload_twiddles<float>(c, &c->tw_welch, dc.L, dc.L);
+    if (s == GW_OK) s = upload_cpx(c, &c->tw_welch, plan_tables<float>(dc.L));
     if (s == GW_OK && NC > 16384) s = upload_long_tables(c, NC);
   }
   if (s != GW_OK) {
