@@ -19,7 +19,7 @@ struct gw_ctx {
   double* k53 = nullptr;      // [F]  k^(-5/3) (0 at k = 0)
   void* tw_win = nullptr;     // pass twiddle tables of the window (or row) transform, both orders
   void* twr_win = nullptr;    // cpx<T>[N/4 + 1]
-  void* tw_welch = nullptr;   // pass twiddle tables of the L-point transform, both orders
+  void* tw_welch = nullptr;   // Welch table of L (WelchTab)
   void* tw_long = nullptr;    // cpx<float>[N2][N1]: W_NC^(m1 k2), windows longer than 32768 samples
   // windows longer than 32768 samples: k^(1/3), ln(k)/3 (double[N/2] each) and
   // exp(-2 pi i k / N) (cpx<float>[N/2]) for k < N/2, stored at the position
@@ -104,5 +104,17 @@ inline std::vector<cpx<T>> plan_tables(int nc) {
     case 8192: return plan_tables_of<T, 8192>();
     default: return plan_tables_of<T, 16384>();
   }
+}
+
+// The Welch table of L = l (WelchTab): pass twiddles, the window's first half.
+template <class T>
+inline std::vector<cpx<T>> welch_tables(int l) {
+  std::vector<cpx<T>> h = plan_tables<T>(l);
+  auto hann = [&](int n) {
+    const double sp = std::sin(M_PI * double(n) / double(l));
+    return T(sp * sp);
+  };
+  for (int n = 0; n < l / 2; n += 2) h.push_back({hann(n), hann(n + 1)});
+  return h;
 }
 }  // namespace gw

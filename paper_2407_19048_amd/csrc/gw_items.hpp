@@ -476,50 +476,56 @@ __device__ __forceinline__ void window_item(const DevCfg& cf, const WinArgs& a, 
   if (active && flag) atomicOr(sflag, flag);
 }
 
-// Welch PSD of one (sample, detector) stretch x = background + o, by the
-// NC/16 threads t of a (sub-)block: K periodic-Hann segments of L = NC samples
-// at stride L/2.  Segments 2p and 2p+1 go through ONE complex FFT as real and
+// Welch sums of (sample, detector) stretches x = background + o, by the NC/16
+// threads t of a (sub-)block: periodic-Hann segments of L = NC samples at
+// stride L/2.  Segments 2p and 2p+1 go through ONE complex FFT as real and
 // imaginary parts; since |A_k|^2 + |B_k|^2 = (|X_k|^2 + |X_{L-k}|^2)/2 for
 // X = FFT(a + i b), the accumulated |X|^2 is folded once at the end.
 // With ACC wider than T (mixed precision) every transform's |X|^2 is added
 // to ACC totals.  With ACC equal to T it is summed in two levels, runs of
-// kWelchRun transforms and then the run sums, so that the rounding error
-// grows with kWelchRun + K/(2 kWelchRun) terms rather than K/2.  The fold and
-// the normalisation are done in ACC.
-template <class T, class ACC, int NC, int ORD>
-__device__ __forceinline__ void welch_item(int K, double norm, int t, const float* x, float* out, const cpx<T>* twtab,
-                                           T* sre, T* sim, bool active) {
-  constexpr int NT = NC / 16;
-  constexpr int LS = LdsSize<NC>::value;
+// kRun transforms and then the run sums, so that the rounding error grows with
+// kRun + K/(2 kRun) terms rather than K/2.  The fold and the normalisation are
+// done in ACC.
+//
+// The kernel is bound by the issue of vector instructions: per pair and thread
+// 32 for the window, 148 + 192 + 192 for the three radix-16 passes and 64 for
+// the sums.  The matrix cores do not help: binary32 MFMA shares the vector
+// units' multipliers, and a first pass as 32 products of 16 x 16 x 4 (575
+// vector instructions left) took 1.20 against 0.93 ms at 6144 items of K = 63.
+template <int NC> struct WelchTab {  // the table of one L = NC, in values of T
+  static constexpr int hann = 2 * (PlanTw<NC, 0>::size + PlanTw<NC, 1>::size);  // pass tables, then sin^2(pi n / L)
+  static constexpr int size = hann + NC / 2;                                    // for n < L/2
+};
+
+template <class T, class ACC, int NC, int ORD> struct WelchItem {
+  static constexpr int NT = NC / 16, LS = LdsSize<NC>::value;
+  static constexpr bool kWide = sizeof(ACC) > sizeof(T);
+  static constexpr int kRun = 16;
   static_assert(NC * sizeof(ACC) <= 2 * LS * sizeof(T), "fold buffer must fit in the FFT buffer");
-  // periodic Hann window sin^2(pi n / L) at n = t + NT r, r < 8; half a
-  // segment later it is cos^2 = 1 - sin^2, applied as x - w x
+  // sin^2 window at n = t + NT r, r < 8; half a segment later it is
+  // cos^2 = 1 - sin^2, applied as x - w x
   T w[8];
-#pragma unroll
-  for (int r = 0; r < 8; ++r) {
-    const T sp = sinpi_t(T(t + NT * r) / T(NC));
-    w[r] = sp * sp;
-  }
   HeldTwiddle<T, NC, ORD> tw;
-  tw.init(twtab, t);
-  constexpr bool kWide = sizeof(ACC) > sizeof(T);
-  constexpr int kWelchRun = 16;
   ACC tot[16];
-  T run[16];
+  T run[kWide ? 1 : 16];
+  int t;
+  T *sre, *sim;
+
+  __device__ __forceinline__ WelchItem(const T* tab, int t_, T* sre_, T* sim_) : t(t_), sre(sre_), sim(sim_) {
 #pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    tot[e] = ACC(0);
-    run[e] = T(0);
+    for (int r = 0; r < 8; ++r) w[r] = tab[WelchTab<NC>::hann + t + NT * r];
+    tw.init(reinterpret_cast<const cpx<T>*>(tab), t);
   }
-  // |X|^2 of transform p (p < 0: the last, single-segment transform)
-  auto add_power = [&](const cpx<T>* v, int p) {
+
+  // |X|^2 of transform p
+  __device__ __forceinline__ void add_power(const cpx<T>* v, int p) {
     if constexpr (kWide) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) tot[e] += ACC(fma_t(v[e].y, v[e].y, v[e].x * v[e].x));
     } else {
 #pragma unroll
       for (int e = 0; e < 16; ++e) run[e] = fma_t(v[e].y, v[e].y, fma_t(v[e].x, v[e].x, run[e]));
-      if (p % kWelchRun == kWelchRun - 1) {
+      if (p % kRun == kRun - 1) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
           tot[e] += run[e];
@@ -527,67 +533,81 @@ __device__ __forceinline__ void welch_item(int K, double norm, int t, const floa
         }
       }
     }
-  };
-  // Pair p covers [p L, p L + 3L/2).  Its first half-segment was read by
-  // pair p-1; the next pair's 16 new values per thread are requested before
-  // the current transform so that their latency hides behind it.
-  const int npairs = (K + 1) / 2;
-  const int nfull = K / 2;  // pairs holding two segments; with K odd the last pair holds one
-  float cur[8], na[8], nb[8];
-#pragma unroll
-  for (int r = 0; r < 8; ++r) {
-    cur[r] = x[t + NT * r];
-    na[r] = x[t + NT * (r + 8)];
-    nb[r] = (K > 1) ? x[NC / 2 + t + NT * (r + 8)] : 0.f;
   }
-#pragma unroll 1
-  for (int p = 0; p < nfull; ++p) {
-    cpx<T> v[16];
+
+  __device__ __forceinline__ void load_half(const float* half, float* v) const {
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      v[fft_in_slot<NC, ORD>(r)] = {w[r] * T(cur[r]), w[r] * T(na[r])};
-      v[fft_in_slot<NC, ORD>(r + 8)] = {T(na[r]) - w[r] * T(na[r]), T(nb[r]) - w[r] * T(nb[r])};
-      cur[r] = nb[r];
+    for (int r = 0; r < 8; ++r) v[r] = half[t + NT * r];
+  }
+
+  // Sums of the segment pairs p0 <= p < p1 of the stretch x (K segments; with
+  // K odd the last pair holds one).  Pair p covers [p L, p L + 3L/2): its first
+  // half segment was read by pair p-1, and the next pair's two new ones are
+  // requested before the current transform so that their latency hides behind
+  // it (in the last trip, or for a single segment, half segments that were
+  // read already are requested again, so that no branch splits the loop).
+  __device__ __forceinline__ void pairs(const float* x, int K, int p0, int p1) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      tot[e] = ACC(0);
+      if constexpr (!kWide) run[e] = T(0);
     }
-    const float* xn = x + int64_t(p + 1) * NC;
-    if (p + 1 < nfull) {
+    float cur[8], na[8], nb[8];
+    // half segment h of the stretch; K + 1 of them exist
+    load_half(x + int64_t(p0) * NC, cur);
+    load_half(x + int64_t(2 * p0 + 1) * (NC / 2), na);
+    load_half(x + int64_t(min(2 * p0 + 2, K)) * (NC / 2), nb);
+#pragma unroll 1
+    for (int p = p0; p < p1; ++p) {
+      cpx<T> v[16];
 #pragma unroll
       for (int r = 0; r < 8; ++r) {
-        na[r] = xn[t + NT * (r + 8)];
-        nb[r] = xn[NC / 2 + t + NT * (r + 8)];
+        const T b = w[r] * T(na[r]);
+        v[fft_in_slot<NC, ORD>(r)] = {w[r] * T(cur[r]), b};
+        v[fft_in_slot<NC, ORD>(r + 8)] = {T(na[r]) - b, T(nb[r]) - w[r] * T(nb[r])};
+        cur[r] = nb[r];
       }
-    } else if (p + 1 < npairs) {
+      if (2 * p + 1 >= K) {  // a single segment: zero imaginary part
 #pragma unroll
-      for (int r = 0; r < 8; ++r) na[r] = xn[t + NT * (r + 8)];
+        for (int r = 0; r < 16; ++r) v[r].y = T(0);
+      }
+      const int pn = min(p + 1, p1 - 1);
+      load_half(x + int64_t(2 * pn + 1) * (NC / 2), na);
+      load_half(x + int64_t(min(2 * pn + 2, K)) * (NC / 2), nb);
+      lds_barrier();  // the previous transform's last reads are done
+      block_fft<T, NC, -1, false, ORD>(v, sre, sim, t, tw);
+      add_power(v, p);
     }
-    if (p > 0) lds_barrier();
-    block_fft<T, NC, -1, false, ORD>(v, sre, sim, t, tw);
-    add_power(v, p);
   }
-  if (nfull < npairs) {
-    // the last segment alone: real input, zero imaginary part
-    cpx<T> v[16];
+
+  // One-sided sums of bins k = t, t + NT, ... in [0, L/2] handed to
+  // store(k, sum).
+  template <class F> __device__ __forceinline__ void fold(F store) {
+    lds_barrier();
+    ACC* f = reinterpret_cast<ACC*>(sre);
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      v[fft_in_slot<NC, ORD>(r)] = {w[r] * T(cur[r]), T(0)};
-      v[fft_in_slot<NC, ORD>(r + 8)] = {T(na[r]) - w[r] * T(na[r]), T(0)};
+    for (int e = 0; e < 16; ++e) {
+      if constexpr (kWide) f[fft_out_index<NC, ORD>(t, e)] = tot[e];
+      else f[fft_out_index<NC, ORD>(t, e)] = tot[e] + ACC(run[e]);
     }
-    if (nfull > 0) lds_barrier();
-    block_fft<T, NC, -1, false, ORD>(v, sre, sim, t, tw);
-    add_power(v, -1);
-  }
-  lds_barrier();
-  ACC* fold = reinterpret_cast<ACC*>(sre);
-#pragma unroll
-  for (int e = 0; e < 16; ++e) fold[fft_out_index<NC, ORD>(t, e)] = tot[e] + ACC(run[e]);
-  lds_barrier();
-  if (active) {
+    lds_barrier();
     for (int k = t; k <= NC / 2; k += NT) {
-      const ACC s = (fold[k] + fold[(NC - k) & (NC - 1)]) * ACC(0.5);
+      const ACC s = (f[k] + f[(NC - k) & (NC - 1)]) * ACC(0.5);
       const ACC ck = (k == 0 || k == NC / 2) ? ACC(1) : ACC(2);
-      out[k] = float(s * ck * ACC(norm));
+      store(k, s * ck);
     }
   }
+};
+
+// Welch PSD of one stretch.  active false: compute but store nothing.
+template <class T, class ACC, int NC, int ORD>
+__device__ __forceinline__ void welch_item(int K, double norm, int t, const float* x, float* out, const T* tab, T* sre,
+                                           T* sim, bool active) {
+  WelchItem<T, ACC, NC, ORD> w(tab, t, sre, sim);
+  w.pairs(x, K, 0, (K + 1) / 2);
+  w.fold([&](int k, ACC s) {
+    if (active) out[k] = float(s * ACC(norm));
+  });
 }
 
 }  // namespace gw

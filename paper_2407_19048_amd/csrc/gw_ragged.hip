@@ -59,6 +59,7 @@ struct gw_ragged {
   double* kcbrt = nullptr;
   double* lnk3 = nullptr;
   void* tw[4] = {nullptr, nullptr, nullptr, nullptr};   // pass twiddle tables of M points, M = 2048 << s
+  void* tw_welch[2] = {nullptr, nullptr};               // Welch tables of L = 2048 << s
   void* twr[4] = {nullptr, nullptr, nullptr, nullptr};  // exp(-2 pi i k / 2M), k <= M/2
   int n_cu = 256;
   int ord_win = 0, ord_welch = 0, grid_win = 1, grid_welch = 2;
@@ -130,7 +131,7 @@ __device__ __forceinline__ void welch_group(const RWelchArgs& a, int4 gr, int t,
   const int b = it / D, d = it - b * D;
   const float* x = a.bg[gr.x] + int64_t(d) * a.L_bg[gr.x] + load_const(a.offset + b);
   float* out = a.psd + load_const(a.psd_off + b) + int64_t(d) * cf.Fw;
-  const cpx<float>* tw = opaque(reinterpret_cast<const cpx<float>*>(L == 4096 ? a.tw4096 : a.tw2048));
+  const float* tw = opaque(reinterpret_cast<const float*>(L == 4096 ? a.tw4096 : a.tw2048));
   welch_item<float, ACC, L, ORD>(cf.K, a.norm[gr.x], tl, x, out, tw, lds + j * 2 * LS, lds + j * 2 * LS + LS, active);
 }
 
@@ -161,7 +162,7 @@ __global__ __launch_bounds__(L / 16, 3) void k_welch_class(RWelchArgs a, int cls
   const int b = it / D, d = it - b * D;
   const float* x = a.bg[cls] + int64_t(d) * a.L_bg[cls] + load_const(a.offset + b);
   float* out = a.psd + load_const(a.psd_off + b) + int64_t(d) * cf.Fw;
-  const cpx<float>* tw = reinterpret_cast<const cpx<float>*>(L == 4096 ? a.tw4096 : a.tw2048);
+  const float* tw = reinterpret_cast<const float*>(L == 4096 ? a.tw4096 : a.tw2048);
   welch_item<float, ACC, L, ORD>(cf.K, a.norm[cls], threadIdx.x, x, out, tw, lds, lds + LS, true);
 }
 
@@ -468,8 +469,8 @@ gw_status enqueue_ragged(gw_ragged* r, uint64_t seed, uint64_t batch_index, bool
       a.L_bg[c] = L_bg[c];
       a.norm[c] = r->welch_norm[c];
     }
-    a.tw2048 = r->tw[0];
-    a.tw4096 = r->tw[1];
+    a.tw2048 = r->tw_welch[0];
+    a.tw4096 = r->tw_welch[1];
     a.queue = queue;
     a.end[0] = r->wend[0];
     a.end[1] = r->wend[1];
@@ -529,6 +530,7 @@ gw_status gw_ragged_destroy(gw_ragged* r) {
   for (int k = 0; k < 4; ++k) {
     if (r->tw[k]) (void)hipFree(r->tw[k]);
     if (r->twr[k]) (void)hipFree(r->twr[k]);
+    if (k < 2 && r->tw_welch[k]) (void)hipFree(r->tw_welch[k]);
   }
   delete r;
   return GW_OK;
@@ -623,10 +625,11 @@ gw_status gw_ragged_create(const gw_config* classes, int32_t n_classes, const in
   // tables
   int Fmax = 0;
   bool need_tw[4] = {false, false, false, false}, need_twr[4] = {false, false, false, false};
+  bool need_welch[2] = {false, false};
   for (int c = 0; c < n_classes; ++c) {
     Fmax = std::max(Fmax, r->dc[c].F);
     need_tw[size_slot(r->dc[c].N / 2)] = need_twr[size_slot(r->dc[c].N / 2)] = true;
-    need_tw[size_slot(r->dc[c].L)] = true;
+    need_welch[size_slot(r->dc[c].L)] = true;
   }
   std::vector<double> hc(Fmax), hl(Fmax);
   for (int k = 0; k < Fmax; ++k) {
@@ -645,6 +648,7 @@ gw_status gw_ragged_create(const gw_config* classes, int32_t n_classes, const in
     const int M = 2048 << k;
     if (need_tw[k]) ok = upload(&r->tw[k], plan_tables<float>(M));
     if (ok && need_twr[k]) ok = upload(&r->twr[k], twiddles(M / 2 + 1, 2 * M));
+    if (ok && k < 2 && need_welch[k]) ok = upload(&r->tw_welch[k], welch_tables<float>(M));
   }
   if (!ok) return bail(GW_ENOMEM);
   int dev = 0, ncu = 0;

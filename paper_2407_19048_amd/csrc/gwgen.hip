@@ -184,7 +184,7 @@ struct WelchArgs {
   int64_t L_bg;
   const int64_t* offset;
   float* psd;
-  const void* tw;  // pass twiddle tables of the L-point transform
+  const void* tw;  // Welch table of L (WelchTab)
   double norm;     // 1 / (K fs sum w^2)
 };
 
@@ -199,7 +199,7 @@ __global__ __launch_bounds__(NC / 16, OCC) void k_welch(WelchArgs a) {
   const int64_t b = bd / D;
   const int d = int(bd - b * D);
   welch_item<T, ACC, NC, ORD>(a.cf.K, a.norm, threadIdx.x, a.bg + int64_t(d) * a.L_bg + a.offset[b],
-                              a.psd + bd * a.cf.Fw, reinterpret_cast<const cpx<T>*>(a.tw), lds, lds + LS, true);
+                              a.psd + bd * a.cf.Fw, reinterpret_cast<const T*>(a.tw), lds, lds + LS, true);
 }
 
 __global__ void k_fill_u32(uint32_t* p, int64_t n, uint32_t v) {
@@ -886,13 +886,13 @@ gw_status gw_create(const gw_config* cfg, gw_ctx** out) {
   if (dc.precision == 2) {
     s = upload_cpx(c, &c->tw_win, plan_tables<double>(NC));
     if (s == GW_OK) s = upload_twiddles<double>(c, &c->twr_win, NC / 2 + 1, dc.N);
-    if (s == GW_OK) s = upload_cpx(c, &c->tw_welch, plan_tables<double>(dc.L));
+    if (s == GW_OK) s = upload_cpx(c, &c->tw_welch, welch_tables<double>(dc.L));
   } else {
     // windows longer than 32768 samples transform rows of N1 (four-step)
     const int NCt = NC > 16384 ? long_row_length(NC) : NC;
     s = upload_cpx(c, &c->tw_win, plan_tables<float>(NCt));
     if (s == GW_OK) s = upload_twiddles<float>(c, &c->twr_win, NC / 2 + 1, dc.N);
-    if (s == GW_OK) s = upload_cpx(c, &c->tw_welch, plan_tables<float>(dc.L));
+    if (s == GW_OK) s = upload_cpx(c, &c->tw_welch, welch_tables<float>(dc.L));
     if (s == GW_OK && NC > 16384) s = upload_long_tables(c, NC);
   }
   if (s != GW_OK) {
