@@ -26,6 +26,7 @@ struct gw_ctx {
   // (k mod N2) N1 + k / N2 of bin k in the transposed four-step spectrum
   void* long_tabs = nullptr;
   int device = 0;             // HIP device the context was created on
+  int n_cu = 256;             // its compute units
   void* scratch = nullptr;    // that device's copy of the library's static scratch area
   std::string err;
 };

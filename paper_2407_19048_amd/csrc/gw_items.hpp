@@ -12,71 +12,81 @@
 namespace gw {
 
 // ---------------------------------------- window kernels (FFT of length N)
+// Background offset of global sample index g in [0, span) (with ext_k sky
+// positions per intrinsic draw, see draw_sample).
+__device__ __forceinline__ int64_t draw_offset(uint64_t seed, uint64_t g, uint32_t ext_k, int64_t span) {
+  const uint64_t gi = ext_k == 1u ? g : g / ext_k;
+  return int64_t(floor(philox_uniform(seed, gi, 12u, uint32_t(g - gi * ext_k)) * double(span)));
+}
+
+// Where a batch's draws go.
+struct DrawOut {
+  double* params;      // [12][B]
+  int64_t* offset;     // [B]
+  float* params_f32;   // [12][B] or NULL
+  WfScalars* wf;       // [B] waveform constants for the fused kernel, or NULL
+  DetScalars* dsc;     // [B][D] antenna patterns and delays (with wf)
+  uint32_t* status;    // [B] or NULL (set with wf only)
+};
+
 // Prior draws for global sample index g (the densities of Table 1 with the
 // ranges in c), the window's background offset in [0, span), status
-// initialisation, and the per-sample constants of the fused window kernel.
+// initialisation, and the per-sample constants of the fused window kernel, by
+// the kSetupLanes lanes of one group: lane r draws and transforms row r.
 // Row 11 of the parameters receives p11.  With ext_k sky positions per
 // intrinsic draw, g is sky position g % ext_k of intrinsic draw g / ext_k:
 // every row is drawn at counter index g / ext_k, and alpha, delta, psi and
 // the offset use the sub-counter g % ext_k (ext_k = 1: ordinary draws).
-__device__ __forceinline__ void draw_sample(const DevCfg& c, uint64_t seed, uint64_t g, int64_t i, int64_t B,
-                                            int64_t span, double p11, double* params, int64_t* offset,
-                                            float* params_f32, uint32_t* status, WfScalars* wf, DetScalars* dsc,
-                                            uint32_t ext_k = 1u) {
+__device__ __forceinline__ double draw_row(const DevCfg& c, int r, double u) {
 #pragma clang fp contract(off)
-  const uint64_t gi = g / ext_k;
-  const uint32_t j = uint32_t(g - gi * ext_k);
-  double u[11];
-#pragma unroll
-  for (int s = 0; s < 11; ++s) u[s] = philox_uniform(seed, gi, uint32_t(s), (s >= 6 && s <= 8) ? j : 0u);
-  const double uo = philox_uniform(seed, gi, 12u, j);
-  double p[12];
+  if (r == 5) return acos(2.0 * u - 1.0);
+  if (r == 7) return asin(2.0 * u - 1.0);
   if (c.approximant == 2) {
     // sine-Gaussian: f0 and Q uniform, hrss log-uniform
-    p[0] = c.f0r[0] + u[0] * (c.f0r[1] - c.f0r[0]);
-    p[1] = c.Qr[0] + u[1] * (c.Qr[1] - c.Qr[0]);
-    p[2] = exp(log(c.hrssr[0]) + u[2] * (log(c.hrssr[1]) - log(c.hrssr[0])));
-    p[3] = 0.0;
-    p[4] = 0.0;
-  } else {
-    p[0] = c.mc[0] + u[0] * (c.mc[1] - c.mc[0]);
-    p[1] = c.q[0] + u[1] * (c.q[1] - c.q[0]);
-    p[2] = c.chi[0] + u[2] * (c.chi[1] - c.chi[0]);
-    p[3] = c.chi[0] + u[3] * (c.chi[1] - c.chi[0]);
+    if (r == 2) return exp(log(c.hrssr[0]) + u * (log(c.hrssr[1]) - log(c.hrssr[0])));
+    if (r == 3 || r == 4) return 0.0;
+  } else if (r == 4) {
     const double a3 = c.dl[0] * c.dl[0] * c.dl[0], b3 = c.dl[1] * c.dl[1] * c.dl[1];
-    p[4] = pow(a3 + u[4] * (b3 - a3), 1.0 / 3.0);
+    return cbrt(a3 + u * (b3 - a3));
   }
-  p[5] = acos(2.0 * u[5] - 1.0);
-  p[6] = 2.0 * kPi * u[6];
-  p[7] = asin(2.0 * u[7] - 1.0);
-  p[8] = kPi * u[8];
-  p[9] = 2.0 * kPi * u[9];
-  p[10] = c.T - 1.5 + u[10] * 1.0;
-  p[11] = p11;
-#pragma unroll
-  for (int r = 0; r < 12; ++r) params[r * B + i] = p[r];
-  offset[i] = int64_t(floor(uo * double(span)));
-  if (params_f32) {
-#pragma unroll
-    for (int r = 0; r < 12; ++r) params_f32[r * B + i] = float(p[r]);
+  const bool burst = c.approximant == 2;
+  const double lo = r == 0 ? (burst ? c.f0r[0] : c.mc[0]) : r == 1 ? (burst ? c.Qr[0] : c.q[0]) : c.chi[0];
+  const double hi = r == 0 ? (burst ? c.f0r[1] : c.mc[1]) : r == 1 ? (burst ? c.Qr[1] : c.q[1]) : c.chi[1];
+  if (r <= 3) return lo + u * (hi - lo);
+  if (r == 8) return kPi * u;
+  if (r == 10) return c.T - 1.5 + u * 1.0;
+  return 2.0 * kPi * u;
+}
+
+__device__ __forceinline__ void draw_sample(const DevCfg& c, uint64_t seed, uint64_t g, int64_t i, int64_t B,
+                                            int64_t span, double p11, const DrawOut& o, int lane, uint32_t ext_k = 1u) {
+  const uint64_t gi = ext_k == 1u ? g : g / ext_k;
+  const uint32_t j = uint32_t(g - gi * ext_k);
+  const double mine =
+      lane < 11 ? draw_row(c, lane, philox_uniform(seed, gi, uint32_t(lane), (lane >= 6 && lane <= 8) ? j : 0u)) : p11;
+  if (lane < 12) {
+    o.params[lane * B + i] = mine;
+    if (o.params_f32) o.params_f32[lane * B + i] = float(mine);
+  } else if (lane == 12) {
+    o.offset[i] = draw_offset(seed, g, ext_k, span);
   }
-  if (status) {
-    double f_cut;
-    if (c.approximant == 2) {
-      f_cut = p[0] + 5.0 / (kPi * (p[1] / (sqrt(2.0) * kPi * p[0])));  // f0 + 5/(pi tau)
-    } else {
-      const double eta = p[1] / ((1.0 + p[1]) * (1.0 + p[1]));
-      const double Ms = p[0] * pow(eta, -0.6) * kMsunSec;
-      f_cut = c.approximant == 0 ? 1.0 / (pow(6.0, 1.5) * kPi * Ms) : 0.2 / Ms;
+  if (!o.wf) return;
+  double p[11];
+#pragma unroll
+  for (int r = 0; r < 11; ++r) p[r] = lane_value(mine, r);
+  WfScalars w = {};
+  SkyAngles sky;
+  wf_setup(p, c, lane, w, sky);
+  if (lane == 0) {
+    o.wf[i] = w;
+    if (o.status) {
+      // sine-Gaussian: f0 + 5/(pi tau) beyond Nyquist
+      const bool cut = c.approximant == 2 ? p[0] + 5.0 / (kPi * (p[1] / (sqrt(2.0) * kPi * p[0]))) > 0.5 * c.fs
+                                          : w.cut_nyquist != 0;
+      o.status[i] = cut ? GW_STATUS_CUT_AT_NYQUIST : 0u;
     }
-    status[i] = f_cut > 0.5 * c.fs ? GW_STATUS_CUT_AT_NYQUIST : 0u;
   }
-  if (wf) {
-    WfScalars w;
-    wf_setup(params, B, i, c, w);
-    wf[i] = w;
-    for (int d = 0; d < c.n_det; ++d) dsc[i * c.n_det + d] = det_response(c.det[d], w.ra, w.dec, w.psi, w.tc);
-  }
+  if (lane < c.n_det) o.dsc[i * c.n_det + lane] = det_response(c.det[lane], sky, w.tc);
 }
 
 // Load through the constant address space: for memory that no thread writes
@@ -608,6 +618,60 @@ __device__ __forceinline__ void welch_item(int K, double norm, int t, const floa
   w.fold([&](int k, ACC s) {
     if (active) out[k] = float(s * ACC(norm));
   });
+}
+
+// A Welch launch in which workgroup w of G takes the segment pairs
+// [start(w), start(w + 1)) of all items' pairs laid end to end, so that every
+// workgroup has the same share whatever the number of items.  An item that one
+// workgroup holds whole is stored at once; of one that is cut, each piece's
+// binary64 sums go to a slot of the launch's own, and welch_sum adds the slots
+// in order.  (The sums of at most a few dozen binary32 values of similar size
+// are exact in binary64, so where an item is cut does not change its PSD.)
+struct WelchCut {
+  int G, q, r;   // workgroups; pairs = q G + r
+  int np;        // pairs of an item
+  // one item per workgroup: nothing is cut (G np may exceed 32 bits then)
+  __host__ __device__ bool whole() const { return q == np && r == 0; }
+  __device__ __forceinline__ int start(int w) const { return w * q + int(uint32_t(w) * uint32_t(r) / uint32_t(G)); }
+};
+
+// Runs workgroup w's pieces: src(item) gives the stretch, whole(item, k, sum)
+// and piece(slot, k, sum) take bin k's one-sided sum.
+template <class T, class ACC, int NC, int ORD, class Src, class Whole, class Piece>
+__device__ __forceinline__ void welch_pieces(const WelchCut& cut, int w, int K, int t, const T* tab, T* sre, T* sim,
+                                             Src src, Whole whole, Piece piece) {
+  WelchItem<T, ACC, NC, ORD> wi(tab, t, sre, sim);
+  int item = w, p0 = 0, left = cut.np;
+  if (!cut.whole()) {
+    const int begin = cut.start(w);
+    item = begin / cut.np;
+    p0 = begin - item * cut.np;
+    left = cut.start(w + 1) - begin;
+  }
+  const int first = item;
+#pragma unroll 1
+  while (left > 0) {
+    const int p1 = min(cut.np, p0 + left);
+    wi.pairs(src(item), K, p0, p1);
+    if (p1 - p0 == cut.np) wi.fold([&](int k, ACC s) { whole(item, k, s); });
+    else wi.fold([&](int k, ACC s) { piece(2 * w + (item == first ? 0 : 1), k, s); });
+    left -= p1 - p0;
+    p0 = 0;
+    ++item;
+  }
+}
+
+// Sum over the pieces of the item that workgroup boundary w (1 <= w < G) cuts,
+// where it is the item's first: -1 if it cuts none or not first, else the item;
+// add(slot) is called for its slots in order.
+template <class Add>
+__device__ __forceinline__ int welch_cut_item(const WelchCut& cut, int w, Add add) {
+  const int at = cut.start(w), item = at / cut.np;
+  const int before = cut.start(w - 1);
+  if (at == item * cut.np || before > item * cut.np) return -1;
+  add(2 * (w - 1) + (before / cut.np == item ? 0 : 1));
+  for (int v = w; v < cut.G && cut.start(v) < (item + 1) * cut.np; ++v) add(2 * v);
+  return item;
 }
 
 }  // namespace gw

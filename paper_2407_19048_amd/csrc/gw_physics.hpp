@@ -133,6 +133,7 @@ __device__ __forceinline__ void pn_coefficients(double eta, double q, double chi
   const double dm = (1.0 - q) / (1.0 + q);
   const double chis = 0.5 * (chi1 + chi2), chia = 0.5 * (chi1 - chi2);
   const double pi = kPi;
+#pragma unroll
   for (int k = 0; k < 8; ++k) { c[k] = 0.0; lg[k] = 0.0; }
   c[0] = 1.0;
   c[2] = 3715.0 / 756.0 + 55.0 * eta / 9.0;
@@ -152,112 +153,150 @@ __device__ __forceinline__ void pn_coefficients(double eta, double q, double chi
   c[7] = pi * (77096675.0 / 254016.0 + 378515.0 * eta / 1512.0 - 74045.0 * eta * eta / 756.0);
 }
 
-// TaylorF2 intrinsic phase P(f) [rad] and dP/df, full binary64, direct powers
-__device__ __forceinline__ void tf2_phase_and_slope(double f, double Ms, double eta, const double* c,
+// The per-sample set-up runs in groups of kSetupLanes consecutive lanes of a
+// wavefront that hold the same sample: every lane does the cheap arithmetic,
+// and the powers, roots, logarithms and sines, which are what the set-up's
+// latency is made of, are evaluated one per lane and exchanged.  One thread
+// per sample took 25 us for a single sample, a chain of 27 pow() calls.
+constexpr int kSetupLanes = 16;
+__device__ __forceinline__ double lane_value(double v, int lane) { return __shfl(v, lane, kSetupLanes); }
+__device__ __forceinline__ int lane_value(int v, int lane) { return __shfl(v, lane, kSetupLanes); }
+
+// TaylorF2 intrinsic phase P(f) [rad] and dP/df at v = (pi M f)^(1/3), full binary64
+__device__ __forceinline__ void tf2_phase_and_slope(double f, double v, double lnv, double eta, const double* c,
                                                     const double* lg, double* P, double* dP) {
-  const double v = cbrt(kPi * Ms * f), lnv = log(v);
+  const double iv = 1.0 / v, iv2 = iv * iv;
+  double vk = iv2 * iv2 * iv;  // v^(k-5)
   double s = 0.0, ds = 0.0;
+#pragma unroll
   for (int k = 0; k < 8; ++k) {
     const double ck = c[k] + lg[k] * lnv;
-    s += ck * pow(v, double(k - 5));
-    ds += ((k - 5) * ck + lg[k]) * pow(v, double(k - 6));
+    s += ck * vk;
+    ds += ((k - 5) * ck + lg[k]) * (vk * iv);
+    vk *= v;
   }
   const double pre = 3.0 / (128.0 * eta);
   *P = pre * s;
   *dP = pre * ds * v / (3.0 * f);
 }
 
-__device__ __forceinline__ void wf_setup(const double* __restrict__ params, int64_t B, int64_t b,
-                                         const DevCfg& cf, WfScalars& w) {
+// Sines and cosines of the sky angles.
+struct SkyAngles { double sr, cr, sd, cd, sp, cp; };
+
+// Waveform constants of one sample from its parameter rows p[0..10] (held by
+// every lane of the group; lane = this lane's place in it).  All lanes return
+// the same values.
+__device__ __forceinline__ void wf_setup(const double* p, const DevCfg& cf, int lane, WfScalars& w, SkyAngles& sky) {
+  // iota, RA, dec, psi: one sine and cosine per lane
+  const double iota = p[5], ra = p[6], dec = p[7], psi = p[8];
+  const double ang = lane == 0 ? iota : lane == 1 ? ra : lane == 2 ? dec : psi;
+  double sn, cs;
+  sincos(ang, &sn, &cs);
+  w.cosi = lane_value(cs, 0);
+  sky = {lane_value(sn, 1), lane_value(cs, 1), lane_value(sn, 2), lane_value(cs, 2), lane_value(sn, 3), lane_value(cs, 3)};
+  w.ra = ra;
+  w.dec = dec;
+  w.psi = psi;
+  w.tc = p[10];
   if (cf.approximant == 2) {
     // sine-Gaussian: rows 0 f0, 1 Q, 2 hrss, 5 iota, 9 phi0, 10 t0
-    const double f0 = params[0 * B + b], Q = params[1 * B + b], hrss = params[2 * B + b];
-    w.ra = params[6 * B + b];
-    w.dec = params[7 * B + b];
-    w.psi = params[8 * B + b];
-    w.tc = params[10 * B + b];
-    w.cosi = cos(params[5 * B + b]);
+    const double f0 = p[0], Q = p[1], hrss = p[2];
     const double tau = Q / (sqrt(2.0) * kPi * f0);
     const double A = kStrainScale * hrss / sqrt(tau * sqrt(0.5 * kPi));
     w.sg_f0 = f0;
     w.sg_pt2 = kPi * kPi * tau * tau;
     w.sg_G0 = A * 0.5 * sqrt(kPi) * tau;
-    w.sg_rphi = params[9 * B + b] / (2.0 * kPi);
+    w.sg_rphi = p[9] / (2.0 * kPi);
     w.kend = cf.N / 2;
     w.kt = w.krd = w.kend;
     w.cut_nyquist = f0 + 5.0 / (kPi * tau) >= 0.5 * cf.fs ? 1 : 0;
     return;
   }
-  const double mc = params[0 * B + b], q = params[1 * B + b];
-  const double chi1 = params[2 * B + b], chi2 = params[3 * B + b];
-  const double dl = params[4 * B + b], iota = params[5 * B + b];
-  w.ra = params[6 * B + b];
-  w.dec = params[7 * B + b];
-  w.psi = params[8 * B + b];
-  const double phic = params[9 * B + b];
-  w.tc = params[10 * B + b];
-  w.cosi = cos(iota);
+  const double mc = p[0], q = p[1], chi1 = p[2], chi2 = p[3], dl = p[4], phic = p[9];
   const double eta = q / ((1.0 + q) * (1.0 + q));
-  const double M = mc * pow(eta, -0.6);
-  const double Ms = M * kMsunSec;
+  // remnant: aligned-spin final-spin fit, non-spinning radiated-energy fit
+  const double a_tot = (chi1 + chi2 * q * q) / (1.0 + q * q);
+  double af = a_tot - 0.1229 * a_tot * a_tot * eta + 0.4537 * a_tot * eta * eta
+              - 2.8904 * a_tot * eta + 2.0 * sqrt(3.0) * eta - 3.5171 * eta * eta
+              + 2.5763 * eta * eta * eta;
+  af = fmin(fmax(af, -0.99), 0.99);
+  const double px = lane == 0 ? eta : lane == 1 ? mc * kMsunSec : lane == 2 ? cf.T : 1.0 - af;
+  const double py = lane == 0 ? -0.6 : lane == 1 ? 5.0 / 6.0 : lane == 2 ? 7.0 / 6.0 : lane == 3 ? 0.1292 : -0.4990;
+  const double pw = pow(px, py);
+  const double Ms = mc * lane_value(pw, 0) * kMsunSec;
   double c[8], lg[8];
   pn_coefficients(eta, q, chi1, chi2, c, lg);
   const double rev = 3.0 / (128.0 * eta) / (2.0 * kPi);
+#pragma unroll
   for (int k = 0; k < 8; ++k) w.a[k] = rev * c[k];
   w.b5 = rev * lg[5];
   w.b6 = rev * lg[6];
-  w.v1 = cbrt(kPi * Ms * cf.invT);
-  w.lnv1 = log(w.v1);
-  w.cN = w.a[0] / (w.v1 * w.v1 * w.v1 * w.v1 * w.v1);
   w.pconst = (-phic - 0.25 * kPi) / (2.0 * kPi);
-  const double A0 = kStrainScale * sqrt(5.0 / 24.0) * pow(kPi, -2.0 / 3.0) *
-                    pow(mc * kMsunSec, 5.0 / 6.0) / (dl * kMpcSec);
-  w.A0T = A0 * pow(cf.T, 7.0 / 6.0);
+  const double A0 = kStrainScale * sqrt(5.0 / 24.0) * pow(kPi, -2.0 / 3.0) * lane_value(pw, 1) / (dl * kMpcSec);
+  w.A0T = A0 * lane_value(pw, 2);
   const int knyq = cf.N / 2;
-  double f_cut;
+  double f_cut, f_t = 1.0, f_rd = 1.0, f_damp = 1.0;
   if (cf.approximant == 0) {
     f_cut = 1.0 / (pow(6.0, 1.5) * kPi * Ms);
-    w.kend = first_bin_at_or_above(f_cut, cf.T, knyq);
+  } else {
+    f_cut = 0.2 / Ms;
+    const double erad = 0.0559745 * eta + 0.580951 * eta * eta - 0.960673 * eta * eta * eta
+                        + 3.35241 * eta * eta * eta * eta;
+    const double Mf = Ms * (1.0 - erad);
+    const double omega = 1.5251 - 1.1568 * lane_value(pw, 3);
+    const double Q = 0.7 + 1.4187 * lane_value(pw, 4);
+    f_rd = omega / (2.0 * kPi * Mf);
+    f_damp = f_rd / (2.0 * Q);
+    f_t = 0.5 * f_rd;
+  }
+  // v and ln v at bin 1 (lane 0) and at f_t; the band edges one per lane
+  const double v = cbrt(kPi * Ms * (lane == 0 ? cf.invT : f_t)), lnv = log(v);
+  const int kb = first_bin_at_or_above(lane == 0 ? f_cut : lane == 1 ? f_t : f_rd, cf.T, knyq);
+  w.v1 = lane_value(v, 0);
+  w.lnv1 = lane_value(lnv, 0);
+  w.cN = w.a[0] / (w.v1 * w.v1 * w.v1 * w.v1 * w.v1);
+  w.kend = lane_value(kb, 0);
+  w.cut_nyquist = f_cut > 0.5 * cf.fs ? 1 : 0;
+  if (cf.approximant == 0) {
     w.kt = w.kend;
     w.krd = w.kend;
     w.mr_b0 = w.mr_b1 = w.f_rd = w.inv_fdamp = 0.0;
     w.At = w.Ard = w.ft = w.fdamp2 = w.Apl = 0.0;
-  } else {
-    f_cut = 0.2 / Ms;
-    w.kend = first_bin_at_or_above(f_cut, cf.T, knyq);
-    // remnant: aligned-spin final-spin fit, non-spinning radiated-energy fit
-    const double a_tot = (chi1 + chi2 * q * q) / (1.0 + q * q);
-    double af = a_tot - 0.1229 * a_tot * a_tot * eta + 0.4537 * a_tot * eta * eta
-                - 2.8904 * a_tot * eta + 2.0 * sqrt(3.0) * eta - 3.5171 * eta * eta
-                + 2.5763 * eta * eta * eta;
-    af = fmin(fmax(af, -0.99), 0.99);
-    const double erad = 0.0559745 * eta + 0.580951 * eta * eta - 0.960673 * eta * eta * eta
-                        + 3.35241 * eta * eta * eta * eta;
-    const double Mf = Ms * (1.0 - erad);
-    const double omega = 1.5251 - 1.1568 * pow(1.0 - af, 0.1292);
-    const double Q = 0.7 + 1.4187 * pow(1.0 - af, -0.4990);
-    const double f_rd = omega / (2.0 * kPi * Mf);
-    const double f_damp = f_rd / (2.0 * Q);
-    const double f_t = 0.5 * f_rd;
-    double Pt, dPt;
-    tf2_phase_and_slope(f_t, Ms, eta, c, lg, &Pt, &dPt);
-    const double x_t = (f_t - f_rd) / f_damp;
-    const double b1 = dPt - (1.0 / f_damp) / (1.0 + x_t * x_t);
-    const double b0 = Pt - b1 * f_t - atan(x_t);
-    w.mr_b0 = b0 / (2.0 * kPi);
-    w.mr_b1 = b1 / (2.0 * kPi);
-    w.f_rd = f_rd;
-    w.inv_fdamp = 1.0 / f_damp;
-    const double At = A0 * pow(f_t, -7.0 / 6.0);
-    w.At = At;
-    w.Ard = At * pow(f_rd / f_t, -2.0 / 3.0);
-    w.ft = f_t;
-    w.fdamp2 = f_damp * f_damp;
-    w.Apl = At * pow(f_t * cf.T, 2.0 / 3.0);
-    w.kt = min(first_bin_at_or_above(f_t, cf.T, knyq), w.kend);
-    w.krd = min(first_bin_at_or_above(f_rd, cf.T, knyq), w.kend);
+    return;
   }
-  w.cut_nyquist = f_cut > 0.5 * cf.fs ? 1 : 0;
+  double Pt, dPt;
+  tf2_phase_and_slope(f_t, lane_value(v, 1), lane_value(lnv, 1), eta, c, lg, &Pt, &dPt);
+  const double x_t = (f_t - f_rd) / f_damp;
+  const double b1 = dPt - (1.0 / f_damp) / (1.0 + x_t * x_t);
+  const double b0 = Pt - b1 * f_t - atan(x_t);
+  w.mr_b0 = b0 / (2.0 * kPi);
+  w.mr_b1 = b1 / (2.0 * kPi);
+  w.f_rd = f_rd;
+  w.inv_fdamp = 1.0 / f_damp;
+  const double pw2 = pow(lane == 0 ? f_t : lane == 1 ? f_rd / f_t : f_t * cf.T,
+                         lane == 0 ? -7.0 / 6.0 : lane == 1 ? -2.0 / 3.0 : 2.0 / 3.0);
+  const double At = A0 * lane_value(pw2, 0);
+  w.At = At;
+  w.Ard = At * lane_value(pw2, 1);
+  w.ft = f_t;
+  w.fdamp2 = f_damp * f_damp;
+  w.Apl = At * lane_value(pw2, 2);
+  w.kt = min(lane_value(kb, 1), w.kend);
+  w.krd = min(lane_value(kb, 2), w.kend);
+}
+
+// The same for column b of params [11 or 12][B], by the first kSetupLanes
+// threads of a workgroup (thread t of them); lane 0 writes w.
+__device__ __forceinline__ void wf_setup_column(const double* __restrict__ params, int64_t B, int64_t b,
+                                                const DevCfg& cf, int t, WfScalars* w) {
+  const double mine = params[min(t, 10) * B + b];
+  double p[11];
+#pragma unroll
+  for (int r = 0; r < 11; ++r) p[r] = lane_value(mine, r);
+  WfScalars v = {};
+  SkyAngles sky;
+  wf_setup(p, cf, t, v, sky);
+  if (t == 0) *w = v;
 }
 
 // Waveform phase in revolutions (without the time shift) at bin k.  TP is
@@ -301,12 +340,12 @@ __device__ __forceinline__ TA wf_amplitude(const WfScalars& w, int k, double kcb
 // -------------------------------------------------------- detector response
 struct DetScalars { double fp, fx, tau; };
 
-__device__ __forceinline__ DetScalars det_response(const DetGeom& g, double ra, double dec, double psi, double tc) {
-  const double sr = sin(ra), cr = cos(ra), sd = sin(dec), cd = cos(dec);
-  const double sp = sin(psi), cp = cos(psi);
+__device__ __forceinline__ DetScalars det_response(const DetGeom& g, const SkyAngles& a, double tc) {
+  const double sr = a.sr, cr = a.cr, sd = a.sd, cd = a.cd, sp = a.sp, cp = a.cp;
   const double et[3] = {sd * cr, sd * sr, -cd};
   const double ep[3] = {-sr, cr, 0.0};
   double p[3], qv[3];
+#pragma unroll
   for (int i = 0; i < 3; ++i) {
     p[i] = cp * et[i] + sp * ep[i];
     qv[i] = -sp * et[i] + cp * ep[i];
@@ -314,7 +353,9 @@ __device__ __forceinline__ DetScalars det_response(const DetGeom& g, double ra, 
   const double* D = g.D;
   const double Dm[3][3] = {{D[0], D[1], D[2]}, {D[1], D[3], D[4]}, {D[2], D[4], D[5]}};
   double fp = 0.0, fx = 0.0;
+#pragma unroll
   for (int i = 0; i < 3; ++i)
+#pragma unroll
     for (int j = 0; j < 3; ++j) {
       fp += Dm[i][j] * (p[i] * p[j] - qv[i] * qv[j]);
       fx += Dm[i][j] * (p[i] * qv[j] + qv[i] * p[j]);

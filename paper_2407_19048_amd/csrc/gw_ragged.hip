@@ -81,16 +81,11 @@ struct RSampleArgs {
   const uint64_t* batch;  // device batch index (graph replays) or NULL
   int64_t B;
   int64_t span[kMaxCls];
-  double* params;
-  int64_t* offset;
-  float* params_f32;
-  uint32_t* status;
-  WfScalars* wf;
-  DetScalars* dsc;
+  DrawOut out;
 };
 
 __global__ __launch_bounds__(256) void k_sample_params_ragged(RSampleArgs a) {
-  const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
+  const int64_t i = (int64_t(blockIdx.x) * 256 + threadIdx.x) / kSetupLanes;
   if (i >= a.B) return;
   const int c = a.cls[i];
   const uint64_t first = a.batch ? *a.batch * uint64_t(a.B) : a.first;
@@ -98,8 +93,7 @@ __global__ __launch_bounds__(256) void k_sample_params_ragged(RSampleArgs a) {
 #pragma unroll
   for (int k = 1; k < kMaxCls; ++k)
     if (c == k) span = a.span[k];
-  draw_sample(a.cfgs[c], a.seed, first + uint64_t(i), i, a.B, span, double(c), a.params, a.offset, a.params_f32,
-              a.status, a.wf, a.dsc);
+  draw_sample(a.cfgs[c], a.seed, first + uint64_t(i), i, a.B, span, double(c), a.out, threadIdx.x % kSetupLanes);
 }
 
 struct RWelchArgs {
@@ -443,13 +437,9 @@ gw_status enqueue_ragged(gw_ragged* r, uint64_t seed, uint64_t batch_index, bool
     a.batch = use_counter ? batch : nullptr;
     a.B = B;
     for (int c = 0; c < kMaxCls; ++c) a.span[c] = span[c];
-    a.params = params;
-    a.offset = offset;
-    a.params_f32 = params_f32;
-    a.status = status;
-    a.wf = wf;
-    a.dsc = dsc;
-    hipLaunchKernelGGL(k_sample_params_ragged, dim3(unsigned((B + 255) / 256)), dim3(256), 0, st, a);
+    a.out = DrawOut{params, offset, params_f32, wf, dsc, status};
+    const int64_t blocks = (B * kSetupLanes + 255) / 256;
+    hipLaunchKernelGGL(k_sample_params_ragged, dim3(unsigned(blocks)), dim3(256), 0, st, a);
     if ((s = rcheck(r, "k_sample_params_ragged")) != GW_OK) return s;
   }
   if (stages & kStageWelch) {

@@ -90,8 +90,8 @@ __global__ __launch_bounds__(256) void k_targets(TargetArgs a) {
   __shared__ WfScalars w;
   __shared__ double Ms_s, eta_s;
   const int64_t b = blockIdx.x;
+  if (threadIdx.x < kSetupLanes) wf_setup_column(a.params, a.B, b, a.cf, threadIdx.x, &w);
   if (threadIdx.x == 0) {
-    wf_setup(a.params, a.B, b, a.cf, w);
     const double q = a.params[1 * a.B + b], mc = a.params[0 * a.B + b];
     const double eta = q / ((1.0 + q) * (1.0 + q));
     eta_s = eta;

@@ -38,21 +38,23 @@ struct SampleArgs {
   uint64_t seed, first;
   const uint64_t* batch;  // device batch index (graph replays): first = *batch * B, or NULL
   int64_t B, span;
-  double* params;
-  int64_t* offset;
-  float* params_f32;
-  uint32_t* status;
-  WfScalars* wf;     // [B] waveform constants for the fused kernel, or NULL
-  DetScalars* dsc;   // [B][D] antenna patterns and delays, or NULL
+  DrawOut out;
   uint32_t ext_k = 1;  // sky positions per intrinsic draw
+  __device__ __forceinline__ uint64_t first_index() const { return batch ? *batch * uint64_t(B) : first; }
 };
 
-__global__ __launch_bounds__(256) void k_sample_params(SampleArgs a) {
-  const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
+constexpr int kDrawThreads = 256;
+int64_t draw_blocks(int64_t B, int threads) { return (B * kSetupLanes + threads - 1) / threads; }
+
+// samples of one workgroup of `threads` threads, one group of lanes each
+__device__ __forceinline__ void draw_block(const SampleArgs& a, const DevCfg& cf, int64_t block, int t, int threads) {
+  const int64_t i = (block * threads + t) / kSetupLanes;
   if (i >= a.B) return;
-  const uint64_t first = a.batch ? *a.batch * uint64_t(a.B) : a.first;
-  draw_sample(a.cf, a.seed, first + uint64_t(i), i, a.B, a.span, 0.0, a.params, a.offset, a.params_f32, a.status,
-              a.wf, a.dsc, a.ext_k);
+  draw_sample(cf, a.seed, a.first_index() + uint64_t(i), i, a.B, a.span, 0.0, a.out, t % kSetupLanes, a.ext_k);
+}
+
+__global__ __launch_bounds__(kDrawThreads) void k_sample_params(SampleArgs a) {
+  draw_block(a, a.cf, blockIdx.x, threadIdx.x, kDrawThreads);
 }
 
 // -------------------------------------------------------- plus / cross
@@ -70,7 +72,7 @@ template <class TP, bool FULL>
 __global__ __launch_bounds__(256) void k_gen_fd_waveform(WaveArgs a) {
   __shared__ WfScalars w;
   const int64_t b = blockIdx.x;
-  if (threadIdx.x == 0) wf_setup(a.params, a.B, b, a.cf, w);
+  if (threadIdx.x < kSetupLanes) wf_setup_column(a.params, a.B, b, a.cf, threadIdx.x, &w);
   __syncthreads();
   const int F = a.cf.F;
   for (int k = threadIdx.x; k < F; k += 256) {
@@ -122,8 +124,11 @@ __global__ __launch_bounds__(256) void k_project(ProjArgs a) {
   const int D = a.cf.n_det;
   if (threadIdx.x < D) {
     const int64_t B = a.B;
-    ds[threadIdx.x] = det_response(a.cf.det[threadIdx.x], a.params[6 * B + b], a.params[7 * B + b],
-                                   a.params[8 * B + b], a.params[10 * B + b]);
+    SkyAngles sky;
+    sincos(a.params[6 * B + b], &sky.sr, &sky.cr);
+    sincos(a.params[7 * B + b], &sky.sd, &sky.cd);
+    sincos(a.params[8 * B + b], &sky.sp, &sky.cp);
+    ds[threadIdx.x] = det_response(a.cf.det[threadIdx.x], sky, a.params[10 * B + b]);
   }
   __syncthreads();
   const int k = blockIdx.x * 256 + threadIdx.x;
@@ -178,28 +183,55 @@ __global__ __launch_bounds__(NC / 16, WinOcc<NC>::value) void k_window(WinArgs a
 }
 
 // ------------------------------------------------------------------ Welch
+// Launched with the batch's prior draws: the first n_draw workgroups make them,
+// so that they run beside the Welch workgroups, which draw the one number they
+// need themselves (the background offset).  As a launch of its own ahead of
+// Welch the draws took 25 us of a single sample's 113 us.
 struct WelchArgs {
   DevCfg cf;
   const float* bg;
   int64_t L_bg;
-  const int64_t* offset;
+  const int64_t* offset;  // [B] (n_draw = 0)
   float* psd;
   const void* tw;  // Welch table of L (WelchTab)
   double norm;     // 1 / (K fs sum w^2)
+  WelchCut cut;
+  void* part;      // ACC[2 G][L/2 + 1] sums of cut items
+  int64_t n_draw;
+  SampleArgs draw;  // (its cf is unused)
 };
 
-// OCC: waves per SIMD the register allocation must allow (2, or 3 with the
-// loop-invariant twiddles partly spilled and reloaded per segment pair).
+// OCC: waves per SIMD the register allocation must allow.
 template <class T, class ACC, int NC, int ORD, int OCC>
 __global__ __launch_bounds__(NC / 16, OCC) void k_welch(WelchArgs a) {
-  constexpr int LS = LdsSize<NC>::value;
+  constexpr int LS = LdsSize<NC>::value, Fw = NC / 2 + 1;
   __shared__ T lds[2 * LS];
-  const int64_t bd = blockIdx.x;
-  const int D = a.cf.n_det;
-  const int64_t b = bd / D;
-  const int d = int(bd - b * D);
-  welch_item<T, ACC, NC, ORD>(a.cf.K, a.norm, threadIdx.x, a.bg + int64_t(d) * a.L_bg + a.offset[b],
-                              a.psd + bd * a.cf.Fw, reinterpret_cast<const T*>(a.tw), lds, lds + LS, true);
+  const int t = threadIdx.x;
+  if (blockIdx.x < a.n_draw) {
+    draw_block(a.draw, a.cf, blockIdx.x, t, NC / 16);
+    return;
+  }
+  ACC* part = static_cast<ACC*>(a.part);
+  welch_pieces<T, ACC, NC, ORD>(
+      a.cut, int(blockIdx.x - a.n_draw), a.cf.K, t, static_cast<const T*>(a.tw), lds, lds + LS,
+      [&](int item) {
+        const int b = item / a.cf.n_det, d = item - b * a.cf.n_det;
+        const int64_t o = a.n_draw ? draw_offset(a.draw.seed, a.draw.first_index() + uint64_t(b), a.draw.ext_k, a.draw.span)
+                                   : a.offset[b];
+        return a.bg + int64_t(d) * a.L_bg + o;
+      },
+      [&](int item, int k, ACC sum) { a.psd[int64_t(item) * Fw + k] = float(sum * ACC(a.norm)); },
+      [&](int slot, int k, ACC sum) { part[int64_t(slot) * Fw + k] = sum; });
+}
+
+// PSDs of the items that were cut: grid (ceil(Fw/256), G - 1).
+template <class ACC>
+__global__ __launch_bounds__(256) void k_welch_sum(WelchCut cut, const ACC* part, int Fw, double norm, float* psd) {
+  const int k = blockIdx.x * 256 + threadIdx.x;
+  const int kc = min(k, Fw - 1);
+  ACC sum = ACC(0);
+  const int item = welch_cut_item(cut, int(blockIdx.y) + 1, [&](int slot) { sum += part[int64_t(slot) * Fw + kc]; });
+  if (item >= 0 && k < Fw) psd[int64_t(item) * Fw + k] = float(sum * ACC(norm));
 }
 
 __global__ void k_fill_u32(uint32_t* p, int64_t n, uint32_t v) {
@@ -643,6 +675,39 @@ static int64_t ws_counter_offset(const DevCfg& d, int64_t B) {
   return ws_params_bytes(B) + ws_offset_bytes(B) + ws_psd_bytes(d, B) + ws_wf_bytes(B) + ws_det_bytes(d, B);
 }
 
+// bytes of the batch's arrays and counter, the least a batch call accepts
+static int64_t ws_base_bytes(const DevCfg& d, int64_t B) { return ws_counter_offset(d, B) + 256; }
+
+// How `items` stretches are divided over the Welch workgroups a launch keeps
+// resident (`slots`).  One item per workgroup leaves the chip idle for part of
+// the last round, and wholly so with fewer items than slots: 6144 items are 8
+// rounds of 768, but 903 took as long as 1536 (190 us) and 3 as long as 256
+// (81 us, one workgroup's chain of 32 transforms).  Cutting costs the pieces'
+// sums (2 * slots * 16 KB written and read, about 8 transforms' time with the
+// launch that adds them), so items are cut where the whole rounds would take
+// longer than equal shares by more than that.  Binary32 sums (mode 0) are not
+// cut: their order would show in the result.
+static WelchCut welch_whole(const DevCfg& d, int64_t items) {
+  const int np = (d.K + 1) / 2;
+  return WelchCut{int(items), np, 0, np};
+}
+static WelchCut welch_cut(const gw_ctx* c, int64_t items) {
+  const DevCfg& d = c->dc;
+  const int64_t np = (d.K + 1) / 2, total = items * np;
+  // workgroups per CU: registers allow 3 waves per SIMD (binary64 transforms: 1)
+  const int64_t waves = d.precision == 2 ? 1 : 3;
+  const int64_t slots = c->n_cu * (waves * 4 / (d.L / 1024));
+  if (d.precision == 0 || items <= 0 || items > 16 * slots || total >= (int64_t(1) << 31)) return welch_whole(d, items);
+  const int64_t rounds = (items + slots - 1) / slots * np, share = (total + slots - 1) / slots;
+  if (rounds <= share + 8) return welch_whole(d, items);
+  const int64_t G = std::min(slots, total);
+  return WelchCut{int(G), int(total / G), int(total % G), int(np)};
+}
+static int64_t ws_cut_bytes(const gw_ctx* c, int64_t items) {
+  const WelchCut cut = welch_cut(c, items);
+  return cut.whole() ? 0 : 2 * int64_t(cut.G) * c->dc.Fw * int64_t(sizeof(double));
+}
+
 // dispatch a k_window instantiation on the window FFT size and radix order
 template <class T, class TP, bool FULL, int SRC, int ORD>
 static void launch_window_ord(const DevCfg& d, int64_t blocks, const WinArgs& a, hipStream_t stream) {
@@ -689,26 +754,28 @@ static WinArgs win_args(gw_ctx* c) {
 }
 
 template <class T, class ACC, int OCC>
-static void launch_welch_occ(const DevCfg& d, int64_t blocks, const WelchArgs& a, hipStream_t stream) {
+static void launch_welch_occ(const DevCfg& d, const WelchArgs& a, hipStream_t stream) {
+  const dim3 grid(unsigned(a.n_draw + a.cut.G));
   if (d.L == 2048) {
-    if (d.ord_welch)
-      hipLaunchKernelGGL((k_welch<T, ACC, 2048, 1, OCC>), dim3(unsigned(blocks)), dim3(128), 0, stream, a);
+    if (sizeof(T) == 4 && d.ord_welch)
+      hipLaunchKernelGGL((k_welch<T, ACC, 2048, sizeof(T) == 4 ? 1 : 0, OCC>), grid, dim3(128), 0, stream, a);
     else
-      hipLaunchKernelGGL((k_welch<T, ACC, 2048, 0, OCC>), dim3(unsigned(blocks)), dim3(128), 0, stream, a);
+      hipLaunchKernelGGL((k_welch<T, ACC, 2048, 0, OCC>), grid, dim3(128), 0, stream, a);
   } else {
-    hipLaunchKernelGGL((k_welch<T, ACC, 4096, 0, OCC>), dim3(unsigned(blocks)), dim3(256), 0, stream, a);
+    hipLaunchKernelGGL((k_welch<T, ACC, 4096, 0, OCC>), grid, dim3(256), 0, stream, a);
   }
 }
 
+// binary64 transforms: one radix order, occupancy as the registers allow
 template <class T, class ACC>
-static void launch_welch(const DevCfg& d, int64_t blocks, const WelchArgs& a, hipStream_t stream) {
-  if constexpr (sizeof(T) == 4) {
-    if (d.occ_welch == 3) launch_welch_occ<T, ACC, 3>(d, blocks, a, stream);
-    else launch_welch_occ<T, ACC, 2>(d, blocks, a, stream);
-  } else {
-    // binary64: one radix order, occupancy as the registers allow
-    if (d.L == 2048) hipLaunchKernelGGL((k_welch<T, ACC, 2048, 0, 1>), dim3(unsigned(blocks)), dim3(128), 0, stream, a);
-    else hipLaunchKernelGGL((k_welch<T, ACC, 4096, 0, 1>), dim3(unsigned(blocks)), dim3(256), 0, stream, a);
+static void launch_welch(const DevCfg& d, const WelchArgs& a, hipStream_t stream) {
+  if constexpr (sizeof(T) == 8) launch_welch_occ<T, ACC, 1>(d, a, stream);
+  else if (d.occ_welch == 3) launch_welch_occ<T, ACC, 3>(d, a, stream);
+  else launch_welch_occ<T, ACC, 2>(d, a, stream);
+  if (!a.cut.whole()) {
+    const dim3 grid(unsigned((d.Fw + 255) / 256), unsigned(a.cut.G - 1));
+    hipLaunchKernelGGL((k_welch_sum<ACC>), grid, dim3(256), 0, stream, a.cut, static_cast<const ACC*>(a.part), d.Fw,
+                       a.norm, a.psd);
   }
 }
 
@@ -726,14 +793,30 @@ static void launch_filter(const DevCfg& d, const FiltArgs& a, hipStream_t stream
   }
 }
 
+// Welch PSDs of B samples.  part (part_bytes, may be NULL): room for the sums
+// of cut items; too little of it and no item is cut.  draw: the batch's prior
+// draws, made by the same launch (offset is then not read), or NULL.
 static gw_status welch_launch(gw_ctx* c, const float* bg, int64_t L_bg, const int64_t* offset, int64_t B,
-                              float* psd, hipStream_t stream) {
+                              float* psd, void* part, int64_t part_bytes, const SampleArgs* draw, hipStream_t stream) {
   const DevCfg& d = c->dc;
-  WelchArgs a{d, bg, L_bg, offset, psd, c->tw_welch, 1.0 / (double(d.K) * d.fs * (3.0 * d.L / 8.0))};
-  const int64_t blocks = B * d.n_det;
-  if (d.precision == 0) launch_welch<float, float>(d, blocks, a, stream);
-  else if (d.precision == 1) launch_welch<float, double>(d, blocks, a, stream);
-  else launch_welch<double, double>(d, blocks, a, stream);
+  WelchArgs a{};
+  a.cf = d;
+  a.bg = bg;
+  a.L_bg = L_bg;
+  a.offset = offset;
+  a.psd = psd;
+  a.tw = c->tw_welch;
+  a.norm = 1.0 / (double(d.K) * d.fs * (3.0 * d.L / 8.0));
+  const int64_t items = B * d.n_det;
+  a.cut = part && ws_cut_bytes(c, items) <= part_bytes ? welch_cut(c, items) : welch_whole(d, items);
+  a.part = part;
+  if (draw) {
+    a.draw = *draw;
+    a.n_draw = draw_blocks(B, d.L / 16);
+  }
+  if (d.precision == 0) launch_welch<float, float>(d, a, stream);
+  else if (d.precision == 1) launch_welch<float, double>(d, a, stream);
+  else launch_welch<double, double>(d, a, stream);
   return check_launch(c, "k_welch");
 }
 
@@ -750,11 +833,14 @@ static gw_status check_batch_args(gw_ctx* c, int64_t B, const float* bg, int64_t
   if (!aligned4(bg) || !aligned16(out) || !aligned16(workspace) || (params_f32 && !aligned16(params_f32)) ||
       (status && !aligned4(status)))
     return fail(c, GW_EINVAL, "misaligned pointer");
-  int64_t need = 0;
-  gw_workspace_size(c, B, &need);
-  if (workspace_bytes < need) return fail(c, GW_EINVAL, "workspace too small");
+  if (workspace_bytes < ws_base_bytes(c->dc, B)) return fail(c, GW_EINVAL, "workspace too small");
   if (L_bg - c->dc.P - c->dc.N + 1 <= 0) return fail(c, GW_EINVAL, "L_bg < P + N");
   return GW_OK;
+}
+
+static gw_status draw_launch(gw_ctx* c, const SampleArgs& a, hipStream_t stream) {
+  hipLaunchKernelGGL(k_sample_params, dim3(unsigned(draw_blocks(a.B, kDrawThreads))), dim3(kDrawThreads), 0, stream, a);
+  return check_launch(c, "k_sample_params");
 }
 
 // Queue the fused batch (prior draws, Welch PSDs, fused window kernel), or
@@ -762,8 +848,8 @@ static gw_status check_batch_args(gw_ctx* c, int64_t B, const float* bg, int64_t
 // batch index at run time for graph replays.
 static gw_status enqueue_batch(gw_ctx* c, uint64_t seed, uint64_t batch_index, const uint64_t* batch, int64_t B,
                                const float* bg, int64_t L_bg, float* out, float* params_f32, uint32_t* status,
-                               void* workspace, int stages, hipStream_t stream, uint32_t ext_k = 1,
-                               float* out_ref = nullptr) {
+                               void* workspace, int64_t workspace_bytes, int stages, hipStream_t stream,
+                               uint32_t ext_k = 1, float* out_ref = nullptr) {
   const int64_t span = L_bg - c->dc.P - c->dc.N + 1;
   char* ws = static_cast<char*>(workspace);
   double* params = reinterpret_cast<double*>(ws);
@@ -772,15 +858,15 @@ static gw_status enqueue_batch(gw_ctx* c, uint64_t seed, uint64_t batch_index, c
   WfScalars* wf = reinterpret_cast<WfScalars*>(ws + ws_params_bytes(B) + ws_offset_bytes(B) + ws_psd_bytes(c->dc, B));
   DetScalars* dsc = reinterpret_cast<DetScalars*>(reinterpret_cast<char*>(wf) + ws_wf_bytes(B));
   gw_status s = GW_OK;
-  if (stages & kStageParams) {
-    SampleArgs sa{c->dc, seed, batch_index * uint64_t(B), batch, B, span, params, offset, params_f32, status, wf, dsc,
-                  ext_k};
-    hipLaunchKernelGGL(k_sample_params, dim3(unsigned((B + 255) / 256)), dim3(256), 0, stream, sa);
-    s = check_launch(c, "k_sample_params");
-    if (s != GW_OK) return s;
-  }
+  const SampleArgs sa{c->dc, seed, batch_index * uint64_t(B), batch, B, span, {params, offset, params_f32, wf, dsc, status},
+                      ext_k};
   if (stages & kStageWelch) {
-    s = welch_launch(c, bg, L_bg, offset, B, psd, stream);
+    const int64_t base = ws_base_bytes(c->dc, B);
+    s = welch_launch(c, bg, L_bg, offset, B, psd, ws + base, workspace_bytes - base,
+                     (stages & kStageParams) ? &sa : nullptr, stream);
+    if (s != GW_OK) return s;
+  } else if (stages & kStageParams) {
+    s = draw_launch(c, sa, stream);
     if (s != GW_OK) return s;
   }
   if (stages & kStageWindow) {
@@ -859,6 +945,8 @@ gw_status gw_create(const gw_config* cfg, gw_ctx** out) {
     gw_destroy(c);
     return GW_EHIP;
   }
+  if (hipDeviceGetAttribute(&c->n_cu, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess || c->n_cu < 1)
+    c->n_cu = 256;
   s = resolve_scratch(c->device, &c->scratch, &c->err);
   if (s != GW_OK) {
     gw_destroy(c);
@@ -922,7 +1010,7 @@ gw_status gw_query(const gw_ctx* c, int32_t key, int64_t* value) {
 
 gw_status gw_workspace_size(const gw_ctx* c, int64_t B, int64_t* bytes) {
   if (!c || !bytes || B < 0) return GW_EINVAL;
-  *bytes = ws_counter_offset(c->dc, B) + 256;
+  *bytes = ws_base_bytes(c->dc, B) + ws_cut_bytes(c, B * c->dc.n_det);
   return GW_OK;
 }
 
@@ -938,9 +1026,7 @@ gw_status sample_params(gw_ctx* c, uint64_t seed, uint64_t first_index, int64_t 
   if (!aligned16(params) || !aligned16(offset)) return fail(c, GW_EINVAL, "params/offset not 16-byte aligned");
   const int64_t span = L_bg - c->dc.P - c->dc.N + 1;
   if (span <= 0) return fail(c, GW_EINVAL, "L_bg < P + N");
-  SampleArgs a{c->dc, seed, first_index, nullptr, B, span, params, offset, nullptr, nullptr, nullptr, nullptr};
-  hipLaunchKernelGGL(k_sample_params, dim3(unsigned((B + 255) / 256)), dim3(256), 0, stream, a);
-  return check_launch(c, "k_sample_params");
+  return draw_launch(c, SampleArgs{c->dc, seed, first_index, nullptr, B, span, {params, offset}}, stream);
 }
 
 gw_status gen_fd_waveform(gw_ctx* c, const double* params, int64_t B, float* hp, float* hc, hipStream_t stream) {
@@ -1000,7 +1086,7 @@ gw_status welch_psd(gw_ctx* c, const float* bg, int64_t L_bg, const int64_t* off
   if (!bg || !offset || !psd) return fail(c, GW_EINVAL, "NULL pointer");
   if (!aligned4(bg) || !aligned16(offset) || !aligned16(psd)) return fail(c, GW_EINVAL, "misaligned pointer");
   if (L_bg < int64_t(c->dc.P) + c->dc.N) return fail(c, GW_EINVAL, "L_bg < P + N");
-  return welch_launch(c, bg, L_bg, offset, B, psd, stream);
+  return welch_launch(c, bg, L_bg, offset, B, psd, nullptr, 0, nullptr, stream);
 }
 
 gw_status whiten(gw_ctx* c, const float* strain, const float* psd, int64_t B, float* out, uint32_t* status,
@@ -1029,10 +1115,13 @@ gw_status whiten(gw_ctx* c, const float* strain, const float* psd, int64_t B, fl
 static int64_t ws_nodes_bytes(int64_t B) { return ((B * 2 * 1024 * 4 + 255) / 256) * 256; }
 static int64_t ws_logmm_bytes(int64_t B) { return ((B * 4 + 255) / 256) * 256; }
 
+static int64_t ws_surrogate_bytes(const DevCfg& d, int64_t B) {
+  return ws_base_bytes(d, B) + ws_nodes_bytes(B) + ws_logmm_bytes(B);
+}
+
 gw_status gw_workspace_size_surrogate(const gw_ctx* c, int64_t B, int64_t* bytes) {
-  gw_status s = gw_workspace_size(c, B, bytes);
-  if (s != GW_OK) return s;
-  *bytes += ws_nodes_bytes(B) + ws_logmm_bytes(B);
+  if (!c || !bytes || B < 0) return GW_EINVAL;
+  *bytes = ws_surrogate_bytes(c->dc, B) + ws_cut_bytes(c, B * c->dc.n_det);
   return GW_OK;
 }
 
@@ -1049,9 +1138,8 @@ gw_status gw_generate_batch_surrogate(gw_ctx* c, gw_surrogate* sg, uint64_t seed
   if (!aligned4(bg) || !aligned16(out) || !aligned16(workspace) || (params_f32 && !aligned16(params_f32)) ||
       (status && !aligned4(status)))
     return fail(c, GW_EINVAL, "misaligned pointer");
-  int64_t need = 0;
-  gw_workspace_size_surrogate(c, B, &need);
-  if (workspace_bytes < need) return fail(c, GW_EINVAL, "workspace too small");
+  const int64_t base = ws_surrogate_bytes(c->dc, B);
+  if (workspace_bytes < base) return fail(c, GW_EINVAL, "workspace too small");
   const int64_t span = L_bg - c->dc.P - c->dc.N + 1;
   if (span <= 0) return fail(c, GW_EINVAL, "L_bg < P + N");
   if (batch_index > (UINT64_MAX - uint64_t(B)) / uint64_t(B)) return fail(c, GW_EINVAL, "batch_index overflows");
@@ -1061,15 +1149,14 @@ gw_status gw_generate_batch_surrogate(gw_ctx* c, gw_surrogate* sg, uint64_t seed
   float* psd = reinterpret_cast<float*>(ws + ws_params_bytes(B) + ws_offset_bytes(B));
   WfScalars* wf = reinterpret_cast<WfScalars*>(ws + ws_params_bytes(B) + ws_offset_bytes(B) + ws_psd_bytes(c->dc, B));
   DetScalars* dsc = reinterpret_cast<DetScalars*>(reinterpret_cast<char*>(wf) + ws_wf_bytes(B));
-  float* nodes = reinterpret_cast<float*>(ws + ws_counter_offset(c->dc, B) + 256);
+  float* nodes = reinterpret_cast<float*>(ws + ws_base_bytes(c->dc, B));
   float* logmm = reinterpret_cast<float*>(reinterpret_cast<char*>(nodes) + ws_nodes_bytes(B));
-  SampleArgs sa{c->dc, seed, batch_index * uint64_t(B), nullptr, B, span, params, offset, params_f32, status, wf, dsc};
-  hipLaunchKernelGGL(k_sample_params, dim3(unsigned((B + 255) / 256)), dim3(256), 0, stream, sa);
-  gw_status s = check_launch(c, "k_sample_params");
+  gw_status s = draw_launch(c, SampleArgs{c->dc, seed, batch_index * uint64_t(B), nullptr, B, span,
+                                          {params, offset, params_f32, wf, dsc, status}}, stream);
   if (s != GW_OK) return s;
   s = gw_surrogate_nodes(sg, params, B, nodes, logmm, stream);
   if (s != GW_OK) return fail(c, s, std::string("surrogate: ") + gw_surrogate_last_error(sg));
-  s = welch_launch(c, bg, L_bg, offset, B, psd, stream);
+  s = welch_launch(c, bg, L_bg, offset, B, psd, ws + base, workspace_bytes - base, nullptr, stream);
   if (s != GW_OK) return s;
   WinArgs a = win_args(c);
   a.src = bg;
@@ -1096,8 +1183,8 @@ gw_status gw_generate_batch(gw_ctx* c, uint64_t seed, uint64_t batch_index, int6
   gw_status s = check_batch_args(c, B, bg, L_bg, out, params_f32, status, workspace, workspace_bytes);
   if (s != GW_OK || B == 0) return s;
   if (batch_index > (UINT64_MAX - uint64_t(B)) / uint64_t(B)) return fail(c, GW_EINVAL, "batch_index overflows");
-  return enqueue_batch(c, seed, batch_index, nullptr, B, bg, L_bg, out, params_f32, status, workspace, kStageAll,
-                       stream);
+  return enqueue_batch(c, seed, batch_index, nullptr, B, bg, L_bg, out, params_f32, status, workspace, workspace_bytes,
+                       kStageAll, stream);
 }
 
 gw_status gw_generate_batch_noalloc(gw_ctx* c, uint64_t seed, uint64_t batch_index, int64_t B, const float* bg,
@@ -1105,8 +1192,7 @@ gw_status gw_generate_batch_noalloc(gw_ctx* c, uint64_t seed, uint64_t batch_ind
                                     hipStream_t stream) {
   GW_CHECK_CTX(c);
   if (B < 0) return fail(c, GW_EINVAL, "bad B");
-  int64_t need = 0;
-  gw_workspace_size(c, B, &need);
+  const int64_t need = ws_base_bytes(c->dc, B);
   if (need > GW_SCRATCH_BYTES)
     return fail(c, GW_EINVAL, "batch too large for the static scratch area (needs " + std::to_string(need) +
                                   " bytes, the area holds " + std::to_string(int64_t(GW_SCRATCH_BYTES)) + ")");
@@ -1130,7 +1216,8 @@ gw_status gw_graph_create(gw_ctx* c, uint64_t seed, uint64_t first_batch, int64_
   std::string why;
   s = capture_graph(
       [&](hipStream_t st) {
-        return enqueue_batch(c, seed, 0, batch, B, bg, L_bg, out, params_f32, status, workspace, kStageAll, st);
+        return enqueue_batch(c, seed, 0, batch, B, bg, L_bg, out, params_f32, status, workspace, workspace_bytes,
+                             kStageAll, st);
       },
       batch, first_batch, graph, &why);
   if (s != GW_OK) return fail(c, s, why);
@@ -1213,10 +1300,10 @@ gw_status gw_autotune(gw_ctx* c, int64_t B, const float* bg, int64_t L_bg, float
   const bool b64 = c->dc.precision == 2;
   const int saved[3] = {c->dc.ord_welch, c->dc.occ_welch, c->dc.ord_win};
   auto time_stage = [&](int mask, double* res) {
-    s = enqueue_batch(c, 1, 0, nullptr, B, bg, L_bg, out, nullptr, nullptr, workspace, mask, st);  // warm-up
+    s = enqueue_batch(c, 1, 0, nullptr, B, bg, L_bg, out, nullptr, nullptr, workspace, workspace_bytes, mask, st);  // warm-up
     if (s == GW_OK && hipEventRecord(e0, st) != hipSuccess) s = fail(c, GW_EHIP, "hipEventRecord");
     for (int r = 0; r < reps && s == GW_OK; ++r)
-      s = enqueue_batch(c, 1, 0, nullptr, B, bg, L_bg, out, nullptr, nullptr, workspace, mask, st);
+      s = enqueue_batch(c, 1, 0, nullptr, B, bg, L_bg, out, nullptr, nullptr, workspace, workspace_bytes, mask, st);
     if (s == GW_OK && hipEventRecord(e1, st) != hipSuccess) s = fail(c, GW_EHIP, "hipEventRecord");
     if (s == GW_OK && hipEventSynchronize(e1) != hipSuccess) s = fail(c, GW_EHIP, "hipEventSynchronize");
     // a failed timing query fails the tuner rather than reading as 0 ms
@@ -1227,7 +1314,7 @@ gw_status gw_autotune(gw_ctx* c, int64_t B, const float* bg, int64_t L_bg, float
   if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) {
     s = fail(c, GW_EHIP, "hipEventCreate");
   } else {
-    s = enqueue_batch(c, 1, 0, nullptr, B, bg, L_bg, out, nullptr, nullptr, workspace, kStageAll, st);
+    s = enqueue_batch(c, 1, 0, nullptr, B, bg, L_bg, out, nullptr, nullptr, workspace, workspace_bytes, kStageAll, st);
     for (int round = 0; round < kTuneRounds && s == GW_OK; ++round) {
       for (int v = 0; v < 4 && s == GW_OK; ++v) {
         if (b64 && v > 0) { ms[v] = ms[0]; continue; }
@@ -1289,7 +1376,7 @@ gw_status gw_run_psd(gw_ctx* c, const float* bg, int64_t L_bg, int64_t n_chunks,
                      stride);
   gw_status s = check_launch(c, "k_chunk_offsets");
   if (s != GW_OK) return s;
-  s = welch_launch(c, bg, L_bg, off, n_chunks, part, stream);
+  s = welch_launch(c, bg, L_bg, off, n_chunks, part, nullptr, 0, nullptr, stream);
   if (s != GW_OK) return s;
   const int n = d.n_det * d.Fw;
   hipLaunchKernelGGL(k_mean_chunks, dim3(unsigned((n + 255) / 256)), dim3(256), 0, stream, part, n_chunks, d.n_det,
@@ -1322,8 +1409,8 @@ gw_status gw_generate_batch_runpsd(gw_ctx* c, uint64_t seed, uint64_t batch_inde
   if (c->dc.N > 32768) return fail(c, GW_EUNSUPPORTED, "the per-run mode needs N <= 32768");
   if (crop < 0 || (crop & 1) || 2 * crop >= c->dc.N) return fail(c, GW_EINVAL, "crop must be even with 2 crop < N");
   if (batch_index > (UINT64_MAX - uint64_t(B)) / uint64_t(B)) return fail(c, GW_EINVAL, "batch_index overflows");
-  s = enqueue_batch(c, seed, batch_index, nullptr, B, bg, L_bg, out, params_f32, status, workspace, kStageParams,
-                    stream);
+  s = enqueue_batch(c, seed, batch_index, nullptr, B, bg, L_bg, out, params_f32, status, workspace, workspace_bytes,
+                    kStageParams, stream);
   if (s != GW_OK) return s;
   char* ws = static_cast<char*>(workspace);
   WinArgs a = win_args(c);
@@ -1352,8 +1439,8 @@ gw_status gw_generate_batch_pairs(gw_ctx* c, uint64_t seed, uint64_t batch_index
   if (s != GW_OK || B == 0) return s;
   if (!out_ref || !aligned16(out_ref)) return fail(c, GW_EINVAL, "out_ref NULL or misaligned");
   if (batch_index > (UINT64_MAX - uint64_t(B)) / uint64_t(B)) return fail(c, GW_EINVAL, "batch_index overflows");
-  return enqueue_batch(c, seed, batch_index, nullptr, B, bg, L_bg, out_shift, params_f32, status, workspace, kStageAll,
-                       stream, 1u, out_ref);
+  return enqueue_batch(c, seed, batch_index, nullptr, B, bg, L_bg, out_shift, params_f32, status, workspace,
+                       workspace_bytes, kStageAll, stream, 1u, out_ref);
 }
 
 gw_status gw_generate_batch_oversampled(gw_ctx* c, uint64_t seed, uint64_t batch_index, int64_t B, int32_t ext_k,
@@ -1365,8 +1452,8 @@ gw_status gw_generate_batch_oversampled(gw_ctx* c, uint64_t seed, uint64_t batch
   gw_status s = check_batch_args(c, B, bg, L_bg, out, params_f32, status, workspace, workspace_bytes);
   if (s != GW_OK || B == 0) return s;
   if (batch_index > (UINT64_MAX - uint64_t(B)) / uint64_t(B)) return fail(c, GW_EINVAL, "batch_index overflows");
-  return enqueue_batch(c, seed, batch_index, nullptr, B, bg, L_bg, out, params_f32, status, workspace, kStageAll,
-                       stream, uint32_t(ext_k));
+  return enqueue_batch(c, seed, batch_index, nullptr, B, bg, L_bg, out, params_f32, status, workspace,
+                       workspace_bytes, kStageAll, stream, uint32_t(ext_k));
 }
 
 }  // extern "C"
