@@ -124,7 +124,10 @@ const char* gw_last_error(const gw_ctx* ctx);
 #define GW_Q_NDET     6
 #define GW_Q_NPARAMS  7
 gw_status gw_query(const gw_ctx* ctx, int32_t key, int64_t* value);
-/* Bytes of device workspace gw_generate_batch needs for batch size B. */
+/* Bytes of device workspace gw_generate_batch uses for batch size B.  The last
+ * part holds the sums of background stretches that the Welch stage divides
+ * between workgroups (at most 26 MB, for batches of few stretches); a workspace
+ * without it is accepted and no stretch is divided then. */
 gw_status gw_workspace_size(const gw_ctx* ctx, int64_t B, int64_t* bytes);
 
 /* sample_params -- prior draws (Table 1, section 5; ranges from gw_config).
@@ -195,9 +198,11 @@ gw_status welch_psd(gw_ctx* ctx, const float* bg, int64_t L_bg,
 gw_status whiten(gw_ctx* ctx, const float* strain, const float* psd,
                  int64_t B, float* out, uint32_t* status, hipStream_t stream);
 
-/* gw_generate_batch -- the whole per-batch path (section 3.2) in three
- * launches: prior draws, per-(sample, detector) Welch PSDs, then one fused
- * kernel per (sample, detector).  The fused kernel loads the noise window,
+/* gw_generate_batch -- the whole per-batch path (section 3.2): one launch of
+ * the prior draws and the per-(sample, detector) Welch PSDs (with few or
+ * unevenly many stretches a second one that adds the sums of stretches divided
+ * between workgroups), then one fused kernel per (sample, detector).  The
+ * fused kernel loads the noise window,
  * transforms it, adds the in-register waveform + projection + time shift,
  * whitens, inverse-transforms and stores.  The result equals
  * sample_params -> gen_fd_waveform -> project_detectors -> inject ->
@@ -353,10 +358,11 @@ gw_status gw_autotune(gw_ctx* ctx, int64_t B, const float* bg, int64_t L_bg,
  * handle is created (host array cls[B]); parameters, offsets and noise are
  * drawn per batch exactly as gw_generate_batch draws them for the class's
  * configuration at global index batch_index*B + i, with parameter row 11
- * set to the class index.  Each stage is ONE persistent launch over all
- * classes: a Welch kernel and a fused window kernel pull groups of
- * (signal, detector) items of one class from an atomic queue, largest
- * transforms first; small transforms share a workgroup as sub-blocks.
+ * set to the class index.  Each stage runs as one persistent launch over all
+ * classes, whose workgroups pull groups of (signal, detector) items of one
+ * class from an atomic queue, largest transforms first (small transforms share
+ * a workgroup as sub-blocks), or as one launch per transform size (see
+ * GW_RTUNE_*).
  * Output: one flat float buffer; signal i occupies [n_det][N_i] floats from
  * out_offset[i] (gw_ragged_offsets).
  * ------------------------------------------------------------------------ */
@@ -384,7 +390,9 @@ gw_status gw_ragged_offsets(const gw_ragged* r, int64_t* out_offset, int64_t* ps
  * [GW_RQ_OUT_FLOATS]; params_f32: float [12][B] or NULL; status: uint32
  * [B] or NULL.  Workspace layout: params double [12][B], offsets int64 [B],
  * then per-sample constants, the queue/batch counters, and the PSDs from
- * byte GW_RQ_PSD_OFFSET. */
+ * byte GW_RQ_PSD_OFFSET, then the sums of items that Welch mode 1 divides
+ * between workgroups.  A workspace that ends with the PSDs is accepted too:
+ * no item is divided then. */
 gw_status gw_generate_ragged(gw_ragged* r, uint64_t seed, uint64_t batch_index,
                              const float* const* bg, const int64_t* L_bg,
                              float* out, float* params_f32, uint32_t* status,
@@ -399,11 +407,11 @@ gw_status gw_ragged_graph_create(gw_ragged* r, uint64_t seed, uint64_t first_bat
 /* Ragged kernel variants: radix orders as for gw_set_tuning, the
  * persistent grid of each stage in workgroups per compute unit (1..8), and
  * each stage's issue mode.  Window mode: 0 one persistent launch over all
- * classes (default), 1 one launch per class (largest first) with one
+ * classes (default), 1 one launch per window length (largest first) with one
  * NC/16-thread workgroup per item.  Welch mode: 0 one persistent launch, 1
- * one launch per class (largest transform first, default) with one
- * L/16-thread workgroup per item at 3 waves per SIMD; the Welch grid only
- * applies to mode 0. */
+ * one launch per segment length (largest first, default) of L/16-thread
+ * workgroups at 3 waves per SIMD, the items' segments in equal shares; the
+ * Welch grid only applies to mode 0. */
 #define GW_RTUNE_ORD_WINDOW 1
 #define GW_RTUNE_ORD_WELCH  2
 #define GW_RTUNE_GRID_WINDOW 3

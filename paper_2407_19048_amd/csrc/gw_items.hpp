@@ -635,26 +635,28 @@ struct WelchCut {
   __device__ __forceinline__ int start(int w) const { return w * q + int(uint32_t(w) * uint32_t(r) / uint32_t(G)); }
 };
 
-// Runs workgroup w's pieces: src(item) gives the stretch, whole(item, k, sum)
-// and piece(slot, k, sum) take bin k's one-sided sum.
-template <class T, class ACC, int NC, int ORD, class Src, class Whole, class Piece>
-__device__ __forceinline__ void welch_pieces(const WelchCut& cut, int w, int K, int t, const T* tab, T* sre, T* sim,
-                                             Src src, Whole whole, Piece piece) {
+// A stretch to sum: its first sample, segments and segment pairs.
+struct WelchStretch {
+  const float* x;
+  int K, np;
+};
+
+// Runs a workgroup's `left` pairs from pair p0 of `item` on: stretch(item)
+// gives the item, whole(item, k, sum) and piece(n, item, k, sum) take bin k's
+// one-sided sum of a whole item and of a piece (n = 0: of the first item, 1: of
+// the last).
+template <class T, class ACC, int NC, int ORD, class Stretch, class Whole, class Piece>
+__device__ __forceinline__ void welch_pieces(int item, int p0, int left, int t, const T* tab, T* sre, T* sim,
+                                             Stretch stretch, Whole whole, Piece piece) {
   WelchItem<T, ACC, NC, ORD> wi(tab, t, sre, sim);
-  int item = w, p0 = 0, left = cut.np;
-  if (!cut.whole()) {
-    const int begin = cut.start(w);
-    item = begin / cut.np;
-    p0 = begin - item * cut.np;
-    left = cut.start(w + 1) - begin;
-  }
   const int first = item;
 #pragma unroll 1
   while (left > 0) {
-    const int p1 = min(cut.np, p0 + left);
-    wi.pairs(src(item), K, p0, p1);
-    if (p1 - p0 == cut.np) wi.fold([&](int k, ACC s) { whole(item, k, s); });
-    else wi.fold([&](int k, ACC s) { piece(2 * w + (item == first ? 0 : 1), k, s); });
+    const WelchStretch st = stretch(item);
+    const int p1 = min(st.np, p0 + left);
+    wi.pairs(st.x, st.K, p0, p1);
+    if (p1 - p0 == st.np) wi.fold([&](int k, ACC s) { whole(item, k, s); });
+    else wi.fold([&](int k, ACC s) { piece(item == first ? 0 : 1, item, k, s); });
     left -= p1 - p0;
     p0 = 0;
     ++item;

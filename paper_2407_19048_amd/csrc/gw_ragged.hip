@@ -1,21 +1,24 @@
 // Uneven (ragged) batches: signals of several size classes (sample rate,
-// window length, Welch stretch) generated together.  Each stage is one
-// persistent launch over every class:
-//   k_sample_params_ragged  ceil(B/256) / 256   prior draws with the class's
+// window length, Welch stretch) generated together, in two issue modes a stage:
+//   k_sample_params_ragged  ceil(16 B/256) / 256 prior draws with the class's
 //                                              configuration per signal
-//   k_welch_ragged          CUs*gw / 256        Welch PSDs; a group is one
-//                                              L = 4096 item or two L = 2048
+//   k_welch_size            G / L/16           one launch per segment length:
+//                                              the segment pairs of all its
+//                                              items in equal shares
+//   k_welch_ragged          CUs*gw / 256       one persistent launch: a group is
+//                                              one L = 4096 item or two L = 2048
 //                                              items (128-thread sub-blocks)
-//   k_window_ragged         CUs*gv / 1024       fused window items; a group
-//                                              holds 16384/NC items of one
-//                                              class, one NC/16-thread
-//                                              sub-block each
-// Workgroups pull group indices from an atomic counter until the queue is
-// empty.  Groups are ordered largest transform first, so the tail of the
-// launch is made of the shortest items.  The two stages are separate
-// launches because the persistent Welch kernel keeps ~240 VGPRs of twiddles
-// and accumulators live (two waves per SIMD), while a 1024-thread window
-// workgroup is limited to 128 VGPRs.
+//   k_window_ragged         CUs*gv / 1024      one persistent launch of fused
+//                                              window items; a group holds
+//                                              16384/NC items of one class, one
+//                                              NC/16-thread sub-block each
+//   k_window_size           items / NC/16      one launch per window length
+// The persistent launches' workgroups pull group indices from an atomic
+// counter until the queue is empty.  Groups are ordered largest transform
+// first, so the tail of the launch is made of the shortest items.  The two
+// stages are separate launches: the Welch kernel keeps about 150 VGPRs of
+// twiddles and sums live, while a 1024-thread window workgroup is limited to
+// 128.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -63,10 +66,14 @@ struct gw_ragged {
   void* twr[4] = {nullptr, nullptr, nullptr, nullptr};  // exp(-2 pi i k / 2M), k <= M/2
   int n_cu = 256;
   int ord_win = 0, ord_welch = 0, grid_win = 1, grid_welch = 2;
-  int win_mode = 0;                      // 0: one persistent launch, 1: one launch per class
-  int cls_first[kMaxCls], cls_items[kMaxCls];  // window item range of each class
-  int wcls_first[kMaxCls], wcls_items[kMaxCls];  // Welch item range of each class
-  int welch_mode = 1;  // Welch issue: 0 one persistent launch, 1 one launch per class
+  int win_mode = 0;     // 0: one persistent launch, 1: one launch per transform size
+  int win_first[4] = {}, win_items[4] = {};  // window items of N/2 = 2048 << s
+  int welch_mode = 1;   // Welch issue: 0 one persistent launch, 1 one launch per transform size
+  // Welch items of L = 2048 << s and how mode 1 divides them (G = 0: one item
+  // per workgroup)
+  int welch_first[2] = {}, welch_items[2] = {}, welch_G[2] = {};
+  int4* d_starts[2] = {nullptr, nullptr};
+  int32_t* d_wpairs = nullptr;  // segment pairs of each Welch item
   std::string err;
 };
 
@@ -111,6 +118,16 @@ struct RWelchArgs {
   const void* tw4096;
   uint32_t* queue;
   int end[2];  // groups of L = 2048 << s end at end[s] (sizes in decreasing order)
+  const int32_t* cls;            // class of each signal
+  const int32_t* pairs_of_item;  // segment pairs of each item of `items`
+  int n_det;
+};
+
+// The items first .. of one transform size and how its launch divides them.
+struct RWelchCut {
+  int first, G;
+  const int4* starts;  // [G + 1] {item, pair, pairs of the workgroup}, or NULL: one item per workgroup
+  void* part;          // ACC[2 G][L/2 + 1]
 };
 
 template <class ACC, int L, int ORD>
@@ -144,20 +161,56 @@ __device__ __forceinline__ int welch_size_loop(const RWelchArgs& a, int g, int e
   return g;
 }
 
-// One class per launch: block i takes the class's i-th Welch item, L/16
-// threads, 3 waves per SIMD (no queue loop, so only one item's state is live).
+// One transform size per launch, 3 waves per SIMD: workgroup w takes the
+// segment pairs from starts[w] on, of the size's items laid end to end (see
+// WelchCut), or without starts the w-th item.
 template <class ACC, int L, int ORD>
-__global__ __launch_bounds__(L / 16, 3) void k_welch_class(RWelchArgs a, int cls, int first) {
+__global__ __launch_bounds__(L / 16, 3) void k_welch_size(RWelchArgs a, RWelchCut cut) {
   constexpr int LS = LdsSize<L>::value;
   __shared__ float lds[2 * LS];
-  const int it = load_const(a.items + first + int(blockIdx.x));
-  const DevCfg cf = load_const(a.cfgs + cls);
-  const int D = cf.n_det;
-  const int b = it / D, d = it - b * D;
-  const float* x = a.bg[cls] + int64_t(d) * a.L_bg[cls] + load_const(a.offset + b);
-  float* out = a.psd + load_const(a.psd_off + b) + int64_t(d) * cf.Fw;
-  const float* tw = reinterpret_cast<const float*>(L == 4096 ? a.tw4096 : a.tw2048);
-  welch_item<float, ACC, L, ORD>(cf.K, a.norm[cls], threadIdx.x, x, out, tw, lds, lds + LS, true);
+  const int w = int(blockIdx.x);
+  int4 at = {w, 0, 1 << 30, 0};  // one item: its pairs, clipped below
+  if (cut.starts) at = load_const(cut.starts + w);
+  ACC* part = static_cast<ACC*>(cut.part);
+  auto item_of = [&](int i, int& b, int& d, int& c) {
+    const int it = load_const(a.items + cut.first + i);
+    const int D = a.n_det;
+    b = it / D;
+    d = it - b * D;
+    c = load_const(a.cls + b);
+  };
+  welch_pieces<float, ACC, L, ORD>(
+      at.x, at.y, cut.starts ? at.z : load_const(a.pairs_of_item + cut.first + w), threadIdx.x,
+      static_cast<const float*>(L == 4096 ? a.tw4096 : a.tw2048), lds, lds + LS,
+      [&](int i) {
+        int b, d, c;
+        item_of(i, b, d, c);
+        const int K = load_const(&a.cfgs[c].K);
+        return WelchStretch{a.bg[c] + int64_t(d) * a.L_bg[c] + load_const(a.offset + b), K, (K + 1) / 2};
+      },
+      [&](int i, int k, ACC sum) {
+        int b, d, c;
+        item_of(i, b, d, c);
+        a.psd[load_const(a.psd_off + b) + int64_t(d) * (L / 2 + 1) + k] = float(sum * ACC(a.norm[c]));
+      },
+      [&](int n, int, int k, ACC sum) { part[int64_t(2 * w + n) * (L / 2 + 1) + k] = sum; });
+}
+
+// PSDs of the items that were cut: grid (ceil(Fw/256), G - 1); workgroup
+// boundary w = y + 1 handles the item it cuts where it is the item's first.
+template <class ACC>
+__global__ __launch_bounds__(256) void k_welch_size_sum(RWelchArgs a, RWelchCut cut, int Fw) {
+  const int w = int(blockIdx.y) + 1;
+  const int4 at = load_const(cut.starts + w), before = load_const(cut.starts + w - 1);
+  if (at.y == 0 || (before.x == at.x && before.y > 0)) return;
+  const int k = blockIdx.x * 256 + threadIdx.x;
+  if (k >= Fw) return;
+  const ACC* part = static_cast<const ACC*>(cut.part);
+  ACC sum = part[int64_t(2 * (w - 1) + (before.x == at.x ? 0 : 1)) * Fw + k];
+  for (int v = w; v < cut.G && load_const(cut.starts + v).x == at.x; ++v) sum += part[int64_t(2 * v) * Fw + k];
+  const int it = load_const(a.items + cut.first + at.x);
+  const int b = it / a.n_det, d = it - b * a.n_det;
+  a.psd[load_const(a.psd_off + b) + int64_t(d) * Fw + k] = float(sum * ACC(a.norm[load_const(a.cls + b)]));
 }
 
 template <class ACC, int ORD>
@@ -185,6 +238,7 @@ struct RWinArgs {
   int64_t L_bg[kMaxCls];
   const void* tw[4];
   const void* twr[4];
+  const int32_t* cls;  // class of each signal
   uint32_t* queue;
   int end[4];  // groups of NC = 2048 << s end at end[s] (sizes in decreasing order)
 };
@@ -245,22 +299,23 @@ __global__ __launch_bounds__(kWinThreads) void k_window_ragged(RWinArgs a) {
   window_size_loop<TP, 2048, ORD>(a, g, a.end[0], t, lds, &s_g, sflag);
 }
 
-// Window stage issued per class: one NC/16-thread workgroup per item of
-// class `cls` (items first .. first + gridDim.x - 1), at the occupancy of the
-// batch kernel of that size.
-template <int NC> struct ClassOcc { static constexpr int value = NC >= 16384 ? 1 : NC >= 8192 ? 4 : 8; };
+// Window stage issued per transform size: one NC/16-thread workgroup per item
+// (items first .. first + gridDim.x - 1), at the occupancy of the batch kernel
+// of that size.
+template <int NC> struct SizeOcc { static constexpr int value = NC >= 16384 ? 1 : NC >= 8192 ? 4 : 8; };
 
 template <class TP, int NC, int ORD>
-__global__ __launch_bounds__(NC / 16, ClassOcc<NC>::value) void k_window_class(RWinArgs a, int cls, int first) {
+__global__ __launch_bounds__(NC / 16, SizeOcc<NC>::value) void k_window_size(RWinArgs a, int first) {
   constexpr int LS = LdsSize<NC>::value, S = Log2Sub2048<NC>::value;
   __shared__ float lds[2 * LS];
   __shared__ uint32_t sflag;
   const int t = threadIdx.x;
   if (t == 0) sflag = 0u;
   const int it = load_const(a.items + first + int(blockIdx.x));
-  const DevCfg cf = load_const(a.cfgs + cls);
-  const int D = cf.n_det;
+  const int D = a.w.cf.n_det;
   const int b = it / D, d = it - b * D;
+  const int cls = load_const(a.cls + b);
+  const DevCfg cf = load_const(a.cfgs + cls);
   const float* x = a.bg[cls] + int64_t(d) * a.L_bg[cls] + load_const(a.w.offset + b) + cf.P;
   const float* psd = a.psd + load_const(a.psd_off + b) + int64_t(d) * cf.Fw;
   float* o = a.w.out + load_const(a.out_off + b) + int64_t(d) * cf.N;
@@ -292,8 +347,15 @@ gw_status rcheck(gw_ragged* r, const char* what) {
 int64_t align256(int64_t v) { return ((v + 255) / 256) * 256; }
 
 struct RLayout {
-  int64_t params, offset, wf, dsc, ctr, psd, total;
+  int64_t params, offset, wf, dsc, ctr, psd, part, total;
 };
+
+// bytes of the cut items' sums (binary64): the launches of the two sizes share them
+int64_t cut_bytes(const gw_ragged* r) {
+  int64_t n = 0;
+  for (int s = 0; s < 2; ++s) n = std::max(n, 2 * int64_t(r->welch_G[s]) * ((1024 << s) + 1) * int64_t(sizeof(double)));
+  return n;
+}
 
 RLayout layout(const gw_ragged* r) {
   RLayout l;
@@ -304,7 +366,8 @@ RLayout layout(const gw_ragged* r) {
   l.dsc = l.wf + align256(B * int64_t(sizeof(WfScalars)));
   l.ctr = l.dsc + align256(B * r->n_det * int64_t(sizeof(DetScalars)));
   l.psd = l.ctr + 256;  // batch counter (u64) at +0, queue heads (u32) at +64
-  l.total = l.psd + align256(r->psd_off[B] * 4);
+  l.part = l.psd + align256(r->psd_off[B] * 4);  // the least a call accepts: then no item is cut
+  l.total = l.part + cut_bytes(r);
   return l;
 }
 
@@ -345,7 +408,7 @@ gw_status check_call(gw_ragged* r, const float* const* bg, const int64_t* L_bg, 
       (params_f32 && (reinterpret_cast<uintptr_t>(params_f32) & 15u)) ||
       (status && (reinterpret_cast<uintptr_t>(status) & 3u)))
     return rfail(r, GW_EINVAL, "misaligned pointer");
-  if (ws_bytes < layout(r).total) return rfail(r, GW_EINVAL, "workspace too small");
+  if (ws_bytes < layout(r).part) return rfail(r, GW_EINVAL, "workspace too small");
   for (int c = 0; c < kMaxCls; ++c) span[c] = 1;
   for (int c = 0; c < r->n_cls; ++c) {
     if (!bg[c]) return rfail(r, GW_EINVAL, "background pointer is NULL");
@@ -358,22 +421,25 @@ gw_status check_call(gw_ragged* r, const float* const* bg, const int64_t* L_bg, 
 
 constexpr int kStageParams = 1, kStageWelch = 2, kStageWindow = 4, kStageAll = 7;
 
+template <class ACC, int L>
+void launch_welch_size(const gw_ragged* r, const RWelchArgs& a, void* part, int64_t part_bytes, hipStream_t st) {
+  constexpr int S = L == 4096 ? 1 : 0, Fw = L / 2 + 1;
+  if (r->welch_items[S] == 0) return;
+  const bool cut = r->welch_G[S] > 0 && part_bytes >= cut_bytes(r);
+  const RWelchCut c{r->welch_first[S], cut ? r->welch_G[S] : r->welch_items[S], cut ? r->d_starts[S] : nullptr, part};
+  const dim3 grid(unsigned(c.G));
+  if (L == 2048 && r->ord_welch) hipLaunchKernelGGL((k_welch_size<ACC, L, L == 2048 ? 1 : 0>), grid, dim3(L / 16), 0, st, a, c);
+  else hipLaunchKernelGGL((k_welch_size<ACC, L, 0>), grid, dim3(L / 16), 0, st, a, c);
+  if (cut)
+    hipLaunchKernelGGL((k_welch_size_sum<ACC>), dim3(unsigned((Fw + 255) / 256), unsigned(c.G - 1)), dim3(256), 0, st, a,
+                       c, Fw);
+}
+
 template <class ACC>
-void launch_welch_ragged(const gw_ragged* r, const RWelchArgs& a, hipStream_t st) {
+void launch_welch_ragged(const gw_ragged* r, const RWelchArgs& a, void* part, int64_t part_bytes, hipStream_t st) {
   if (r->welch_mode == 1) {
-    // largest transforms first
-    for (int pass = 0; pass < 2; ++pass)
-      for (int c = 0; c < r->n_cls; ++c) {
-        const int L = r->dc[c].L;
-        if (r->wcls_items[c] == 0 || (pass == 0) != (L == 4096)) continue;
-        const dim3 grid(unsigned(r->wcls_items[c]));
-        if (L == 4096)
-          hipLaunchKernelGGL((k_welch_class<ACC, 4096, 0>), grid, dim3(256), 0, st, a, c, r->wcls_first[c]);
-        else if (r->ord_welch)
-          hipLaunchKernelGGL((k_welch_class<ACC, 2048, 1>), grid, dim3(128), 0, st, a, c, r->wcls_first[c]);
-        else
-          hipLaunchKernelGGL((k_welch_class<ACC, 2048, 0>), grid, dim3(128), 0, st, a, c, r->wcls_first[c]);
-      }
+    launch_welch_size<ACC, 4096>(r, a, part, part_bytes, st);
+    launch_welch_size<ACC, 2048>(r, a, part, part_bytes, st);
     return;
   }
   const dim3 grid = dim3(unsigned(r->n_cu * r->grid_welch));
@@ -382,30 +448,26 @@ void launch_welch_ragged(const gw_ragged* r, const RWelchArgs& a, hipStream_t st
 }
 
 template <class TP, int ORD>
-void launch_window_class(const gw_ragged* r, const RWinArgs& a, int c, hipStream_t st) {
-  const dim3 grid = dim3(unsigned(r->cls_items[c]));
-  const int first = r->cls_first[c];
-  switch (r->dc[c].N / 2) {
-    case 16384: hipLaunchKernelGGL((k_window_class<TP, 16384, ORD>), grid, dim3(1024), 0, st, a, c, first); break;
-    case 8192: hipLaunchKernelGGL((k_window_class<TP, 8192, ORD>), grid, dim3(512), 0, st, a, c, first); break;
-    case 4096: hipLaunchKernelGGL((k_window_class<TP, 4096, 0>), grid, dim3(256), 0, st, a, c, first); break;
-    default: hipLaunchKernelGGL((k_window_class<TP, 2048, ORD>), grid, dim3(128), 0, st, a, c, first); break;
+void launch_window_sizes(const gw_ragged* r, const RWinArgs& a, hipStream_t st) {
+  // largest transforms first, as in the persistent queue
+  for (int s = 3; s >= 0; --s) {
+    if (r->win_items[s] == 0) continue;
+    const dim3 grid = dim3(unsigned(r->win_items[s]));
+    const int first = r->win_first[s];
+    switch (s) {
+      case 3: hipLaunchKernelGGL((k_window_size<TP, 16384, ORD>), grid, dim3(1024), 0, st, a, first); break;
+      case 2: hipLaunchKernelGGL((k_window_size<TP, 8192, ORD>), grid, dim3(512), 0, st, a, first); break;
+      case 1: hipLaunchKernelGGL((k_window_size<TP, 4096, 0>), grid, dim3(256), 0, st, a, first); break;
+      default: hipLaunchKernelGGL((k_window_size<TP, 2048, ORD>), grid, dim3(128), 0, st, a, first); break;
+    }
   }
 }
 
 template <class TP>
 void launch_window_ragged(const gw_ragged* r, const RWinArgs& a, hipStream_t st) {
   if (r->win_mode == 1) {
-    // largest transforms first, as in the persistent queue
-    int order[kMaxCls];
-    for (int c = 0; c < r->n_cls; ++c) order[c] = c;
-    std::stable_sort(order, order + r->n_cls, [&](int x, int y) { return r->dc[x].N > r->dc[y].N; });
-    for (int k = 0; k < r->n_cls; ++k) {
-      const int c = order[k];
-      if (r->cls_items[c] == 0) continue;
-      if (r->ord_win) launch_window_class<TP, 1>(r, a, c, st);
-      else launch_window_class<TP, 0>(r, a, c, st);
-    }
+    if (r->ord_win) launch_window_sizes<TP, 1>(r, a, st);
+    else launch_window_sizes<TP, 0>(r, a, st);
     return;
   }
   const dim3 grid = dim3(unsigned(r->n_cu * r->grid_win));
@@ -415,7 +477,7 @@ void launch_window_ragged(const gw_ragged* r, const RWinArgs& a, hipStream_t st)
 
 gw_status enqueue_ragged(gw_ragged* r, uint64_t seed, uint64_t batch_index, bool use_counter,
                          const float* const* bg, const int64_t* L_bg, const int64_t* span, float* out,
-                         float* params_f32, uint32_t* status, void* ws, int stages, hipStream_t st) {
+                         float* params_f32, uint32_t* status, void* ws, int64_t ws_bytes, int stages, hipStream_t st) {
   const RLayout l = layout(r);
   char* w = static_cast<char*>(ws);
   double* params = reinterpret_cast<double*>(w + l.params);
@@ -443,7 +505,7 @@ gw_status enqueue_ragged(gw_ragged* r, uint64_t seed, uint64_t batch_index, bool
     if ((s = rcheck(r, "k_sample_params_ragged")) != GW_OK) return s;
   }
   if (stages & kStageWelch) {
-    hipLaunchKernelGGL(k_fill_u32_r, dim3(1), dim3(256), 0, st, queue, int64_t(1), 0u);
+    if (r->welch_mode == 0) hipLaunchKernelGGL(k_fill_u32_r, dim3(1), dim3(256), 0, st, queue, int64_t(1), 0u);
     if ((s = rcheck(r, "k_fill_u32")) != GW_OK) return s;
     RWelchArgs a;
     std::memset(&a, 0, sizeof(a));
@@ -464,12 +526,15 @@ gw_status enqueue_ragged(gw_ragged* r, uint64_t seed, uint64_t batch_index, bool
     a.queue = queue;
     a.end[0] = r->wend[0];
     a.end[1] = r->wend[1];
-    if (r->precision == 0) launch_welch_ragged<float>(r, a, st);
-    else launch_welch_ragged<double>(r, a, st);
+    a.cls = r->d_cls;
+    a.pairs_of_item = r->d_wpairs;
+    a.n_det = r->n_det;
+    if (r->precision == 0) launch_welch_ragged<float>(r, a, w + l.part, ws_bytes - l.part, st);
+    else launch_welch_ragged<double>(r, a, w + l.part, ws_bytes - l.part, st);
     if ((s = rcheck(r, "k_welch_ragged")) != GW_OK) return s;
   }
   if (stages & kStageWindow) {
-    hipLaunchKernelGGL(k_fill_u32_r, dim3(1), dim3(256), 0, st, queue + 1, int64_t(1), 0u);
+    if (r->win_mode == 0) hipLaunchKernelGGL(k_fill_u32_r, dim3(1), dim3(256), 0, st, queue + 1, int64_t(1), 0u);
     if ((s = rcheck(r, "k_fill_u32")) != GW_OK) return s;
     RWinArgs a;
     std::memset(&a, 0, sizeof(a));
@@ -490,6 +555,7 @@ gw_status enqueue_ragged(gw_ragged* r, uint64_t seed, uint64_t batch_index, bool
     a.out_off = r->d_out_off;
     a.psd_off = r->d_psd_off;
     a.psd = psd;
+    a.cls = r->d_cls;
     for (int c = 0; c < r->n_cls; ++c) {
       a.bg[c] = bg[c];
       a.L_bg[c] = L_bg[c];
@@ -514,7 +580,7 @@ extern "C" {
 gw_status gw_ragged_destroy(gw_ragged* r) {
   if (!r) return GW_OK;
   void* ptrs[] = {r->d_cfgs, r->d_cls, r->d_out_off, r->d_psd_off, r->d_wgroups, r->d_witems,
-                  r->d_vgroups, r->d_vitems, r->kcbrt, r->lnk3};
+                  r->d_vgroups, r->d_vitems, r->kcbrt, r->lnk3, r->d_starts[0], r->d_starts[1], r->d_wpairs};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   for (int k = 0; k < 4; ++k) {
@@ -587,14 +653,44 @@ gw_status gw_ragged_create(const gw_config* classes, int32_t n_classes, const in
   std::vector<int32_t> wi, vi;
   build(true, wg, wi);
   build(false, vg, vi);
-  for (int c = 0; c < kMaxCls; ++c) r->cls_first[c] = r->cls_items[c] = r->wcls_first[c] = r->wcls_items[c] = 0;
   for (const int4& g : vg) {
-    if (r->cls_items[g.x] == 0) r->cls_first[g.x] = g.y;
-    r->cls_items[g.x] += g.z;
+    const int k = size_slot(g.w);
+    if (r->win_items[k] == 0) r->win_first[k] = g.y;
+    r->win_items[k] += g.z;
   }
   for (const int4& g : wg) {
-    if (r->wcls_items[g.x] == 0) r->wcls_first[g.x] = g.y;
-    r->wcls_items[g.x] += g.z;
+    const int k = size_slot(g.w);
+    if (r->welch_items[k] == 0) r->welch_first[k] = g.y;
+    r->welch_items[k] += g.z;
+  }
+  int dev = 0, ncu = 0;
+  if (hipGetDevice(&dev) == hipSuccess &&
+      hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && ncu > 0)
+    r->n_cu = ncu;
+  // how the Welch launches of mode 1 divide their items (the rule of the
+  // uniform batch: equal shares where whole rounds would take longer)
+  std::vector<int32_t> wpairs(wi.size());
+  for (size_t i = 0; i < wi.size(); ++i) wpairs[i] = (r->dc[hcls[wi[i] / D]].K + 1) / 2;
+  std::vector<int4> starts[2];
+  for (int k = 0; k < 2; ++k) {
+    const int64_t n = r->welch_items[k], slots = int64_t(r->n_cu) * (k ? 3 : 6);
+    int64_t total = 0, most = 0;
+    for (int64_t i = 0; i < n; ++i) {
+      const int64_t np = wpairs[r->welch_first[k] + i];
+      total += np;
+      most = std::max(most, np);
+    }
+    if (r->precision == 0 || n == 0 || n > 16 * slots || total >= (int64_t(1) << 31) ||
+        (n + slots - 1) / slots * most <= (total + slots - 1) / slots + 8)
+      continue;
+    const int64_t G = std::min(slots, total);
+    int64_t item = 0, passed = 0;  // pairs of the items before `item`
+    for (int64_t w = 0; w <= G; ++w) {
+      const int64_t at = total * w / G;
+      while (item < n && passed + wpairs[r->welch_first[k] + item] <= at) passed += wpairs[r->welch_first[k] + item++];
+      starts[k].push_back(int4{int(item), int(at - passed), int(total * (w + 1) / G - at), 0});
+    }
+    r->welch_G[k] = int(G);
   }
   r->n_wgroups = int(wg.size());
   r->n_vgroups = int(vg.size());
@@ -633,6 +729,9 @@ gw_status gw_ragged_create(const gw_config* classes, int32_t n_classes, const in
             upload(reinterpret_cast<void**>(&r->d_psd_off), hpsd) &&
             upload(reinterpret_cast<void**>(&r->d_wgroups), wg) && upload(reinterpret_cast<void**>(&r->d_witems), wi) &&
             upload(reinterpret_cast<void**>(&r->d_vgroups), vg) && upload(reinterpret_cast<void**>(&r->d_vitems), vi) &&
+            upload(reinterpret_cast<void**>(&r->d_wpairs), wpairs) &&
+            upload(reinterpret_cast<void**>(&r->d_starts[0]), starts[0]) &&
+            upload(reinterpret_cast<void**>(&r->d_starts[1]), starts[1]) &&
             upload(reinterpret_cast<void**>(&r->kcbrt), hc) && upload(reinterpret_cast<void**>(&r->lnk3), hl);
   for (int k = 0; k < 4 && ok; ++k) {
     const int M = 2048 << k;
@@ -641,10 +740,6 @@ gw_status gw_ragged_create(const gw_config* classes, int32_t n_classes, const in
     if (ok && k < 2 && need_welch[k]) ok = upload(&r->tw_welch[k], welch_tables<float>(M));
   }
   if (!ok) return bail(GW_ENOMEM);
-  int dev = 0, ncu = 0;
-  if (hipGetDevice(&dev) == hipSuccess &&
-      hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && ncu > 0)
-    r->n_cu = ncu;
   *out = r;
   return GW_OK;
 }
@@ -679,8 +774,8 @@ gw_status gw_generate_ragged(gw_ragged* r, uint64_t seed, uint64_t batch_index, 
   if (s != GW_OK) return s;
   if (batch_index > (UINT64_MAX - uint64_t(r->B)) / uint64_t(r->B))
     return rfail(r, GW_EINVAL, "batch_index overflows");
-  return enqueue_ragged(r, seed, batch_index, false, bg, L_bg, span, out, params_f32, status, workspace, kStageAll,
-                        stream);
+  return enqueue_ragged(r, seed, batch_index, false, bg, L_bg, span, out, params_f32, status, workspace, workspace_bytes,
+                        kStageAll, stream);
 }
 
 gw_status gw_ragged_graph_create(gw_ragged* r, uint64_t seed, uint64_t first_batch, const float* const* bg,
@@ -696,7 +791,8 @@ gw_status gw_ragged_graph_create(gw_ragged* r, uint64_t seed, uint64_t first_bat
   std::string why;
   s = capture_graph(
       [&](hipStream_t st) {
-        return enqueue_ragged(r, seed, 0, true, bg, L_bg, span, out, params_f32, status, workspace, kStageAll, st);
+        return enqueue_ragged(r, seed, 0, true, bg, L_bg, span, out, params_f32, status, workspace,
+                              workspace_bytes, kStageAll, st);
       },
       batch, first_batch, graph, &why);
   if (s != GW_OK) return rfail(r, s, why + (r->err.empty() ? "" : ": " + r->err));
@@ -757,10 +853,10 @@ gw_status gw_ragged_autotune(gw_ragged* r, const float* const* bg, const int64_t
   double ms[12];
   std::fill(ms, ms + 12, 1e300);  // best of kTuneRounds interleaved rounds
   auto time_stage = [&](int stage, double* res) {
-    s = enqueue_ragged(r, 1, 0, false, bg, L_bg, span, out, nullptr, nullptr, workspace, stage, st);  // warm-up
+    s = enqueue_ragged(r, 1, 0, false, bg, L_bg, span, out, nullptr, nullptr, workspace, workspace_bytes, stage, st);  // warm-up
     if (s == GW_OK && hipEventRecord(e0, st) != hipSuccess) s = rfail(r, GW_EHIP, "hipEventRecord");
     for (int k = 0; k < reps && s == GW_OK; ++k)
-      s = enqueue_ragged(r, 1, 0, false, bg, L_bg, span, out, nullptr, nullptr, workspace, stage, st);
+      s = enqueue_ragged(r, 1, 0, false, bg, L_bg, span, out, nullptr, nullptr, workspace, workspace_bytes, stage, st);
     if (s == GW_OK && hipEventRecord(e1, st) != hipSuccess) s = rfail(r, GW_EHIP, "hipEventRecord");
     if (s == GW_OK && hipEventSynchronize(e1) != hipSuccess) s = rfail(r, GW_EHIP, "hipEventSynchronize");
     // a failed timing query fails the tuner rather than reading as 0 ms
@@ -771,7 +867,7 @@ gw_status gw_ragged_autotune(gw_ragged* r, const float* const* bg, const int64_t
   if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) {
     s = rfail(r, GW_EHIP, "hipEventCreate");
   } else {
-    s = enqueue_ragged(r, 1, 0, false, bg, L_bg, span, out, nullptr, nullptr, workspace, kStageAll, st);
+    s = enqueue_ragged(r, 1, 0, false, bg, L_bg, span, out, nullptr, nullptr, workspace, workspace_bytes, kStageAll, st);
     for (int round = 0; round < kTuneRounds && s == GW_OK; ++round) {
       r->welch_mode = 0;
       for (int o = 0; o < 2 && s == GW_OK; ++o)

@@ -212,16 +212,24 @@ __global__ __launch_bounds__(NC / 16, OCC) void k_welch(WelchArgs a) {
     return;
   }
   ACC* part = static_cast<ACC*>(a.part);
+  const int w = int(blockIdx.x - a.n_draw);
+  int item = w, p0 = 0, left = a.cut.np;
+  if (!a.cut.whole()) {
+    const int begin = a.cut.start(w);
+    item = begin / a.cut.np;
+    p0 = begin - item * a.cut.np;
+    left = a.cut.start(w + 1) - begin;
+  }
   welch_pieces<T, ACC, NC, ORD>(
-      a.cut, int(blockIdx.x - a.n_draw), a.cf.K, t, static_cast<const T*>(a.tw), lds, lds + LS,
-      [&](int item) {
-        const int b = item / a.cf.n_det, d = item - b * a.cf.n_det;
+      item, p0, left, t, static_cast<const T*>(a.tw), lds, lds + LS,
+      [&](int i) {
+        const int b = i / a.cf.n_det, d = i - b * a.cf.n_det;
         const int64_t o = a.n_draw ? draw_offset(a.draw.seed, a.draw.first_index() + uint64_t(b), a.draw.ext_k, a.draw.span)
                                    : a.offset[b];
-        return a.bg + int64_t(d) * a.L_bg + o;
+        return WelchStretch{a.bg + int64_t(d) * a.L_bg + o, a.cf.K, a.cut.np};
       },
-      [&](int item, int k, ACC sum) { a.psd[int64_t(item) * Fw + k] = float(sum * ACC(a.norm)); },
-      [&](int slot, int k, ACC sum) { part[int64_t(slot) * Fw + k] = sum; });
+      [&](int i, int k, ACC sum) { a.psd[int64_t(i) * Fw + k] = float(sum * ACC(a.norm)); },
+      [&](int n, int, int k, ACC sum) { part[int64_t(2 * w + n) * Fw + k] = sum; });
 }
 
 // PSDs of the items that were cut: grid (ceil(Fw/256), G - 1).
