@@ -633,6 +633,11 @@ struct WelchCut {
   // one item per workgroup: nothing is cut (G np may exceed 32 bits then)
   __host__ __device__ bool whole() const { return q == np && r == 0; }
   __device__ __forceinline__ int start(int w) const { return w * q + int(uint32_t(w) * uint32_t(r) / uint32_t(G)); }
+  // the last workgroup that starts before pair x
+  __device__ __forceinline__ int before(int x) const {
+    const int64_t total = int64_t(q) * G + r;
+    return int((int64_t(x) * G + total - 1) / total) - 1;
+  }
 };
 
 // A stretch to sum: its first sample, segments and segment pairs.
@@ -663,17 +668,15 @@ __device__ __forceinline__ void welch_pieces(int item, int p0, int left, int t, 
   }
 }
 
-// Sum over the pieces of the item that workgroup boundary w (1 <= w < G) cuts,
-// where it is the item's first: -1 if it cuts none or not first, else the item;
-// add(slot) is called for its slots in order.
-template <class Add>
-__device__ __forceinline__ int welch_cut_item(const WelchCut& cut, int w, Add add) {
-  const int at = cut.start(w), item = at / cut.np;
-  const int before = cut.start(w - 1);
-  if (at == item * cut.np || before > item * cut.np) return -1;
-  add(2 * (w - 1) + (before / cut.np == item ? 0 : 1));
-  for (int v = w; v < cut.G && cut.start(v) < (item + 1) * cut.np; ++v) add(2 * v);
-  return item;
+// The slots of cut item `item`, in order, are n of them from workgroup w on:
+// slot(w, 0), then slot 2 v of the following workgroups v.
+struct WelchSlots {
+  int w, n, first;
+  __device__ __forceinline__ int64_t slot(int i) const { return i == 0 ? first : 2 * int64_t(w + i); }
+};
+// (w: the last workgroup that starts at or before the item)
+__device__ __forceinline__ WelchSlots welch_slots(const WelchCut& cut, int w, int item) {
+  return WelchSlots{w, cut.before((item + 1) * cut.np) - w + 1, 2 * w + (cut.start(w) / cut.np == item ? 0 : 1)};
 }
 
 }  // namespace gw

@@ -191,9 +191,10 @@ struct WelchArgs {
   DevCfg cf;
   const float* bg;
   int64_t L_bg;
-  const int64_t* offset;  // [B] (n_draw = 0)
+  const int64_t* offset;  // [B] (n_draw = 0), or NULL: the rows' starts
   float* psd;
   const void* tw;  // Welch table of L (WelchTab)
+  int K;           // segments of an item
   double norm;     // 1 / (K fs sum w^2)
   WelchCut cut;
   void* part;      // ACC[2 G][L/2 + 1] sums of cut items
@@ -225,21 +226,46 @@ __global__ __launch_bounds__(NC / 16, OCC) void k_welch(WelchArgs a) {
       [&](int i) {
         const int b = i / a.cf.n_det, d = i - b * a.cf.n_det;
         const int64_t o = a.n_draw ? draw_offset(a.draw.seed, a.draw.first_index() + uint64_t(b), a.draw.ext_k, a.draw.span)
-                                   : a.offset[b];
-        return WelchStretch{a.bg + int64_t(d) * a.L_bg + o, a.cf.K, a.cut.np};
+                                   : a.offset ? a.offset[b] : 0;
+        return WelchStretch{a.bg + int64_t(d) * a.L_bg + o, a.K, a.cut.np};
       },
       [&](int i, int k, ACC sum) { a.psd[int64_t(i) * Fw + k] = float(sum * ACC(a.norm)); },
       [&](int n, int, int k, ACC sum) { part[int64_t(2 * w + n) * Fw + k] = sum; });
 }
 
-// PSDs of the items that were cut: grid (ceil(Fw/256), G - 1).
+// PSDs of the items that were cut, few pieces each: grid (ceil(Fw/256), G - 1);
+// workgroup boundary w = y + 1 handles the item it cuts, where it is the
+// item's first.
 template <class ACC>
 __global__ __launch_bounds__(256) void k_welch_sum(WelchCut cut, const ACC* part, int Fw, double norm, float* psd) {
+  const int w = int(blockIdx.y) + 1, at = cut.start(w), item = at / cut.np;
   const int k = blockIdx.x * 256 + threadIdx.x;
-  const int kc = min(k, Fw - 1);
+  if (at == item * cut.np || cut.start(w - 1) > item * cut.np || k >= Fw) return;
+  const WelchSlots s = welch_slots(cut, w - 1, item);
   ACC sum = ACC(0);
-  const int item = welch_cut_item(cut, int(blockIdx.y) + 1, [&](int slot) { sum += part[int64_t(slot) * Fw + kc]; });
-  if (item >= 0 && k < Fw) psd[int64_t(item) * Fw + k] = float(sum * ACC(norm));
+  for (int i = 0; i < s.n; ++i) sum += part[s.slot(i) * Fw + k];
+  psd[int64_t(item) * Fw + k] = float(sum * ACC(norm));
+}
+
+// The same with many pieces to an item: grid (ceil(Fw/32), items), 32 bins a
+// workgroup, their pieces added by 8 threads each.
+template <class ACC>
+__global__ __launch_bounds__(256) void k_welch_sum_many(WelchCut cut, const ACC* part, int Fw, double norm, float* psd) {
+  __shared__ ACC red[8][32];
+  const int item = int(blockIdx.y), lo = item * cut.np;
+  const int w = cut.before(lo + 1);
+  if (cut.start(w + 1) >= lo + cut.np) return;  // held whole by workgroup w
+  const WelchSlots s = welch_slots(cut, w, item);
+  const int j = threadIdx.x >> 5, k = blockIdx.x * 32 + (threadIdx.x & 31), kc = min(k, Fw - 1);
+  ACC sum = ACC(0);
+#pragma unroll 4
+  for (int i = j; i < s.n; i += 8) sum += part[s.slot(i) * Fw + kc];
+  red[j][threadIdx.x & 31] = sum;
+  __syncthreads();
+  if (j != 0 || k >= Fw) return;
+#pragma unroll
+  for (int i = 1; i < 8; ++i) sum += red[i][threadIdx.x];
+  psd[int64_t(item) * Fw + k] = float(sum * ACC(norm));
 }
 
 __global__ void k_fill_u32(uint32_t* p, int64_t n, uint32_t v) {
@@ -332,9 +358,12 @@ __global__ __launch_bounds__(NC / 16) void k_filter(FiltArgs a) {
     for (int j = 0; j < 2; ++j) {
       const int m = 2 * n + j;
       const int lag = m <= NC ? m : m - N;
-      T sn, cs;
-      sincospi_t(T(lag) / T(a.M), &sn, &cs);
-      h[j] = 2 * abs(lag) < a.M ? cs * cs : T(0);
+      h[j] = T(0);
+      if (2 * abs(lag) < a.M) {  // most wavefronts hold lags of one side only
+        T sn, cs;
+        sincospi_t(T(lag) / T(a.M), &sn, &cs);
+        h[j] = cs * cs;
+      }
     }
     v[e] = {v[e].x * sc * h[0], v[e].y * sc * h[1]};
   }
@@ -695,24 +724,26 @@ static int64_t ws_base_bytes(const DevCfg& d, int64_t B) { return ws_counter_off
 // launch that adds them), so items are cut where the whole rounds would take
 // longer than equal shares by more than that.  Binary32 sums (mode 0) are not
 // cut: their order would show in the result.
-static WelchCut welch_whole(const DevCfg& d, int64_t items) {
-  const int np = (d.K + 1) / 2;
+static WelchCut welch_whole(int64_t items, int64_t K) {
+  const int np = int((K + 1) / 2);
   return WelchCut{int(items), np, 0, np};
 }
-static WelchCut welch_cut(const gw_ctx* c, int64_t items) {
+static WelchCut welch_cut(const gw_ctx* c, int64_t items, int64_t K, int64_t part_bytes) {
   const DevCfg& d = c->dc;
-  const int64_t np = (d.K + 1) / 2, total = items * np;
+  const int64_t np = (K + 1) / 2, total = items * np;
   // workgroups per CU: registers allow 3 waves per SIMD (binary64 transforms: 1)
   const int64_t waves = d.precision == 2 ? 1 : 3;
-  const int64_t slots = c->n_cu * (waves * 4 / (d.L / 1024));
-  if (d.precision == 0 || items <= 0 || items > 16 * slots || total >= (int64_t(1) << 31)) return welch_whole(d, items);
+  const int64_t slots = std::min(c->n_cu * (waves * 4 / (d.L / 1024)), part_bytes / (2 * d.Fw * int64_t(sizeof(double))));
+  if (d.precision == 0 || items <= 0 || items > 16 * c->n_cu * 12 || total >= (int64_t(1) << 31) || slots < 1)
+    return welch_whole(items, K);
   const int64_t rounds = (items + slots - 1) / slots * np, share = (total + slots - 1) / slots;
-  if (rounds <= share + 8) return welch_whole(d, items);
+  if (rounds <= share + 8) return welch_whole(items, K);
   const int64_t G = std::min(slots, total);
   return WelchCut{int(G), int(total / G), int(total % G), int(np)};
 }
-static int64_t ws_cut_bytes(const gw_ctx* c, int64_t items) {
-  const WelchCut cut = welch_cut(c, items);
+// bytes of the sums of `items` stretches of K segments
+static int64_t ws_cut_bytes(const gw_ctx* c, int64_t items, int64_t K) {
+  const WelchCut cut = welch_cut(c, items, K, INT64_MAX);
   return cut.whole() ? 0 : 2 * int64_t(cut.G) * c->dc.Fw * int64_t(sizeof(double));
 }
 
@@ -780,10 +811,16 @@ static void launch_welch(const DevCfg& d, const WelchArgs& a, hipStream_t stream
   if constexpr (sizeof(T) == 8) launch_welch_occ<T, ACC, 1>(d, a, stream);
   else if (d.occ_welch == 3) launch_welch_occ<T, ACC, 3>(d, a, stream);
   else launch_welch_occ<T, ACC, 2>(d, a, stream);
-  if (!a.cut.whole()) {
+  if (a.cut.whole()) return;
+  const ACC* part = static_cast<const ACC*>(a.part);
+  // items of many pieces are few: a workgroup row per item, else per boundary
+  const int64_t items = (int64_t(a.cut.G) * a.cut.q + a.cut.r) / a.cut.np;
+  if (items * 8 <= a.cut.G) {
+    const dim3 grid(unsigned((d.Fw + 31) / 32), unsigned(items));
+    hipLaunchKernelGGL((k_welch_sum_many<ACC>), grid, dim3(256), 0, stream, a.cut, part, d.Fw, a.norm, a.psd);
+  } else {
     const dim3 grid(unsigned((d.Fw + 255) / 256), unsigned(a.cut.G - 1));
-    hipLaunchKernelGGL((k_welch_sum<ACC>), grid, dim3(256), 0, stream, a.cut, static_cast<const ACC*>(a.part), d.Fw,
-                       a.norm, a.psd);
+    hipLaunchKernelGGL((k_welch_sum<ACC>), grid, dim3(256), 0, stream, a.cut, part, d.Fw, a.norm, a.psd);
   }
 }
 
@@ -801,10 +838,11 @@ static void launch_filter(const DevCfg& d, const FiltArgs& a, hipStream_t stream
   }
 }
 
-// Welch PSDs of B samples.  part (part_bytes, may be NULL): room for the sums
-// of cut items; too little of it and no item is cut.  draw: the batch's prior
-// draws, made by the same launch (offset is then not read), or NULL.
-static gw_status welch_launch(gw_ctx* c, const float* bg, int64_t L_bg, const int64_t* offset, int64_t B,
+// Welch PSDs of B samples (K segments from each one's offset; offset NULL: from
+// the rows' starts).  part (part_bytes, may be NULL): room for the sums of cut
+// items; without it no item is cut.  draw: the batch's prior draws, made by the
+// same launch (offset is then not read), or NULL.
+static gw_status welch_launch(gw_ctx* c, const float* bg, int64_t L_bg, const int64_t* offset, int64_t B, int64_t K,
                               float* psd, void* part, int64_t part_bytes, const SampleArgs* draw, hipStream_t stream) {
   const DevCfg& d = c->dc;
   WelchArgs a{};
@@ -814,9 +852,9 @@ static gw_status welch_launch(gw_ctx* c, const float* bg, int64_t L_bg, const in
   a.offset = offset;
   a.psd = psd;
   a.tw = c->tw_welch;
-  a.norm = 1.0 / (double(d.K) * d.fs * (3.0 * d.L / 8.0));
-  const int64_t items = B * d.n_det;
-  a.cut = part && ws_cut_bytes(c, items) <= part_bytes ? welch_cut(c, items) : welch_whole(d, items);
+  a.K = int(K);
+  a.norm = 1.0 / (double(K) * d.fs * (3.0 * d.L / 8.0));
+  a.cut = welch_cut(c, B * d.n_det, K, part ? part_bytes : 0);
   a.part = part;
   if (draw) {
     a.draw = *draw;
@@ -870,7 +908,7 @@ static gw_status enqueue_batch(gw_ctx* c, uint64_t seed, uint64_t batch_index, c
                       ext_k};
   if (stages & kStageWelch) {
     const int64_t base = ws_base_bytes(c->dc, B);
-    s = welch_launch(c, bg, L_bg, offset, B, psd, ws + base, workspace_bytes - base,
+    s = welch_launch(c, bg, L_bg, offset, B, c->dc.K, psd, ws + base, workspace_bytes - base,
                      (stages & kStageParams) ? &sa : nullptr, stream);
     if (s != GW_OK) return s;
   } else if (stages & kStageParams) {
@@ -1018,7 +1056,7 @@ gw_status gw_query(const gw_ctx* c, int32_t key, int64_t* value) {
 
 gw_status gw_workspace_size(const gw_ctx* c, int64_t B, int64_t* bytes) {
   if (!c || !bytes || B < 0) return GW_EINVAL;
-  *bytes = ws_base_bytes(c->dc, B) + ws_cut_bytes(c, B * c->dc.n_det);
+  *bytes = ws_base_bytes(c->dc, B) + ws_cut_bytes(c, B * c->dc.n_det, c->dc.K);
   return GW_OK;
 }
 
@@ -1094,7 +1132,7 @@ gw_status welch_psd(gw_ctx* c, const float* bg, int64_t L_bg, const int64_t* off
   if (!bg || !offset || !psd) return fail(c, GW_EINVAL, "NULL pointer");
   if (!aligned4(bg) || !aligned16(offset) || !aligned16(psd)) return fail(c, GW_EINVAL, "misaligned pointer");
   if (L_bg < int64_t(c->dc.P) + c->dc.N) return fail(c, GW_EINVAL, "L_bg < P + N");
-  return welch_launch(c, bg, L_bg, offset, B, psd, nullptr, 0, nullptr, stream);
+  return welch_launch(c, bg, L_bg, offset, B, c->dc.K, psd, nullptr, 0, nullptr, stream);
 }
 
 gw_status whiten(gw_ctx* c, const float* strain, const float* psd, int64_t B, float* out, uint32_t* status,
@@ -1129,7 +1167,7 @@ static int64_t ws_surrogate_bytes(const DevCfg& d, int64_t B) {
 
 gw_status gw_workspace_size_surrogate(const gw_ctx* c, int64_t B, int64_t* bytes) {
   if (!c || !bytes || B < 0) return GW_EINVAL;
-  *bytes = ws_surrogate_bytes(c->dc, B) + ws_cut_bytes(c, B * c->dc.n_det);
+  *bytes = ws_surrogate_bytes(c->dc, B) + ws_cut_bytes(c, B * c->dc.n_det, c->dc.K);
   return GW_OK;
 }
 
@@ -1164,7 +1202,7 @@ gw_status gw_generate_batch_surrogate(gw_ctx* c, gw_surrogate* sg, uint64_t seed
   if (s != GW_OK) return s;
   s = gw_surrogate_nodes(sg, params, B, nodes, logmm, stream);
   if (s != GW_OK) return fail(c, s, std::string("surrogate: ") + gw_surrogate_last_error(sg));
-  s = welch_launch(c, bg, L_bg, offset, B, psd, ws + base, workspace_bytes - base, nullptr, stream);
+  s = welch_launch(c, bg, L_bg, offset, B, c->dc.K, psd, ws + base, workspace_bytes - base, nullptr, stream);
   if (s != GW_OK) return s;
   WinArgs a = win_args(c);
   a.src = bg;
@@ -1360,9 +1398,14 @@ gw_status gw_autotune(gw_ctx* c, int64_t B, const float* bg, int64_t L_bg, float
 // ------------------------------------------------------- per-run PSD mode
 static int64_t align256(int64_t v) { return ((v + 255) / 256) * 256; }
 
+// least workspace of a run PSD: the chunks' offsets and PSDs (binary32 sums)
+static int64_t run_psd_base(const DevCfg& d, int64_t n_chunks) {
+  return align256(n_chunks * 8) + align256(n_chunks * d.n_det * int64_t(d.Fw) * 4);
+}
+
 gw_status gw_run_psd_workspace_size(const gw_ctx* c, int64_t n_chunks, int64_t* bytes) {
   if (!c || !bytes || n_chunks < 1) return GW_EINVAL;
-  *bytes = align256(n_chunks * 8) + align256(n_chunks * c->dc.n_det * int64_t(c->dc.Fw) * 4);
+  *bytes = std::max(run_psd_base(c->dc, n_chunks), ws_cut_bytes(c, c->dc.n_det, n_chunks * c->dc.K));
   return GW_OK;
 }
 
@@ -1375,16 +1418,20 @@ gw_status gw_run_psd(gw_ctx* c, const float* bg, int64_t L_bg, int64_t n_chunks,
   if (!aligned4(bg) || !aligned16(psd) || !aligned16(workspace)) return fail(c, GW_EINVAL, "misaligned pointer");
   const int64_t stride = int64_t(d.K) * d.S;
   if ((n_chunks - 1) * stride + d.P > L_bg) return fail(c, GW_EINVAL, "n_chunks stretches exceed the background");
-  int64_t need = 0;
-  gw_run_psd_workspace_size(c, n_chunks, &need);
-  if (workspace_bytes < need) return fail(c, GW_EINVAL, "workspace too small");
+  if (workspace_bytes < run_psd_base(d, n_chunks)) return fail(c, GW_EINVAL, "workspace too small");
+  // With binary64 sums the chunks are one stretch per detector, cut into equal
+  // shares: 600 chunks of 63 segments in whole took 131 us (768 workgroups at
+  // once, 168 of them idle) and averaging the chunks' PSDs another 51 us.
+  // Binary32 sums (mode 0) stay within a chunk.
+  if (d.precision != 0 && n_chunks * d.K * d.n_det < (int64_t(1) << 31))
+    return welch_launch(c, bg, L_bg, nullptr, 1, n_chunks * d.K, psd, workspace, workspace_bytes, nullptr, stream);
   int64_t* off = static_cast<int64_t*>(workspace);
   float* part = reinterpret_cast<float*>(static_cast<char*>(workspace) + align256(n_chunks * 8));
   hipLaunchKernelGGL(k_chunk_offsets, dim3(unsigned((n_chunks + 255) / 256)), dim3(256), 0, stream, off, n_chunks,
                      stride);
   gw_status s = check_launch(c, "k_chunk_offsets");
   if (s != GW_OK) return s;
-  s = welch_launch(c, bg, L_bg, off, n_chunks, part, nullptr, 0, nullptr, stream);
+  s = welch_launch(c, bg, L_bg, off, n_chunks, d.K, part, nullptr, 0, nullptr, stream);
   if (s != GW_OK) return s;
   const int n = d.n_det * d.Fw;
   hipLaunchKernelGGL(k_mean_chunks, dim3(unsigned((n + 255) / 256)), dim3(256), 0, stream, part, n_chunks, d.n_det,

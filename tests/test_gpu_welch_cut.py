@@ -46,3 +46,35 @@ def test_cut_stretches_equal_whole_ones(name, over, B):
     gen.generate_batch(11, 2, B, bg, out, ws, status=status)
     torch.cuda.synchronize()
     assert torch.equal(first, out)
+
+
+@pytest.mark.parametrize("name,over,chunks", [("paper_scale", dict(psd_length=16.0), 9), ("pr1_plain", {}, 1),
+                                              ("pr1_plain", dict(psd_length=5.0), 40),
+                                              ("paper_scale", dict(psd_length=8.0, precision=2), 21)])
+def test_run_psd_whatever_the_workspace(name, over, chunks):
+    """The run PSD with the workspace the query names and with the least that is accepted (fewer shares), against the
+    mean of the chunks' PSDs in binary64 (each rounded to binary32: 2^-24 relative, as the result is)."""
+    import ctypes
+
+    import torch
+    cfg = inputs.config(name, **over)
+    gen = gwgen.Generator(cfg)
+    z = gen.sizes
+    bg = torch.from_numpy(inputs.background(z["D"], 1 << 20, cfg["fs"], seed=4)).cuda()
+    offs = torch.arange(chunks, device="cuda") * (z["K"] * z["L"] // 2)
+    each = torch.empty((chunks, z["D"], z["Fw"]), dtype=torch.float32, device="cuda")
+    gen.welch_psd(bg, offs, each)
+    want = each.double().mean(0).cpu().numpy()
+    size = ctypes.c_int64()
+    assert gwgen.lib().gw_run_psd_workspace_size(gen._h, chunks, ctypes.byref(size)) == 0
+    least = -(-8 * chunks // 256) * 256 + -(-4 * chunks * z["D"] * z["Fw"] // 256) * 256
+    for nbytes in (size.value, least):
+        ws = torch.empty(nbytes // 8, dtype=torch.float64, device="cuda")
+        psd = torch.zeros((z["D"], z["Fw"]), dtype=torch.float32, device="cuda")
+        assert gwgen.lib().gw_run_psd(gen._h, gwgen._ptr(bg), bg.shape[1], chunks, gwgen._ptr(psd), gwgen._ptr(ws), nbytes,
+                                      gwgen._stream()) == 0
+        torch.cuda.synchronize()
+        # binary32 transforms pair other segments than the chunks do: 1e-6 covers their rounding
+        assert np.max(np.abs(psd.cpu().numpy() / want - 1.0)) <= (1e-6 if cfg["precision"] == 1 else 2.0 ** -22)
+    assert gwgen.lib().gw_run_psd(gen._h, gwgen._ptr(bg), bg.shape[1], chunks, gwgen._ptr(psd), gwgen._ptr(ws), least - 8,
+                                  gwgen._stream()) == gwgen.GW_EINVAL
