@@ -268,43 +268,434 @@ __global__ __launch_bounds__(256) void k_colstats(const float* Z, int64_t n, int
   }
 }
 
-// -------------------------------------------------- MLP input normalisation
-// x[B][16] bf16: 2 (theta - lo)/(hi - lo) - 1 for (M_c, q, chi1, chi2), zero pad
-struct NormArgs { const float* theta; int64_t B; float lo[4], hi[4]; uint16_t* x; };
-__global__ __launch_bounds__(256) void k_norm_inputs(NormArgs a) {
-  const int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x;
-  if (e >= a.B * 16) return;
-  const int64_t i = e / 16;
-  const int c = int(e % 16);
-  float v = 0.f;
-  if (c < 4) v = 2.f * (a.theta[i * 4 + c] - a.lo[c]) / (a.hi[c] - a.lo[c]) - 1.f;
-  a.x[e] = f2bf(v);
+// ------------------------------------------------------------- network
+// 4-256-256-256-128 MLP on bf16 MFMA (16x16x16, binary32 accumulation, K in
+// increasing steps of 16), 32 rows per 512-thread workgroup through every
+// layer: activations in LDS as bf16, each wave owning 32 columns (16 of the
+// output layer).  At the training batch of 8192 that is one workgroup per CU;
+// what bounds it is the 800 KB of weights each workgroup reads from L2 (forward
+// and backward order), so they are stored as the MFMA operands' own fragments
+// and read 1 KB per wave and load.
+//
+// Fragments (4 bf16 per lane, lane = c + 16 g): the operand's element
+// (index along its rows or columns c, k = 4 g + r).  Two steps of 16 along k
+// lie side by side, so that a lane reads 16 bytes.
+typedef short v4s __attribute__((ext_vector_type(4)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+constexpr int kMlpRows = 32;
+constexpr int kMlpThreads = 512;
+constexpr int kActStride = HID + 4;  // bf16 per LDS row: 8-byte reads of 16 rows hit 32 distinct banks
+constexpr int kBiasCols = 3 * HID + NOUT;
+
+__host__ __device__ constexpr int bias_col(int l) { return l * HID; }  // first column of layer l's bias gradient
+
+// Position of W[k][n] (k < nin, n < nout) in the fragments of the product
+// x W (contraction over k, 16 columns n a tile)
+__host__ __device__ inline int frag_fwd(int nin, int k, int n) {
+  const int lane = (n & 15) + 16 * ((k & 15) >> 2), ks = k >> 4;
+  if (nin == 16) return ((n >> 4) * 64 + lane) * 4 + (k & 3);
+  return (((n >> 4) * (nin / 32) + (ks >> 1)) * 64 + lane) * 8 + (ks & 1) * 4 + (k & 3);
+}
+// and of the product dz W^T (contraction over n, 16 rows k a tile)
+__host__ __device__ inline int frag_bwd(int nout, int k, int n) {
+  const int lane = (k & 15) + 16 * ((n & 15) >> 2), ks = n >> 4;
+  return (((k >> 4) * (nout / 32) + (ks >> 1)) * 64 + lane) * 8 + (ks & 1) * 4 + (n & 3);
 }
 
-// theta [nb][4] float for columns b0 .. b0+nb-1 of params [12][B] double
-__global__ __launch_bounds__(256) void k_theta_from_params_off(const double* params, int64_t B, int64_t b0, int64_t nb,
-                                                               float* theta) {
-  const int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x;
-  if (e >= nb * 4) return;
-  const int64_t i = e / 4;
-  const int c = int(e % 4);
-  theta[e] = float(params[c * B + b0 + i]);
+struct MlpArgs {
+  // inputs: theta [B][4], or columns b0 .. of params [12][pB] (theta NULL)
+  const float* theta;
+  const double* params;
+  int64_t pB, b0, B;
+  float lo[4], hi[4];
+  const uint16_t* wf[NLAYER];   // fragments of x W
+  const uint16_t* wb[NLAYER];   // fragments of dz W^T (training; layers 1..)
+  const float* bias[NLAYER];
+  // inference
+  uint16_t* h_last;             // [B][HID] last hidden layer, or NULL
+  float* z_out;                 // [B][NOUT]
+  // training: targets, and per 32 rows the fragments (two steps of 16 rows) of
+  // every layer's input and output gradient, the bias gradients' column sums
+  // and the squared error
+  const float* y;               // [B][NOUT]
+  uint4* hfrag[NLAYER];         // [blocks][nin / 16][64]
+  uint4* dfrag[NLAYER];         // [blocks][nout / 16][64]
+  float* bias_part;             // [blocks][kBiasCols]
+  float* loss_part;             // [blocks]
+};
+
+// acc[i][j] = rows 16 i .. of the LDS matrix `in` times the j-th tile of the
+// fragments w (K rows), tiles tile0 ..
+template <int K, int NT>
+__device__ __forceinline__ void mlp_product(const uint16_t (*in)[kActStride], const uint16_t* w, int tile0, int lane,
+                                            v4f (*acc)[NT]) {
+  constexpr int KP = K >= 32 ? K / 32 : 1;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+  auto frag = [&](int i, int ks) {
+    return *reinterpret_cast<const v4s*>(&in[16 * i + (lane & 15)][16 * ks + 4 * (lane >> 4)]);
+  };
+  if constexpr (K == 16) {
+    const v4s a0 = frag(0, 0), a1 = frag(1, 0);
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+      const v4s b = reinterpret_cast<const v4s*>(w)[(tile0 + j) * 64 + lane];
+      acc[0][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a0, b, acc[0][j], 0, 0, 0);
+      acc[1][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a1, b, acc[1][j], 0, 0, 0);
+    }
+  } else {
+    struct alignas(16) Two { v4s s[2]; };
+    const Two* wp = reinterpret_cast<const Two*>(w) + int64_t(tile0) * KP * 64 + lane;
+    Two q[KP][NT];
+#pragma unroll
+    for (int kp = 0; kp < KP; ++kp)
+#pragma unroll
+      for (int j = 0; j < NT; ++j) q[kp][j] = wp[(j * KP + kp) * 64];
+#pragma unroll
+    for (int kp = 0; kp < KP; ++kp)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const v4s a0 = frag(0, 2 * kp + h), a1 = frag(1, 2 * kp + h);
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+          acc[0][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a0, q[kp][j].s[h], acc[0][j], 0, 0, 0);
+          acc[1][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a1, q[kp][j].s[h], acc[1][j], 0, 0, 0);
+        }
+      }
+  }
 }
 
-// skip-path features phi for columns b0 .. b0+nb-1 of params
-__global__ __launch_bounds__(256) void k_features_off(const double* params, int64_t B, int64_t b0, int64_t nb, double* feat) {
-  const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
-  if (i >= nb) return;
-  const double q = params[1 * B + b0 + i], chi1 = params[2 * B + b0 + i], chi2 = params[3 * B + b0 + i];
-  const double eta = q / ((1.0 + q) * (1.0 + q));
-  double c[8], lg[8];
-  pn_coefficients(eta, q, chi1, chi2, c, lg);
-  const double pre = 3.0 / (128.0 * eta);
-  double* f = feat + i * NFEAT;
-  for (int k = 0; k < 6; ++k) f[k] = pre * c[k + 2];
-  f[6] = pre * lg[5];
-  f[7] = pre * lg[6];
-  f[8] = 1.0;
+// Four rounded values of each of the two row halves, as one fragment pair.
+__device__ __forceinline__ uint4 frag_pair(const uint16_t (*h)[4]) {
+  return uint4{uint32_t(h[0][0]) | uint32_t(h[0][1]) << 16, uint32_t(h[0][2]) | uint32_t(h[0][3]) << 16,
+               uint32_t(h[1][0]) | uint32_t(h[1][1]) << 16, uint32_t(h[1][2]) | uint32_t(h[1][3]) << 16};
+}
+
+// Hidden layer L: z = x W + b kept by the wave, silu(z) rounded to LDS (and to
+// the next layer's input fragments).
+template <int L, bool TRAIN>
+__device__ __forceinline__ void mlp_hidden(const MlpArgs& a, const uint16_t (*in)[kActStride], uint16_t (*out)[kActStride],
+                                           int lane, int wv, v4f (*z)[2]) {
+  constexpr int K = L == 0 ? 16 : HID;
+  mlp_product<K, 2>(in, a.wf[L], 2 * wv, lane, z);
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int tile = 2 * wv + j, col = 16 * tile + (lane & 15);
+    const float b = a.bias[L][col];
+    uint16_t h[2][4];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float zz = z[i][j][r] + b;
+        z[i][j][r] = zz;
+        h[i][r] = f2bf(zz / (1.f + __expf(-zz)));
+        out[16 * i + 4 * (lane >> 4) + r][col] = h[i][r];
+      }
+    if constexpr (TRAIN) a.hfrag[L + 1][(int64_t(blockIdx.x) * (HID / 16) + tile) * 64 + lane] = frag_pair(h);
+  }
+}
+
+// Rounded gradient dz of layer L's output for tile `tile`: fragments, LDS (if
+// another layer follows) and the column sums of the bias gradient.
+template <int L>
+__device__ __forceinline__ void mlp_store_grad(const MlpArgs& a, const float (*g)[4], uint16_t (*out)[kActStride], int tile,
+                                               int lane) {
+  constexpr int N = L == NLAYER - 1 ? NOUT : HID;
+  uint16_t h[2][4];
+  float s = 0.f;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      h[i][r] = f2bf(g[i][r]);
+      s += g[i][r];
+      if constexpr (L > 0) out[16 * i + 4 * (lane >> 4) + r][16 * tile + (lane & 15)] = h[i][r];
+    }
+  a.dfrag[L][(int64_t(blockIdx.x) * (N / 16) + tile) * 64 + lane] = frag_pair(h);
+  s += __shfl_xor(s, 16);
+  s += __shfl_xor(s, 32);
+  if (lane < 16) a.bias_part[int64_t(blockIdx.x) * kBiasCols + bias_col(L) + 16 * tile + lane] = s;
+}
+
+// dz of layer L - 1 from dz of layer L (in LDS): dH = dz W^T, times silu'(z).
+template <int L>
+__device__ __forceinline__ void mlp_backward_layer(const MlpArgs& a, const uint16_t (*in)[kActStride],
+                                                   uint16_t (*out)[kActStride], int lane, int wv, const v4f (*z)[2]) {
+  constexpr int K = L == NLAYER - 1 ? NOUT : HID;
+  v4f dh[2][2];
+  mlp_product<K, 2>(in, a.wb[L], 2 * wv, lane, dh);
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    float g[2][4];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float zz = z[i][j][r];
+        const float s = 1.f / (1.f + __expf(-zz));
+        g[i][r] = dh[i][j][r] * s * (1.f + zz * (1.f - s));
+      }
+    mlp_store_grad<L - 1>(a, g, out, 2 * wv + j, lane);
+  }
+}
+
+template <bool TRAIN>
+__global__ __launch_bounds__(kMlpThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_mlp(MlpArgs a) {
+  __shared__ uint16_t act[2][kMlpRows][kActStride];
+  __shared__ float red[kMlpThreads / 64];
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  const int64_t r0 = int64_t(blockIdx.x) * kMlpRows;
+  {
+    // x = 2 (theta - lo)/(hi - lo) - 1 for (M_c, q, chi1, chi2), zero pad
+    const int r = t / 16, c = t % 16;
+    const int64_t row = r0 + r;
+    uint16_t h = 0;
+    if (c < 4 && row < a.B) {
+      const float v = a.theta ? a.theta[row * 4 + c] : float(a.params[c * a.pB + a.b0 + row]);
+      h = f2bf(2.f * (v - a.lo[c]) / (a.hi[c] - a.lo[c]) - 1.f);
+    }
+    act[0][r][c] = h;
+  }
+  __syncthreads();
+  if constexpr (TRAIN) {
+    if (wv == 0) {
+      uint16_t h[2][4];
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) h[i][r] = act[0][16 * i + 4 * (lane >> 4) + r][lane & 15];
+      a.hfrag[0][int64_t(blockIdx.x) * 64 + lane] = frag_pair(h);
+    }
+  }
+  v4f z0[2][2], z1[2][2], z2[2][2], zo[2][1];
+  mlp_hidden<0, TRAIN>(a, act[0], act[1], lane, wv, z0);
+  __syncthreads();
+  mlp_hidden<1, TRAIN>(a, act[1], act[0], lane, wv, z1);
+  __syncthreads();
+  mlp_hidden<2, TRAIN>(a, act[0], act[1], lane, wv, z2);
+  __syncthreads();
+  mlp_product<HID, 1>(act[1], a.wf[NLAYER - 1], wv, lane, zo);
+  const int col = 16 * wv + (lane & 15);
+  const float b = a.bias[NLAYER - 1][col];
+  if constexpr (!TRAIN) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int64_t row = r0 + 16 * i + 4 * (lane >> 4) + r;
+        if (a.z_out && row < a.B) a.z_out[row * NOUT + col] = zo[i][0][r] + b;
+      }
+    if (a.h_last) {
+      // whole rows, 8 bytes a lane
+      for (int e = t; e < kMlpRows * (HID / 4); e += kMlpThreads) {
+        const int r = e / (HID / 4), c = 4 * (e % (HID / 4));
+        if (r0 + r < a.B)
+          *reinterpret_cast<uint2*>(a.h_last + (r0 + r) * HID + c) = *reinterpret_cast<const uint2*>(&act[1][r][c]);
+      }
+    }
+    return;
+  }
+  // output gradient 2 (out - y) / (B NOUT), rows beyond the batch zero
+  float g[2][4], lsum = 0.f;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int64_t row = r0 + 16 * i + 4 * (lane >> 4) + r;
+      g[i][r] = 0.f;
+      if (row < a.B) {
+        const float d = (zo[i][0][r] + b) - a.y[row * NOUT + col];
+        g[i][r] = 2.f * d / float(a.B * NOUT);
+        lsum += d * d;
+      }
+    }
+  mlp_store_grad<NLAYER - 1>(a, g, act[0], wv, lane);
+#pragma unroll
+  for (int w = 32; w > 0; w >>= 1) lsum += __shfl_xor(lsum, w);
+  if (lane == 0) red[wv] = lsum;
+  __syncthreads();
+  if (t == 0) {
+    float s = 0.f;
+    for (int w = 0; w < kMlpThreads / 64; ++w) s += red[w];
+    a.loss_part[blockIdx.x] = s;
+  }
+  mlp_backward_layer<3>(a, act[0], act[1], lane, wv, z2);
+  __syncthreads();
+  mlp_backward_layer<2>(a, act[1], act[0], lane, wv, z1);
+  __syncthreads();
+  mlp_backward_layer<1>(a, act[0], act[1], lane, wv, z0);
+}
+
+// ------------------------------------------------------ weight gradients
+// dW = x^T dz of every layer in one launch: a workgroup takes 64 x 64 of one
+// layer's gradient (16 x 64 of the first) and one of the `parts` ranges of row
+// blocks, its four waves every fourth block, straight from the fragments that
+// k_mlp left (they are both operands' own layout: the rows are contracted).
+// The waves' sums are added in LDS; the parts in k_params.
+constexpr int kGradParts = 8;
+constexpr int kGradUnits = 4 + 16 + 16 + 8;
+
+__host__ __device__ constexpr int flat_w(int l) {  // layer l's weights in the flat layout
+  return l == 0 ? 0 : l == 1 ? 16 * HID + HID : l == 2 ? 16 * HID + HID + HID * HID + HID
+                                              : 16 * HID + HID + 2 * (HID * HID + HID);
+}
+__host__ __device__ constexpr int flat_b(int l) { return flat_w(l) + (l == 0 ? 16 * HID : l < 3 ? HID * HID : HID * NOUT); }
+constexpr int kFlat = flat_b(3) + NOUT;
+
+struct GradArgs {
+  const uint4* hfrag[NLAYER];
+  const uint4* dfrag[NLAYER];
+  int64_t blocks;  // of 32 rows
+  float* parts;    // [parts][kFlat]
+};
+
+template <int MT>
+__device__ __forceinline__ void weight_grad(const GradArgs& a, int l, int m0, int n0, float* lds) {
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  const int mts = layer_in(l) / 16, nts = layer_out(l) / 16;
+  const int64_t lo = a.blocks * blockIdx.y / gridDim.y, hi = a.blocks * (blockIdx.y + 1) / gridDim.y;
+  struct alignas(16) Two { v4s s[2]; };
+  const Two* hp = reinterpret_cast<const Two*>(a.hfrag[l]);
+  const Two* dp = reinterpret_cast<const Two*>(a.dfrag[l]);
+  v4f acc[MT][4];
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+  Two x[MT], d[4];
+  auto load = [&](int64_t blk) {
+#pragma unroll
+    for (int i = 0; i < MT; ++i) x[i] = hp[(blk * mts + m0 + i) * 64 + lane];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) d[j] = dp[(blk * nts + n0 + j) * 64 + lane];
+  };
+  if (lo + wv < hi) load(lo + wv);
+  for (int64_t blk = lo + wv; blk < hi; blk += 4) {
+    Two cx[MT], cd[4];
+#pragma unroll
+    for (int i = 0; i < MT; ++i) cx[i] = x[i];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) cd[j] = d[j];
+    if (blk + 4 < hi) load(blk + 4);
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(cx[i].s[h], cd[j].s[h], acc[i][j], 0, 0, 0);
+  }
+  // element (tile, r, lane) of each wave
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) lds[((wv * MT * 4 + i * 4 + j) * 4 + r) * 64 + lane] = acc[i][j][r];
+  __syncthreads();
+  float* out = a.parts + int64_t(blockIdx.y) * kFlat + flat_w(l);
+  for (int e = t; e < MT * 1024; e += 256) {
+    float s = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) s += lds[w * MT * 1024 + e];
+    const int tile = e >> 8, r = (e >> 6) & 3, ln = e & 63;
+    const int row = 16 * (m0 + tile / 4) + 4 * (ln >> 4) + r, col = 16 * (n0 + tile % 4) + (ln & 15);
+    out[row * layer_out(l) + col] = s;
+  }
+}
+
+__global__ __launch_bounds__(256) void k_weight_grads(GradArgs a) {
+  __shared__ float lds[4 * 4 * 1024];
+  const int u = blockIdx.x;
+  if (u < 4) weight_grad<1>(a, 0, 0, 4 * u, lds);
+  else if (u < 36) weight_grad<4>(a, 1 + (u - 4) / 16, 4 * ((u - 4) % 16 / 4), 4 * ((u - 4) % 4), lds);
+  else weight_grad<4>(a, 3, 4 * ((u - 36) / 2), 4 * ((u - 36) % 2), lds);
+}
+
+// Sums the parts and either stores the gradient (flat layout) or makes the
+// AdamW step, refreshing the bf16 fragments: workgroups 0 .. take 256 weights
+// each, then 28 take 32 biases each, then one the loss.
+struct ParamArgs {
+  const float* parts;
+  int n_parts;
+  const float* bias_part;
+  const float* loss_part;
+  int64_t blocks;
+  float* grads;   // flat gradient, or NULL: AdamW
+  float* loss;    // or NULL
+  float *p[NLAYER], *m[NLAYER], *v[NLAYER];     // weights
+  float *pb[NLAYER], *mb[NLAYER], *vb[NLAYER];  // biases
+  uint16_t *wf[NLAYER], *wb[NLAYER];
+  float lr, b1, b2, eps, wd, c1, c2;
+};
+constexpr int kWeights = kFlat - kBiasCols;
+constexpr int kWeightBlocks = kWeights / 256, kBiasBlocks = kBiasCols / 32;
+static_assert(kWeights % 256 == 0 && kBiasCols % 32 == 0, "whole workgroups");
+
+__device__ __forceinline__ float adamw(const ParamArgs& a, float* p, float* mm, float* vv, float g, float wd) {
+  const float m = a.b1 * *mm + (1.f - a.b1) * g;
+  const float v = a.b2 * *vv + (1.f - a.b2) * g * g;
+  *mm = m;
+  *vv = v;
+  float x = *p;
+  x -= a.lr * (wd * x + (m * a.c1) / (sqrtf(v * a.c2) + a.eps));
+  *p = x;
+  return x;
+}
+
+__global__ __launch_bounds__(256) void k_params(ParamArgs a) {
+  __shared__ float red[256];
+  const int t = threadIdx.x, blk = blockIdx.x;
+  if (blk < kWeightBlocks) {
+    // every layer's weights are whole workgroups
+    int e = blk * 256 + t, l = 0;
+    while (l < NLAYER - 1 && e >= layer_in(l) * layer_out(l)) e -= layer_in(l) * layer_out(l), ++l;
+    float g = 0.f;
+    for (int p = 0; p < a.n_parts; ++p) g += a.parts[int64_t(p) * kFlat + flat_w(l) + e];
+    if (a.grads) {
+      a.grads[flat_w(l) + e] = g;
+      return;
+    }
+    const uint16_t h = f2bf(adamw(a, a.p[l] + e, a.m[l] + e, a.v[l] + e, g, a.wd));
+    const int k = e / layer_out(l), n = e % layer_out(l);
+    a.wf[l][frag_fwd(layer_in(l), k, n)] = h;
+    if (l > 0) a.wb[l][frag_bwd(layer_out(l), k, n)] = h;
+  } else if (blk < kWeightBlocks + kBiasBlocks) {
+    const int c = 32 * (blk - kWeightBlocks) + (t & 31), j = t >> 5;
+    float s = 0.f;
+    for (int64_t b = j; b < a.blocks; b += 8) s += a.bias_part[b * kBiasCols + c];
+    red[t] = s;
+    __syncthreads();
+    if (t >= 32) return;
+#pragma unroll
+    for (int i = 1; i < 8; ++i) s += red[32 * i + t];
+    const int l = min(c / HID, NLAYER - 1), o = c - bias_col(l);
+    if (a.grads) a.grads[flat_b(l) + o] = s;
+    else adamw(a, a.pb[l] + o, a.mb[l] + o, a.vb[l] + o, s, 0.f);  // biases are not decayed
+  } else {
+    float s = 0.f;
+    for (int64_t b = t; b < a.blocks; b += 256) s += a.loss_part[b];
+    red[t] = s;
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+      if (t < w) red[t] += red[t + w];
+      __syncthreads();
+    }
+    if (t == 0) a.loss[0] = red[0];
+  }
+}
+
+// bf16 fragments of layer l's weights W [nin][nout]
+__global__ __launch_bounds__(256) void k_weights_bf16(const float* W, int nin, int nout, uint16_t* wf, uint16_t* wb) {
+  const int e = blockIdx.x * 256 + threadIdx.x;
+  if (e >= nin * nout) return;
+  const uint16_t h = f2bf(W[e]);
+  wf[frag_fwd(nin, e / nout, e % nout)] = h;
+  if (nin > 16) wb[frag_bwd(nout, e / nout, e % nout)] = h;
 }
 
 __global__ void k_bf16_to_f32(const uint16_t* x, int64_t n, float* y) {
@@ -312,321 +703,12 @@ __global__ void k_bf16_to_f32(const uint16_t* x, int64_t n, float* y) {
   if (e < n) y[e] = bf2f(x[e]);
 }
 
-// ------------------------------------------------------ bf16 MFMA GEMM
-// C[M][N] = op(A)[M][K] op(B)[K][N] with binary32 accumulation.
-//   TA = false: A stored [M][lda];  TA = true: A stored [K][lda] (A^T)
-//   TB = false: B stored [K][ldb];  TB = true: B stored [N][ldb] (B^T)
-// 64x64 tile per 256-thread block, 4 waves of 32x32, 16x16x16 MFMA; K in
-// steps of 32 through LDS.  grid.z splits K (partial results at C + z*M*ldc).
-// Epilogues: 0 store; 1 z = acc + bias -> Zout (float) and Hout = bf16(silu z);
-// 2 z = acc + bias -> Zout (float).
-typedef short v4s __attribute__((ext_vector_type(4)));
-typedef float v4f __attribute__((ext_vector_type(4)));
-
-struct GemmArgs {
-  const uint16_t* A; int lda;
-  const uint16_t* B; int ldb;
-  float* C; int ldc;
-  int M, N, K, kchunk;
-  const float* bias;
-  float* Zout;
-  uint16_t* Hout;
-};
-
-template <bool TA, bool TB, int EPI>
-__global__ __launch_bounds__(256) void k_gemm_bf16(GemmArgs g) {
-  __shared__ uint16_t As[64][32 + 8];  // [row][k]
-  __shared__ uint16_t Bs[64][32 + 8];  // [col][k]
-  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  const int kbeg = blockIdx.z * g.kchunk;
-  const int kend = min(g.K, kbeg + g.kchunk);
-  const int wm = (wv >> 1) * 32, wn = (wv & 1) * 32;
-  // Staging: every thread moves eight consecutive elements of each operand
-  // with one 16-byte load.  Along k (A stored [M][lda], B stored [N][ldb]):
-  // row t / 4, k offset 8 (t % 4).  Along m or n (A^T stored [K][lda], B
-  // stored [K][ldb]): k offset t / 8, row 8 (t % 8), written to LDS
-  // transposed.  The launcher keeps every vector either wholly inside or
-  // wholly outside the operand (dimensions along the vector are multiples of
-  // 8), so each vector needs one bounds test.
-  const int ar = TA ? 8 * (t & 7) : t >> 2, ak = TA ? t >> 3 : 8 * (t & 3);
-  const int br = TB ? t >> 2 : 8 * (t & 7), bk = TB ? 8 * (t & 3) : t >> 3;
-  auto load_a = [&](int k0) {
-    const int gm = m0 + ar, gk = k0 + ak;
-    uint4 v = {0u, 0u, 0u, 0u};
-    if (gm < g.M && gk < kend)
-      v = *reinterpret_cast<const uint4*>(TA ? g.A + int64_t(gk) * g.lda + gm : g.A + int64_t(gm) * g.lda + gk);
-    return v;
-  };
-  auto load_b = [&](int k0) {
-    const int gn = n0 + br, gk = k0 + bk;
-    uint4 v = {0u, 0u, 0u, 0u};
-    if (gn < g.N && gk < kend)
-      v = *reinterpret_cast<const uint4*>(TB ? g.B + int64_t(gn) * g.ldb + gk : g.B + int64_t(gk) * g.ldb + gn);
-    return v;
-  };
-  auto store = [&](uint16_t (*S)[32 + 8], bool along_k, int r, int k, uint4 v) {
-    if (along_k) {
-      *reinterpret_cast<uint4*>(&S[r][k]) = v;
-    } else {
-      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        S[r + 2 * i][k] = uint16_t(w[i] & 0xffff);
-        S[r + 2 * i + 1][k] = uint16_t(w[i] >> 16);
-      }
-    }
-  };
-  v4f acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
-  uint4 va = load_a(kbeg), vb = load_b(kbeg);
-  for (int k0 = kbeg; k0 < kend; k0 += 32) {
-    store(As, !TA, ar, ak, va);
-    store(Bs, TB, br, bk, vb);
-    __syncthreads();
-    // the next tile's operands are requested before this tile's products
-    if (k0 + 32 < kend) {
-      va = load_a(k0 + 32);
-      vb = load_b(k0 + 32);
-    }
-#pragma unroll
-    for (int ks = 0; ks < 32; ks += 16) {
-      const int kk = ks + 4 * (lane >> 4);
-      v4s af[2], bfr[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const uint16_t* pa = &As[wm + 16 * i + (lane & 15)][kk];
-        af[i] = v4s{short(pa[0]), short(pa[1]), short(pa[2]), short(pa[3])};
-        const uint16_t* pb = &Bs[wn + 16 * i + (lane & 15)][kk];
-        bfr[i] = v4s{short(pb[0]), short(pb[1]), short(pb[2]), short(pb[3])};
-      }
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(af[i], bfr[j], acc[i][j], 0, 0, 0);
-    }
-    __syncthreads();
-  }
-  float* C = g.C + int64_t(blockIdx.z) * g.M * g.ldc;
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = m0 + wm + 16 * i + 4 * (lane >> 4) + r;
-        const int col = n0 + wn + 16 * j + (lane & 15);
-        if (row >= g.M || col >= g.N) continue;
-        const float v = acc[i][j][r];
-        if constexpr (EPI == 0) {
-          C[int64_t(row) * g.ldc + col] = v;
-        } else {
-          const float z = v + g.bias[col];
-          g.Zout[int64_t(row) * g.ldc + col] = z;
-          if constexpr (EPI == 1) {
-            const float h = z / (1.f + __expf(-z));
-            g.Hout[int64_t(row) * g.ldc + col] = f2bf(h);
-          }
-        }
-      }
-}
-
-// sum of `parts` partial [M][N] arrays -> out (binary32, fixed order)
-__global__ __launch_bounds__(256) void k_sum_parts(const float* parts, int parts_n, int64_t mn, float* out) {
-  const int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x;
-  if (e >= mn) return;
-  float s = 0.f;
-  for (int p = 0; p < parts_n; ++p) s += parts[p * mn + e];
-  out[e] = s;
-}
-
-// output layer: loss pieces and dZ = 2 (out - y) / (B NOUT); bf16 copy
-__global__ __launch_bounds__(256) void k_out_grad(const float* out, const float* y, int64_t B, float* dz, uint16_t* dzb,
-                                                  float* sqerr) {
-  const int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x;
-  if (e >= B * NOUT) return;
-  const float d = out[e] - y[e];
-  const float g = 2.f * d / float(B * NOUT);
-  dz[e] = g;
-  dzb[e] = f2bf(g);
-  sqerr[e] = d * d;
-}
-
-// hidden layer: dZ = dH * silu'(Z)
-__global__ __launch_bounds__(256) void k_silu_back(const float* dh, const float* z, int64_t n, float* dz, uint16_t* dzb) {
-  const int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x;
-  if (e >= n) return;
-  const float zz = z[e];
-  const float s = 1.f / (1.f + __expf(-zz));
-  const float g = dh[e] * s * (1.f + zz * (1.f - s));
-  dz[e] = g;
-  dzb[e] = f2bf(g);
-}
-
-// column sums (bias gradient, loss sum), binary32 partials in fixed order
-// Column sums of x [rows][cols] in two launches with one fixed order: the
-// partial p[t][col] sums rows t, t + 256, t + 512, ... (t < 256), read by
-// 64 consecutive columns per wave so that the loads are coalesced; then each
-// column's 256 partials are reduced pairwise (t and t + w for w = 128 .. 1).
-__global__ __launch_bounds__(256) void k_colsum_part(const float* x, int64_t rows, int cols, float* part) {
-  const int col = blockIdx.x * 64 + (threadIdx.x & 63);
-  const int t = blockIdx.y * 4 + (threadIdx.x >> 6);
-  if (col >= cols) return;
-  float s = 0.f;
-  for (int64_t i = t; i < rows; i += 256) s += x[i * cols + col];
-  part[int64_t(t) * cols + col] = s;
-}
-__global__ __launch_bounds__(256) void k_colsum_tree(const float* part, int cols, float* out) {
-  __shared__ float red[256];
-  const int col = blockIdx.x, t = threadIdx.x;
-  red[t] = part[int64_t(t) * cols + col];
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (t < w) red[t] += red[t + w];
-    __syncthreads();
-  }
-  if (t == 0) out[col] = red[0];
-}
-
-// AdamW on one parameter array; refreshes the bf16 copy and, for a weight
-// matrix [nin][nout], its transposed bf16 copy [nout][nin]
-struct AdamArgs {
-  float* p; const float* g; float* m; float* v; uint16_t* pb; int64_t n; float lr, b1, b2, eps, wd, c1, c2;
-  uint16_t* pt; int nin, nout;
-};
-__global__ __launch_bounds__(256) void k_adamw(AdamArgs a) {
-  const int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x;
-  if (e >= a.n) return;
-  const float g = a.g[e];
-  const float m = a.b1 * a.m[e] + (1.f - a.b1) * g;
-  const float v = a.b2 * a.v[e] + (1.f - a.b2) * g * g;
-  a.m[e] = m;
-  a.v[e] = v;
-  float p = a.p[e];
-  p -= a.lr * (a.wd * p + (m * a.c1) / (sqrtf(v * a.c2) + a.eps));
-  a.p[e] = p;
-  if (a.pb) a.pb[e] = f2bf(p);
-  if (a.pt) {
-    const int ei = int(e);  // a weight matrix has at most 65536 elements
-    a.pt[(ei % a.nout) * a.nin + ei / a.nout] = f2bf(p);
-  }
-}
-
-// bf16 copies of a weight matrix W [nin][nout]: Wb in the same layout, Wt
-// transposed [nout][nin]
-__global__ __launch_bounds__(256) void k_weights_bf16(const float* W, int nin, int nout, uint16_t* Wb, uint16_t* Wt) {
-  const int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x;
-  if (e >= int64_t(nin) * nout) return;
-  const uint16_t h = f2bf(W[e]);
-  Wb[e] = h;
-  const int ei = int(e);
-  Wt[(ei % nout) * nin + ei / nout] = h;
-}
-
-__global__ __launch_bounds__(256) void k_to_bf16(const float* x, int64_t n, uint16_t* y) {
-  const int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x;
-  if (e < n) y[e] = f2bf(x[e]);
-}
-
-// ------------------------------------------------------ inference MLP
-// The four layers for 32 rows per 256-thread workgroup in one pass, for the
-// node values of a batch (no training state).  Activations stay in LDS as
-// bf16; weights are read as W^T [out][in] (bf16) from global memory, four
-// consecutive inputs per lane.  Products and sums are those of k_gemm_bf16
-// (16x16x16 MFMA with the same lane layout, K in increasing steps of 16,
-// binary32 accumulation, bias and SiLU in binary32, bf16 rounding of the
-// hidden layers), so the outputs equal the layer-by-layer forward's bit for
-// bit.  Writes the last hidden layer (bf16, for the mismatch head) and the
-// output layer (binary32).
-constexpr int kInferRows = 32;
-constexpr int kActStride = HID + 4;  // bf16 per LDS row: 8-byte reads of 16 rows hit 32 distinct banks
-struct InferArgs {
-  const uint16_t* x0;            // [B][16] normalised inputs
-  const uint16_t* wt[NLAYER];    // W^T [out][in]
-  const float* bias[NLAYER];
-  int64_t B;
-  uint16_t* h_last;              // [B][HID]
-  float* z_out;                  // [B][NOUT]
-};
-
-template <int L>
-__device__ __forceinline__ void infer_layer(const InferArgs& a, const uint16_t (*in)[kActStride],
-                                            uint16_t (*out)[kActStride], int64_t r0, int lane, int wv) {
-  constexpr int K = L == 0 ? 16 : HID;
-  constexpr int N = L == NLAYER - 1 ? NOUT : HID;
-  constexpr int NTW = N / 64;  // 16-column tiles per wave
-  const int n0 = wv * (N / 4);
-  const uint16_t* wt = a.wt[L];
-  v4f acc[2][NTW];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < NTW; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    const int kk = k0 + 4 * (lane >> 4);
-    v4s af[2], bfr[NTW];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const uint16_t* pa = &in[16 * i + (lane & 15)][kk];
-      af[i] = v4s{short(pa[0]), short(pa[1]), short(pa[2]), short(pa[3])};
-    }
-#pragma unroll
-    for (int j = 0; j < NTW; ++j) {
-      const uint2 q = *reinterpret_cast<const uint2*>(wt + int64_t(n0 + 16 * j + (lane & 15)) * K + kk);
-      bfr[j] = v4s{short(q.x & 0xffff), short(q.x >> 16), short(q.y & 0xffff), short(q.y >> 16)};
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < NTW; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(af[i], bfr[j], acc[i][j], 0, 0, 0);
-  }
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < NTW; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = 16 * i + 4 * (lane >> 4) + r;
-        const int col = n0 + 16 * j + (lane & 15);
-        const int64_t grow = r0 + row;
-        const float z = acc[i][j][r] + a.bias[L][col];
-        if constexpr (L == NLAYER - 1) {
-          if (grow < a.B) a.z_out[grow * NOUT + col] = z;
-        } else {
-          const uint16_t h = f2bf(z / (1.f + __expf(-z)));
-          out[row][col] = h;
-          if (L == NLAYER - 2 && grow < a.B) a.h_last[grow * HID + col] = h;
-        }
-      }
-}
-
-__global__ __launch_bounds__(256) void k_mlp_infer(InferArgs a) {
-  __shared__ uint16_t act[2][kInferRows][kActStride];
-  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  const int64_t r0 = int64_t(blockIdx.x) * kInferRows;
-  for (int e = t; e < kInferRows * 16; e += 256) {
-    const int r = e / 16, c = e % 16;
-    act[0][r][c] = r0 + r < a.B ? a.x0[(r0 + r) * 16 + c] : uint16_t(0);
-  }
-  __syncthreads();
-  infer_layer<0>(a, act[0], act[1], r0, lane, wv);
-  __syncthreads();
-  infer_layer<1>(a, act[1], act[0], r0, lane, wv);
-  __syncthreads();
-  infer_layer<2>(a, act[0], act[1], r0, lane, wv);
-  __syncthreads();
-  infer_layer<3>(a, act[1], act[0], r0, lane, wv);
-}
-
 // --------------------------------------------------------- reconstruction
 // coefficients = phi A + zstd * z + zmean; node values = mean + coef V;
 // also the predicted log10 mismatch from the last hidden layer.
 struct ReconArgs {
-  const double* feat;    // [B][NFEAT]
+  const double* params;  // [12][pB], columns b0 ..
+  int64_t pB, b0;
   const float* z;        // [B][NOUT]
   const float* A;        // [NFEAT][NOUT]
   const float* zmean;
@@ -640,14 +722,24 @@ struct ReconArgs {
   float* logmm;          // [B] or NULL
 };
 
-// per sample: coefficients and predicted log10 mismatch
+// per sample: skip-path features phi (the PN coefficients times 3/(128 eta)),
+// coefficients and predicted log10 mismatch
 __global__ __launch_bounds__(256) void k_coefficients(ReconArgs a, float* coef) {
   __shared__ float red[256];
   const int64_t b = blockIdx.x;
   const int t = threadIdx.x;
   if (t < NOUT) {
+    const double* p = a.params + a.b0 + b;
+    const double q = p[a.pB], chi1 = p[2 * a.pB], chi2 = p[3 * a.pB];
+    const double eta = q / ((1.0 + q) * (1.0 + q));
+    double c[8], lg[8];
+    pn_coefficients(eta, q, chi1, chi2, c, lg);
+    const double pre = 3.0 / (128.0 * eta);
+    const double f[NFEAT] = {pre * c[2], pre * c[3], pre * c[4], pre * c[5], pre * c[6], pre * c[7], pre * lg[5],
+                             pre * lg[6], 1.0};
     double s = 0.0;
-    for (int fi = 0; fi < NFEAT; ++fi) s += a.feat[b * NFEAT + fi] * double(a.A[fi * NOUT + t]);
+#pragma unroll
+    for (int fi = 0; fi < NFEAT; ++fi) s += f[fi] * double(a.A[fi * NOUT + t]);
     coef[b * NOUT + t] = float(s + double(a.zstd[t]) * double(a.z[b * NOUT + t]) + double(a.zmean[t]));
   }
   if (!a.logmm) return;
@@ -659,49 +751,52 @@ __global__ __launch_bounds__(256) void k_coefficients(ReconArgs a, float* coef) 
   if (t == 0) a.logmm[b] = red[0] + a.head[HID];
 }
 
-// nodes[b][part][j] = mean[part][j] + sum_k coef[b][part*64 + k] V[part][k][j]:
-// 64 samples x 64 nodes per block, 4 x 4 per thread, K = 64 through LDS.
+// nodes[b][part][j] = mean[part][j] + sum_k coef[b][part*64 + k] V[part][k][j]
+// on the matrix cores (binary32, 16x16x4): 32 samples by 64 nodes per wave,
+// grid (NN/256, ceil(B/32), 2).  Lane c + 16 g supplies k = 16 g + s in step s,
+// so that it reads a sample's coefficients as four 16-byte loads.
 __global__ __launch_bounds__(256) void k_reconstruct(ReconArgs a, const float* coef) {
-  __shared__ float cs[NBAS][64 + 4];   // [k][sample]
-  __shared__ float vs[NBAS][64 + 4];   // [k][node]
-  const int part = blockIdx.z;
-  const int64_t b0 = int64_t(blockIdx.y) * 64;
-  const int j0 = blockIdx.x * 64;
-  const int t = threadIdx.x;
-  const float* V = a.basis + size_t(part) * NBAS * NN;
-  for (int e = t; e < 64 * NBAS; e += 256) {
-    const int r = e / NBAS, k = e % NBAS;
-    const int64_t b = b0 + r;
-    cs[k][r] = b < a.B ? coef[b * NOUT + part * NBAS + k] : 0.f;
-    const int k2 = e / 64, jj = e % 64;
-    vs[k2][jj] = V[size_t(k2) * NN + j0 + jj];
+  const int part = blockIdx.z, t = threadIdx.x, lane = t & 63, c = lane & 15, g = lane >> 4;
+  const int64_t b0 = int64_t(blockIdx.y) * 32;
+  const int j0 = blockIdx.x * 256 + (t >> 6) * 64;
+  const float* V = a.basis + (size_t(part) * NBAS + 16 * g) * NN + j0 + c;
+  float ca[2][16];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int64_t b = min(b0 + 16 * i + c, a.B - 1);  // rows beyond the batch repeat its last and are not stored
+    const float4* p = reinterpret_cast<const float4*>(coef + b * NOUT + part * NBAS + 16 * g);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float4 v = p[q];
+      ca[i][4 * q] = v.x;
+      ca[i][4 * q + 1] = v.y;
+      ca[i][4 * q + 2] = v.z;
+      ca[i][4 * q + 3] = v.w;
+    }
   }
-  __syncthreads();
-  const int tr = (t / 16) * 4, tc = (t % 16) * 4;
-  float acc[4][4];
+  v4f acc[2][4];
 #pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    const float m = float(a.mean[part * NN + j0 + tc + c]);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) acc[r][c] = m;
-  }
-#pragma unroll 8
-  for (int k = 0; k < NBAS; ++k) {
-    float ca[4], va[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) { ca[q] = cs[k][tr + q]; va[q] = vs[k][tc + q]; }
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-      for (int c = 0; c < 4; ++c) acc[r][c] = fmaf(ca[r], va[c], acc[r][c]);
+  for (int j = 0; j < 4; ++j) {
+    const float m = float(a.mean[part * NN + j0 + 16 * j + c]);
+    acc[0][j] = acc[1][j] = v4f{m, m, m, m};
   }
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int64_t b = b0 + tr + r;
-    if (b < a.B)
+  for (int s = 0; s < 16; ++s)
 #pragma unroll
-      for (int c = 0; c < 4; ++c) a.nodes[(b * 2 + part) * NN + j0 + tc + c] = acc[r][c];
-  }
+    for (int j = 0; j < 4; ++j) {
+      const float v = V[size_t(s) * NN + 16 * j];
+      acc[0][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(ca[0][s], v, acc[0][j], 0, 0, 0);
+      acc[1][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(ca[1][s], v, acc[1][j], 0, 0, 0);
+    }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int64_t b = b0 + 16 * i + 4 * g + r;
+      if (b < a.B)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) a.nodes[(b * 2 + part) * NN + j0 + 16 * j + c] = acc[i][j][r];
+    }
 }
 
 // h+, hx on the window grid from node values (binary64 Newtonian phase,
@@ -971,35 +1066,28 @@ struct gw_surrogate {
   float* head = nullptr;    // [HID + 1]
   float* W[NLAYER] = {};
   float* b[NLAYER] = {};
-  uint16_t* Wb[NLAYER] = {};
-  uint16_t* Wt[NLAYER] = {};    // transposed bf16 copies [out][in] (inference)
+  uint16_t* wf[NLAYER] = {};    // bf16 fragments of the weights, forward order
+  uint16_t* wb[NLAYER] = {};    // and backward order (layers 1..)
   float* mW[NLAYER] = {};
   float* vW[NLAYER] = {};
   float* mb[NLAYER] = {};
   float* vb[NLAYER] = {};
-  float* gW[NLAYER] = {};
-  float* gb[NLAYER] = {};
   int64_t step = 0;
   double beta1 = 0.9, beta2 = 0.999, eps = 1e-8;  // AdamW hyper-parameters
   int64_t bmax = 0;
-  uint16_t* X0 = nullptr;       // [bmax][16]
-  float* Z[NLAYER] = {};        // [bmax][out]
-  uint16_t* H[NLAYER] = {};     // [bmax][out] (H[3] unused)
-  float* dZ = nullptr;          // [bmax][HID]
-  uint16_t* dZb = nullptr;      // [bmax][HID]
-  float* dH = nullptr;          // [bmax][HID]
-  float* parts = nullptr;       // split-K partials
-  float* sqerr = nullptr;       // [bmax][NOUT]
-  float* colbuf = nullptr;      // [NOUT]
-  float* theta = nullptr;       // [bmax][4]
-  double* feat = nullptr;       // [bmax][NFEAT]
-  float* zbuf = nullptr;        // [bmax][NOUT]
+  // scratch for bmax rows (bblk = ceil(bmax/32) blocks of 32)
+  uint4* hfrag[NLAYER] = {};    // [bblk][in/16][64]
+  uint4* dfrag[NLAYER] = {};    // [bblk][out/16][64]
+  float* bias_part = nullptr;   // [bblk][kBiasCols]
+  float* loss_part = nullptr;   // [bblk]
+  float* parts = nullptr;       // [kGradParts][kFlat]
+  float* zout = nullptr;        // [bmax][NOUT] output layer
+  uint16_t* hlast = nullptr;    // [bmax][HID] last hidden layer
+  float* coef = nullptr;        // [bmax][NOUT]
   std::string err;
 };
 
 namespace {
-
-constexpr int kSplitK = 16;
 
 gw_status sfail(gw_surrogate* s, gw_status st, const std::string& m) {
   if (s) s->err = m;
@@ -1012,100 +1100,76 @@ gw_status slaunch(gw_surrogate* s, const char* what) {
 }
 unsigned nblk(int64_t n) { return unsigned((n + 255) / 256); }
 
-// column sums of x [rows][cols] (cols <= 256) through the partials buffer
-// part (256 * cols floats)
-void colsum(const float* x, int64_t rows, int cols, float* part, float* out, hipStream_t st) {
-  hipLaunchKernelGGL(k_colsum_part, dim3(unsigned((cols + 63) / 64), 64), dim3(256), 0, st, x, rows, cols, part);
-  hipLaunchKernelGGL(k_colsum_tree, dim3(unsigned(cols)), dim3(256), 0, st, part, cols, out);
-}
-
 template <class T> bool dalloc(T** p, size_t n) { return hipMalloc(reinterpret_cast<void**>(p), sizeof(T) * n) == hipSuccess; }
 
-// The staging vectors run along k for A [M][lda] and B^T [N][ldb], along m
-// for A^T [K][lda] and along n for B [K][ldb].  Every call here has those
-// dimensions, the K chunks and the leading dimensions at multiples of 8 (the
-// layer widths 16, 128 and 256; the batch only ever runs across vectors).
-void launch_gemm(bool ta, bool tb, int epi, const GemmArgs& g, int splits, hipStream_t st) {
-  dim3 grid(unsigned((g.N + 63) / 64), unsigned((g.M + 63) / 64), unsigned(splits));
-  if (!ta && !tb && epi == 1) hipLaunchKernelGGL((k_gemm_bf16<false, false, 1>), grid, dim3(256), 0, st, g);
-  else if (!ta && !tb && epi == 2) hipLaunchKernelGGL((k_gemm_bf16<false, false, 2>), grid, dim3(256), 0, st, g);
-  else if (!ta && !tb) hipLaunchKernelGGL((k_gemm_bf16<false, false, 0>), grid, dim3(256), 0, st, g);
-  else if (!ta && tb) hipLaunchKernelGGL((k_gemm_bf16<false, true, 0>), grid, dim3(256), 0, st, g);
-  else hipLaunchKernelGGL((k_gemm_bf16<true, false, 0>), grid, dim3(256), 0, st, g);
+MlpArgs mlp_args(const gw_surrogate* s, const float* theta, int64_t B) {
+  MlpArgs a{};
+  a.theta = theta;
+  a.B = B;
+  for (int c = 0; c < 4; ++c) { a.lo[c] = s->lo[c]; a.hi[c] = s->hi[c]; }
+  for (int l = 0; l < NLAYER; ++l) {
+    a.wf[l] = s->wf[l];
+    a.wb[l] = s->wb[l];
+    a.bias[l] = s->b[l];
+  }
+  return a;
 }
 
-// inference pass for B rows of theta (k_mlp_infer): leaves the output layer
-// in Z[NLAYER - 1] and the last hidden layer in H[NLAYER - 2], as mlp_forward
-gw_status mlp_infer(gw_surrogate* s, const float* theta, int64_t B, hipStream_t st) {
-  NormArgs na;
-  na.theta = theta;
-  na.B = B;
-  for (int c = 0; c < 4; ++c) { na.lo[c] = s->lo[c]; na.hi[c] = s->hi[c]; }
-  na.x = s->X0;
-  hipLaunchKernelGGL(k_norm_inputs, dim3(nblk(B * 16)), dim3(256), 0, st, na);
-  InferArgs ia{};
-  ia.x0 = s->X0;
-  for (int l = 0; l < NLAYER; ++l) {
-    ia.wt[l] = s->Wt[l];
-    ia.bias[l] = s->b[l];
-  }
-  ia.B = B;
-  ia.h_last = s->H[NLAYER - 2];
-  ia.z_out = s->Z[NLAYER - 1];
-  hipLaunchKernelGGL(k_mlp_infer, dim3(unsigned((B + kInferRows - 1) / kInferRows)), dim3(256), 0, st, ia);
+unsigned mlp_blocks(int64_t B) { return unsigned((B + kMlpRows - 1) / kMlpRows); }
+
+// output layer to z_out, last hidden layer to h_last (either may be NULL)
+gw_status mlp_infer(gw_surrogate* s, MlpArgs a, float* z_out, uint16_t* h_last, hipStream_t st) {
+  a.z_out = z_out;
+  a.h_last = h_last;
+  hipLaunchKernelGGL((k_mlp<false>), dim3(mlp_blocks(a.B)), dim3(kMlpThreads), 0, st, a);
   return slaunch(s, "mlp inference");
 }
 
-// forward pass for B rows of theta; leaves Z[l], H[l] in scratch
-gw_status mlp_forward(gw_surrogate* s, const float* theta, int64_t B, hipStream_t st) {
-  NormArgs na;
-  na.theta = theta;
-  na.B = B;
-  for (int c = 0; c < 4; ++c) { na.lo[c] = s->lo[c]; na.hi[c] = s->hi[c]; }
-  na.x = s->X0;
-  hipLaunchKernelGGL(k_norm_inputs, dim3(nblk(B * 16)), dim3(256), 0, st, na);
-  const uint16_t* in = s->X0;
+// Forward and backward pass, then the gradients (flat layout) or, with grads
+// NULL, the AdamW step of `u`.  Three launches: 37 of layer-by-layer products,
+// sums and element-wise passes took 258 us at 8192 rows, of which the products'
+// arithmetic is 7 us at the rate of a large matrix product.
+gw_status mlp_train(gw_surrogate* s, const float* theta, const float* z, int64_t B, float* grads, float* loss, ParamArgs u,
+                    hipStream_t st) {
+  MlpArgs a = mlp_args(s, theta, B);
+  a.y = z;
+  GradArgs g{};
   for (int l = 0; l < NLAYER; ++l) {
-    GemmArgs g{};
-    g.A = in; g.lda = layer_in(l);
-    g.B = s->Wb[l]; g.ldb = layer_out(l);
-    g.C = nullptr; g.ldc = layer_out(l);
-    g.M = int(B); g.N = layer_out(l); g.K = layer_in(l); g.kchunk = layer_in(l);
-    g.bias = s->b[l];
-    g.Zout = s->Z[l];
-    g.Hout = s->H[l];
-    launch_gemm(false, false, l < NLAYER - 1 ? 1 : 2, g, 1, st);
-    in = s->H[l];
+    g.hfrag[l] = a.hfrag[l] = s->hfrag[l];
+    g.dfrag[l] = a.dfrag[l] = s->dfrag[l];
   }
-  return slaunch(s, "mlp forward");
-}
-
-// backward pass from the output gradient in s->dZ/s->dZb ([B][NOUT]); fills gW, gb
-gw_status mlp_backward(gw_surrogate* s, int64_t B, hipStream_t st) {
-  for (int l = NLAYER - 1; l >= 0; --l) {
-    const int nin = layer_in(l), nout = layer_out(l);
-    // dW = H_{l-1}^T dZ  (split over the batch), db = colsum(dZ)
-    GemmArgs g{};
-    g.A = l > 0 ? s->H[l - 1] : s->X0; g.lda = nin;
-    g.B = s->dZb; g.ldb = nout;
-    g.C = s->parts; g.ldc = nout;
-    g.M = nin; g.N = nout; g.K = int(B);
-    g.kchunk = int(((B + kSplitK - 1) / kSplitK + 31) / 32 * 32);
-    launch_gemm(true, false, 0, g, kSplitK, st);
-    hipLaunchKernelGGL(k_sum_parts, dim3(nblk(int64_t(nin) * nout)), dim3(256), 0, st, s->parts, kSplitK,
-                       int64_t(nin) * nout, s->gW[l]);
-    colsum(s->dZ, B, nout, s->parts, s->gb[l], st);
-    if (l == 0) break;
-    // dH_{l-1} = dZ W_l^T, then dZ_{l-1} = dH * silu'(Z_{l-1})
-    GemmArgs h{};
-    h.A = s->dZb; h.lda = nout;
-    h.B = s->Wb[l]; h.ldb = nout;  // W stored [nin][nout] = B^T layout [N][K]
-    h.C = s->dH; h.ldc = nin;
-    h.M = int(B); h.N = nin; h.K = nout; h.kchunk = nout;
-    launch_gemm(false, true, 0, h, 1, st);
-    hipLaunchKernelGGL(k_silu_back, dim3(nblk(B * nin)), dim3(256), 0, st, s->dH, s->Z[l - 1], B * nin, s->dZ, s->dZb);
+  a.bias_part = s->bias_part;
+  a.loss_part = s->loss_part;
+  const unsigned blocks = mlp_blocks(B);
+  hipLaunchKernelGGL((k_mlp<true>), dim3(blocks), dim3(kMlpThreads), 0, st, a);
+  gw_status r = slaunch(s, "mlp forward and backward");
+  if (r != GW_OK) return r;
+  g.blocks = blocks;
+  g.parts = s->parts;
+  // a wave of a part takes every fourth of its blocks
+  const int parts = int(std::min<int64_t>(kGradParts, (blocks + 3) / 4));
+  hipLaunchKernelGGL(k_weight_grads, dim3(kGradUnits, unsigned(parts)), dim3(256), 0, st, g);
+  r = slaunch(s, "weight gradients");
+  if (r != GW_OK) return r;
+  u.parts = s->parts;
+  u.n_parts = parts;
+  u.bias_part = s->bias_part;
+  u.loss_part = s->loss_part;
+  u.blocks = blocks;
+  u.grads = grads;
+  u.loss = loss;
+  for (int l = 0; l < NLAYER; ++l) {
+    u.p[l] = s->W[l];
+    u.m[l] = s->mW[l];
+    u.v[l] = s->vW[l];
+    u.pb[l] = s->b[l];
+    u.mb[l] = s->mb[l];
+    u.vb[l] = s->vb[l];
+    u.wf[l] = s->wf[l];
+    u.wb[l] = s->wb[l];
   }
-  return slaunch(s, "mlp backward");
+  hipLaunchKernelGGL(k_params, dim3(unsigned(kWeightBlocks + kBiasBlocks + (loss ? 1 : 0))), dim3(256), 0, st, u);
+  return slaunch(s, "parameter update");
 }
 
 int64_t layer_wn(int l) { return int64_t(layer_in(l)) * layer_out(l); }
@@ -1121,11 +1185,11 @@ extern "C" {
 
 gw_status gw_surrogate_destroy(gw_surrogate* s) {
   if (!s) return GW_OK;
-  void* ptrs[] = {s->basis, s->mean, s->A, s->zmean, s->zstd, s->head, s->X0, s->dZ, s->dZb, s->dH, s->parts,
-                  s->sqerr, s->colbuf, s->theta, s->feat, s->zbuf};
+  void* ptrs[] = {s->basis, s->mean, s->A, s->zmean, s->zstd, s->head, s->bias_part, s->loss_part, s->parts,
+                  s->zout, s->hlast, s->coef};
   for (void* p : ptrs) (void)hipFree(p);
   for (int l = 0; l < NLAYER; ++l) {
-    void* q[] = {s->W[l], s->b[l], s->Wb[l], s->Wt[l], s->mW[l], s->vW[l], s->mb[l], s->vb[l], s->gW[l], s->gb[l], s->Z[l], s->H[l]};
+    void* q[] = {s->W[l], s->b[l], s->wf[l], s->wb[l], s->mW[l], s->vW[l], s->mb[l], s->vb[l], s->hfrag[l], s->dfrag[l]};
     for (void* p : q) (void)hipFree(p);
   }
   delete s;
@@ -1146,17 +1210,17 @@ gw_status gw_surrogate_create(gw_ctx* ctx, int64_t max_batch, gw_surrogate** out
   for (int i = 0; i < 4; ++i)
     if (!(s->hi[i] > s->lo[i])) s->hi[i] = s->lo[i] + 1.0f;
   s->bmax = max_batch;
-  const int64_t B = max_batch;
+  const int64_t B = max_batch, blocks = mlp_blocks(max_batch);
   bool ok = dalloc(&s->basis, 2 * NBAS * NN) && dalloc(&s->mean, 2 * NN) && dalloc(&s->A, NFEAT * NOUT) &&
             dalloc(&s->zmean, NOUT) && dalloc(&s->zstd, NOUT) && dalloc(&s->head, HID + 1) &&
-            dalloc(&s->X0, B * 16) && dalloc(&s->dZ, B * HID) && dalloc(&s->dZb, B * HID) && dalloc(&s->dH, B * HID) &&
-            dalloc(&s->parts, size_t(kSplitK) * HID * HID) && dalloc(&s->sqerr, B * NOUT) && dalloc(&s->colbuf, NOUT) &&
-            dalloc(&s->theta, B * 4) && dalloc(&s->feat, B * NFEAT) && dalloc(&s->zbuf, B * NOUT);
+            dalloc(&s->bias_part, size_t(blocks) * kBiasCols) && dalloc(&s->loss_part, size_t(blocks)) &&
+            dalloc(&s->parts, size_t(kGradParts) * kFlat) && dalloc(&s->zout, B * NOUT) && dalloc(&s->hlast, B * HID) &&
+            dalloc(&s->coef, B * NOUT);
   for (int l = 0; l < NLAYER && ok; ++l) {
     const int64_t wn = layer_wn(l), bo = layer_out(l);
-    ok = dalloc(&s->W[l], wn) && dalloc(&s->b[l], bo) && dalloc(&s->Wb[l], wn) && dalloc(&s->Wt[l], wn) && dalloc(&s->mW[l], wn) &&
-         dalloc(&s->vW[l], wn) && dalloc(&s->mb[l], bo) && dalloc(&s->vb[l], bo) && dalloc(&s->gW[l], wn) &&
-         dalloc(&s->gb[l], bo) && dalloc(&s->Z[l], B * bo) && dalloc(&s->H[l], B * bo);
+    ok = dalloc(&s->W[l], wn) && dalloc(&s->b[l], bo) && dalloc(&s->wf[l], wn) && dalloc(&s->wb[l], wn) && dalloc(&s->mW[l], wn) &&
+         dalloc(&s->vW[l], wn) && dalloc(&s->mb[l], bo) && dalloc(&s->vb[l], bo) &&
+         dalloc(&s->hfrag[l], size_t(blocks) * (layer_in(l) / 16) * 64) && dalloc(&s->dfrag[l], size_t(blocks) * (bo / 16) * 64);
   }
   if (!ok) {
     gw_surrogate_destroy(s);
@@ -1181,8 +1245,8 @@ gw_status gw_surrogate_create(gw_ctx* ctx, int64_t max_batch, gw_surrogate** out
     up(s->vW[l], zeros.data(), sizeof(float) * wn);
     up(s->mb[l], zeros.data(), sizeof(float) * bo);
     up(s->vb[l], zeros.data(), sizeof(float) * bo);
-    up(s->Wb[l], zeros.data(), sizeof(uint16_t) * wn);
-    up(s->Wt[l], zeros.data(), sizeof(uint16_t) * wn);
+    up(s->wf[l], zeros.data(), sizeof(uint16_t) * wn);
+    up(s->wb[l], zeros.data(), sizeof(uint16_t) * wn);
   }
   if (!ok || hipDeviceSynchronize() != hipSuccess) {
     gw_surrogate_destroy(s);
@@ -1205,8 +1269,8 @@ gw_status gw_surrogate_set_weights(gw_surrogate* s, const float* host_flat, int6
     p += wn;
     if (hipMemcpy(s->b[l], p, sizeof(float) * bo, hipMemcpyHostToDevice) != hipSuccess) return GW_EHIP;
     p += bo;
-    hipLaunchKernelGGL(k_weights_bf16, dim3(nblk(wn)), dim3(256), 0, 0, s->W[l], layer_in(l), layer_out(l), s->Wb[l],
-                       s->Wt[l]);
+    hipLaunchKernelGGL(k_weights_bf16, dim3(nblk(wn)), dim3(256), 0, 0, s->W[l], layer_in(l), layer_out(l), s->wf[l],
+                       s->wb[l]);
   }
   s->step = 0;
   for (int l = 0; l < NLAYER; ++l) {
@@ -1338,11 +1402,7 @@ gw_status gw_surrogate_standardise(gw_surrogate* s, const double* feat, const fl
 
 gw_status gw_surrogate_forward(gw_surrogate* s, const float* theta, int64_t B, float* out, hipStream_t st) {
   if (!s || !theta || !out || B < 1 || B > s->bmax) return GW_EINVAL;
-  gw_status r = mlp_forward(s, theta, B, st);
-  if (r != GW_OK) return r;
-  if (hipMemcpyAsync(out, s->Z[NLAYER - 1], sizeof(float) * B * NOUT, hipMemcpyDeviceToDevice, st) != hipSuccess)
-    return sfail(s, GW_EHIP, "forward copy");
-  return GW_OK;
+  return mlp_infer(s, mlp_args(s, theta, B), out, nullptr, st);
 }
 
 // Gradients of the mean-squared loss for (theta, z) without an update.
@@ -1350,25 +1410,7 @@ gw_status gw_surrogate_forward(gw_surrogate* s, const float* theta, int64_t B, f
 gw_status gw_surrogate_gradients(gw_surrogate* s, const float* theta, const float* z, int64_t B, float* grads, float* loss,
                                  hipStream_t st) {
   if (!s || !theta || !z || !grads || B < 1 || B > s->bmax) return GW_EINVAL;
-  gw_status r = mlp_forward(s, theta, B, st);
-  if (r != GW_OK) return r;
-  hipLaunchKernelGGL(k_out_grad, dim3(nblk(B * NOUT)), dim3(256), 0, st, s->Z[NLAYER - 1], z, B, s->dZ, s->dZb, s->sqerr);
-  r = mlp_backward(s, B, st);
-  if (r != GW_OK) return r;
-  float* p = grads;
-  for (int l = 0; l < NLAYER; ++l) {
-    if (hipMemcpyAsync(p, s->gW[l], sizeof(float) * layer_wn(l), hipMemcpyDeviceToDevice, st) != hipSuccess)
-      return sfail(s, GW_EHIP, "hipMemcpyAsync (weight gradients)");
-    p += layer_wn(l);
-    if (hipMemcpyAsync(p, s->gb[l], sizeof(float) * layer_out(l), hipMemcpyDeviceToDevice, st) != hipSuccess)
-      return sfail(s, GW_EHIP, "hipMemcpyAsync (bias gradients)");
-    p += layer_out(l);
-  }
-  if (loss) {
-    colsum(s->sqerr, B, NOUT, s->parts, s->colbuf, st);
-    colsum(s->colbuf, NOUT, 1, s->parts, loss, st);
-  }
-  return slaunch(s, "gradients");
+  return mlp_train(s, theta, z, B, grads, loss, ParamArgs{}, st);
 }
 
 gw_status gw_surrogate_set_adam(gw_surrogate* s, double beta1, double beta2, double eps) {
@@ -1384,37 +1426,24 @@ gw_status gw_surrogate_set_adam(gw_surrogate* s, double beta1, double beta2, dou
 gw_status gw_surrogate_train_step(gw_surrogate* s, const float* theta, const float* z, int64_t B, float lr,
                                   float weight_decay, float* loss, hipStream_t st) {
   if (!s || !theta || !z || B < 1 || B > s->bmax || !(lr >= 0.f) || !(weight_decay >= 0.f)) return GW_EINVAL;
-  gw_status r = mlp_forward(s, theta, B, st);
-  if (r != GW_OK) return r;
-  hipLaunchKernelGGL(k_out_grad, dim3(nblk(B * NOUT)), dim3(256), 0, st, s->Z[NLAYER - 1], z, B, s->dZ, s->dZb, s->sqerr);
-  r = mlp_backward(s, B, st);
-  if (r != GW_OK) return r;
   s->step += 1;
   // bias corrections 1/(1 - beta^t) in binary64 on the host
-  const float b1 = float(s->beta1), b2 = float(s->beta2), eps = float(s->eps);
-  const float c1 = float(1.0 / (1.0 - std::pow(s->beta1, double(s->step))));
-  const float c2 = float(1.0 / (1.0 - std::pow(s->beta2, double(s->step))));
-  for (int l = 0; l < NLAYER; ++l) {
-    AdamArgs aw{s->W[l], s->gW[l], s->mW[l], s->vW[l], s->Wb[l], layer_wn(l), lr, b1, b2, eps, weight_decay, c1, c2,
-                s->Wt[l], layer_in(l), layer_out(l)};
-    hipLaunchKernelGGL(k_adamw, dim3(nblk(layer_wn(l))), dim3(256), 0, st, aw);
-    // biases are not decayed
-    AdamArgs ab{s->b[l], s->gb[l], s->mb[l], s->vb[l], nullptr, layer_out(l), lr, b1, b2, eps, 0.f, c1, c2,
-                nullptr, 0, 0};
-    hipLaunchKernelGGL(k_adamw, dim3(nblk(layer_out(l))), dim3(256), 0, st, ab);
-  }
-  if (loss) {
-    colsum(s->sqerr, B, NOUT, s->parts, s->colbuf, st);
-    colsum(s->colbuf, NOUT, 1, s->parts, loss, st);
-  }
-  return slaunch(s, "train_step");
+  ParamArgs u{};
+  u.lr = lr;
+  u.b1 = float(s->beta1);
+  u.b2 = float(s->beta2);
+  u.eps = float(s->eps);
+  u.wd = weight_decay;
+  u.c1 = float(1.0 / (1.0 - std::pow(s->beta1, double(s->step))));
+  u.c2 = float(1.0 / (1.0 - std::pow(s->beta2, double(s->step))));
+  return mlp_train(s, theta, z, B, nullptr, loss, u, st);
 }
 
 gw_status gw_surrogate_hidden(gw_surrogate* s, const float* theta, int64_t B, float* h3, hipStream_t st) {
   if (!s || !theta || !h3 || B < 1 || B > s->bmax) return GW_EINVAL;
-  gw_status r = mlp_forward(s, theta, B, st);
+  gw_status r = mlp_infer(s, mlp_args(s, theta, B), nullptr, s->hlast, st);
   if (r != GW_OK) return r;
-  hipLaunchKernelGGL(k_bf16_to_f32, dim3(nblk(B * HID)), dim3(256), 0, st, s->H[NLAYER - 2], B * HID, h3);
+  hipLaunchKernelGGL(k_bf16_to_f32, dim3(nblk(B * HID)), dim3(256), 0, st, s->hlast, B * HID, h3);
   return slaunch(s, "hidden");
 }
 
@@ -1467,16 +1496,17 @@ gw_status gw_surrogate_nodes(gw_surrogate* s, const double* params, int64_t B, f
   if (B == 0) return GW_OK;
   for (int64_t b0 = 0; b0 < B; b0 += s->bmax) {
     const int64_t nb = std::min(s->bmax, B - b0);
-    // this chunk's parameter columns are strided by B: gather theta and features
-    hipLaunchKernelGGL(k_theta_from_params_off, dim3(nblk(nb * 4)), dim3(256), 0, st, params, B, b0, nb, s->theta);
-    hipLaunchKernelGGL(k_features_off, dim3(nblk(nb)), dim3(256), 0, st, params, B, b0, nb, s->feat);
-    gw_status r = mlp_infer(s, s->theta, nb, st);
+    MlpArgs a = mlp_args(s, nullptr, nb);
+    a.params = params;
+    a.pB = B;
+    a.b0 = b0;
+    gw_status r = mlp_infer(s, a, s->zout, s->hlast, st);
     if (r != GW_OK) return r;
-    ReconArgs ra{s->feat, s->Z[NLAYER - 1], s->A, s->zmean, s->zstd, s->basis, s->mean, s->H[NLAYER - 2], s->head,
+    ReconArgs ra{params, B, b0, s->zout, s->A, s->zmean, s->zstd, s->basis, s->mean, s->hlast, s->head,
                  nb, nodes + b0 * 2 * NN, logmm ? logmm + b0 : nullptr};
-    hipLaunchKernelGGL(k_coefficients, dim3(unsigned(nb)), dim3(256), 0, st, ra, s->zbuf);
-    hipLaunchKernelGGL(k_reconstruct, dim3(NN / 64, unsigned((nb + 63) / 64), 2), dim3(256), 0, st, ra,
-                       static_cast<const float*>(s->zbuf));
+    hipLaunchKernelGGL(k_coefficients, dim3(unsigned(nb)), dim3(256), 0, st, ra, s->coef);
+    hipLaunchKernelGGL(k_reconstruct, dim3(NN / 256, unsigned((nb + 31) / 32), 2), dim3(256), 0, st, ra,
+                       static_cast<const float*>(s->coef));
   }
   return slaunch(s, "nodes");
 }
@@ -1577,7 +1607,7 @@ gw_status gw_surrogate_load(gw_surrogate* s, const char* path) {
     ok = get(s->W[l], sizeof(float) * layer_wn(l)) && get(s->b[l], sizeof(float) * layer_out(l));
     if (ok)
       hipLaunchKernelGGL(k_weights_bf16, dim3(nblk(layer_wn(l))), dim3(256), 0, 0, s->W[l], layer_in(l), layer_out(l),
-                         s->Wb[l], s->Wt[l]);
+                         s->wf[l], s->wb[l]);
   }
   int64_t step = 0;
   double hyper[3] = {0.9, 0.999, 1e-8};
