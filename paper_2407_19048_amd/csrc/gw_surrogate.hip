@@ -49,6 +49,21 @@ __device__ __forceinline__ uint16_t f2bf(float x) {
   u += 0x7FFFu + ((u >> 16) & 1u);
   return uint16_t(u >> 16);
 }
+// two at a time (v_cvt_pk_bf16_f32, the same rounding to nearest even): x in the low half
+__device__ __forceinline__ uint32_t f2bf2(float x, float y) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{x, y}, bf16x2));
+}
+// a / d for d >= 1: the reciprocal's quotient corrected by its exact remainder
+// (correctly rounded but for rare ties; a fifth of the instructions of a
+// division that scales its operands)
+__device__ __forceinline__ float div_ge1(float a, float d) {
+  const float r = __builtin_amdgcn_rcpf(d), q = a * r;
+  return __builtin_fmaf(__builtin_fmaf(-q, d, a), r, q);
+}
+// 1 + exp(-z), at most 2^126 (its reciprocal must stay normal)
+__device__ __forceinline__ float one_plus_exp(float z) { return fminf(1.f + __expf(-z), 0x1p126f); }
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float(uint32_t(h) << 16); }
 
 // -------------------------------------------------------- targets at nodes
@@ -270,9 +285,9 @@ __global__ __launch_bounds__(256) void k_colstats(const float* Z, int64_t n, int
 
 // ------------------------------------------------------------- network
 // 4-256-256-256-128 MLP on bf16 MFMA (16x16x16, binary32 accumulation, K in
-// increasing steps of 16), 32 rows per 512-thread workgroup through every
-// layer: activations in LDS as bf16, each wave owning 32 columns (16 of the
-// output layer).  At the training batch of 8192 that is one workgroup per CU;
+// increasing steps of 16), 32 rows per 1024-thread workgroup through every
+// layer: activations in LDS as bf16, each wave owning 16 columns (of the
+// output layer, for one half of the rows).  At the training batch of 8192 that is one workgroup per CU;
 // what bounds it is the 800 KB of weights each workgroup reads from L2 (forward
 // and backward order), so they are stored as the MFMA operands' own fragments
 // and read 1 KB per wave and load.
@@ -284,7 +299,7 @@ typedef short v4s __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr int kMlpRows = 32;
-constexpr int kMlpThreads = 512;
+constexpr int kMlpThreads = 1024;
 constexpr int kActStride = HID + 4;  // bf16 per LDS row: 8-byte reads of 16 rows hit 32 distinct banks
 constexpr int kBiasCols = 3 * HID + NOUT;
 
@@ -325,131 +340,110 @@ struct MlpArgs {
   float* loss_part;             // [blocks]
 };
 
-// acc[i][j] = rows 16 i .. of the LDS matrix `in` times the j-th tile of the
-// fragments w (K rows), tiles tile0 ..
-template <int K, int NT>
-__device__ __forceinline__ void mlp_product(const uint16_t (*in)[kActStride], const uint16_t* w, int tile0, int lane,
-                                            v4f (*acc)[NT]) {
-  constexpr int KP = K >= 32 ? K / 32 : 1;
+// A wave's fragments of one layer's weights (K rows, one tile of 16 columns).
+// They do not depend on the activations, so each layer's are requested before
+// the product ahead of it; the workgroup's barriers wait for LDS only.
+template <int K> struct MlpFrags {
+  static constexpr int KS = K / 16, STEP = K == 16 ? 1 : 2;  // steps of 16, steps per load
+  struct alignas(8 * STEP) Load { v4s s[STEP]; };
+  Load q[KS / STEP];
+  __device__ __forceinline__ void load(const uint16_t* w, int tile, int lane) {
+    const Load* wp = reinterpret_cast<const Load*>(w) + tile * (KS / STEP) * 64 + lane;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+    for (int kp = 0; kp < KS / STEP; ++kp) q[kp] = wp[kp * 64];
+  }
+};
+
+// acc[i] = rows 16 (i0 + i) .. of the LDS matrix `in` times w, for NI halves i
+template <int NI, int K>
+__device__ __forceinline__ void mlp_product(const uint16_t (*in)[kActStride], const MlpFrags<K>& w, int i0, int lane,
+                                            v4f* acc) {
 #pragma unroll
-    for (int j = 0; j < NT; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
-  auto frag = [&](int i, int ks) {
-    return *reinterpret_cast<const v4s*>(&in[16 * i + (lane & 15)][16 * ks + 4 * (lane >> 4)]);
-  };
-  if constexpr (K == 16) {
-    const v4s a0 = frag(0, 0), a1 = frag(1, 0);
+  for (int i = 0; i < NI; ++i) acc[i] = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int j = 0; j < NT; ++j) {
-      const v4s b = reinterpret_cast<const v4s*>(w)[(tile0 + j) * 64 + lane];
-      acc[0][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a0, b, acc[0][j], 0, 0, 0);
-      acc[1][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a1, b, acc[1][j], 0, 0, 0);
+  for (int ks = 0; ks < K / 16; ++ks) {
+    constexpr int STEP = MlpFrags<K>::STEP;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const v4s af = *reinterpret_cast<const v4s*>(&in[16 * (i0 + i) + (lane & 15)][16 * ks + 4 * (lane >> 4)]);
+      acc[i] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(af, w.q[ks / STEP].s[ks % STEP], acc[i], 0, 0, 0);
     }
-  } else {
-    struct alignas(16) Two { v4s s[2]; };
-    const Two* wp = reinterpret_cast<const Two*>(w) + int64_t(tile0) * KP * 64 + lane;
-    Two q[KP][NT];
-#pragma unroll
-    for (int kp = 0; kp < KP; ++kp)
-#pragma unroll
-      for (int j = 0; j < NT; ++j) q[kp][j] = wp[(j * KP + kp) * 64];
-#pragma unroll
-    for (int kp = 0; kp < KP; ++kp)
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const v4s a0 = frag(0, 2 * kp + h), a1 = frag(1, 2 * kp + h);
-#pragma unroll
-        for (int j = 0; j < NT; ++j) {
-          acc[0][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a0, q[kp][j].s[h], acc[0][j], 0, 0, 0);
-          acc[1][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a1, q[kp][j].s[h], acc[1][j], 0, 0, 0);
-        }
-      }
   }
 }
 
-// Four rounded values of each of the two row halves, as one fragment pair.
-__device__ __forceinline__ uint4 frag_pair(const uint16_t (*h)[4]) {
-  return uint4{uint32_t(h[0][0]) | uint32_t(h[0][1]) << 16, uint32_t(h[0][2]) | uint32_t(h[0][3]) << 16,
-               uint32_t(h[1][0]) | uint32_t(h[1][1]) << 16, uint32_t(h[1][2]) | uint32_t(h[1][3]) << 16};
+// A lane's rounded values of one tile (four rows of each of the two row
+// halves): as a fragment pair and, in `out`, at their rows' column.
+__device__ __forceinline__ uint4 frag_pair(const float (*x)[4]) {
+  return uint4{f2bf2(x[0][0], x[0][1]), f2bf2(x[0][2], x[0][3]), f2bf2(x[1][0], x[1][1]), f2bf2(x[1][2], x[1][3])};
+}
+__device__ __forceinline__ void frag_to_rows(uint4 h, uint16_t (*out)[kActStride], int tile, int lane) {
+  const uint32_t w[4] = {h.x, h.y, h.z, h.w};
+  const int row = 4 * (lane >> 4), col = 16 * tile + (lane & 15);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    out[16 * (i >> 1) + row + 2 * (i & 1)][col] = uint16_t(w[i]);
+    out[16 * (i >> 1) + row + 2 * (i & 1) + 1][col] = uint16_t(w[i] >> 16);
+  }
 }
 
 // Hidden layer L: z = x W + b kept by the wave, silu(z) rounded to LDS (and to
 // the next layer's input fragments).
-template <int L, bool TRAIN>
+template <int L, bool TRAIN, int K>
 __device__ __forceinline__ void mlp_hidden(const MlpArgs& a, const uint16_t (*in)[kActStride], uint16_t (*out)[kActStride],
-                                           int lane, int wv, v4f (*z)[2]) {
-  constexpr int K = L == 0 ? 16 : HID;
-  mlp_product<K, 2>(in, a.wf[L], 2 * wv, lane, z);
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int tile = 2 * wv + j, col = 16 * tile + (lane & 15);
-    const float b = a.bias[L][col];
-    uint16_t h[2][4];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float zz = z[i][j][r] + b;
-        z[i][j][r] = zz;
-        h[i][r] = f2bf(zz / (1.f + __expf(-zz)));
-        out[16 * i + 4 * (lane >> 4) + r][col] = h[i][r];
-      }
-    if constexpr (TRAIN) a.hfrag[L + 1][(int64_t(blockIdx.x) * (HID / 16) + tile) * 64 + lane] = frag_pair(h);
-  }
-}
-
-// Rounded gradient dz of layer L's output for tile `tile`: fragments, LDS (if
-// another layer follows) and the column sums of the bias gradient.
-template <int L>
-__device__ __forceinline__ void mlp_store_grad(const MlpArgs& a, const float (*g)[4], uint16_t (*out)[kActStride], int tile,
-                                               int lane) {
-  constexpr int N = L == NLAYER - 1 ? NOUT : HID;
-  uint16_t h[2][4];
-  float s = 0.f;
+                                           const MlpFrags<K>& w, int lane, int tile, v4f* z) {
+  const float b = a.bias[L][16 * tile + (lane & 15)];
+  mlp_product<2>(in, w, 0, lane, z);
+  float x[2][4];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      h[i][r] = f2bf(g[i][r]);
-      s += g[i][r];
-      if constexpr (L > 0) out[16 * i + 4 * (lane >> 4) + r][16 * tile + (lane & 15)] = h[i][r];
+      z[i][r] += b;
+      x[i][r] = div_ge1(z[i][r], one_plus_exp(z[i][r]));
     }
-  a.dfrag[L][(int64_t(blockIdx.x) * (N / 16) + tile) * 64 + lane] = frag_pair(h);
-  s += __shfl_xor(s, 16);
-  s += __shfl_xor(s, 32);
-  if (lane < 16) a.bias_part[int64_t(blockIdx.x) * kBiasCols + bias_col(L) + 16 * tile + lane] = s;
+  const uint4 h = frag_pair(x);
+  frag_to_rows(h, out, tile, lane);
+  if constexpr (TRAIN) a.hfrag[L + 1][(int64_t(blockIdx.x) * (HID / 16) + tile) * 64 + lane] = h;
 }
 
-// dz of layer L - 1 from dz of layer L (in LDS): dH = dz W^T, times silu'(z).
-template <int L>
+// dz of layer L - 1 from dz of layer L (in LDS): dH = dz W^T, times silu'(z);
+// its fragments, LDS rows (if another layer follows) and bias gradient sums.
+template <int L, int K>
 __device__ __forceinline__ void mlp_backward_layer(const MlpArgs& a, const uint16_t (*in)[kActStride],
-                                                   uint16_t (*out)[kActStride], int lane, int wv, const v4f (*z)[2]) {
-  constexpr int K = L == NLAYER - 1 ? NOUT : HID;
-  v4f dh[2][2];
-  mlp_product<K, 2>(in, a.wb[L], 2 * wv, lane, dh);
+                                                   uint16_t (*out)[kActStride], const MlpFrags<K>& w, int lane, int tile,
+                                                   const v4f* z) {
+  v4f dh[2];
+  mlp_product<2>(in, w, 0, lane, dh);
+  float g[2][4], sum = 0.f;
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    float g[2][4];
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float zz = z[i][j][r];
-        const float s = 1.f / (1.f + __expf(-zz));
-        g[i][r] = dh[i][j][r] * s * (1.f + zz * (1.f - s));
-      }
-    mlp_store_grad<L - 1>(a, g, out, 2 * wv + j, lane);
-  }
+    for (int r = 0; r < 4; ++r) {
+      const float zz = z[i][r];
+      const float s = div_ge1(1.f, one_plus_exp(zz));
+      g[i][r] = dh[i][r] * s * (1.f + zz * (1.f - s));
+      sum += g[i][r];
+    }
+  const uint4 h = frag_pair(g);
+  if constexpr (L > 1) frag_to_rows(h, out, tile, lane);
+  a.dfrag[L - 1][(int64_t(blockIdx.x) * (HID / 16) + tile) * 64 + lane] = h;
+  sum += __shfl_xor(sum, 16);
+  sum += __shfl_xor(sum, 32);
+  if (lane < 16) a.bias_part[int64_t(blockIdx.x) * kBiasCols + bias_col(L - 1) + 16 * tile + lane] = sum;
 }
 
 template <bool TRAIN>
-__global__ __launch_bounds__(kMlpThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_mlp(MlpArgs a) {
+__global__ __launch_bounds__(kMlpThreads) void k_mlp(MlpArgs a) {
   __shared__ uint16_t act[2][kMlpRows][kActStride];
-  __shared__ float red[kMlpThreads / 64];
+  __shared__ float red[kMlpThreads / 64], bsum[NOUT];
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const int64_t r0 = int64_t(blockIdx.x) * kMlpRows;
-  {
+  MlpFrags<16> w0;
+  MlpFrags<HID> w1, w2, w3, v2, v1;
+  MlpFrags<NOUT> v3;
+  w0.load(a.wf[0], wv, lane);
+  w1.load(a.wf[1], wv, lane);
+  if (t < kMlpRows * 16) {
     // x = 2 (theta - lo)/(hi - lo) - 1 for (M_c, q, chi1, chi2), zero pad
     const int r = t / 16, c = t % 16;
     const int64_t row = r0 + r;
@@ -460,35 +454,42 @@ __global__ __launch_bounds__(kMlpThreads) __attribute__((amdgpu_waves_per_eu(2, 
     }
     act[0][r][c] = h;
   }
-  __syncthreads();
+  lds_barrier();
   if constexpr (TRAIN) {
     if (wv == 0) {
-      uint16_t h[2][4];
+      uint32_t h[4];
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) h[i][r] = act[0][16 * i + 4 * (lane >> 4) + r][lane & 15];
-      a.hfrag[0][int64_t(blockIdx.x) * 64 + lane] = frag_pair(h);
+      for (int i = 0; i < 4; ++i) {
+        const int row = 16 * (i >> 1) + 4 * (lane >> 4) + 2 * (i & 1);
+        h[i] = uint32_t(act[0][row][lane & 15]) | uint32_t(act[0][row + 1][lane & 15]) << 16;
+      }
+      a.hfrag[0][int64_t(blockIdx.x) * 64 + lane] = uint4{h[0], h[1], h[2], h[3]};
     }
   }
-  v4f z0[2][2], z1[2][2], z2[2][2], zo[2][1];
-  mlp_hidden<0, TRAIN>(a, act[0], act[1], lane, wv, z0);
-  __syncthreads();
-  mlp_hidden<1, TRAIN>(a, act[1], act[0], lane, wv, z1);
-  __syncthreads();
-  mlp_hidden<2, TRAIN>(a, act[0], act[1], lane, wv, z2);
-  __syncthreads();
-  mlp_product<HID, 1>(act[1], a.wf[NLAYER - 1], wv, lane, zo);
-  const int col = 16 * wv + (lane & 15);
+  v4f z0[2], z1[2], z2[2], zo;
+  mlp_hidden<0, TRAIN>(a, act[0], act[1], w0, lane, wv, z0);
+  w2.load(a.wf[2], wv, lane);
+  lds_barrier();
+  mlp_hidden<1, TRAIN>(a, act[1], act[0], w1, lane, wv, z1);
+  // output layer: tile wv % 8 for the rows of half wv / 8
+  const int tile = wv & 7, half = wv >> 3, col = 16 * tile + (lane & 15);
+  const int64_t row0 = r0 + 16 * half + 4 * (lane >> 4);
+  w3.load(a.wf[3], tile, lane);
+  float y[4] = {};
+  if constexpr (TRAIN) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) y[r] = a.y[min(row0 + r, a.B - 1) * NOUT + col];
+  }
+  lds_barrier();
+  mlp_hidden<2, TRAIN>(a, act[0], act[1], w2, lane, wv, z2);
   const float b = a.bias[NLAYER - 1][col];
+  lds_barrier();
+  if constexpr (TRAIN) v3.load(a.wb[3], wv, lane);
+  mlp_product<1>(act[1], w3, half, lane, &zo);
   if constexpr (!TRAIN) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int64_t row = r0 + 16 * i + 4 * (lane >> 4) + r;
-        if (a.z_out && row < a.B) a.z_out[row * NOUT + col] = zo[i][0][r] + b;
-      }
+    for (int r = 0; r < 4; ++r)
+      if (a.z_out && row0 + r < a.B) a.z_out[(row0 + r) * NOUT + col] = zo[r] + b;
     if (a.h_last) {
       // whole rows, 8 bytes a lane
       for (int e = t; e < kMlpRows * (HID / 4); e += kMlpThreads) {
@@ -500,34 +501,44 @@ __global__ __launch_bounds__(kMlpThreads) __attribute__((amdgpu_waves_per_eu(2, 
     return;
   }
   // output gradient 2 (out - y) / (B NOUT), rows beyond the batch zero
-  float g[2][4], lsum = 0.f;
+  float g[4], lsum = 0.f, sum = 0.f;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int64_t row = r0 + 16 * i + 4 * (lane >> 4) + r;
-      g[i][r] = 0.f;
-      if (row < a.B) {
-        const float d = (zo[i][0][r] + b) - a.y[row * NOUT + col];
-        g[i][r] = 2.f * d / float(a.B * NOUT);
-        lsum += d * d;
-      }
-    }
-  mlp_store_grad<NLAYER - 1>(a, g, act[0], wv, lane);
+  for (int r = 0; r < 4; ++r) {
+    const float d = row0 + r < a.B ? (zo[r] + b) - y[r] : 0.f;
+    g[r] = 2.f * d / float(a.B * NOUT);
+    lsum += d * d;
+    sum += g[r];
+  }
+  const uint2 h = {f2bf2(g[0], g[1]), f2bf2(g[2], g[3])};
+  {
+    uint16_t(*out)[kActStride] = act[0] + 16 * half + 4 * (lane >> 4);
+    out[0][col] = uint16_t(h.x);
+    out[1][col] = uint16_t(h.x >> 16);
+    out[2][col] = uint16_t(h.y);
+    out[3][col] = uint16_t(h.y >> 16);
+  }
+  reinterpret_cast<uint2*>(a.dfrag[NLAYER - 1])[((int64_t(blockIdx.x) * (NOUT / 16) + tile) * 64 + lane) * 2 + half] = h;
+  sum += __shfl_xor(sum, 16);
+  sum += __shfl_xor(sum, 32);
+  if (half == 1 && lane < 16) bsum[col] = sum;
 #pragma unroll
   for (int w = 32; w > 0; w >>= 1) lsum += __shfl_xor(lsum, w);
   if (lane == 0) red[wv] = lsum;
-  __syncthreads();
+  lds_barrier();
+  v2.load(a.wb[2], wv, lane);
+  if (half == 0 && lane < 16)
+    a.bias_part[int64_t(blockIdx.x) * kBiasCols + bias_col(NLAYER - 1) + col] = sum + bsum[col];
   if (t == 0) {
     float s = 0.f;
     for (int w = 0; w < kMlpThreads / 64; ++w) s += red[w];
     a.loss_part[blockIdx.x] = s;
   }
-  mlp_backward_layer<3>(a, act[0], act[1], lane, wv, z2);
-  __syncthreads();
-  mlp_backward_layer<2>(a, act[1], act[0], lane, wv, z1);
-  __syncthreads();
-  mlp_backward_layer<1>(a, act[0], act[1], lane, wv, z0);
+  mlp_backward_layer<3>(a, act[0], act[1], v3, lane, wv, z2);
+  lds_barrier();
+  v1.load(a.wb[1], wv, lane);
+  mlp_backward_layer<2>(a, act[1], act[0], v2, lane, wv, z1);
+  lds_barrier();
+  mlp_backward_layer<1>(a, act[0], act[1], v1, lane, wv, z0);
 }
 
 // ------------------------------------------------------ weight gradients
@@ -535,7 +546,9 @@ __global__ __launch_bounds__(kMlpThreads) __attribute__((amdgpu_waves_per_eu(2, 
 // layer's gradient (16 x 64 of the first) and one of the `parts` ranges of row
 // blocks, its four waves every fourth block, straight from the fragments that
 // k_mlp left (they are both operands' own layout: the rows are contracted).
-// The waves' sums are added in LDS; the parts in k_params.
+// The waves' sums are added in LDS; the parts in k_params.  The part is the
+// fastest index of the grid: consecutive workgroups go to different XCDs, so
+// with 8 parts each XCD's L2 reads its own eighth of the fragments.
 constexpr int kGradParts = 8;
 constexpr int kGradUnits = 4 + 16 + 16 + 8;
 
@@ -550,14 +563,15 @@ struct GradArgs {
   const uint4* hfrag[NLAYER];
   const uint4* dfrag[NLAYER];
   int64_t blocks;  // of 32 rows
-  float* parts;    // [parts][kFlat]
+  float* parts;    // [n_parts][kFlat]
+  int n_parts;
 };
 
 template <int MT>
-__device__ __forceinline__ void weight_grad(const GradArgs& a, int l, int m0, int n0, float* lds) {
+__device__ __forceinline__ void weight_grad(const GradArgs& a, int part, int l, int m0, int n0, float* lds) {
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const int mts = layer_in(l) / 16, nts = layer_out(l) / 16;
-  const int64_t lo = a.blocks * blockIdx.y / gridDim.y, hi = a.blocks * (blockIdx.y + 1) / gridDim.y;
+  const int64_t lo = a.blocks * part / a.n_parts, hi = a.blocks * (part + 1) / a.n_parts;
   struct alignas(16) Two { v4s s[2]; };
   const Two* hp = reinterpret_cast<const Two*>(a.hfrag[l]);
   const Two* dp = reinterpret_cast<const Two*>(a.dfrag[l]);
@@ -597,7 +611,7 @@ __device__ __forceinline__ void weight_grad(const GradArgs& a, int l, int m0, in
 #pragma unroll
       for (int r = 0; r < 4; ++r) lds[((wv * MT * 4 + i * 4 + j) * 4 + r) * 64 + lane] = acc[i][j][r];
   __syncthreads();
-  float* out = a.parts + int64_t(blockIdx.y) * kFlat + flat_w(l);
+  float* out = a.parts + int64_t(part) * kFlat + flat_w(l);
   for (int e = t; e < MT * 1024; e += 256) {
     float s = 0.f;
 #pragma unroll
@@ -610,10 +624,10 @@ __device__ __forceinline__ void weight_grad(const GradArgs& a, int l, int m0, in
 
 __global__ __launch_bounds__(256) void k_weight_grads(GradArgs a) {
   __shared__ float lds[4 * 4 * 1024];
-  const int u = blockIdx.x;
-  if (u < 4) weight_grad<1>(a, 0, 0, 4 * u, lds);
-  else if (u < 36) weight_grad<4>(a, 1 + (u - 4) / 16, 4 * ((u - 4) % 16 / 4), 4 * ((u - 4) % 4), lds);
-  else weight_grad<4>(a, 3, 4 * ((u - 36) / 2), 4 * ((u - 36) % 2), lds);
+  const int u = blockIdx.x / a.n_parts, part = blockIdx.x % a.n_parts;
+  if (u < 4) weight_grad<1>(a, part, 0, 0, 4 * u, lds);
+  else if (u < 36) weight_grad<4>(a, part, 1 + (u - 4) / 16, 4 * ((u - 4) % 16 / 4), 4 * ((u - 4) % 4), lds);
+  else weight_grad<4>(a, part, 3, 4 * ((u - 36) / 2), 4 * ((u - 36) % 2), lds);
 }
 
 // Sums the parts and either stores the gradient (flat layout) or makes the
@@ -655,6 +669,7 @@ __global__ __launch_bounds__(256) void k_params(ParamArgs a) {
     int e = blk * 256 + t, l = 0;
     while (l < NLAYER - 1 && e >= layer_in(l) * layer_out(l)) e -= layer_in(l) * layer_out(l), ++l;
     float g = 0.f;
+#pragma unroll 8
     for (int p = 0; p < a.n_parts; ++p) g += a.parts[int64_t(p) * kFlat + flat_w(l) + e];
     if (a.grads) {
       a.grads[flat_w(l) + e] = g;
@@ -667,6 +682,7 @@ __global__ __launch_bounds__(256) void k_params(ParamArgs a) {
   } else if (blk < kWeightBlocks + kBiasBlocks) {
     const int c = 32 * (blk - kWeightBlocks) + (t & 31), j = t >> 5;
     float s = 0.f;
+#pragma unroll 8
     for (int64_t b = j; b < a.blocks; b += 8) s += a.bias_part[b * kBiasCols + c];
     red[t] = s;
     __syncthreads();
@@ -1148,7 +1164,8 @@ gw_status mlp_train(gw_surrogate* s, const float* theta, const float* z, int64_t
   g.parts = s->parts;
   // a wave of a part takes every fourth of its blocks
   const int parts = int(std::min<int64_t>(kGradParts, (blocks + 3) / 4));
-  hipLaunchKernelGGL(k_weight_grads, dim3(kGradUnits, unsigned(parts)), dim3(256), 0, st, g);
+  g.n_parts = parts;
+  hipLaunchKernelGGL(k_weight_grads, dim3(unsigned(kGradUnits * parts)), dim3(256), 0, st, g);
   r = slaunch(s, "weight gradients");
   if (r != GW_OK) return r;
   u.parts = s->parts;
