@@ -141,23 +141,41 @@ __device__ __forceinline__ int psd_index(const DevCfg& cf, int k, int NC) {
   return min(k >> cf.log2_ratio, (NC >> cf.log2_ratio) - 1);
 }
 
-// Whitening factor for window bin k in [0, N/2] from the PSD values
-// s0 = psd[i], s1 = psd[i + 1], i = psd_index(k); sets status bits.
-template <class T>
-__device__ __forceinline__ T whiten_gain_at(const DevCfg& cf, float s0, float s1, int k, int NC, uint32_t& flag) {
-  if (k == 0 || k >= NC || k < cf.kmin) return T(0);
-  const int i = k >> cf.log2_ratio;
-  const T tt = T(k - (i << cf.log2_ratio)) * T(cf.inv_ratio);
-  const T S = (T(1) - tt) * T(s0) + tt * T(s1);
-  if (!isfinite(S)) { flag |= GW_STATUS_NONFINITE_PSD; return T(0); }
-  if (!(S > T(0))) { flag |= GW_STATUS_NONPOSITIVE_PSD; return T(0); }
-  return rsqrt_t(T(cf.fs) * S * T(0.5));
+// The PSD values around window bins k and NC - k.
+struct PsdAround { float lo[2], hi[2]; };
+__device__ __forceinline__ PsdAround psd_around(const DevCfg& cf, const float* psd, int k, int NC) {
+  PsdAround q;
+  __builtin_memcpy(q.lo, psd + psd_index(cf, k, NC), 8);
+  __builtin_memcpy(q.hi, psd + psd_index(cf, NC - k, NC), 8);
+  return q;
 }
 
+// S at window bin k from the values around it.
+template <class T> __device__ __forceinline__ T psd_at(const DevCfg& cf, const float* s, int k) {
+  return fma_t(T(k & (cf.ratio - 1)) * T(cf.inv_ratio), T(s[1]) - T(s[0]), T(s[0]));
+}
+
+// 1/sqrt(S) for a kept bin's PSD value S; sets status bits.
+template <class T>
+__device__ __forceinline__ T psd_gain(T S, bool kept, uint32_t& flag) {
+  const bool good = S > T(0) && S < T(INFINITY);
+  if (kept && !good) flag |= isfinite(S) ? GW_STATUS_NONPOSITIVE_PSD : GW_STATUS_NONFINITE_PSD;
+  return kept && good ? rsqrt_t(S) : T(0);
+}
+
+// Whitening factors times sqrt(fs/2) of bins k and NC - k, k in [0, NC/2].
+template <class T>
+__device__ __forceinline__ void psd_gains(const DevCfg& cf, const PsdAround& q, int k, int NC, uint32_t& flag, T* gk, T* gm) {
+  const bool inner = k != 0;  // bins 0 and NC are dropped
+  *gk = psd_gain<T>(psd_at<T>(cf, q.lo, k), inner && k >= cf.kmin, flag);
+  *gm = psd_gain<T>(psd_at<T>(cf, q.hi, NC - k), inner && NC - k >= cf.kmin, flag);
+}
+
+// Whitening factor for window bin k in [0, N/2] (zero outside the kept band).
 template <class T>
 __device__ __forceinline__ T whiten_gain(const DevCfg& cf, const float* psd, int k, int NC, uint32_t& flag) {
-  const int i = psd_index(cf, k, NC);
-  return whiten_gain_at<T>(cf, psd[i], psd[i + 1], k, NC, flag);
+  const T S = psd_at<T>(cf, psd + psd_index(cf, k, NC), k);
+  return psd_gain<T>(S, k > 0 && k < NC && k >= cf.kmin, flag) * rsqrt_t(T(cf.fs) * T(0.5));
 }
 
 // Gain g = filt[k] of a precomputed whitening filter; sets status bits.
@@ -167,65 +185,93 @@ __device__ __forceinline__ T filter_gain_at(float g, uint32_t& flag) {
   return T(g);
 }
 
-// Projected signal (DFT coefficients) at window bin k, generated in registers.
-// Projected sine-Gaussian at bin k: fs sg_G0 [G(f - f0)(cpl - i cxx) e^{-2 pi i rm}
+// Real-spectrum unpack of the packed bins A = Z_k and B = Z_(NC-k), with
+// W = exp(-2 pi i k / N): twice the real input's spectrum at k and NC - k.
+template <class T>
+__device__ __forceinline__ void unpack_pair(cpx<T> A, cpx<T> B, cpx<T> W, cpx<T>* Xk, cpx<T>* Xm) {
+  const T sx = A.x + B.x, sy = A.y - B.y, dx = A.x - B.x, dy = A.y + B.y;  // A + conj B, A - conj B
+  // X_k = s - i W d, X_m = conj(s + i W d)
+  *Xk = {fma_t(W.x, dy, fma_t(W.y, dx, sx)), fma_t(-W.x, dx, fma_t(W.y, dy, sy))};
+  *Xm = {fma_t(-W.x, dy, fma_t(-W.y, dx, sx)), fma_t(-W.x, dx, fma_t(W.y, dy, -sy))};
+}
+
+// The inverse packing: twice Z'_k and Z'_(NC-k) from the spectrum Y_k = gk Xk,
+// Y_m = gm Xm at both bins.  (Products and sums are fused explicitly, so that
+// every kernel that includes this rounds alike.)
+template <class T>
+__device__ __forceinline__ void repack_pair(cpx<T> Xk, T gk, cpx<T> Xm, T gm, cpx<T> W, cpx<T>* zk, cpx<T>* zm) {
+  const T mx = gm * Xm.x, my = gm * Xm.y;
+  const T px = fma_t(gk, Xk.x, mx), py = fma_t(gk, Xk.y, -my);  // p = Y_k + conj Y_m
+  const T dx = fma_t(gk, Xk.x, -mx), dy = fma_t(gk, Xk.y, my);  // d = Y_k - conj Y_m
+  // q = conj(W) d; Z'_k = p + i q, Z'_m = conj(p) + i conj(q)
+  *zk = {fma_t(-W.x, dy, fma_t(W.y, dx, px)), fma_t(W.x, dx, fma_t(W.y, dy, py))};
+  *zm = {fma_t(T(2), px, -zk->x), fma_t(T(-2), py, zk->y)};
+}
+
+// What unpack_pair, psd_gains and repack_pair leave out of a whitened window,
+// applied where it is stored: 1/2 each for the two packings, sqrt(2/fs) and
+// the inverse transform's 1/NC.
+template <class T> __device__ __forceinline__ T whitened_scale(const DevCfg& cf, int NC) {
+  return T(0.25) * rsqrt_t(T(cf.fs) * T(0.5)) / T(NC);
+}
+
+// The detector's projection of one item: the signal is added to twice the
+// spectrum, so the antenna factors carry 2 fs.
+template <class T> struct Projection {
+  T cpl, cxx;
+  double tauT;  // time shift in windows
+};
+
+// Projected sine-Gaussian at bin k: sg_G0 [G(f - f0)(cpl - i cxx) e^{-2 pi i rm}
 // + G(f + f0)(cpl + i cxx) e^{-2 pi i rp}], rm/rp = k tau/T -/+ phi0/(2 pi).
 template <class T, class TP>
-__device__ __forceinline__ cpx<T> burst_bin(const DevCfg& cf, const WfScalars& w, T cpl, T cxx, double tauT, int k) {
+__device__ __forceinline__ cpx<T> burst_bin(const DevCfg& cf, const WfScalars& w, const Projection<T>& pr, int k) {
+  const T cpl = pr.cpl, cxx = pr.cxx;
   const double f = double(k) * cf.invT;
   const T xm = T(f - w.sg_f0), xp = T(f + w.sg_f0);
   const T gm = exp(-T(w.sg_pt2) * xm * xm), gp = exp(-T(w.sg_pt2) * xp * xp);
-  const TP base = frac1(TP(k) * TP(tauT));
+  const TP base = frac1(TP(k) * TP(pr.tauT));
   T sm, cm, sp, cp;
   sincos_rev(T(frac1(base - TP(w.sg_rphi))), &sm, &cm);
   sincos_rev(T(frac1(base + TP(w.sg_rphi))), &sp, &cp);
-  const T A = T(cf.fs) * T(w.sg_G0);
+  const T A = T(w.sg_G0);
   return {A * (gm * (cpl * cm - cxx * sm) + gp * (cpl * cp + cxx * sp)),
           A * (gp * (cxx * cp - cpl * sp) - gm * (cpl * sm + cxx * cm))};
 }
 
-// Same, with k^(1/3) and ln(k)/3 given by the caller (kc, lk).
-template <class T, class TP, bool FULL>
-__device__ __forceinline__ cpx<T> signal_bin_at(const DevCfg& cf, const WfScalars& w, T cpl, T cxx, double tauT,
-                                                int k, double kc, double lk) {
-  if (k <= 0 || k < cf.kmin || k >= w.kend) return {T(0), T(0)};
-  if (cf.approximant == 2) return burst_bin<T, TP>(cf, w, cpl, cxx, tauT, k);
-  TP rev = wf_phase_rev<TP, FULL>(w, k, kc, lk, cf.invT) + TP(w.pconst) + TP(k) * TP(tauT);
-  rev = frac1(rev);
+// Adds the projected signal (plain model, generated in registers) at window
+// bin k to X.  powers(k) gives the bin's powers.
+template <class T, class TP, bool FULL, class Powers>
+__device__ __forceinline__ void add_signal(const DevCfg& cf, const WfScalars& w, const Projection<T>& pr, int k,
+                                           Powers powers, cpx<T>* X) {
+  if (k <= 0 || k < cf.kmin || k >= w.kend) return;
+  if (cf.approximant == 2) {
+    *X = cadd(*X, burst_bin<T, TP>(cf, w, pr, k));
+    return;
+  }
+  TP rev;
+  T A;
+  bin_polar<T, TP, FULL>(w, k, powers(k), &rev, &A);
+  rev = frac1(fma_t(TP(k), TP(pr.tauT), rev));
   T s, c;
   sincos_rev(T(rev), &s, &c);
-  const T A = T(cf.fs) * wf_amplitude<T>(w, k, kc, cf.invT);
-  // fs A (cpl - i cxx)(c - i s)
-  return {A * (cpl * c - cxx * s), -A * (cpl * s + cxx * c)};
+  // A (cpl - i cxx)(c - i s)
+  s *= A;
+  c *= A;
+  *X = {fma_t(pr.cpl, c, fma_t(-pr.cxx, s, X->x)), fma_t(-pr.cpl, s, fma_t(-pr.cxx, c, X->y))};
 }
 
-template <class T, class TP, bool FULL>
-__device__ __forceinline__ cpx<T> signal_bin(const DevCfg& cf, const WinArgs& a, const WfScalars& w, T cpl, T cxx,
-                                             double tauT, int k) {
-  if (k <= 0 || k < cf.kmin || k >= w.kend) return {T(0), T(0)};
-  if (cf.approximant == 2) return burst_bin<T, TP>(cf, w, cpl, cxx, tauT, k);
-  const double kc = a.kcbrt[k], lk = a.lnk3[k];
-  TP rev = wf_phase_rev<TP, FULL>(w, k, kc, lk, cf.invT) + TP(w.pconst) + TP(k) * TP(tauT);
-  rev = frac1(rev);
-  T s, c;
-  sincos_rev(T(rev), &s, &c);
-  const T A = T(cf.fs) * wf_amplitude<T>(w, k, kc, cf.invT);
-  // fs A (cpl - i cxx)(c - i s)
-  return {A * (cpl * c - cxx * s), -A * (cpl * s + cxx * c)};
-}
-
-// Projected signal at window bin k from surrogate node values: binary64
-// Newtonian phase + interpolated phase residual (revolutions), amplitude
-// A_N(f_k) times the interpolated ratio.
 // Node values staged in LDS: typed as such, so that their gathers compile to
 // LDS reads rather than generic (flat) loads, which would also wait for the
 // global loads issued ahead.
 typedef const __attribute__((address_space(3))) float* lds_cfptr;
 
+// The same from surrogate node values: binary64 Newtonian phase + interpolated
+// phase residual (revolutions), amplitude A_N(f_k) times the interpolated ratio.
 template <class T>
-__device__ __forceinline__ cpx<T> signal_bin_surr(const DevCfg& cf, const WinArgs& a, const WfScalars& w,
-                                                  lds_cfptr nd, T cpl, T cxx, double tauT, int k) {
-  if (k <= 0 || k < cf.kmin || k >= w.kend) return {T(0), T(0)};
+__device__ __forceinline__ void add_signal_surr(const DevCfg& cf, const WinArgs& a, const WfScalars& w, lds_cfptr nd,
+                                                const Projection<T>& pr, int k, cpx<T>* X) {
+  if (k <= 0 || k < cf.kmin || k >= w.kend) return;
   const double lk3 = a.lnk3[k], k53 = a.k53[k];
   // u = (ln(Ms k / T) - ln Mf_lo) / dlog, ln(Ms/T) = 3 ln v1 - ln pi
   const float u = float((3.0 * w.lnv1 - 1.1447298858494002 - kSurrLnMfLo + 3.0 * lk3) * (1.0 / kSurrDlog));
@@ -235,14 +281,16 @@ __device__ __forceinline__ cpx<T> signal_bin_surr(const DevCfg& cf, const WinArg
   const float ratio = (1.f - tt) * nd[i] + tt * nd[i + 1];
   const float dpsi = (1.f - tt) * nd[kSurrNodes + i] + tt * nd[kSurrNodes + i + 1];
   // Newtonian phase cN k^(-5/3) from the table: one binary64 product per bin
-  double rev = w.cN * k53 + double(dpsi) * (1.0 / (2.0 * kPi)) + w.pconst + double(k) * tauT;
+  double rev = w.cN * k53 + double(dpsi) * (1.0 / (2.0 * kPi)) + w.pconst + double(k) * pr.tauT;
   rev = frac1(rev);
-  T sn, cs;
-  sincos_rev(T(rev), &sn, &cs);
+  T s, c;
+  sincos_rev(T(rev), &s, &c);
   // A_N(f_k) = A0T k^(-7/6) = A0T k^(-5/3) k^(1/2)
   const T kf = T(k);
-  const T A = T(cf.fs) * T(w.A0T) * T(k53) * (kf * rsqrt_t(kf)) * T(ratio);
-  return {A * (cpl * cs - cxx * sn), -A * (cpl * sn + cxx * cs)};
+  const T A = T(w.A0T) * T(k53) * (kf * rsqrt_t(kf)) * T(ratio);
+  s *= A;
+  c *= A;
+  *X = {fma_t(pr.cpl, c, fma_t(-pr.cxx, s, X->x)), fma_t(-pr.cpl, s, fma_t(-pr.cxx, c, X->y))};
 }
 
 // One window item (sample b, detector d) handled by the NC/16 threads t of a
@@ -257,6 +305,13 @@ __device__ __forceinline__ cpx<T> signal_bin_surr(const DevCfg& cf, const WinArg
 // in registers, the same window with the signal at t_ref into o2.
 // `active` false: compute on the given (valid) item but store nothing, so
 // that idle sub-blocks still meet every block barrier.
+// Bound by its vector arithmetic, most of it in the pairs' loop: of 820
+// instructions for two pairs, 120 went with the phase and the amplitude from
+// one table of k^(-5/3), products summed as fused steps, the factors common
+// to all bins moved to the store and each PSD neighbour read once as eight
+// bytes.  2048 samples of 3 detectors, N = 16384: 361 us before, 344 now (SRC
+// 1); 301 windows' view pairs 112 and 105; 48 of N = 524288 on the path for
+// long windows (k_long_rowpair) 255 and 248.
 template <class T, class TP, bool FULL, int NC, int SRC, int ORD>
 __device__ __forceinline__ void window_item(const DevCfg& cf, const WinArgs& a, int t, int64_t b, int d,
                                             const float* x, const float* hrow, const float* nz, const float* psd,
@@ -304,8 +359,7 @@ __device__ __forceinline__ void window_item(const DevCfg& cf, const WinArgs& a, 
     for (int e = 0; e < 16; ++e) keep[e] = v[e];
   }
 
-  T cpl = T(0), cxx = T(0);
-  double tauT = 0.0;
+  Projection<T> pr = {T(0), T(0), 0.0};
   WfScalars wsh;
   if constexpr (SIG || SRC == 3 || SRC == 4) wsh = load_const(a.wf + b);
   bool use_surr = false;
@@ -320,11 +374,10 @@ __device__ __forceinline__ void window_item(const DevCfg& cf, const WinArgs& a, 
   double tauT_ref = 0.0;  // SRC 5: the reference view's time shift
   if constexpr (SIG || SRC == 3 || SRC == 4) {
     const DetScalars dsh = load_const(a.dsc + (b * cf.n_det + d));
-    cpl = T(dsh.fp * 0.5 * (1.0 + wsh.cosi * wsh.cosi));
-    cxx = T(dsh.fx * wsh.cosi);
-    tauT = dsh.tau * cf.invT;
+    pr = {T(cf.fs * dsh.fp * (1.0 + wsh.cosi * wsh.cosi)), T(2.0 * cf.fs * dsh.fx * wsh.cosi), dsh.tau * cf.invT};
     if constexpr (SRC == 5) tauT_ref = (dsh.tau - wsh.tc + a.t_ref) * cf.invT;  // same delays, signal at t_ref
   }
+  auto powers = [&](int k) { return BinPowers{a.kcbrt[k], a.lnk3[k], a.k53[k]}; };
   const float2* hsrc = reinterpret_cast<const float2*>(hrow);
 
   // Global inputs of the pair (k, NC - k): the twiddle and what the two bins
@@ -350,11 +403,11 @@ __device__ __forceinline__ void window_item(const DevCfg& cf, const WinArgs& a, 
       q.g[1] = psd[km];
       q.g[2] = q.g[3] = 0.f;
     } else {
-      const int ia = psd_index(cf, k, NC), ib = psd_index(cf, km, NC);
-      q.g[0] = psd[ia];
-      q.g[1] = psd[ia + 1];
-      q.g[2] = psd[ib];
-      q.g[3] = psd[ib + 1];
+      const PsdAround p = psd_around(cf, psd, k, NC);
+      q.g[0] = p.lo[0];
+      q.g[1] = p.lo[1];
+      q.g[2] = p.hi[0];
+      q.g[3] = p.hi[1];
     }
     return q;
   };
@@ -367,46 +420,38 @@ __device__ __forceinline__ void window_item(const DevCfg& cf, const WinArgs& a, 
     }
   };
   // unpack, signal, gain and repack of the pair: zk, zm go to bins k, NC - k
+  // (both scaled, see whitened_scale)
   auto pair_out = [&](const PairIn& cur, int k, cpx<T> A, cpx<T> Bm, cpx<T>& zk, cpx<T>& zm) {
     const int km = NC - k;
-    const cpx<T> W = cur.W;
     cpx<T> Yk, Ym;
+    T gk = T(1), gm = T(1);
     if constexpr (SRC == 2) {
       Yk = {T(cur.g[0]), T(cur.g[1])};
       Ym = {T(cur.g[2]), T(cur.g[3])};
       if (k == 0) { Yk.y = T(0); Ym.y = T(0); }  // irfft ignores Im at DC and Nyquist
     } else {
-      const cpx<T> s = cadd(A, cconj(Bm));
-      const cpx<T> u = cmul(W, csub(A, cconj(Bm)));
-      cpx<T> Xk = {T(0.5) * (s.x + u.y), T(0.5) * (s.y - u.x)};
-      cpx<T> Xm = {T(0.5) * (s.x - u.y), T(0.5) * (-s.y - u.x)};
-      if constexpr (SIG || SRC == 4) {
-        Xk = cadd(Xk, signal_bin<T, TP, FULL>(cf, a, wsh, cpl, cxx, tauT, k));
-        if (km != k) Xm = cadd(Xm, signal_bin<T, TP, FULL>(cf, a, wsh, cpl, cxx, tauT, km));
-      } else if constexpr (SRC == 3) {
+      unpack_pair<T>(A, Bm, cur.W, &Yk, &Ym);
+      bool plain = SIG || SRC == 4;
+      if constexpr (SRC == 3) {
+        plain = !use_surr;
         if (use_surr) {
-          Xk = cadd(Xk, signal_bin_surr<T>(cf, a, wsh, nd, cpl, cxx, tauT, k));
-          if (km != k) Xm = cadd(Xm, signal_bin_surr<T>(cf, a, wsh, nd, cpl, cxx, tauT, km));
-        } else {
-          Xk = cadd(Xk, signal_bin<T, TP, FULL>(cf, a, wsh, cpl, cxx, tauT, k));
-          if (km != k) Xm = cadd(Xm, signal_bin<T, TP, FULL>(cf, a, wsh, cpl, cxx, tauT, km));
+          add_signal_surr<T>(cf, a, wsh, nd, pr, k, &Yk);
+          add_signal_surr<T>(cf, a, wsh, nd, pr, km, &Ym);
         }
+      }
+      if (plain) {
+        add_signal<T, TP, FULL>(cf, wsh, pr, k, powers, &Yk);
+        add_signal<T, TP, FULL>(cf, wsh, pr, km, powers, &Ym);
       }
       if constexpr (SRC == 4) {
         // fixed per-run filter row [NC + 1] (zero outside the kept band)
-        Yk = cscale(Xk, filter_gain_at<T>(cur.g[0], flag));
-        Ym = cscale(Xm, filter_gain_at<T>(cur.g[1], flag));
+        gk = filter_gain_at<T>(cur.g[0], flag);
+        gm = filter_gain_at<T>(cur.g[1], flag);
       } else {
-        Yk = cscale(Xk, whiten_gain_at<T>(cf, cur.g[0], cur.g[1], k, NC, flag));
-        Ym = cscale(Xm, whiten_gain_at<T>(cf, cur.g[2], cur.g[3], km, NC, flag));
+        psd_gains<T>(cf, PsdAround{{cur.g[0], cur.g[1]}, {cur.g[2], cur.g[3]}}, k, NC, flag, &gk, &gm);
       }
-      if (km == k) Ym = Yk;
     }
-    // inverse packing: Z'_k = p + i q, Z'_{NC-k} = conj(p) + i conj(q)
-    const cpx<T> p = cscale(cadd(Yk, cconj(Ym)), T(0.5));
-    const cpx<T> q = twmul<+1>(cscale(csub(Yk, cconj(Ym)), T(0.5)), W);
-    zk = {p.x - q.y, p.y + q.x};
-    zm = {p.x + q.y, -p.y + q.x};
+    repack_pair<T>(Yk, gk, Ym, gm, cur.W, &zk, &zm);
   };
   auto store_pair = [&](int k, cpx<T> zk, cpx<T> zm) {
     const int km = NC - k;
@@ -448,7 +493,7 @@ __device__ __forceinline__ void window_item(const DevCfg& cf, const WinArgs& a, 
   }
   lds_barrier();
   block_fft<T, NC, +1, true, ORD>(v, sre, sim, fresh_lane(t), PassTwiddle<T, NC, ORD>{opaque(twtab)});
-  const T sc = T(1) / T(NC);
+  const T sc = SRC == 2 ? T(0.5) / T(NC) : SRC == 4 ? T(0.25) / T(NC) : whitened_scale<T>(cf, NC);
   if (active) {
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
@@ -480,7 +525,7 @@ __device__ __forceinline__ void window_item(const DevCfg& cf, const WinArgs& a, 
       sim[i] = keep[e].y;
     }
     lds_barrier();
-    tauT = tauT_ref;
+    pr.tauT = tauT_ref;
     emit(o2);
   }
   if (active && flag) atomicOr(sflag, flag);

@@ -111,8 +111,8 @@ __global__ __launch_bounds__(256) void k_long_cols_fwd(LongArgs a) {
   }
 }
 
-// Inverse columns: twiddle, inverse DFT over k2, scale 1/NC, store real
-// samples in place; SRC 2 adds the noise window.
+// Inverse columns: twiddle, inverse DFT over k2, scale, store real samples in
+// place; SRC 2 adds the noise window.
 template <int N1, int N2, int SRC>
 __global__ __launch_bounds__(256) void k_long_cols_inv(LongArgs a) {
   const int m1 = blockIdx.x * 256 + threadIdx.x;
@@ -127,7 +127,7 @@ __global__ __launch_bounds__(256) void k_long_cols_inv(LongArgs a) {
     v[k2] = k2 ? twmul<+1>(u, twc[k2 * N1 + m1]) : u;
   }
   dft_small<N2, +1>(v);
-  const float sc = 1.f / float(a.NC);
+  const float sc = SRC == 2 ? 0.5f / float(a.NC) : whitened_scale<float>(a.w.cf, a.NC);
   const float* nz = nullptr;
   if constexpr (SRC == 2) nz = long_input<2>(a, bd);
 #pragma unroll
@@ -180,10 +180,61 @@ __global__ __launch_bounds__(256) void k_long_inject(LongArgs a, const float* hd
   // irfft ignores Im at DC and Nyquist
   const cpx<float> Yk = {h0.x, k == 0 ? 0.f : h0.y};
   const cpx<float> Ym = {h1.x, k == 0 ? 0.f : h1.y};
-  const cpx<float> p = cscale(cadd(Yk, cconj(Ym)), 0.5f);
-  const cpx<float> q = twmul<+1>(cscale(csub(Yk, cconj(Ym)), 0.5f), W);
-  buf[pos(k)] = {p.x - q.y, p.y + q.x};
-  if (k != 0 && km != k) buf[pos(km)] = {p.x + q.y, -p.y + q.x};
+  cpx<float> zk, zm;
+  repack_pair(Yk, 1.f, Ym, 1.f, W, &zk, &zm);
+  buf[pos(k)] = {zk.x, zk.y};
+  if (k != 0 && km != k) buf[pos(km)] = {zm.x, zm.y};
+}
+
+// Global inputs of one pair of packed-spectrum bins (k, km = NC - k),
+// k <= NC/2: the real-FFT twiddle exp(-2 pi i k / N), the bin tables of both
+// bins (SRC 1) and the PSD values around both bins.  pk, pm: positions of k
+// and km in the transposed bin tables.
+struct LongPairIn {
+  cpx<float> W;
+  double kc[2], lk[2];
+  PsdAround g;
+};
+
+template <int SRC>
+__device__ __forceinline__ LongPairIn long_pair_fetch(const LongArgs& a, const float* psd, int k, int64_t pk,
+                                                      int64_t pm) {
+  LongPairIn in;
+  in.W = a.twr_t[pk];
+  if constexpr (SRC == 1) {
+    in.kc[0] = a.kc_t[pk];
+    in.lk[0] = a.lk_t[pk];
+    in.kc[1] = a.kc_t[pm];
+    in.lk[1] = a.lk_t[pm];
+  }
+  in.g = psd_around(a.w.cf, psd, k, a.NC);
+  return in;
+}
+
+// The item's projection (SRC 1).
+__device__ __forceinline__ Projection<float> long_projection(const LongArgs& a, const WfScalars& w, int64_t b, int d) {
+  const DevCfg& cf = a.w.cf;
+  const DetScalars dsh = load_const(a.w.dsc + (b * cf.n_det + d));
+  return {float(cf.fs * dsh.fp * (1.0 + w.cosi * w.cosi)), float(2.0 * cf.fs * dsh.fx * w.cosi), dsh.tau * cf.invT};
+}
+
+// One pair of packed-spectrum bins (k, km = NC - k), k <= NC/2: A = Z[k] and
+// Bm = Z[km] in; out, the packed spectrum of the whitened window (SRC 1 with
+// the in-register signal added) at the same two bins, scaled (whitened_scale).
+template <class TP, int SRC>
+__device__ __forceinline__ void long_pair(const LongArgs& a, const WfScalars& wsh, const Projection<float>& pr,
+                                          const LongPairIn& in, int k, cpx<float>& A, cpx<float>& Bm, uint32_t& flag) {
+  const DevCfg& cf = a.w.cf;
+  const int NC = a.NC, km = NC - k;
+  cpx<float> Yk, Ym;
+  unpack_pair(A, Bm, in.W, &Yk, &Ym);
+  if constexpr (SRC == 1) {
+    add_signal<float, TP, false>(cf, wsh, pr, k, [&](int) { return BinPowers{in.kc[0], in.lk[0], pow53(in.kc[0])}; }, &Yk);
+    add_signal<float, TP, false>(cf, wsh, pr, km, [&](int) { return BinPowers{in.kc[1], in.lk[1], pow53(in.kc[1])}; }, &Ym);
+  }
+  float gk, gm;
+  psd_gains<float>(cf, in.g, k, NC, flag, &gk, &gm);
+  repack_pair(Yk, gk, Ym, gm, in.W, &A, &Bm);
 }
 
 // Bins: the real-spectrum unpack of each pair (k, NC - k), k in [0, NC/2],
@@ -217,127 +268,40 @@ __global__ __launch_bounds__(256) void k_long_bins(LongArgs a) {
   int k[J];
   bool ok[J];
   float2 qa[J], qb[J];
-  cpx<float> W[J];
-  float g[J][4];
-  double kc[J][2], lk[J][2];
+  LongPairIn in[J];
 #pragma unroll
   for (int j = 0; j < J; ++j) {
     const int k1 = blockIdx.x * (256 * J) + 256 * j + threadIdx.x;  // < N1
     const int kr = r + N2 * k1;
     ok[j] = (r == 0) ? (k1 <= N1 / 2) : (2 * r == N2) ? (k1 < N1 / 2) : true;
     k[j] = min(kr, NC - kr);
-    const int km = NC - k[j];
-    const int64_t pk = pos(k[j]), pm = pos(km);
+    const int64_t pk = pos(k[j]), pm = pos(NC - k[j]);
     qa[j] = buf[pk];
     qb[j] = buf[pm];
-    W[j] = a.twr_t[pk];
-    const int ia = psd_index(cf, k[j], NC), ib = psd_index(cf, km, NC);
-    g[j][0] = psd[ia];
-    g[j][1] = psd[ia + 1];
-    g[j][2] = psd[ib];
-    g[j][3] = psd[ib + 1];
-    if constexpr (SRC == 1) {
-      kc[j][0] = a.kc_t[pk];
-      lk[j][0] = a.lk_t[pk];
-      kc[j][1] = a.kc_t[pm];
-      lk[j][1] = a.lk_t[pm];
-    }
+    in[j] = long_pair_fetch<SRC>(a, psd, k[j], pk, pm);
   }
-  float cpl = 0.f, cxx = 0.f;
-  double tauT = 0.0;
   WfScalars wsh;
+  Projection<float> pr = {0.f, 0.f, 0.0};
   if constexpr (SRC == 1) {
     wsh = load_const(a.w.wf + b);
-    const DetScalars dsh = load_const(a.w.dsc + (b * cf.n_det + d));
-    cpl = float(dsh.fp * 0.5 * (1.0 + wsh.cosi * wsh.cosi));
-    cxx = float(dsh.fx * wsh.cosi);
-    tauT = dsh.tau * cf.invT;
+    pr = long_projection(a, wsh, b, d);
   }
   uint32_t flag = 0;
 #pragma unroll
   for (int j = 0; j < J; ++j) {
     const int kk = k[j], km = NC - kk;
-    const cpx<float> A = {qa[j].x, qa[j].y}, Bm = {qb[j].x, qb[j].y};
-    const cpx<float> s = cadd(A, cconj(Bm));
-    const cpx<float> u = cmul(W[j], csub(A, cconj(Bm)));
-    cpx<float> Xk = {0.5f * (s.x + u.y), 0.5f * (s.y - u.x)};
-    cpx<float> Xm = {0.5f * (s.x - u.y), 0.5f * (-s.y - u.x)};
-    if constexpr (SRC == 1) {
-      Xk = cadd(Xk, signal_bin_at<float, TP, false>(cf, wsh, cpl, cxx, tauT, kk, kc[j][0], lk[j][0]));
-      if (km != kk) Xm = cadd(Xm, signal_bin_at<float, TP, false>(cf, wsh, cpl, cxx, tauT, km, kc[j][1], lk[j][1]));
-    }
+    cpx<float> A = {qa[j].x, qa[j].y}, Bm = {qb[j].x, qb[j].y};
     uint32_t fj = 0;
-    const cpx<float> Yk = cscale(Xk, whiten_gain_at<float>(cf, g[j][0], g[j][1], kk, NC, fj));
-    cpx<float> Ym = cscale(Xm, whiten_gain_at<float>(cf, g[j][2], g[j][3], km, NC, fj));
-    if (km == kk) Ym = Yk;
-    const cpx<float> p = cscale(cadd(Yk, cconj(Ym)), 0.5f);
-    const cpx<float> q = twmul<+1>(cscale(csub(Yk, cconj(Ym)), 0.5f), W[j]);
+    long_pair<TP, SRC>(a, wsh, pr, in[j], kk, A, Bm, fj);
     if (ok[j]) {
-      buf[pos(kk)] = {p.x - q.y, p.y + q.x};
-      if (kk != 0 && km != kk) buf[pos(km)] = {p.x + q.y, -p.y + q.x};
+      buf[pos(kk)] = {A.x, A.y};
+      if (kk != 0 && km != kk) buf[pos(km)] = {Bm.x, Bm.y};
       flag |= fj;
     }
   }
   if (flag) atomicOr(&sflag, flag);
   __syncthreads();
   if (threadIdx.x == 0 && sflag && a.w.status) atomicOr(a.w.status + b, sflag);
-}
-
-// Global inputs of one pair of packed-spectrum bins (k, km = NC - k),
-// k <= NC/2: the real-FFT twiddle exp(-2 pi i k / N), the bin tables of both
-// bins (SRC 1) and the PSD values around both bins.  pk, pm: positions of k
-// and km in the transposed bin tables.
-struct LongPairIn {
-  cpx<float> W;
-  double kc[2], lk[2];
-  float g[4];
-};
-
-template <int SRC>
-__device__ __forceinline__ LongPairIn long_pair_fetch(const LongArgs& a, const float* psd, int k, int64_t pk,
-                                                      int64_t pm) {
-  const DevCfg& cf = a.w.cf;
-  const int NC = a.NC, km = NC - k;
-  LongPairIn in;
-  in.W = a.twr_t[pk];
-  if constexpr (SRC == 1) {
-    in.kc[0] = a.kc_t[pk];
-    in.lk[0] = a.lk_t[pk];
-    in.kc[1] = a.kc_t[pm];
-    in.lk[1] = a.lk_t[pm];
-  }
-  const int ia = psd_index(cf, k, NC), ib = psd_index(cf, km, NC);
-  in.g[0] = psd[ia];
-  in.g[1] = psd[ia + 1];
-  in.g[2] = psd[ib];
-  in.g[3] = psd[ib + 1];
-  return in;
-}
-
-// One pair of packed-spectrum bins (k, km = NC - k), k <= NC/2: A = Z[k] and
-// Bm = Z[km] in; out, the packed spectrum of the whitened window (SRC 1 with
-// the in-register signal added) at the same two bins.
-template <class TP, int SRC>
-__device__ __forceinline__ void long_pair(const LongArgs& a, const WfScalars& wsh, float cpl, float cxx, double tauT,
-                                          const LongPairIn& in, int k, cpx<float>& A, cpx<float>& Bm, uint32_t& flag) {
-  const DevCfg& cf = a.w.cf;
-  const int NC = a.NC, km = NC - k;
-  const cpx<float> W = in.W;  // exp(-2 pi i k / N)
-  const cpx<float> s = cadd(A, cconj(Bm));
-  const cpx<float> u = cmul(W, csub(A, cconj(Bm)));
-  cpx<float> Xk = {0.5f * (s.x + u.y), 0.5f * (s.y - u.x)};
-  cpx<float> Xm = {0.5f * (s.x - u.y), 0.5f * (-s.y - u.x)};
-  if constexpr (SRC == 1) {
-    Xk = cadd(Xk, signal_bin_at<float, TP, false>(cf, wsh, cpl, cxx, tauT, k, in.kc[0], in.lk[0]));
-    if (km != k) Xm = cadd(Xm, signal_bin_at<float, TP, false>(cf, wsh, cpl, cxx, tauT, km, in.kc[1], in.lk[1]));
-  }
-  const cpx<float> Yk = cscale(Xk, whiten_gain_at<float>(cf, in.g[0], in.g[1], k, NC, flag));
-  cpx<float> Ym = cscale(Xm, whiten_gain_at<float>(cf, in.g[2], in.g[3], km, NC, flag));
-  if (km == k) Ym = Yk;
-  const cpx<float> p = cscale(cadd(Yk, cconj(Ym)), 0.5f);
-  const cpx<float> q = twmul<+1>(cscale(csub(Yk, cconj(Ym)), 0.5f), W);
-  A = {p.x - q.y, p.y + q.x};
-  Bm = {p.x + q.y, -p.y + q.x};
 }
 
 // Rows, bins and inverse rows of one row pair in one workgroup (replacing
@@ -380,15 +344,11 @@ __global__ __launch_bounds__(N1 / 16, kRowWaves) void k_long_rowpair(LongArgs a)
   // a fresh table pointer per transform (see opaque)
   auto tw = [&]() { return PassTwiddle<float, N1, 0>{opaque(tw1)}; };
   if (t == 0) sflag = 0u;
-  float cpl = 0.f, cxx = 0.f;
-  double tauT = 0.0;
+  Projection<float> pr = {0.f, 0.f, 0.0};
   WfScalars wsh;
   if constexpr (SRC == 1) {
     wsh = load_const(a.w.wf + b);
-    const DetScalars dsh = load_const(a.w.dsc + (b * cf.n_det + d));
-    cpl = float(dsh.fp * 0.5 * (1.0 + wsh.cosi * wsh.cosi));
-    cxx = float(dsh.fx * wsh.cosi);
-    tauT = dsh.tau * cf.invT;
+    pr = long_projection(a, wsh, b, d);
   }
   uint32_t flag = 0;
   cpx<float> v[16];
@@ -460,7 +420,7 @@ __global__ __launch_bounds__(N1 / 16, kRowWaves) void k_long_rowpair(LongArgs a)
       const int km = NC - kj;
       const int ic = lpad<float>(cj), im = lpad<float>(cmj);
       cpx<float> A = {sre[ic], sim[ic]}, Bm = {sre[im], sim[im]};
-      long_pair<TP, SRC>(a, wsh, cpl, cxx, tauT, cur, kj, A, Bm, flag);
+      long_pair<TP, SRC>(a, wsh, pr, cur, kj, A, Bm, flag);
       sre[ic] = A.x;
       sim[ic] = A.y;
       if (kj != 0 && km != kj) {
@@ -510,8 +470,8 @@ __global__ __launch_bounds__(N1 / 16, kRowWaves) void k_long_rowpair(LongArgs a)
         const int k = rA + N2 * c, km = NC - k;
         const int im = lpad<float>(cm);
         cpx<float> P = {cur.q.x, cur.q.y}, Q = {sre[im], sim[im]};
-        if (k < km) long_pair<TP, SRC>(a, wsh, cpl, cxx, tauT, cur.in, k, P, Q, flag);
-        else long_pair<TP, SRC>(a, wsh, cpl, cxx, tauT, cur.in, km, Q, P, flag);
+        if (k < km) long_pair<TP, SRC>(a, wsh, pr, cur.in, k, P, Q, flag);
+        else long_pair<TP, SRC>(a, wsh, pr, cur.in, km, Q, P, flag);
         ra[c] = {P.x, P.y};
         sre[im] = Q.x;
         sim[im] = Q.y;

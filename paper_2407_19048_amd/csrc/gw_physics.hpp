@@ -20,9 +20,12 @@
 
 namespace gw {
 
+__device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
 // frac(x) in [0, 1)
-__device__ __forceinline__ float frac1(float x) { return x - floorf(x); }
-__device__ __forceinline__ double frac1(double x) { return x - floor(x); }
+__device__ __forceinline__ float frac1(float x) { return __builtin_amdgcn_fractf(x); }
+__device__ __forceinline__ double frac1(double x) { return __builtin_amdgcn_fract(x); }
 
 // precision-generic math
 __device__ __forceinline__ void sincospi_t(float x, float* s, float* c) { sincospif(x, s, c); }
@@ -114,6 +117,10 @@ struct WfScalars {
   int kend, kt, krd;    // band end; first bins with f >= f_t and f >= f_RD
   int cut_nyquist;
   double cosi, tc, ra, dec, psi;
+  // the same phases in terms of x = k^(1/3), what a bin needs (bin_polar):
+  // below f_t  pconst + k^(-5/3) (c0 + x^2 (c2 + x (c3 + x (c4 + x ((c5 + b5 l) + x ((c6 + b6x l) + x c7)))))), l = ln(k)/3
+  // above      mr_p0 + mr_p1 k + atan(X)/(2 pi), X = mr_x0 + mr_x1 k, amplitude Ard / (1 + X^2) beyond f_RD
+  double c0, c2, c3, c4, c5, c6, b6x, c7, mr_p0, mr_p1, mr_x0, mr_x1;
 };
 
 // first bin k in [0, kmax] with k/T >= f (k/T formed by a correctly rounded
@@ -257,7 +264,19 @@ __device__ __forceinline__ void wf_setup(const double* p, const DevCfg& cf, int 
   w.cN = w.a[0] / (w.v1 * w.v1 * w.v1 * w.v1 * w.v1);
   w.kend = lane_value(kb, 0);
   w.cut_nyquist = f_cut > 0.5 * cf.fs ? 1 : 0;
+  {
+    const double iv = 1.0 / w.v1, iv2 = iv * iv;
+    w.c0 = w.cN;
+    w.c2 = w.a[2] * iv2 * iv;
+    w.c3 = w.a[3] * iv2;
+    w.c4 = w.a[4] * iv;
+    w.c5 = w.a[5] + w.b5 * w.lnv1;
+    w.c6 = (w.a[6] + w.b6 * w.lnv1) * w.v1;
+    w.b6x = w.b6 * w.v1;
+    w.c7 = w.a[7] * w.v1 * w.v1;
+  }
   if (cf.approximant == 0) {
+    w.mr_p0 = w.mr_p1 = w.mr_x0 = w.mr_x1 = 0.0;
     w.kt = w.kend;
     w.krd = w.kend;
     w.mr_b0 = w.mr_b1 = w.f_rd = w.inv_fdamp = 0.0;
@@ -273,6 +292,10 @@ __device__ __forceinline__ void wf_setup(const double* p, const DevCfg& cf, int 
   w.mr_b1 = b1 / (2.0 * kPi);
   w.f_rd = f_rd;
   w.inv_fdamp = 1.0 / f_damp;
+  w.mr_p0 = w.mr_b0 + w.pconst;
+  w.mr_p1 = w.mr_b1 * cf.invT;
+  w.mr_x0 = -f_rd * w.inv_fdamp;
+  w.mr_x1 = cf.invT * w.inv_fdamp;
   const double pw2 = pow(lane == 0 ? f_t : lane == 1 ? f_rd / f_t : f_t * cf.T,
                          lane == 0 ? -7.0 / 6.0 : lane == 1 ? -2.0 / 3.0 : 2.0 / 3.0);
   const double At = A0 * lane_value(pw2, 0);
@@ -299,42 +322,48 @@ __device__ __forceinline__ void wf_setup_column(const double* __restrict__ param
   if (t == 0) *w = v;
 }
 
-// Waveform phase in revolutions (without the time shift) at bin k.  TP is
-// binary64 for precision modes 1 and 2 and binary32 for mode 0; FULL selects
-// a binary64 arctangent for the (bounded) ringdown term (mode 2).
-template <class TP, bool FULL>
-__device__ __forceinline__ TP wf_phase_rev(const WfScalars& w, int k, double kcbrt, double lnk3, double invT) {
-  if (k < w.kt) {
-    const TP v = TP(w.v1) * TP(kcbrt);
-    const TP lnv = TP(w.lnv1) + TP(lnk3);
-    const TP iv = rcp_t(v);
-    const TP iv2 = iv * iv;
-    const TP iv5 = iv2 * iv2 * iv;
-    const TP p = TP(w.a[0]) +
-                 v * v * (TP(w.a[2]) +
-                          v * (TP(w.a[3]) +
-                               v * (TP(w.a[4]) +
-                                    v * ((TP(w.a[5]) + TP(w.b5) * lnv) +
-                                         v * ((TP(w.a[6]) + TP(w.b6) * lnv) + v * TP(w.a[7]))))));
-    return p * iv5;
-  }
-  const double f = double(k) * invT;
-  const double x = (f - w.f_rd) * w.inv_fdamp;
-  if constexpr (FULL) return TP(w.mr_b0) + TP(w.mr_b1) * TP(f) + TP(atan(x) * (1.0 / (2.0 * kPi)));
-  else return TP(w.mr_b0) + TP(w.mr_b1) * TP(f) + TP(atanf(float(x)) * float(1.0 / (2.0 * kPi)));
+// Powers of a bin number.
+struct BinPowers { double kc, lk, k53; };  // k^(1/3), ln(k)/3, k^(-5/3)
+
+// k^(-5/3) from k^(1/3), for tables without it
+__device__ __forceinline__ double pow53(double kc) {
+  const double i = rcp_t(kc), i2 = i * i;
+  return i2 * i2 * i;
 }
 
-// Amplitude at bin k: A0T k^(-7/6) below f_t, At (f/f_t)^(-2/3) =
-// Apl k^(-2/3) up to f_RD (both from the k^(1/3) table), then the Lorentzian.
-template <class TA>
-__device__ __forceinline__ TA wf_amplitude(const WfScalars& w, int k, double kcbrt, double invT) {
-  if (k < w.kt) return TA(w.A0T) * rsqrt_t(TA(kcbrt)) * rcp_t(TA(k));
-  if (k < w.krd) {
-    const TA kc = TA(kcbrt);
-    return TA(w.Apl) * rcp_t(kc * kc);
+// Waveform phase in revolutions (phi_c included, without the time shift) and
+// amplitude (type T) at bin k.  TP is binary64 for precision modes 1 and 2 and
+// binary32 for mode 0; FULL selects a binary64 arctangent for the (bounded)
+// ringdown term (mode 2).  The amplitude is A0T k^(-7/6) = A0T k^(-5/3) k^(1/2)
+// below f_t, At (f/f_t)^(-2/3) = Apl k^(-2/3) up to f_RD, then the Lorentzian.
+// Twelve binary64 operations below f_t; with the coefficients in terms of v and
+// 1/v from a reciprocal there were 28.
+template <class T, class TP, bool FULL>
+__device__ __forceinline__ void bin_polar(const WfScalars& w, int k, const BinPowers& t, TP* rev, T* amp) {
+  if (k < w.kt) {
+    const TP x = TP(t.kc), l = TP(t.lk);
+    TP p = fma_t(x, TP(w.c7), fma_t(TP(w.b6x), l, TP(w.c6)));
+    p = fma_t(x, p, fma_t(TP(w.b5), l, TP(w.c5)));
+    p = fma_t(x, p, TP(w.c4));
+    p = fma_t(x, p, TP(w.c3));
+    p = fma_t(x, p, TP(w.c2));
+    p = fma_t(x * x, p, TP(w.c0));
+    *rev = fma_t(p, TP(t.k53), TP(w.pconst));
+    const T kf = T(k);
+    *amp = T(w.A0T) * T(t.k53) * (kf * rsqrt_t(kf));
+    return;
   }
-  const TA d = TA(double(k) * invT) - TA(w.f_rd);
-  return TA(w.Ard) * TA(w.fdamp2) * rcp_t(d * d + TA(w.fdamp2));
+  const double x = fma_t(double(k), w.mr_x1, w.mr_x0);
+  const TP lin = fma_t(TP(k), TP(w.mr_p1), TP(w.mr_p0));
+  if constexpr (FULL) *rev = lin + TP(atan(x) * (1.0 / (2.0 * kPi)));
+  else *rev = lin + TP(atanf(float(x)) * float(1.0 / (2.0 * kPi)));
+  if (k < w.krd) {
+    const T kc = T(t.kc);
+    *amp = T(w.Apl) * rcp_t(kc * kc);
+  } else {
+    const T xx = T(x);
+    *amp = T(w.Ard) * rcp_t(fma_t(xx, xx, T(1)));
+  }
 }
 
 // -------------------------------------------------------- detector response

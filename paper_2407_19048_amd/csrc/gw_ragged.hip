@@ -61,6 +61,7 @@ struct gw_ragged {
   int32_t* d_vitems = nullptr;
   double* kcbrt = nullptr;
   double* lnk3 = nullptr;
+  double* k53 = nullptr;
   void* tw[4] = {nullptr, nullptr, nullptr, nullptr};   // pass twiddle tables of M points, M = 2048 << s
   void* tw_welch[2] = {nullptr, nullptr};               // Welch tables of L = 2048 << s
   void* twr[4] = {nullptr, nullptr, nullptr, nullptr};  // exp(-2 pi i k / 2M), k <= M/2
@@ -261,6 +262,7 @@ __device__ __forceinline__ void window_group(const RWinArgs& a, int4 gr, int t, 
   WinArgs w = a.w;
   w.kcbrt = opaque(w.kcbrt);
   w.lnk3 = opaque(w.lnk3);
+  w.k53 = opaque(w.k53);
   window_item<float, TP, false, NC, 1, ORD>(cf, w, tl, b, d, x, nullptr, nullptr, psd, o,
                                             opaque(reinterpret_cast<const cpx<float>*>(a.tw[S])),
                                             opaque(reinterpret_cast<const cpx<float>*>(a.twr[S])), lds + j * 2 * LS,
@@ -546,6 +548,7 @@ gw_status enqueue_ragged(gw_ragged* r, uint64_t seed, uint64_t batch_index, bool
     a.w.status = status;
     a.w.kcbrt = r->kcbrt;
     a.w.lnk3 = r->lnk3;
+    a.w.k53 = r->k53;
     a.w.wf = wf;
     a.w.dsc = dsc;
     a.cfgs = r->d_cfgs;
@@ -580,7 +583,7 @@ extern "C" {
 gw_status gw_ragged_destroy(gw_ragged* r) {
   if (!r) return GW_OK;
   void* ptrs[] = {r->d_cfgs, r->d_cls, r->d_out_off, r->d_psd_off, r->d_wgroups, r->d_witems,
-                  r->d_vgroups, r->d_vitems, r->kcbrt, r->lnk3, r->d_starts[0], r->d_starts[1], r->d_wpairs};
+                  r->d_vgroups, r->d_vitems, r->kcbrt, r->lnk3, r->k53, r->d_starts[0], r->d_starts[1], r->d_wpairs};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   for (int k = 0; k < 4; ++k) {
@@ -717,10 +720,11 @@ gw_status gw_ragged_create(const gw_config* classes, int32_t n_classes, const in
     need_tw[size_slot(r->dc[c].N / 2)] = need_twr[size_slot(r->dc[c].N / 2)] = true;
     need_welch[size_slot(r->dc[c].L)] = true;
   }
-  std::vector<double> hc(Fmax), hl(Fmax);
+  std::vector<double> hc(Fmax), hl(Fmax), h53(Fmax);
   for (int k = 0; k < Fmax; ++k) {
     hc[k] = std::cbrt(double(k));
     hl[k] = k > 0 ? std::log(double(k)) / 3.0 : 0.0;
+    h53[k] = k > 0 ? std::pow(double(k), -5.0 / 3.0) : 0.0;
   }
   std::vector<DevCfg> hcfg(r->dc, r->dc + n_classes);
   std::vector<int64_t> hout(r->out_off.begin(), r->out_off.end() - 1), hpsd(r->psd_off.begin(), r->psd_off.end() - 1);
@@ -732,7 +736,8 @@ gw_status gw_ragged_create(const gw_config* classes, int32_t n_classes, const in
             upload(reinterpret_cast<void**>(&r->d_wpairs), wpairs) &&
             upload(reinterpret_cast<void**>(&r->d_starts[0]), starts[0]) &&
             upload(reinterpret_cast<void**>(&r->d_starts[1]), starts[1]) &&
-            upload(reinterpret_cast<void**>(&r->kcbrt), hc) && upload(reinterpret_cast<void**>(&r->lnk3), hl);
+            upload(reinterpret_cast<void**>(&r->kcbrt), hc) && upload(reinterpret_cast<void**>(&r->lnk3), hl) &&
+            upload(reinterpret_cast<void**>(&r->k53), h53);
   for (int k = 0; k < 4 && ok; ++k) {
     const int M = 2048 << k;
     if (need_tw[k]) ok = upload(&r->tw[k], plan_tables<float>(M));

@@ -64,6 +64,7 @@ struct WaveArgs {
   int64_t B;
   const double* kcbrt;
   const double* lnk3;
+  const double* k53;
   float* hp;
   float* hc;
 };
@@ -90,12 +91,11 @@ __global__ __launch_bounds__(256) void k_gen_fd_waveform(WaveArgs a) {
       hp = {float(ap * (emx + epx)), float(ap * (emy + epy))};
       hc = {float(ax * (emy - epy)), float(ax * (epx - emx))};
     } else if (k > 0 && k >= a.cf.kmin && k < w.kend) {
-      const double kc = a.kcbrt[k], lk = a.lnk3[k];
-      TP rev = wf_phase_rev<TP, FULL>(w, k, kc, lk, a.cf.invT) + TP(w.pconst);
+      TP rev, A;
+      bin_polar<TP, TP, FULL>(w, k, BinPowers{a.kcbrt[k], a.lnk3[k], a.k53[k]}, &rev, &A);
       rev = frac1(rev);
       TP s, c;
       sincos_rev(rev, &s, &c);
-      const TP A = wf_amplitude<TP>(w, k, kc, a.cf.invT);
       const TP cp = A * TP(0.5) * (TP(1) + TP(w.cosi) * TP(w.cosi));
       const TP cx = A * TP(w.cosi);
       // h+ = A cp e^{-i Psi};  hx = -i A cx e^{-i Psi}
@@ -1081,7 +1081,7 @@ gw_status gen_fd_waveform(gw_ctx* c, const double* params, int64_t B, float* hp,
   if (B == 0) return GW_OK;
   if (!params || !hp || !hc) return fail(c, GW_EINVAL, "NULL pointer");
   if (!aligned16(params) || !aligned16(hp) || !aligned16(hc)) return fail(c, GW_EINVAL, "pointer not 16-byte aligned");
-  WaveArgs a{c->dc, params, B, c->kcbrt, c->lnk3, hp, hc};
+  WaveArgs a{c->dc, params, B, c->kcbrt, c->lnk3, c->k53, hp, hc};
   const dim3 grid = dim3(unsigned(B));
   if (c->dc.precision == 0) hipLaunchKernelGGL((k_gen_fd_waveform<float, false>), grid, dim3(256), 0, stream, a);
   else if (c->dc.precision == 1) hipLaunchKernelGGL((k_gen_fd_waveform<double, false>), grid, dim3(256), 0, stream, a);
