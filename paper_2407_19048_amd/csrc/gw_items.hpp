@@ -310,8 +310,8 @@ __device__ __forceinline__ void add_signal_surr(const DevCfg& cf, const WinArgs&
 // one table of k^(-5/3), products summed as fused steps, the factors common
 // to all bins moved to the store and each PSD neighbour read once as eight
 // bytes.  2048 samples of 3 detectors, N = 16384: 361 us before, 344 now (SRC
-// 1); 301 windows' view pairs 112 and 105; 48 of N = 524288 on the path for
-// long windows (k_long_rowpair) 255 and 248.
+// 1); view pairs of 301 samples 112 and 105; 32 samples, N = 524288, on the path for
+// long windows (the pairs of k_long_rowpair) 255 and 248.
 template <class T, class TP, bool FULL, int NC, int SRC, int ORD>
 __device__ __forceinline__ void window_item(const DevCfg& cf, const WinArgs& a, int t, int64_t b, int d,
                                             const float* x, const float* hrow, const float* nz, const float* psd,

@@ -304,20 +304,25 @@ __global__ __launch_bounds__(256) void k_long_bins(LongArgs a) {
   if (threadIdx.x == 0 && sflag && a.w.status) atomicOr(a.w.status + b, sflag);
 }
 
-// Rows, bins and inverse rows of one row pair in one workgroup (replacing
-// three passes through HBM).  Bin k = r + N2 c sits at row r, column c of the
+// Rows, bins and inverse rows of two rows in one workgroup (replacing three
+// passes through HBM).  Bin k = r + N2 c sits at row r, column c of the
 // transposed spectrum, and its partner NC - k at row N2 - r, column N1 - 1 - c
 // (row 0 and row N2/2 pair with themselves: columns N1 - c and N1 - 1 - c).
-// Grid: B*D*(N2/2 + 1) workgroups of N1/16 threads; workgroup (item, r) owns
-// rows r and N2 - r.  Two-row pairs: the spectrum of row r goes back to its
-// row of the buffer; thread t writes, and later reads back, exactly the
-// columns t + NT j (the output layout of the transform covers them), so the
-// round trip needs no barrier and holds no registers while row N2 - r is
-// transformed and stored to LDS in natural order.  Each thread then pairs
-// its row-r columns with their partners read from LDS, writes row r's
-// results to the buffer and row N2 - r's to LDS in place (every LDS word is
-// read and written by one thread only); then the inverse transforms of row
-// N2 - r (from LDS) and of row r (from its own writes).  Rows are left
+// Grid: B*D*N2/2 workgroups of N1/16 threads; workgroup (item, r) owns rows r
+// and N2 - r, workgroup (item, 0) the self-paired rows 0 and N2/2, one after
+// the other: all workgroups have two rows to do, so that whole rounds of them
+// fill the chip (with the self-paired rows as workgroups of their own, 96
+// windows of N2 = 32 took 3.2 rounds of 512 instead of 3).
+// Two-row pairs: the spectrum of row r stays in registers (thread t holds the
+// columns t + NT j) while row N2 - r is transformed and stored to LDS in
+// natural order.  Each thread then pairs its row-r columns with their
+// partners read from LDS, keeps row r's results and writes row N2 - r's to
+// LDS in place (every LDS word is read and written by one thread only); then
+// the inverse transforms of row N2 - r (from LDS) and of row r (from
+// registers).  Each row is read and written once, where row r made two more
+// round trips through the buffer to save registers.  96 windows of 2^19
+// samples: 248 us with both of these as they were, 222 now, of which the
+// vector arithmetic takes 120 to 145 and the rows' 400 MB 80.  Rows are left
 // unscaled, as the separate row passes leave them.
 template <int N1, class TP, int SRC>
 __global__ __launch_bounds__(N1 / 16, kRowWaves) void k_long_rowpair(LongArgs a) {
@@ -330,15 +335,11 @@ __global__ __launch_bounds__(N1 / 16, kRowWaves) void k_long_rowpair(LongArgs a)
   const int t = threadIdx.x;
   const DevCfg& cf = a.w.cf;
   const int NC = a.NC, N2 = a.N2;
-  const int npair = N2 / 2 + 1;
-  const int64_t bd = blockIdx.x / npair;
-  const int rA = int(blockIdx.x - bd * npair);
-  const int rB = rA == 0 ? 0 : N2 - rA;
+  const int64_t bd = blockIdx.x / (N2 / 2);
+  const int rA = int(blockIdx.x - bd * (N2 / 2));
   const int64_t b = bd / cf.n_det;
   const int d = int(bd - b * cf.n_det);
   float2* buf = reinterpret_cast<float2*>(a.w.out) + bd * NC;
-  float2* rowA = buf + int64_t(rA) * N1;
-  float2* rowB = buf + int64_t(rB) * N1;
   const float* psd = a.w.psd + bd * cf.Fw;
   const cpx<float>* tw1 = reinterpret_cast<const cpx<float>*>(a.tw1);
   // a fresh table pointer per transform (see opaque)
@@ -351,12 +352,11 @@ __global__ __launch_bounds__(N1 / 16, kRowWaves) void k_long_rowpair(LongArgs a)
     pr = long_projection(a, wsh, b, d);
   }
   uint32_t flag = 0;
-  cpx<float> v[16];
   // Each phase below takes its own copy of the lane index and row pointers
   // (fresh_lane, fresh): without them the compiler shares the index and
-  // address arithmetic of the five transforms and keeps it live throughout,
+  // address arithmetic of the transforms and keeps it live throughout,
   // beyond the 128 registers a 1024-thread workgroup allows.
-  auto load_row = [&](float2* row) {
+  auto load_row = [&](cpx<float>* v, float2* row) {
     const int tl = fresh_lane(t);
     float2* r = fresh(row);
 #pragma unroll
@@ -365,13 +365,13 @@ __global__ __launch_bounds__(N1 / 16, kRowWaves) void k_long_rowpair(LongArgs a)
       v[fft_in_slot<N1, 0>(j)] = {q.x, q.y};
     }
   };
-  auto store_row = [&](float2* row) {
+  auto store_row = [&](const cpx<float>* v, float2* row) {
     const int tl = fresh_lane(t);
     float2* r = fresh(row);
 #pragma unroll
     for (int e = 0; e < 16; ++e) r[fft_out_index<N1, 0>(tl, e)] = {v[e].x, v[e].y};
   };
-  auto store_lds = [&]() {
+  auto store_lds = [&](const cpx<float>* v) {
     const int tl = fresh_lane(t);
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
@@ -380,111 +380,129 @@ __global__ __launch_bounds__(N1 / 16, kRowWaves) void k_long_rowpair(LongArgs a)
       sim[i] = v[e].y;
     }
   };
-  // forward transform of row rA
-  load_row(rowA);
-  block_fft<float, N1, -1, false, 0>(v, sre, sim, fresh_lane(t), tw());
-  if (rA == rB) {
-    // self-paired row (uniform over the workgroup): spectrum to LDS, pairs
+  if (rA == 0) {
+    // self-paired rows (uniform over the workgroup): spectrum to LDS, pairs
     // in LDS, inverse transform from LDS
-    lds_barrier();
-    store_lds();
-    lds_barrier();
-    const int tl = fresh_lane(t);
-    // column of iteration j and its mirror; the pair's global inputs are
-    // fetched one iteration ahead (clamped to the lower bin, so that every
-    // iteration loads a valid pair) to overlap their latency
-    auto cols = [&](int j, int& c, int& cm, int& k) {
-      c = tl + NT * j;
-      cm = rA == 0 ? ((N1 - c) & (N1 - 1)) : (N1 - 1 - c);
-      k = rA + N2 * c;
-      if (k > NC - k) {  // the partner's thread handles the pair; fetch it anyway
-        const int x = c;
-        c = cm;
-        cm = x;
-        k = NC - k;
-      }
-    };
-    int c, cm, k;
-    cols(0, c, cm, k);
-    LongPairIn nxt = long_pair_fetch<SRC>(a, psd, k, int64_t(rA) * N1 + c, int64_t(rA) * N1 + cm);
 #pragma unroll 1
-    for (int j = 0; j < 16; ++j) {
-      const LongPairIn cur = nxt;
-      const int cj = c, cmj = cm, kj = k;
-      const bool mine = rA + N2 * (tl + NT * j) <= NC - (rA + N2 * (tl + NT * j));
-      if (j + 1 < 16) {
-        cols(j + 1, c, cm, k);
-        nxt = long_pair_fetch<SRC>(a, psd, k, int64_t(rA) * N1 + c, int64_t(rA) * N1 + cm);
+    for (int r = 0; r < N2; r += N2 / 2) {
+      float2* row = buf + int64_t(r) * N1;
+      cpx<float> v[16];
+      load_row(v, row);
+      if (r) lds_barrier();  // the row before is done with LDS
+      block_fft<float, N1, -1, false, 0>(v, sre, sim, fresh_lane(t), tw());
+      lds_barrier();
+      store_lds(v);
+      lds_barrier();
+      const int tl = fresh_lane(t);
+      // column of iteration j and its mirror; the pair's global inputs are
+      // fetched one iteration ahead (clamped to the lower bin, so that every
+      // iteration loads a valid pair) to overlap their latency
+      auto cols = [&](int j, int& c, int& cm, int& k) {
+        c = tl + NT * j;
+        cm = r == 0 ? ((N1 - c) & (N1 - 1)) : (N1 - 1 - c);
+        k = r + N2 * c;
+        if (k > NC - k) {  // the partner's thread handles the pair; fetch it anyway
+          const int x = c;
+          c = cm;
+          cm = x;
+          k = NC - k;
+        }
+      };
+      int c, cm, k;
+      cols(0, c, cm, k);
+      LongPairIn nxt = long_pair_fetch<SRC>(a, psd, k, int64_t(r) * N1 + c, int64_t(r) * N1 + cm);
+#pragma unroll 1
+      for (int j = 0; j < 16; ++j) {
+        const LongPairIn cur = nxt;
+        const int cj = c, cmj = cm, kj = k;
+        const bool mine = r + N2 * (tl + NT * j) <= NC - (r + N2 * (tl + NT * j));
+        if (j + 1 < 16) {
+          cols(j + 1, c, cm, k);
+          nxt = long_pair_fetch<SRC>(a, psd, k, int64_t(r) * N1 + c, int64_t(r) * N1 + cm);
+        }
+        if (!mine) continue;  // the partner's thread handles the pair
+        const int km = NC - kj;
+        const int ic = lpad<float>(cj), im = lpad<float>(cmj);
+        cpx<float> A = {sre[ic], sim[ic]}, Bm = {sre[im], sim[im]};
+        long_pair<TP, SRC>(a, wsh, pr, cur, kj, A, Bm, flag);
+        sre[ic] = A.x;
+        sim[ic] = A.y;
+        if (kj != 0 && km != kj) {
+          sre[im] = Bm.x;
+          sim[im] = Bm.y;
+        }
       }
-      if (!mine) continue;  // the partner's thread handles the pair
-      const int km = NC - kj;
-      const int ic = lpad<float>(cj), im = lpad<float>(cmj);
-      cpx<float> A = {sre[ic], sim[ic]}, Bm = {sre[im], sim[im]};
-      long_pair<TP, SRC>(a, wsh, pr, cur, kj, A, Bm, flag);
-      sre[ic] = A.x;
-      sim[ic] = A.y;
-      if (kj != 0 && km != kj) {
-        sre[im] = Bm.x;
-        sim[im] = Bm.y;
-      }
+      lds_barrier();
+      block_fft<float, N1, +1, true, 0>(v, sre, sim, fresh_lane(t), tw());
+      store_row(v, row);
     }
-    lds_barrier();
-    block_fft<float, N1, +1, true, 0>(v, sre, sim, fresh_lane(t), tw());
-    store_row(rowA);
   } else {
-    // row rA's spectrum back to its row (columns t + NT j of this thread);
-    // row rB transformed and stored to LDS
-    store_row(rowA);
-    load_row(rowB);
+    const int rB = N2 - rA;
+    float2* rowA = buf + int64_t(rA) * N1;
+    float2* rowB = buf + int64_t(rB) * N1;
+    cpx<float> A[16], v[16];
+    load_row(v, rowA);
+    block_fft<float, N1, -1, false, 0>(v, sre, sim, fresh_lane(t), tw());
+    // A[j]: column t + NT j of row rA
+    constexpr int RL = PlanEnds<N1, 0>::RLAST;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) A[e / RL + (e % RL) * (16 / RL)] = v[e];
+    load_row(v, rowB);
     lds_barrier();
     block_fft<float, N1, -1, false, 0>(v, sre, sim, fresh_lane(t), tw());
     lds_barrier();
-    store_lds();
+    store_lds(v);
     lds_barrier();
     {
       const int tl = fresh_lane(t);
-      float2* ra = fresh(rowA);
-      // the pair's global inputs (own row-r bin, tables, PSD values) are
-      // fetched one iteration ahead to overlap their latency
-      struct Ahead {
-        float2 q;
-        LongPairIn in;
-      };
+      // the pair's global inputs (tables, PSD values) are fetched one
+      // iteration ahead to overlap their latency
       auto fetch = [&](int j) {
         const int c = tl + NT * j;
         const int cm = N1 - 1 - c;
         const int k = rA + N2 * c, km = NC - k;
         const int64_t pa = int64_t(rA) * N1 + c, pb = int64_t(rB) * N1 + cm;
-        Ahead h;
-        h.q = ra[c];  // this thread's own write above
-        h.in = k < km ? long_pair_fetch<SRC>(a, psd, k, pa, pb) : long_pair_fetch<SRC>(a, psd, km, pb, pa);
-        return h;
+        return k < km ? long_pair_fetch<SRC>(a, psd, k, pa, pb) : long_pair_fetch<SRC>(a, psd, km, pb, pa);
       };
-      Ahead nxt = fetch(0);
+      LongPairIn nxt = fetch(0);
+      // A stays in registers: each round of kTurn pairs works on the first
+      // kTurn elements and moves them to the end
+      constexpr int kTurn = 2;
 #pragma unroll 1
-      for (int j = 0; j < 16; ++j) {
-        const Ahead cur = nxt;
-        if (j + 1 < 16) nxt = fetch(j + 1);
-        const int c = tl + NT * j;
-        const int cm = N1 - 1 - c;
-        const int k = rA + N2 * c, km = NC - k;
-        const int im = lpad<float>(cm);
-        cpx<float> P = {cur.q.x, cur.q.y}, Q = {sre[im], sim[im]};
-        if (k < km) long_pair<TP, SRC>(a, wsh, pr, cur.in, k, P, Q, flag);
-        else long_pair<TP, SRC>(a, wsh, pr, cur.in, km, Q, P, flag);
-        ra[c] = {P.x, P.y};
-        sre[im] = Q.x;
-        sim[im] = Q.y;
+      for (int j0 = 0; j0 < 16; j0 += kTurn) {
+#pragma unroll
+        for (int u = 0; u < kTurn; ++u) {
+          const int j = j0 + u;
+          const LongPairIn cur = nxt;
+          nxt = fetch(min(j + 1, 15));
+          const int c = tl + NT * j;
+          const int cm = N1 - 1 - c;
+          const int k = rA + N2 * c, km = NC - k;
+          const int im = lpad<float>(cm);
+          cpx<float> P = A[u], Q = {sre[im], sim[im]};
+          if (k < km) long_pair<TP, SRC>(a, wsh, pr, cur, k, P, Q, flag);
+          else long_pair<TP, SRC>(a, wsh, pr, cur, km, Q, P, flag);
+          A[u] = P;
+          sre[im] = Q.x;
+          sim[im] = Q.y;
+        }
+        cpx<float> done[kTurn];
+#pragma unroll
+        for (int u = 0; u < kTurn; ++u) done[u] = A[u];
+#pragma unroll
+        for (int i = 0; i + kTurn < 16; ++i) A[i] = A[i + kTurn];
+#pragma unroll
+        for (int u = 0; u < kTurn; ++u) A[16 - kTurn + u] = done[u];
       }
     }
     lds_barrier();
     block_fft<float, N1, +1, true, 0>(v, sre, sim, fresh_lane(t), tw());
-    store_row(rowB);
-    // row rA: its bins as this thread wrote them, in the transform's input layout
-    load_row(rowA);
+    store_row(v, rowB);
+#pragma unroll
+    for (int j = 0; j < 16; ++j) v[fft_in_slot<N1, 0>(j)] = A[j];
     lds_barrier();
     block_fft<float, N1, +1, false, 0>(v, sre, sim, fresh_lane(t), tw());
-    store_row(rowA);
+    store_row(v, rowA);
   }
   if (flag) atomicOr(&sflag, flag);
   __syncthreads();
@@ -537,7 +555,7 @@ void long_passes(const DevCfg& d, int src, const LongArgs& a, const float* hdet,
   else launch_cols_fwd<N1, 1>(a, items, st);
   if (d.ord_win) {
     // rows, bins and inverse rows fused per row pair
-    const dim3 pair_grid(unsigned(items * (a.N2 / 2 + 1)));
+    const dim3 pair_grid(unsigned(items * (a.N2 / 2)));
     if (src == 0) hipLaunchKernelGGL((k_long_rowpair<N1, double, 0>), pair_grid, dim3(N1 / 16), 0, st, a);
     else if (d.precision == 0) hipLaunchKernelGGL((k_long_rowpair<N1, float, 1>), pair_grid, dim3(N1 / 16), 0, st, a);
     else hipLaunchKernelGGL((k_long_rowpair<N1, double, 1>), pair_grid, dim3(N1 / 16), 0, st, a);
