@@ -346,6 +346,7 @@ template <int NC, int ORD> struct PlanTw {
 
 // The 8 twiddles of a thread's 16/R butterflies in pass PASS.
 template <class T, int NC, int ORD> struct PassTwiddle {
+  static constexpr bool kLate = false;
   const cpx<T>* __restrict__ tab;  // tables of both orders
   template <int PASS> struct Regs { cpx<T> w[8]; };
   template <int PASS> __device__ __forceinline__ Regs<PASS> load(int t) const {
@@ -370,6 +371,7 @@ template <class T, int NC, int ORD> struct PassTwiddle {
 
 // All passes' twiddles held in registers (many transforms per thread).
 template <class T, int NC, int ORD> struct HeldTwiddle {
+  static constexpr bool kLate = false;
   using Src = PassTwiddle<T, NC, ORD>;
   typename Src::template Regs<1> w1;
   typename Src::template Regs<2> w2;
@@ -387,13 +389,27 @@ template <class T, int NC, int ORD> struct HeldTwiddle {
   }
 };
 
+// Each pass's twiddles requested only after the arithmetic of the pass ahead
+// of it, when that pass's own are dead (see block_fft): a binary64 transform
+// whose thread also holds sums has no registers for two passes' twiddles.
+template <class T, int NC, int ORD> struct LateTwiddle {
+  static constexpr bool kLate = true;
+  const cpx<T>* tab;
+  __device__ __forceinline__ void init(const cpx<T>* tab_, int) { tab = tab_; }
+  template <int PASS> __device__ __forceinline__ auto load(int t) const {
+    return PassTwiddle<T, NC, ORD>{opaque(tab)}.template load<PASS>(fresh_lane(t));
+  }
+};
+
 // One Stockham pass.  READ: take input from LDS (else registers already hold
 // it).  WRITE: scatter the output to LDS (else it stays in registers in the
 // final layout).  A barrier separates this pass's LDS reads from its writes;
 // the caller must ensure the LDS buffer is free before a pass that WRITEs
-// without READing.  w: the pass's 8 twiddles (unused in pass 0).
-template <class T, int NC, int PASS, int DIR, bool READ, bool WRITE, int ORD>
-__device__ __forceinline__ void fft_pass(cpx<T>* v, T* sre, T* sim, int t, const cpx<T>* w) {
+// without READing.  w: the pass's 8 twiddles (unused in pass 0).  after() is
+// called between the pass's arithmetic and its writes.
+struct Nothing { __device__ __forceinline__ void operator()() const {} };
+template <class T, int NC, int PASS, int DIR, bool READ, bool WRITE, int ORD, class After = Nothing>
+__device__ __forceinline__ void fft_pass(cpx<T>* v, T* sre, T* sim, int t, const cpx<T>* w, After after = {}) {
   constexpr int R = PassInfo<NC, PASS, ORD>::R, NS = PassInfo<NC, PASS, ORD>::NS;
   constexpr int NT = NC / 16, NB = 16 / R, STRIDE = NC / R;
   // layout of the buffer read: written by the previous pass, or natural order
@@ -412,6 +428,7 @@ __device__ __forceinline__ void fft_pass(cpx<T>* v, T* sre, T* sim, int t, const
   }
 #pragma unroll
   for (int m = 0; m < NB; ++m) dit_fft<R, DIR, (NS > 1)>(v + m * R, w + m * (R / 2));
+  after();
   if constexpr (WRITE) {
     if constexpr (READ) lds_barrier();
 #pragma unroll
@@ -435,19 +452,35 @@ __device__ __forceinline__ void fft_pass(cpx<T>* v, T* sre, T* sim, int t, const
 // The result stays in registers in the final layout (see fft_out_index).
 // Ends with LDS still being read by other threads: barrier before reusing it.
 // Each pass's twiddles are requested before the pass ahead of it, so that
-// their latency is hidden behind that pass.
-template <class T, int NC, int DIR, bool FIRST_FROM_LDS, int ORD = 0, class TW>
-__device__ __forceinline__ void block_fft(cpx<T>* v, T* sre, T* sim, int t, const TW& tw) {
-  const auto w1 = tw.template load<1>(t);
-  fft_pass<T, NC, 0, DIR, FIRST_FROM_LDS, true, ORD>(v, sre, sim, t, w1.w);
-  const auto w2 = tw.template load<2>(t);
-  fft_pass<T, NC, 1, DIR, true, true, ORD>(v, sre, sim, t, w1.w);
-  if constexpr (FftPlan<NC>::NPASS == 3) {
+// their latency is hidden behind that pass.  Late twiddles (three passes) are
+// requested behind its arithmetic; ahead() is then called after the last
+// request, for loads of the caller's that take longer: loads return in order.
+template <class T, int NC, int DIR, bool FIRST_FROM_LDS, int ORD = 0, class TW, class Ahead = Nothing>
+__device__ __forceinline__ void block_fft(cpx<T>* v, T* sre, T* sim, int t, const TW& tw, Ahead ahead = {}) {
+  if constexpr (TW::kLate) {
+    static_assert(FftPlan<NC>::NPASS == 3, "three passes");
+    using Src = PassTwiddle<T, NC, ORD>;
+    typename Src::template Regs<1> w1;
+    typename Src::template Regs<2> w2;
+    fft_pass<T, NC, 0, DIR, FIRST_FROM_LDS, true, ORD>(v, sre, sim, t, nullptr,
+                                                       [&]() { w1 = tw.template load<1>(t); });
+    fft_pass<T, NC, 1, DIR, true, true, ORD>(v, sre, sim, t, w1.w, [&]() {
+      w2 = tw.template load<2>(t);
+      ahead();
+    });
     fft_pass<T, NC, 2, DIR, true, false, ORD>(v, sre, sim, t, w2.w);
   } else {
-    const auto w3 = tw.template load<3>(t);
-    fft_pass<T, NC, 2, DIR, true, true, ORD>(v, sre, sim, t, w2.w);
-    fft_pass<T, NC, 3, DIR, true, false, ORD>(v, sre, sim, t, w3.w);
+    const auto w1 = tw.template load<1>(t);
+    fft_pass<T, NC, 0, DIR, FIRST_FROM_LDS, true, ORD>(v, sre, sim, t, w1.w);
+    const auto w2 = tw.template load<2>(t);
+    fft_pass<T, NC, 1, DIR, true, true, ORD>(v, sre, sim, t, w1.w);
+    if constexpr (FftPlan<NC>::NPASS == 3) {
+      fft_pass<T, NC, 2, DIR, true, false, ORD>(v, sre, sim, t, w2.w);
+    } else {
+      const auto w3 = tw.template load<3>(t);
+      fft_pass<T, NC, 2, DIR, true, true, ORD>(v, sre, sim, t, w2.w);
+      fft_pass<T, NC, 3, DIR, true, false, ORD>(v, sre, sim, t, w3.w);
+    }
   }
 }
 

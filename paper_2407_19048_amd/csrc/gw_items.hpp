@@ -560,7 +560,10 @@ template <class T, class ACC, int NC, int ORD> struct WelchItem {
   // sin^2 window at n = t + NT r, r < 8; half a segment later it is
   // cos^2 = 1 - sin^2, applied as x - w x
   T w[8];
-  HeldTwiddle<T, NC, ORD> tw;
+  // binary64: with the twiddles held, a thread took 290 registers, one wave to
+  // a SIMD; 300 stretches of 32 pairs of L = 4096 took 131 us, now 104
+  static constexpr bool kLate = sizeof(T) == 8;
+  std::conditional_t<kLate, LateTwiddle<T, NC, ORD>, HeldTwiddle<T, NC, ORD>> tw;
   ACC tot[16];
   T run[kWide ? 1 : 16];
   int t;
@@ -627,10 +630,13 @@ template <class T, class ACC, int NC, int ORD> struct WelchItem {
         for (int r = 0; r < 16; ++r) v[r].y = T(0);
       }
       const int pn = min(p + 1, p1 - 1);
-      load_half(x + int64_t(2 * pn + 1) * (NC / 2), na);
-      load_half(x + int64_t(min(2 * pn + 2, K)) * (NC / 2), nb);
+      auto next = [&]() {
+        load_half(x + int64_t(2 * pn + 1) * (NC / 2), na);
+        load_half(x + int64_t(min(2 * pn + 2, K)) * (NC / 2), nb);
+      };
+      if constexpr (!kLate) next();
       lds_barrier();  // the previous transform's last reads are done
-      block_fft<T, NC, -1, false, ORD>(v, sre, sim, t, tw);
+      block_fft<T, NC, -1, false, ORD>(v, sre, sim, t, tw, next);
       add_power(v, p);
     }
   }
