@@ -56,6 +56,9 @@ gw_status validate_config(const gw_config* g, DevCfg* dc, std::string* why);
 gw_status capture_graph(const std::function<gw_status(hipStream_t)>& enqueue, uint64_t* batch, uint64_t first,
                         gw_graph** out, std::string* why);
 
+// Long windows' table entry of a bin: ln(k)/3 and k^(-5/3) (both 0 at k = 0).
+struct alignas(16) BinTab { double lk = 0.0, k53 = 0.0; };
+
 // {cosine, tangent} of the angle -2 pi num / den, 0 <= num <= den / 2.  At the
 // quarter turn, where the tangent has no value, the cosine is set to 2^-28
 // (binary32) or 2^-56: a quarter of a unit in the last place of the sine, and

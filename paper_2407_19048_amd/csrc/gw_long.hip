@@ -65,6 +65,15 @@ __device__ __forceinline__ void dft_small(cpx<T>* a) {
   }
 }
 
+// Powers of bin k from its table entry: k^(1/3) = k^(-5/3) k^2.  (The power
+// -5/3 from a table of k^(1/3) took a binary64 reciprocal, 14 of the 220
+// instructions of a bin; in the kernels of short windows, which read k^(1/3)
+// as well, two tables instead of three changed nothing.)
+__device__ __forceinline__ BinPowers bin_powers(int k, BinTab t) {
+  const double kd = double(k);
+  return {t.k53 * (kd * kd), t.lk, t.k53};
+}
+
 struct LongArgs {
   WinArgs w;           // cf, tables, per-sample data, psd, status; out = the in-place buffer
   const void* twc;     // cpx<float>[N2][N1]: exp(-2 pi i m1 k2 / NC) at [k2][m1]
@@ -73,8 +82,7 @@ struct LongArgs {
   const float* x;      // real input of the forward columns (strain rows or the background)
   int NC, N2, l2n2;    // NC = N1 N2, l2n2 = log2(N2)
   // bin tables in the transposed layout (bin k at (k mod N2) N1 + k / N2):
-  const double* kc_t;        // k^(1/3)
-  const double* lk_t;        // ln(k)/3
+  const BinTab* bins_t;
   const cpx<float>* twr_t;   // exp(-2 pi i k / N)
 };
 
@@ -192,7 +200,7 @@ __global__ __launch_bounds__(256) void k_long_inject(LongArgs a, const float* hd
 // and km in the transposed bin tables.
 struct LongPairIn {
   cpx<float> W;
-  double kc[2], lk[2];
+  BinTab b[2];
   PsdAround g;
 };
 
@@ -202,10 +210,8 @@ __device__ __forceinline__ LongPairIn long_pair_fetch(const LongArgs& a, const f
   LongPairIn in;
   in.W = a.twr_t[pk];
   if constexpr (SRC == 1) {
-    in.kc[0] = a.kc_t[pk];
-    in.lk[0] = a.lk_t[pk];
-    in.kc[1] = a.kc_t[pm];
-    in.lk[1] = a.lk_t[pm];
+    in.b[0] = a.bins_t[pk];
+    in.b[1] = a.bins_t[pm];
   }
   in.g = psd_around(a.w.cf, psd, k, a.NC);
   return in;
@@ -229,8 +235,8 @@ __device__ __forceinline__ void long_pair(const LongArgs& a, const WfScalars& ws
   cpx<float> Yk, Ym;
   unpack_pair(A, Bm, in.W, &Yk, &Ym);
   if constexpr (SRC == 1) {
-    add_signal<float, TP, false>(cf, wsh, pr, k, [&](int) { return BinPowers{in.kc[0], in.lk[0], pow53(in.kc[0])}; }, &Yk);
-    add_signal<float, TP, false>(cf, wsh, pr, km, [&](int) { return BinPowers{in.kc[1], in.lk[1], pow53(in.kc[1])}; }, &Ym);
+    add_signal<float, TP, false>(cf, wsh, pr, k, [&](int kk) { return bin_powers(kk, in.b[0]); }, &Yk);
+    add_signal<float, TP, false>(cf, wsh, pr, km, [&](int kk) { return bin_powers(kk, in.b[1]); }, &Ym);
   }
   float gk, gm;
   psd_gains<float>(cf, in.g, k, NC, flag, &gk, &gm);
@@ -322,7 +328,8 @@ __global__ __launch_bounds__(256) void k_long_bins(LongArgs a) {
 // registers).  Each row is read and written once, where row r made two more
 // round trips through the buffer to save registers.  96 windows of 2^19
 // samples: 248 us with both of these as they were, 222 now, of which the
-// vector arithmetic takes 120 to 145 and the rows' 400 MB 80.  Rows are left
+// vector arithmetic takes 120 to 145 and the rows' 400 MB 80 (207 since with
+// k^(-5/3) from a table, see bin_powers).  Rows are left
 // unscaled, as the separate row passes leave them.
 template <int N1, class TP, int SRC>
 __global__ __launch_bounds__(N1 / 16, kRowWaves) void k_long_rowpair(LongArgs a) {
@@ -598,9 +605,8 @@ gw_status long_window(gw_ctx* c, int src, const WinArgs& w, const float* x, cons
   a.l2n2 = 0;
   while ((1 << a.l2n2) < a.N2) ++a.l2n2;
   const char* tabs = static_cast<const char*>(c->long_tabs);
-  a.kc_t = reinterpret_cast<const double*>(tabs);
-  a.lk_t = reinterpret_cast<const double*>(tabs + sizeof(double) * size_t(a.NC));
-  a.twr_t = reinterpret_cast<const cpx<float>*>(tabs + 2 * sizeof(double) * size_t(a.NC));
+  a.bins_t = reinterpret_cast<const BinTab*>(tabs);
+  a.twr_t = reinterpret_cast<const cpx<float>*>(tabs + sizeof(BinTab) * size_t(a.NC));
   if (items <= 0) return GW_OK;
   if (items > 65535) return ctx_fail(c, GW_EINVAL, "long windows: at most 65535 (sample, detector) items per call");
   if (!c->long_tabs) return ctx_fail(c, GW_EUNSUPPORTED, "long windows need the binary32 tables");

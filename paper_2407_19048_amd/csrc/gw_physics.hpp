@@ -325,12 +325,6 @@ __device__ __forceinline__ void wf_setup_column(const double* __restrict__ param
 // Powers of a bin number.
 struct BinPowers { double kc, lk, k53; };  // k^(1/3), ln(k)/3, k^(-5/3)
 
-// k^(-5/3) from k^(1/3), for tables without it
-__device__ __forceinline__ double pow53(double kc) {
-  const double i = rcp_t(kc), i2 = i * i;
-  return i2 * i2 * i;
-}
-
 // Waveform phase in revolutions (phi_c included, without the time shift) and
 // amplitude (type T) at bin k.  TP is binary64 for precision modes 1 and 2 and
 // binary32 for mode 0; FULL selects a binary64 arctangent for the (bounded)

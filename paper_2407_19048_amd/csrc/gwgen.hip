@@ -547,17 +547,16 @@ gw_status upload_twiddles(gw_ctx* c, void** dst, int count, int denom) {
 
 // Per-bin tables of the long-window bins pass in the transposed layout of
 // its spectrum (row k mod N2, column k / N2, rows of N1): one allocation
-// of double[NC] k^(1/3), double[NC] ln(k)/3, cpx<float>[NC] exp(-2 pi i k/N).
+// of BinTab[NC], cpx<float>[NC] exp(-2 pi i k/N).
 // Also the column twiddles W_NC^(m1 k2) at [k2][m1] (c->tw_long), so that a
 // wavefront's threads (consecutive m1) read consecutive entries.
 gw_status upload_long_tables(gw_ctx* c, int NC) {
   const int N1 = long_row_length(NC), N2 = NC / N1;
-  std::vector<double> kc(NC), lk(NC);
+  std::vector<BinTab> bins(NC);
   std::vector<cpx<float>> tw(NC), twc(NC);
   for (int k = 0; k < NC; ++k) {
     const int p = (k % N2) * N1 + k / N2;
-    kc[p] = std::cbrt(double(k));
-    lk[p] = k > 0 ? std::log(double(k)) / 3.0 : 0.0;
+    if (k > 0) bins[p] = {std::log(double(k)) / 3.0, std::pow(double(k), -5.0 / 3.0)};
     const double ang = -2.0 * M_PI * double(k) / double(2 * NC);
     tw[p] = {float(std::cos(ang)), float(std::sin(ang))};
   }
@@ -571,12 +570,11 @@ gw_status upload_long_tables(gw_ctx* c, int NC) {
     return fail(c, GW_ENOMEM, "hipMalloc column twiddles");
   if (hipMemcpy(c->tw_long, twc.data(), sizeof(cpx<float>) * size_t(NC), hipMemcpyHostToDevice) != hipSuccess)
     return fail(c, GW_EHIP, "hipMemcpy column twiddles");
-  const size_t nd = sizeof(double) * size_t(NC), nt = sizeof(cpx<float>) * size_t(NC);
-  if (hipMalloc(&c->long_tabs, 2 * nd + nt) != hipSuccess) return fail(c, GW_ENOMEM, "hipMalloc long tables");
+  const size_t nb = sizeof(BinTab) * size_t(NC), nt = sizeof(cpx<float>) * size_t(NC);
+  if (hipMalloc(&c->long_tabs, nb + nt) != hipSuccess) return fail(c, GW_ENOMEM, "hipMalloc long tables");
   char* base = static_cast<char*>(c->long_tabs);
-  if (hipMemcpy(base, kc.data(), nd, hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(base + nd, lk.data(), nd, hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(base + 2 * nd, tw.data(), nt, hipMemcpyHostToDevice) != hipSuccess)
+  if (hipMemcpy(base, bins.data(), nb, hipMemcpyHostToDevice) != hipSuccess ||
+      hipMemcpy(base + nb, tw.data(), nt, hipMemcpyHostToDevice) != hipSuccess)
     return fail(c, GW_EHIP, "hipMemcpy long tables");
   return GW_OK;
 }
