@@ -67,16 +67,22 @@ struct WaveArgs {
   const double* k53;
   float* hp;
   float* hc;
+  int parts;  // workgroups of a sample
 };
 
+// Every workgroup computes its sample's constants (a chain of some 7 us) and
+// each thread then a number of bins, about 0.8 us of binary64 arithmetic each
+// where a SIMD holds one wave.  With one workgroup per sample, 200 samples of
+// 8193 bins left most of the chip idle: 33 us, with 5 (see gen_fd_waveform) 18.
 template <class TP, bool FULL>
 __global__ __launch_bounds__(256) void k_gen_fd_waveform(WaveArgs a) {
   __shared__ WfScalars w;
-  const int64_t b = blockIdx.x;
+  const int64_t b = blockIdx.x / uint32_t(a.parts);
+  const int part = int(blockIdx.x - uint32_t(b) * uint32_t(a.parts));
   if (threadIdx.x < kSetupLanes) wf_setup_column(a.params, a.B, b, a.cf, threadIdx.x, &w);
   __syncthreads();
   const int F = a.cf.F;
-  for (int k = threadIdx.x; k < F; k += 256) {
+  for (int k = part * 256 + threadIdx.x; k < F; k += a.parts * 256) {
     float2 hp = {0.f, 0.f}, hc = {0.f, 0.f};
     if (k > 0 && k >= a.cf.kmin && k < w.kend && a.cf.approximant == 2) {
       // sine-Gaussian: h+ = ap [e^{i phi0} G(f - f0) + e^{-i phi0} G(f + f0)],
@@ -1087,8 +1093,11 @@ gw_status gen_fd_waveform(gw_ctx* c, const double* params, int64_t B, float* hp,
   if (B == 0) return GW_OK;
   if (!params || !hp || !hc) return fail(c, GW_EINVAL, "NULL pointer");
   if (!aligned16(params) || !aligned16(hp) || !aligned16(hc)) return fail(c, GW_EINVAL, "pointer not 16-byte aligned");
-  WaveArgs a{c->dc, params, B, c->kcbrt, c->lnk3, c->k53, hp, hc};
-  const dim3 grid = dim3(unsigned(B));
+  // up to four workgroups a CU (16 waves, what the registers allow), so long as
+  // each thread has two bins: more would only repeat the sample's constants
+  const int64_t parts = std::max<int64_t>(1, std::min<int64_t>(4 * c->n_cu / B, (c->dc.F + 511) / 512));
+  WaveArgs a{c->dc, params, B, c->kcbrt, c->lnk3, c->k53, hp, hc, int(parts)};
+  const dim3 grid = dim3(unsigned(B * parts));
   if (c->dc.precision == 0) hipLaunchKernelGGL((k_gen_fd_waveform<float, false>), grid, dim3(256), 0, stream, a);
   else if (c->dc.precision == 1) hipLaunchKernelGGL((k_gen_fd_waveform<double, false>), grid, dim3(256), 0, stream, a);
   else hipLaunchKernelGGL((k_gen_fd_waveform<double, true>), grid, dim3(256), 0, stream, a);
