@@ -407,8 +407,9 @@ gw_status gw_ragged_graph_create(gw_ragged* r, uint64_t seed, uint64_t first_bat
 /* Ragged kernel variants: radix orders as for gw_set_tuning, the
  * persistent grid of each stage in workgroups per compute unit (1..8), and
  * each stage's issue mode.  Window mode: 0 one persistent launch over all
- * classes (default), 1 one launch per window length (largest first) with one
- * NC/16-thread workgroup per item.  Welch mode: 0 one persistent launch, 1
+ * classes (default for fewer than 8 (signal, detector) items per compute
+ * unit), 1 one launch per window length (largest first) with one NC/16-thread
+ * workgroup per item.  Welch mode: 0 one persistent launch, 1
  * one launch per segment length (largest first, default) of L/16-thread
  * workgroups at 3 waves per SIMD, the items' segments in equal shares; the
  * Welch grid only applies to mode 0. */

@@ -67,7 +67,7 @@ struct gw_ragged {
   void* twr[4] = {nullptr, nullptr, nullptr, nullptr};  // exp(-2 pi i k / 2M), k <= M/2
   int n_cu = 256;
   int ord_win = 0, ord_welch = 0, grid_win = 1, grid_welch = 2;
-  int win_mode = 0;     // 0: one persistent launch, 1: one launch per transform size
+  int win_mode = 0;     // 0: one persistent launch, 1: one launch per transform size (see gw_ragged_create)
   int win_first[4] = {}, win_items[4] = {};  // window items of N/2 = 2048 << s
   int welch_mode = 1;   // Welch issue: 0 one persistent launch, 1 one launch per transform size
   // Welch items of L = 2048 << s and how mode 1 divides them (G = 0: one item
@@ -697,6 +697,11 @@ gw_status gw_ragged_create(const gw_config* classes, int32_t n_classes, const in
   }
   r->n_wgroups = int(wg.size());
   r->n_vgroups = int(vg.size());
+  // Window stage: a launch per size runs more workgroups to a CU, but each ends
+  // with places empty and the next starts behind it.  Whole batches, persistent
+  // and per size: 400 signals of 3 detectors 275 and 289 us, 1000 534 and 530,
+  // 2048 1018 and 998, 8192 4000 and 3871; the line lies between the first two.
+  r->win_mode = B * r->n_det >= 8 * int64_t(r->n_cu) ? 1 : 0;
   // sizes appear in decreasing order: the groups of size slot s end where
   // the first group of a smaller size starts (or at the end)
   for (int k = 0; k < 2; ++k) {
