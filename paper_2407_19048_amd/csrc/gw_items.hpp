@@ -720,8 +720,9 @@ struct WelchCut {
   __device__ __forceinline__ int start(int w) const { return w * q + int(uint32_t(w) * uint32_t(r) / uint32_t(G)); }
   // the last workgroup that starts before pair x
   __device__ __forceinline__ int before(int x) const {
-    const int64_t total = int64_t(q) * G + r;
-    return int((int64_t(x) * G + total - 1) / total) - 1;
+    // ceil(x G / total) - 1; x G < 2^53 is exact, and a quotient below 2^20 that
+    // is no whole number is at least 2^-31 from one (total < 2^31)
+    return int(ceil(double(x) * double(G) / (double(q) * double(G) + double(r)))) - 1;
   }
 };
 

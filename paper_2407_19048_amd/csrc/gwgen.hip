@@ -253,24 +253,25 @@ __global__ __launch_bounds__(256) void k_welch_sum(WelchCut cut, const ACC* part
   psd[int64_t(item) * Fw + k] = float(sum * ACC(norm));
 }
 
-// The same with many pieces to an item: grid (ceil(Fw/32), items), 32 bins a
-// workgroup, their pieces added by 8 threads each.
-template <class ACC>
+// The same with many pieces to an item: grid (ceil(Fw P/256), items), 256/P
+// bins a workgroup, their pieces added by P threads each.
+template <class ACC, int P>
 __global__ __launch_bounds__(256) void k_welch_sum_many(WelchCut cut, const ACC* part, int Fw, double norm, float* psd) {
-  __shared__ ACC red[8][32];
+  constexpr int NB = 256 / P;
+  __shared__ ACC red[P][NB];
   const int item = int(blockIdx.y), lo = item * cut.np;
   const int w = cut.before(lo + 1);
   if (cut.start(w + 1) >= lo + cut.np) return;  // held whole by workgroup w
   const WelchSlots s = welch_slots(cut, w, item);
-  const int j = threadIdx.x >> 5, k = blockIdx.x * 32 + (threadIdx.x & 31), kc = min(k, Fw - 1);
+  const int j = threadIdx.x / NB, b = threadIdx.x % NB, k = blockIdx.x * NB + b, kc = min(k, Fw - 1);
   ACC sum = ACC(0);
 #pragma unroll 4
-  for (int i = j; i < s.n; i += 8) sum += part[s.slot(i) * Fw + kc];
-  red[j][threadIdx.x & 31] = sum;
+  for (int i = j; i < s.n; i += P) sum += part[s.slot(i) * Fw + kc];
+  red[j][b] = sum;
   __syncthreads();
   if (j != 0 || k >= Fw) return;
 #pragma unroll
-  for (int i = 1; i < 8; ++i) sum += red[i][threadIdx.x];
+  for (int i = 1; i < P; ++i) sum += red[i][b];
   psd[int64_t(item) * Fw + k] = float(sum * ACC(norm));
 }
 
@@ -828,8 +829,16 @@ static void launch_welch(const DevCfg& d, const WelchArgs& a, hipStream_t stream
   // items of many pieces are few: a workgroup row per item, else per boundary
   const int64_t items = (int64_t(a.cut.G) * a.cut.q + a.cut.r) / a.cut.np;
   if (items * 8 <= a.cut.G) {
-    const dim3 grid(unsigned((d.Fw + 31) / 32), unsigned(items));
-    hipLaunchKernelGGL((k_welch_sum_many<ACC>), grid, dim3(256), 0, stream, a.cut, part, d.Fw, a.norm, a.psd);
+    // eight threads a bin where an item has many pieces, which they read side by
+    // side; two where items are many, so that fewer waves are launched (128
+    // items of 12 pieces: 6.4 us with eight, 4.9 with two; 3 of 256: 6.5 with eight)
+    if (items * 24 <= a.cut.G) {
+      const dim3 grid(unsigned((d.Fw + 31) / 32), unsigned(items));
+      hipLaunchKernelGGL((k_welch_sum_many<ACC, 8>), grid, dim3(256), 0, stream, a.cut, part, d.Fw, a.norm, a.psd);
+    } else {
+      const dim3 grid(unsigned((d.Fw + 127) / 128), unsigned(items));
+      hipLaunchKernelGGL((k_welch_sum_many<ACC, 2>), grid, dim3(256), 0, stream, a.cut, part, d.Fw, a.norm, a.psd);
+    }
   } else {
     const dim3 grid(unsigned((d.Fw + 255) / 256), unsigned(a.cut.G - 1));
     hipLaunchKernelGGL((k_welch_sum<ACC>), grid, dim3(256), 0, stream, a.cut, part, d.Fw, a.norm, a.psd);
