@@ -117,7 +117,7 @@ struct WinArgs {
   uint32_t* status;
   const double* kcbrt;
   const double* lnk3;
-  const double* k53;      // k^(-5/3) (SRC 3)
+  const double* k53;      // k^(-5/3)
   const void* tw;         // pass twiddle tables of the N/2-point transform
   const void* twr;        // cpx<T>[N/4 + 1], exp(-2 pi i k / N)
   const WfScalars* wf;    // [B] (SRC 1, 3)

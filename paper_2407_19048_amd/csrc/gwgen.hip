@@ -749,7 +749,9 @@ static WelchCut welch_cut(const gw_ctx* c, int64_t items, int64_t K, int64_t par
     slots = places - n_draw;
   if (d.precision == 0 || items <= 0 || items > 16 * c->n_cu * 12 || total >= (int64_t(1) << 31) || slots < 1)
     return welch_whole(items, K);
-  const int64_t rounds = (items + slots - 1) / slots * np, share = (total + slots - 1) / slots;
+  // in whole rounds the last items start behind the draws if places run out
+  const int64_t rounds = (items + places - 1) / places * np + (n_draw > 0 && items + n_draw > places ? 3 : 0);
+  const int64_t share = (total + slots - 1) / slots;
   if (rounds <= share + 8) return welch_whole(items, K);
   const int64_t G = std::min(slots, total);
   return WelchCut{int(G), int(total / G), int(total % G), int(np)};
