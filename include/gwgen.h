@@ -409,8 +409,9 @@ gw_status gw_ragged_graph_create(gw_ragged* r, uint64_t seed, uint64_t first_bat
  * each stage's issue mode.  Window mode: 0 one persistent launch over all
  * classes (default for fewer than 8 (signal, detector) items per compute
  * unit), 1 one launch per window length (largest first) with one NC/16-thread
- * workgroup per item.  Welch mode: 0 one persistent launch, 1
- * one launch per segment length (largest first, default) of L/16-thread
+ * workgroup per item.  Welch mode: 0 one persistent launch (default from two
+ * groups of items per resident workgroup on), 1
+ * one launch per segment length (largest first) of L/16-thread
  * workgroups at 3 waves per SIMD, the items' segments in equal shares; the
  * Welch grid only applies to mode 0. */
 #define GW_RTUNE_ORD_WINDOW 1

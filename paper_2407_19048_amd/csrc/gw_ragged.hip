@@ -66,10 +66,10 @@ struct gw_ragged {
   void* tw_welch[2] = {nullptr, nullptr};               // Welch tables of L = 2048 << s
   void* twr[4] = {nullptr, nullptr, nullptr, nullptr};  // exp(-2 pi i k / 2M), k <= M/2
   int n_cu = 256;
-  int ord_win = 0, ord_welch = 0, grid_win = 1, grid_welch = 2;
+  int ord_win = 0, ord_welch = 0, grid_win = 1, grid_welch = 3;
   int win_mode = 0;     // 0: one persistent launch, 1: one launch per transform size (see gw_ragged_create)
   int win_first[4] = {}, win_items[4] = {};  // window items of N/2 = 2048 << s
-  int welch_mode = 1;   // Welch issue: 0 one persistent launch, 1 one launch per transform size
+  int welch_mode = 1;   // Welch issue: 0 one persistent launch, 1 one launch per transform size (see gw_ragged_create)
   // Welch items of L = 2048 << s and how mode 1 divides them (G = 0: one item
   // per workgroup)
   int welch_first[2] = {}, welch_items[2] = {}, welch_G[2] = {};
@@ -683,7 +683,7 @@ gw_status gw_ragged_create(const gw_config* classes, int32_t n_classes, const in
       total += np;
       most = std::max(most, np);
     }
-    if (r->precision == 0 || n == 0 || n > 16 * slots || total >= (int64_t(1) << 31) ||
+    if (r->precision == 0 || n == 0 || total >= (int64_t(1) << 31) ||
         (n + slots - 1) / slots * most <= (total + slots - 1) / slots + 8)
       continue;
     const int64_t G = std::min(slots, total);
@@ -697,6 +697,14 @@ gw_status gw_ragged_create(const gw_config* classes, int32_t n_classes, const in
   }
   r->n_wgroups = int(wg.size());
   r->n_vgroups = int(vg.size());
+  // Welch stage: with its 168 registers three workgroups of the persistent launch
+  // share a CU, as of the launches per size, and it needs no sums of divided
+  // items and has one tail instead of two; with few groups dividing them is worth
+  // more.  Whole batches, per size and persistent: 250 signals of 3 detectors (0.7
+  // groups a place) 185 and 190 us, 400 (1.2) 267 and 248, 700 (2.1) 423 and 407,
+  // 2048 (6) 970 and 932, 8192 3806 and 3645.  From two groups a place on the last
+  // round is at most a third of the launch, also where all groups are of one length.
+  r->welch_mode = r->n_wgroups >= 6 * r->n_cu ? 0 : 1;
   // Window stage: a launch per size runs more workgroups to a CU, but each ends
   // with places empty and the next starts behind it.  Whole batches, persistent
   // and per size: 400 signals of 3 detectors 275 and 289 us, 1000 534 and 530,
@@ -863,7 +871,8 @@ gw_status gw_ragged_autotune(gw_ragged* r, const float* const* bg, const int64_t
   double ms[12];
   std::fill(ms, ms + 12, 1e300);  // best of kTuneRounds interleaved rounds
   auto time_stage = [&](int stage, double* res) {
-    s = enqueue_ragged(r, 1, 0, false, bg, L_bg, span, out, nullptr, nullptr, workspace, workspace_bytes, stage, st);  // warm-up
+    for (int k = 0; k < reps && s == GW_OK; ++k)  // untimed: the clock settles
+      s = enqueue_ragged(r, 1, 0, false, bg, L_bg, span, out, nullptr, nullptr, workspace, workspace_bytes, stage, st);
     if (s == GW_OK && hipEventRecord(e0, st) != hipSuccess) s = rfail(r, GW_EHIP, "hipEventRecord");
     for (int k = 0; k < reps && s == GW_OK; ++k)
       s = enqueue_ragged(r, 1, 0, false, bg, L_bg, span, out, nullptr, nullptr, workspace, workspace_bytes, stage, st);
