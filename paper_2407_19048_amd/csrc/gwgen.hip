@@ -1,12 +1,14 @@
 // libgwgen.so: HIP kernels for gfx950 and the C ABI declared in gwgen.h.
 //
 // Kernels (grid / block):
-//   k_sample_params    ceil(B/256) / 256      prior draws, one thread per sample
-//   k_gen_fd_waveform  (ceil(F/256), B) / 256 plus/cross on the window grid
+//   k_sample_params    ceil(16 B/256) / 256   prior draws, 16 lanes per sample
+//   k_gen_fd_waveform  B * parts / 256        plus/cross on the window grid
 //   k_project          (ceil(F/256), B) / 256 detector projection + time shift
-//   k_inject           B*D / (N/32)           irfft of the projected signal + noise
-//   k_welch            B*D / (L/16)           segmented Welch PSD, one block per
-//                                             (sample, detector)
+//   k_welch            n_draw + G / (L/16)    a batch's prior draws, and the
+//                                             segmented Welch PSDs: one workgroup
+//                                             per (sample, detector), or equal
+//                                             shares of all their segment pairs
+//   k_welch_sum, k_welch_sum_many             sums of the items so divided
 //   k_window<SRC>      B*D / (N/32)           rfft -> (+ signal) -> whiten -> irfft;
 //                                             SRC 0 reads strain (whiten), SRC 1
 //                                             reads the background and generates
@@ -749,7 +751,8 @@ static WelchCut welch_cut(const gw_ctx* c, int64_t items, int64_t K, int64_t par
     slots = places - n_draw;
   if (d.precision == 0 || items <= 0 || items > 16 * c->n_cu * 12 || total >= (int64_t(1) << 31) || slots < 1)
     return welch_whole(items, K);
-  // in whole rounds the last items start behind the draws if places run out
+  // in whole rounds the last items start behind the draws if places run out (a
+  // batch of 768 stretches: 162 us whole, 172 cut for the 752 places beside draws)
   const int64_t rounds = (items + places - 1) / places * np + (n_draw > 0 && items + n_draw > places ? 3 : 0);
   const int64_t share = (total + slots - 1) / slots;
   if (rounds <= share + 8) return welch_whole(items, K);
