@@ -150,9 +150,12 @@ __device__ __forceinline__ PsdAround psd_around(const DevCfg& cf, const float* p
   return q;
 }
 
-// S at window bin k from the values around it.
+// S at window bin k from the values around it: t s1 + (1 - t) s0, two terms of
+// one sign, so that where the PSD falls steeply the sum is as accurate as its
+// terms (as s0 + t (s1 - s0), its error was up to N/L times larger).
 template <class T> __device__ __forceinline__ T psd_at(const DevCfg& cf, const float* s, int k) {
-  return fma_t(T(k & (cf.ratio - 1)) * T(cf.inv_ratio), T(s[1]) - T(s[0]), T(s[0]));
+  const T t = T(k & (cf.ratio - 1)) * T(cf.inv_ratio);
+  return fma_t(t, T(s[1]), fma_t(-t, T(s[0]), T(s[0])));
 }
 
 // 1/sqrt(S) for a kept bin's PSD value S; sets status bits.
