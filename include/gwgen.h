@@ -243,7 +243,9 @@ gw_status gw_generate_batch_noalloc(gw_ctx* ctx, uint64_t seed, uint64_t batch_i
  * turned into a truncated whitening filter, then batches that only
  * generate, inject and whiten.
  * ------------------------------------------------------------------------ */
-/* Bytes of workspace gw_run_psd needs. */
+/* Bytes of workspace gw_run_psd uses.  The chunks' offsets and PSDs (8 n_chunks
+ * and 4 n_chunks n_det (L/2 + 1) bytes, each rounded up to 256) are accepted
+ * too: with less than the size named here the chunks' PSDs are averaged. */
 gw_status gw_run_psd_workspace_size(const gw_ctx* ctx, int64_t n_chunks, int64_t* bytes);
 /* Welch PSD of each detector row over its first n_chunks*K segments
  * (segment s starts at s*S), computed as the mean of n_chunks psd_length

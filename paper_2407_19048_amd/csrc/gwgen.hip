@@ -739,7 +739,10 @@ static WelchCut welch_whole(int64_t items, int64_t K) {
 // pairs, and the last n_draw of a full set would start that much later than the
 // others: they are left out of the count where the larger share costs less
 // than that (300 binary64 items with 7 draw workgroups: 111 us without, 104 with).
-static WelchCut welch_cut(const gw_ctx* c, int64_t items, int64_t K, int64_t part_bytes, int64_t n_draw) {
+// price: what the cut's sums cost, in pairs.
+constexpr int64_t kCutPrice = 8;
+static WelchCut welch_cut(const gw_ctx* c, int64_t items, int64_t K, int64_t part_bytes, int64_t n_draw,
+                          int64_t price = kCutPrice) {
   const DevCfg& d = c->dc;
   const int64_t np = (K + 1) / 2, total = items * np;
   // workgroups per CU: registers allow 3 waves per SIMD (binary64 transforms: 2)
@@ -755,13 +758,13 @@ static WelchCut welch_cut(const gw_ctx* c, int64_t items, int64_t K, int64_t par
   // batch of 768 stretches: 162 us whole, 172 cut for the 752 places beside draws)
   const int64_t rounds = (items + places - 1) / places * np + (n_draw > 0 && items + n_draw > places ? 3 : 0);
   const int64_t share = (total + slots - 1) / slots;
-  if (rounds <= share + 8) return welch_whole(items, K);
+  if (rounds <= share + price) return welch_whole(items, K);
   const int64_t G = std::min(slots, total);
   return WelchCut{int(G), int(total / G), int(total % G), int(np)};
 }
 // bytes of the sums of `items` stretches of K segments
-static int64_t ws_cut_bytes(const gw_ctx* c, int64_t items, int64_t K, int64_t n_draw) {
-  const WelchCut cut = welch_cut(c, items, K, INT64_MAX, n_draw);
+static int64_t ws_cut_bytes(const gw_ctx* c, int64_t items, int64_t K, int64_t n_draw, int64_t price = kCutPrice) {
+  const WelchCut cut = welch_cut(c, items, K, INT64_MAX, n_draw, price);
   return cut.whole() ? 0 : 2 * int64_t(cut.G) * c->dc.Fw * int64_t(sizeof(double));
 }
 
@@ -869,7 +872,8 @@ static void launch_filter(const DevCfg& d, const FiltArgs& a, hipStream_t stream
 // items; without it no item is cut.  draw: the batch's prior draws, made by the
 // same launch (offset is then not read), or NULL.
 static gw_status welch_launch(gw_ctx* c, const float* bg, int64_t L_bg, const int64_t* offset, int64_t B, int64_t K,
-                              float* psd, void* part, int64_t part_bytes, const SampleArgs* draw, hipStream_t stream) {
+                              float* psd, void* part, int64_t part_bytes, const SampleArgs* draw, hipStream_t stream,
+                              int64_t price = kCutPrice) {
   const DevCfg& d = c->dc;
   WelchArgs a{};
   a.cf = d;
@@ -884,7 +888,7 @@ static gw_status welch_launch(gw_ctx* c, const float* bg, int64_t L_bg, const in
     a.draw = *draw;
     a.n_draw = draw_blocks(B, d.L / 16);
   }
-  a.cut = welch_cut(c, B * d.n_det, K, part ? part_bytes : 0, a.n_draw);
+  a.cut = welch_cut(c, B * d.n_det, K, part ? part_bytes : 0, a.n_draw, price);
   a.part = part;
   if (d.precision == 0) launch_welch<float, float>(d, a, stream);
   else if (d.precision == 1) launch_welch<float, double>(d, a, stream);
@@ -1431,14 +1435,19 @@ gw_status gw_autotune(gw_ctx* c, int64_t B, const float* bg, int64_t L_bg, float
 // ------------------------------------------------------- per-run PSD mode
 static int64_t align256(int64_t v) { return ((v + 255) / 256) * 256; }
 
-// least workspace of a run PSD: the chunks' offsets and PSDs (binary32 sums)
+// The price of cutting a run's stretches, of which there are one to four: their
+// sums are a launch of few workgroups, and beyond three pairs a stretch equal
+// shares are faster (3 detectors, L = 4096: 4 pairs 11.5 us whole, 9.5 cut).
+constexpr int64_t kRunCutPrice = 2;
+
+// least workspace of a run PSD: the chunks' offsets and PSDs
 static int64_t run_psd_base(const DevCfg& d, int64_t n_chunks) {
   return align256(n_chunks * 8) + align256(n_chunks * d.n_det * int64_t(d.Fw) * 4);
 }
 
 gw_status gw_run_psd_workspace_size(const gw_ctx* c, int64_t n_chunks, int64_t* bytes) {
   if (!c || !bytes || n_chunks < 1) return GW_EINVAL;
-  *bytes = std::max(run_psd_base(c->dc, n_chunks), ws_cut_bytes(c, c->dc.n_det, n_chunks * c->dc.K, 0));
+  *bytes = std::max(run_psd_base(c->dc, n_chunks), ws_cut_bytes(c, c->dc.n_det, n_chunks * c->dc.K, 0, kRunCutPrice));
   return GW_OK;
 }
 
@@ -1455,9 +1464,14 @@ gw_status gw_run_psd(gw_ctx* c, const float* bg, int64_t L_bg, int64_t n_chunks,
   // With binary64 sums the chunks are one stretch per detector, cut into equal
   // shares: 600 chunks of 63 segments in whole took 131 us (768 workgroups at
   // once, 168 of them idle) and averaging the chunks' PSDs another 51 us.
-  // Binary32 sums (mode 0) stay within a chunk.
-  if (d.precision != 0 && n_chunks * d.K * d.n_det < (int64_t(1) << 31))
-    return welch_launch(c, bg, L_bg, nullptr, 1, n_chunks * d.K, psd, workspace, workspace_bytes, nullptr, stream);
+  // Binary32 sums (mode 0) stay within a chunk, and so does a call whose
+  // workspace holds fewer shares than a full set: the least one holds a quarter
+  // of the chunks' number, which took 260 us for 4 chunks of 63 segments (77 as
+  // chunks).
+  if (d.precision != 0 && n_chunks * d.K * d.n_det < (int64_t(1) << 31) &&
+      workspace_bytes >= ws_cut_bytes(c, d.n_det, n_chunks * d.K, 0, kRunCutPrice))
+    return welch_launch(c, bg, L_bg, nullptr, 1, n_chunks * d.K, psd, workspace, workspace_bytes, nullptr, stream,
+                        kRunCutPrice);
   int64_t* off = static_cast<int64_t*>(workspace);
   float* part = reinterpret_cast<float*>(static_cast<char*>(workspace) + align256(n_chunks * 8));
   hipLaunchKernelGGL(k_chunk_offsets, dim3(unsigned((n_chunks + 255) / 256)), dim3(256), 0, stream, off, n_chunks,
