@@ -126,8 +126,8 @@ const char* gw_last_error(const gw_ctx* ctx);
 gw_status gw_query(const gw_ctx* ctx, int32_t key, int64_t* value);
 /* Bytes of device workspace gw_generate_batch uses for batch size B.  The last
  * part holds the sums of background stretches that the Welch stage divides
- * between workgroups (at most 26 MB, for batches of few stretches); a workspace
- * without it is accepted and no stretch is divided then. */
+ * between workgroups (at most 34 MB, for batches of few stretches); a workspace
+ * without it is accepted and no stretch is divided then, with the same result. */
 gw_status gw_workspace_size(const gw_ctx* ctx, int64_t B, int64_t* bytes);
 
 /* sample_params -- prior draws (Table 1, section 5; ranges from gw_config).

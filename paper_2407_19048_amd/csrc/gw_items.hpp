@@ -568,16 +568,52 @@ __device__ __forceinline__ void window_item(const DevCfg& cf, const WinArgs& a, 
   if (active && flag) atomicOr(sflag, flag);
 }
 
+// a + b = s + e exactly (s the rounded sum)
+__device__ __forceinline__ void two_sum(double a, double b, double& s, double& e) {
+  s = a + b;
+  const double bb = s - a;
+  e = (a - (s - bb)) + (b - bb);
+}
+
+// A binary64 sum h with the rounding errors of its additions, l.
+struct PairSum { double h, l; };
+__device__ __forceinline__ PairSum sum_add(PairSum a, PairSum b) {
+  PairSum r;
+  double e;
+  two_sum(a.h, b.h, r.h, e);
+  r.l = (a.l + b.l) + e;
+  return r;
+}
+__device__ __forceinline__ double sum_add(double a, double b) { return a + b; }
+__device__ __forceinline__ float sum_add(float a, float b) { return a + b; }
+// times a power of two
+__device__ __forceinline__ PairSum sum_scale(PairSum a, double c) { return {a.h * c, a.l * c}; }
+__device__ __forceinline__ double sum_scale(double a, double c) { return a * c; }
+__device__ __forceinline__ float sum_scale(float a, float c) { return a * c; }
+__device__ __forceinline__ double sum_value(PairSum a) { return a.h + a.l; }
+__device__ __forceinline__ double sum_value(double a) { return a; }
+__device__ __forceinline__ float sum_value(float a) { return a; }
+
 // Welch sums of (sample, detector) stretches x = background + o, by the NC/16
 // threads t of a (sub-)block: periodic-Hann segments of L = NC samples at
 // stride L/2.  Segments 2p and 2p+1 go through ONE complex FFT as real and
 // imaginary parts; since |A_k|^2 + |B_k|^2 = (|X_k|^2 + |X_{L-k}|^2)/2 for
 // X = FFT(a + i b), the accumulated |X|^2 is folded once at the end.
 // With ACC wider than T (mixed precision) every transform's |X|^2 is added
-// to ACC totals.  With ACC equal to T it is summed in two levels, runs of
+// to ACC totals.  In binary32 throughout it is summed in two levels, runs of
 // kRun transforms and then the run sums, so that the rounding error grows with
-// kRun + K/(2 kRun) terms rather than K/2.  The fold and the normalisation are
-// done in ACC.
+// kRun + K/(2 kRun) terms rather than K/2.  In binary64 throughout the
+// additions' rounding errors are summed beside the totals (PairSum).  The fold
+// and the normalisation are done in ACC.
+//
+// A stretch may be cut anywhere and its pieces' sums added (WelchCut) without
+// a change in the result, because the sums are exact: binary32 terms in
+// binary64 as long as none but zeros is below 2^-29 of the sum, binary64 terms
+// in a PairSum down to 2^-49.  (A smaller term leaves a rounding at the sum's
+// last place, which the result's own to binary32 shows in one of 10^8 such
+// bins.  Plain binary64 sums of binary64 terms did so in every bin.  The
+// errors' sum costs five more operations a bin; 300 stretches of 32 pairs of
+// L = 4096 take 112 us with it, 101 without.)
 //
 // The kernel is bound by the issue of vector instructions: per pair and thread
 // 32 for the window, 148 + 192 + 192 for the three radix-16 passes and 64 for
@@ -593,16 +629,19 @@ template <class T, class ACC, int NC, int ORD> struct WelchItem {
   static constexpr int NT = NC / 16, LS = LdsSize<NC>::value;
   static constexpr bool kWide = sizeof(ACC) > sizeof(T);
   static constexpr int kRun = 16;
-  static_assert(NC * sizeof(ACC) <= 2 * LS * sizeof(T), "fold buffer must fit in the FFT buffer");
+  static constexpr bool kPair = sizeof(T) == 8;  // PairSum totals
+  using Sum = std::conditional_t<kPair, PairSum, ACC>;
+  static_assert(NC * sizeof(Sum) <= 2 * LS * sizeof(T), "fold buffer must fit in the FFT buffer");
   // sin^2 window at n = t + NT r, r < 8; half a segment later it is
   // cos^2 = 1 - sin^2, applied as x - w x
   T w[8];
   // binary64: with the twiddles held, a thread took 290 registers, one wave to
-  // a SIMD; 300 stretches of 32 pairs of L = 4096 took 131 us, now 104
+  // a SIMD; 300 stretches of 32 pairs of L = 4096 took 131 us, with two
+  // waves 101 (before the sums carried their errors)
   static constexpr bool kLate = sizeof(T) == 8;
   std::conditional_t<kLate, LateTwiddle<T, NC, ORD>, HeldTwiddle<T, NC, ORD>> tw;
   ACC tot[16];
-  T run[kWide ? 1 : 16];
+  T run[kWide ? 1 : 16];  // binary64: the totals' rounding errors
   int t;
   T *sre, *sim;
 
@@ -617,6 +656,14 @@ template <class T, class ACC, int NC, int ORD> struct WelchItem {
     if constexpr (kWide) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) tot[e] += ACC(fma_t(v[e].y, v[e].y, v[e].x * v[e].x));
+    } else if constexpr (kPair) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        // (both addends are at least 0: the larger one's error is none)
+        const double p2 = fma_t(v[e].y, v[e].y, v[e].x * v[e].x), s = tot[e] + p2;
+        run[e] += __builtin_fmin(tot[e], p2) - (s - __builtin_fmax(tot[e], p2));
+        tot[e] = s;
+      }
     } else {
 #pragma unroll
       for (int e = 0; e < 16; ++e) run[e] = fma_t(v[e].y, v[e].y, fma_t(v[e].x, v[e].x, run[e]));
@@ -678,21 +725,22 @@ template <class T, class ACC, int NC, int ORD> struct WelchItem {
     }
   }
 
-  // One-sided sums of bins k = t, t + NT, ... in [0, L/2] handed to
+  // One-sided sums (Sum) of bins k = t, t + NT, ... in [0, L/2] handed to
   // store(k, sum).
   template <class F> __device__ __forceinline__ void fold(F store) {
     lds_barrier();
-    ACC* f = reinterpret_cast<ACC*>(sre);
+    Sum* f = reinterpret_cast<Sum*>(sre);
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      if constexpr (kWide) f[fft_out_index<NC, ORD>(t, e)] = tot[e];
-      else f[fft_out_index<NC, ORD>(t, e)] = tot[e] + ACC(run[e]);
+      const int i = fft_out_index<NC, ORD>(t, e);
+      if constexpr (kPair) f[i] = Sum{tot[e], run[e]};
+      else if constexpr (kWide) f[i] = tot[e];
+      else f[i] = tot[e] + ACC(run[e]);
     }
     lds_barrier();
     for (int k = t; k <= NC / 2; k += NT) {
-      const ACC s = (f[k] + f[(NC - k) & (NC - 1)]) * ACC(0.5);
-      const ACC ck = (k == 0 || k == NC / 2) ? ACC(1) : ACC(2);
-      store(k, s * ck);
+      const ACC half = (k == 0 || k == NC / 2) ? ACC(0.5) : ACC(1);
+      store(k, sum_scale(sum_add(f[k], f[(NC - k) & (NC - 1)]), half));
     }
   }
 };
@@ -703,8 +751,8 @@ __device__ __forceinline__ void welch_item(int K, double norm, int t, const floa
                                            T* sim, bool active) {
   WelchItem<T, ACC, NC, ORD> w(tab, t, sre, sim);
   w.pairs(x, K, 0, (K + 1) / 2);
-  w.fold([&](int k, ACC s) {
-    if (active) out[k] = float(s * ACC(norm));
+  w.fold([&](int k, auto s) {
+    if (active) out[k] = float(sum_value(s) * ACC(norm));
   });
 }
 
@@ -712,9 +760,9 @@ __device__ __forceinline__ void welch_item(int K, double norm, int t, const floa
 // [start(w), start(w + 1)) of all items' pairs laid end to end, so that every
 // workgroup has the same share whatever the number of items.  An item that one
 // workgroup holds whole is stored at once; of one that is cut, each piece's
-// binary64 sums go to a slot of the launch's own, and welch_sum adds the slots
-// in order.  (The sums of at most a few dozen binary32 values of similar size
-// are exact in binary64, so where an item is cut does not change its PSD.)
+// sums go to a slot of the launch's own, and k_welch_sum adds the slots in
+// order.  (The sums are exact, see above: where an item is cut does not change
+// its PSD.)
 struct WelchCut {
   int G, q, r;   // workgroups; pairs = q G + r
   int np;        // pairs of an item
@@ -749,8 +797,8 @@ __device__ __forceinline__ void welch_pieces(int item, int p0, int left, int t, 
     const WelchStretch st = stretch(item);
     const int p1 = min(st.np, p0 + left);
     wi.pairs(st.x, st.K, p0, p1);
-    if (p1 - p0 == st.np) wi.fold([&](int k, ACC s) { whole(item, k, s); });
-    else wi.fold([&](int k, ACC s) { piece(item == first ? 0 : 1, item, k, s); });
+    if (p1 - p0 == st.np) wi.fold([&](int k, auto s) { whole(item, k, s); });
+    else wi.fold([&](int k, auto s) { piece(item == first ? 0 : 1, item, k, s); });
     left -= p1 - p0;
     p0 = 0;
     ++item;

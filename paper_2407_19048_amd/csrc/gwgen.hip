@@ -205,7 +205,7 @@ struct WelchArgs {
   int K;           // segments of an item
   double norm;     // 1 / (K fs sum w^2)
   WelchCut cut;
-  void* part;      // ACC[2 G][L/2 + 1] sums of cut items
+  void* part;      // Sum[2 G][L/2 + 1] sums of cut items (WelchItem::Sum)
   int64_t n_draw;
   SampleArgs draw;  // (its cf is unused)
 };
@@ -220,7 +220,8 @@ __global__ __launch_bounds__(NC / 16, OCC) void k_welch(WelchArgs a) {
     draw_block(a.draw, a.cf, blockIdx.x, t, NC / 16);
     return;
   }
-  ACC* part = static_cast<ACC*>(a.part);
+  using Sum = typename WelchItem<T, ACC, NC, ORD>::Sum;
+  Sum* part = static_cast<Sum*>(a.part);
   const int w = int(blockIdx.x - a.n_draw);
   int item = w, p0 = 0, left = a.cut.np;
   if (!a.cut.whole()) {
@@ -237,44 +238,44 @@ __global__ __launch_bounds__(NC / 16, OCC) void k_welch(WelchArgs a) {
                                    : a.offset ? a.offset[b] : 0;
         return WelchStretch{a.bg + int64_t(d) * a.L_bg + o, a.K, a.cut.np};
       },
-      [&](int i, int k, ACC sum) { a.psd[int64_t(i) * Fw + k] = float(sum * ACC(a.norm)); },
-      [&](int n, int, int k, ACC sum) { part[int64_t(2 * w + n) * Fw + k] = sum; });
+      [&](int i, int k, Sum sum) { a.psd[int64_t(i) * Fw + k] = float(sum_value(sum) * ACC(a.norm)); },
+      [&](int n, int, int k, Sum sum) { part[int64_t(2 * w + n) * Fw + k] = sum; });
 }
 
 // PSDs of the items that were cut, few pieces each: grid (ceil(Fw/256), G - 1);
 // workgroup boundary w = y + 1 handles the item it cuts, where it is the
 // item's first.
-template <class ACC>
-__global__ __launch_bounds__(256) void k_welch_sum(WelchCut cut, const ACC* part, int Fw, double norm, float* psd) {
+template <class Sum>
+__global__ __launch_bounds__(256) void k_welch_sum(WelchCut cut, const Sum* part, int Fw, double norm, float* psd) {
   const int w = int(blockIdx.y) + 1, at = cut.start(w), item = at / cut.np;
   const int k = blockIdx.x * 256 + threadIdx.x;
   if (at == item * cut.np || cut.start(w - 1) > item * cut.np || k >= Fw) return;
   const WelchSlots s = welch_slots(cut, w - 1, item);
-  ACC sum = ACC(0);
-  for (int i = 0; i < s.n; ++i) sum += part[s.slot(i) * Fw + k];
-  psd[int64_t(item) * Fw + k] = float(sum * ACC(norm));
+  Sum sum = {};
+  for (int i = 0; i < s.n; ++i) sum = sum_add(sum, part[s.slot(i) * Fw + k]);
+  psd[int64_t(item) * Fw + k] = float(sum_value(sum) * norm);
 }
 
 // The same with many pieces to an item: grid (ceil(Fw P/256), items), 256/P
 // bins a workgroup, their pieces added by P threads each.
-template <class ACC, int P>
-__global__ __launch_bounds__(256) void k_welch_sum_many(WelchCut cut, const ACC* part, int Fw, double norm, float* psd) {
+template <class Sum, int P>
+__global__ __launch_bounds__(256) void k_welch_sum_many(WelchCut cut, const Sum* part, int Fw, double norm, float* psd) {
   constexpr int NB = 256 / P;
-  __shared__ ACC red[P][NB];
+  __shared__ Sum red[P][NB];
   const int item = int(blockIdx.y), lo = item * cut.np;
   const int w = cut.before(lo + 1);
   if (cut.start(w + 1) >= lo + cut.np) return;  // held whole by workgroup w
   const WelchSlots s = welch_slots(cut, w, item);
   const int j = threadIdx.x / NB, b = threadIdx.x % NB, k = blockIdx.x * NB + b, kc = min(k, Fw - 1);
-  ACC sum = ACC(0);
+  Sum sum = {};
 #pragma unroll 4
-  for (int i = j; i < s.n; i += P) sum += part[s.slot(i) * Fw + kc];
+  for (int i = j; i < s.n; i += P) sum = sum_add(sum, part[s.slot(i) * Fw + kc]);
   red[j][b] = sum;
   __syncthreads();
   if (j != 0 || k >= Fw) return;
 #pragma unroll
-  for (int i = 1; i < P; ++i) sum += red[i][b];
-  psd[int64_t(item) * Fw + k] = float(sum * ACC(norm));
+  for (int i = 1; i < P; ++i) sum = sum_add(sum, red[i][b]);
+  psd[int64_t(item) * Fw + k] = float(sum_value(sum) * norm);
 }
 
 __global__ void k_fill_u32(uint32_t* p, int64_t n, uint32_t v) {
@@ -730,7 +731,8 @@ static int64_t ws_base_bytes(const DevCfg& d, int64_t B) { return ws_counter_off
 // sums (2 * slots * 16 KB written and read, about 8 transforms' time with the
 // launch that adds them), so items are cut where the whole rounds would take
 // longer than equal shares by more than that.  Binary32 sums (mode 0) are not
-// cut: their order would show in the result.
+// cut: their order would show in the result, which that of the other modes' does
+// not (see WelchItem).
 static WelchCut welch_whole(int64_t items, int64_t K) {
   const int np = int((K + 1) / 2);
   return WelchCut{int(items), np, 0, np};
@@ -738,9 +740,13 @@ static WelchCut welch_whole(int64_t items, int64_t K) {
 // n_draw workgroups of the same launch draw first, for about the time of three
 // pairs, and the last n_draw of a full set would start that much later than the
 // others: they are left out of the count where the larger share costs less
-// than that (300 binary64 items with 7 draw workgroups: 111 us without, 104 with).
+// than that (300 binary64 items with 7 draw workgroups took 111 us without, 104 with).
 // price: what the cut's sums cost, in pairs.
 constexpr int64_t kCutPrice = 8;
+// bytes of a workgroup's two slots
+static int64_t welch_slots_bytes(const DevCfg& d) {
+  return 2 * d.Fw * int64_t(d.precision == 2 ? sizeof(PairSum) : sizeof(double));
+}
 static WelchCut welch_cut(const gw_ctx* c, int64_t items, int64_t K, int64_t part_bytes, int64_t n_draw,
                           int64_t price = kCutPrice) {
   const DevCfg& d = c->dc;
@@ -748,7 +754,7 @@ static WelchCut welch_cut(const gw_ctx* c, int64_t items, int64_t K, int64_t par
   // workgroups per CU: registers allow 3 waves per SIMD (binary64 transforms: 2)
   const int64_t waves = d.precision == 2 ? 2 : 3;
   const int64_t places = c->n_cu * (waves * 4 / (d.L / 1024));
-  int64_t slots = std::min(places, part_bytes / (2 * d.Fw * int64_t(sizeof(double))));
+  int64_t slots = std::min(places, part_bytes / welch_slots_bytes(d));
   if (slots + n_draw > places && n_draw < places &&
       double(total) * double(slots + n_draw - places) < 3.0 * double(slots) * double(places - n_draw))
     slots = places - n_draw;
@@ -765,7 +771,7 @@ static WelchCut welch_cut(const gw_ctx* c, int64_t items, int64_t K, int64_t par
 // bytes of the sums of `items` stretches of K segments
 static int64_t ws_cut_bytes(const gw_ctx* c, int64_t items, int64_t K, int64_t n_draw, int64_t price = kCutPrice) {
   const WelchCut cut = welch_cut(c, items, K, INT64_MAX, n_draw, price);
-  return cut.whole() ? 0 : 2 * int64_t(cut.G) * c->dc.Fw * int64_t(sizeof(double));
+  return cut.whole() ? 0 : int64_t(cut.G) * welch_slots_bytes(c->dc);
 }
 
 // dispatch a k_window instantiation on the window FFT size and radix order
@@ -826,14 +832,10 @@ static void launch_welch_occ(const DevCfg& d, const WelchArgs& a, hipStream_t st
   }
 }
 
-// binary64 transforms: one radix order, occupancy as the registers allow
-template <class T, class ACC>
-static void launch_welch(const DevCfg& d, const WelchArgs& a, hipStream_t stream) {
-  if constexpr (sizeof(T) == 8) launch_welch_occ<T, ACC, 2>(d, a, stream);
-  else if (d.occ_welch == 3) launch_welch_occ<T, ACC, 3>(d, a, stream);
-  else launch_welch_occ<T, ACC, 2>(d, a, stream);
-  if (a.cut.whole()) return;
-  const ACC* part = static_cast<const ACC*>(a.part);
+// the launch that adds the sums of a launch's cut items
+template <class Sum>
+static void launch_welch_sums(const DevCfg& d, const WelchArgs& a, hipStream_t stream) {
+  const Sum* part = static_cast<const Sum*>(a.part);
   // items of many pieces are few: a workgroup row per item, else per boundary
   const int64_t items = (int64_t(a.cut.G) * a.cut.q + a.cut.r) / a.cut.np;
   if (items * 8 <= a.cut.G) {
@@ -842,14 +844,25 @@ static void launch_welch(const DevCfg& d, const WelchArgs& a, hipStream_t stream
     // items of 12 pieces: 6.4 us with eight, 4.9 with two; 3 of 256: 6.5 with eight)
     if (items * 24 <= a.cut.G) {
       const dim3 grid(unsigned((d.Fw + 31) / 32), unsigned(items));
-      hipLaunchKernelGGL((k_welch_sum_many<ACC, 8>), grid, dim3(256), 0, stream, a.cut, part, d.Fw, a.norm, a.psd);
+      hipLaunchKernelGGL((k_welch_sum_many<Sum, 8>), grid, dim3(256), 0, stream, a.cut, part, d.Fw, a.norm, a.psd);
     } else {
       const dim3 grid(unsigned((d.Fw + 127) / 128), unsigned(items));
-      hipLaunchKernelGGL((k_welch_sum_many<ACC, 2>), grid, dim3(256), 0, stream, a.cut, part, d.Fw, a.norm, a.psd);
+      hipLaunchKernelGGL((k_welch_sum_many<Sum, 2>), grid, dim3(256), 0, stream, a.cut, part, d.Fw, a.norm, a.psd);
     }
   } else {
     const dim3 grid(unsigned((d.Fw + 255) / 256), unsigned(a.cut.G - 1));
-    hipLaunchKernelGGL((k_welch_sum<ACC>), grid, dim3(256), 0, stream, a.cut, part, d.Fw, a.norm, a.psd);
+    hipLaunchKernelGGL((k_welch_sum<Sum>), grid, dim3(256), 0, stream, a.cut, part, d.Fw, a.norm, a.psd);
+  }
+}
+
+// binary64 transforms: one radix order, occupancy as the registers allow
+template <class T, class ACC>
+static void launch_welch(const DevCfg& d, const WelchArgs& a, hipStream_t stream) {
+  if constexpr (sizeof(T) == 8) launch_welch_occ<T, ACC, 2>(d, a, stream);
+  else if (d.occ_welch == 3) launch_welch_occ<T, ACC, 3>(d, a, stream);
+  else launch_welch_occ<T, ACC, 2>(d, a, stream);
+  if constexpr (sizeof(ACC) == 8) {  // binary32 sums are never cut
+    if (!a.cut.whole()) launch_welch_sums<std::conditional_t<sizeof(T) == 8, PairSum, ACC>>(d, a, stream);
   }
 }
 
