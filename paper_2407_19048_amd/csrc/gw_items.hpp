@@ -158,27 +158,29 @@ template <class T> __device__ __forceinline__ T psd_at(const DevCfg& cf, const f
   return fma_t(t, T(s[1]), fma_t(-t, T(s[0]), T(s[0])));
 }
 
-// 1/sqrt(S) for a kept bin's PSD value S; sets status bits.
+// Whitening factor 1/sqrt(fs S/2) for a kept bin's PSD value S; sets status
+// bits.  (The root is taken of fs S/2 and not of S: the hardware's reads a
+// subnormal argument as zero.)
 template <class T>
-__device__ __forceinline__ T psd_gain(T S, bool kept, uint32_t& flag) {
+__device__ __forceinline__ T psd_gain(const DevCfg& cf, T S, bool kept, uint32_t& flag) {
   const bool good = S > T(0) && S < T(INFINITY);
   if (kept && !good) flag |= isfinite(S) ? GW_STATUS_NONPOSITIVE_PSD : GW_STATUS_NONFINITE_PSD;
-  return kept && good ? rsqrt_t(S) : T(0);
+  return kept && good ? rsqrt_t(T(cf.fs) * T(0.5) * S) : T(0);
 }
 
-// Whitening factors times sqrt(fs/2) of bins k and NC - k, k in [0, NC/2].
+// Whitening factors of bins k and NC - k, k in [0, NC/2].
 template <class T>
 __device__ __forceinline__ void psd_gains(const DevCfg& cf, const PsdAround& q, int k, int NC, uint32_t& flag, T* gk, T* gm) {
   const bool inner = k != 0;  // bins 0 and NC are dropped
-  *gk = psd_gain<T>(psd_at<T>(cf, q.lo, k), inner && k >= cf.kmin, flag);
-  *gm = psd_gain<T>(psd_at<T>(cf, q.hi, NC - k), inner && NC - k >= cf.kmin, flag);
+  *gk = psd_gain<T>(cf, psd_at<T>(cf, q.lo, k), inner && k >= cf.kmin, flag);
+  *gm = psd_gain<T>(cf, psd_at<T>(cf, q.hi, NC - k), inner && NC - k >= cf.kmin, flag);
 }
 
 // Whitening factor for window bin k in [0, N/2] (zero outside the kept band).
 template <class T>
 __device__ __forceinline__ T whiten_gain(const DevCfg& cf, const float* psd, int k, int NC, uint32_t& flag) {
   const T S = psd_at<T>(cf, psd + psd_index(cf, k, NC), k);
-  return psd_gain<T>(S, k > 0 && k < NC && k >= cf.kmin, flag) * rsqrt_t(T(cf.fs) * T(0.5));
+  return psd_gain<T>(cf, S, k > 0 && k < NC && k >= cf.kmin, flag);
 }
 
 // Gain g = filt[k] of a precomputed whitening filter; sets status bits.
@@ -211,12 +213,9 @@ __device__ __forceinline__ void repack_pair(cpx<T> Xk, T gk, cpx<T> Xm, T gm, cp
   *zm = {fma_t(T(2), px, -zk->x), fma_t(T(-2), py, zk->y)};
 }
 
-// What unpack_pair, psd_gains and repack_pair leave out of a whitened window,
-// applied where it is stored: 1/2 each for the two packings, sqrt(2/fs) and
-// the inverse transform's 1/NC.
-template <class T> __device__ __forceinline__ T whitened_scale(const DevCfg& cf, int NC) {
-  return T(0.25) * rsqrt_t(T(cf.fs) * T(0.5)) / T(NC);
-}
+// What unpack_pair and repack_pair leave out of a whitened window, applied where
+// it is stored: 1/2 each for the two packings and the inverse transform's 1/NC.
+template <class T> __device__ __forceinline__ T whitened_scale(int NC) { return T(0.25) / T(NC); }
 
 // The detector's projection of one item: the signal is added to twice the
 // spectrum, so the antenna factors carry 2 fs.
@@ -530,7 +529,7 @@ __device__ __forceinline__ void window_item(const DevCfg& cf, const WinArgs& a, 
     lds_barrier();
   }
   block_fft<T, NC, +1, !kOwn, ORD>(v, sre, sim, fresh_lane(t), PassTwiddle<T, NC, ORD>{opaque(twtab)});
-  const T sc = SRC == 2 ? T(0.5) / T(NC) : SRC == 4 ? T(0.25) / T(NC) : whitened_scale<T>(cf, NC);
+  const T sc = SRC == 2 ? T(0.5) / T(NC) : whitened_scale<T>(NC);
   if (active) {
 #pragma unroll
     for (int e = 0; e < 16; ++e) {

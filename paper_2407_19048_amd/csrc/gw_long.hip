@@ -135,7 +135,7 @@ __global__ __launch_bounds__(256) void k_long_cols_inv(LongArgs a) {
     v[k2] = k2 ? twmul<+1>(u, twc[k2 * N1 + m1]) : u;
   }
   dft_small<N2, +1>(v);
-  const float sc = SRC == 2 ? 0.5f / float(a.NC) : whitened_scale<float>(a.w.cf, a.NC);
+  const float sc = SRC == 2 ? 0.5f / float(a.NC) : whitened_scale<float>(a.NC);
   const float* nz = nullptr;
   if constexpr (SRC == 2) nz = long_input<2>(a, bd);
 #pragma unroll
