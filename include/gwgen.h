@@ -425,13 +425,13 @@ gw_status gw_ragged_graph_create(gw_ragged* r, uint64_t seed, uint64_t first_bat
 gw_status gw_ragged_set_tuning(gw_ragged* r, int32_t key, int64_t value);
 gw_status gw_ragged_get_tuning(const gw_ragged* r, int32_t key, int64_t* value);
 /* Autotuner of the ragged stages (synchronous, private stream): times the
- * Welch stage over radix order x grid {1, 2, 4 per CU} in mode 0 and radix
+ * Welch stage over radix order x grid {1, 2, 3, 4 per CU} in mode 0 and radix
  * order in mode 1, and the window stage over issue mode x radix order,
  * `reps` launches each, in three interleaved rounds, and keeps the fastest.
  * report (host double [12], nullable): the best round's mean ms of Welch
  * mode 0 (order 0, grid 1, 2, 4), (order 1, grid 1, 2, 4), then window
  * (mode 0, order 0), (0, 1), (1, 0), (1, 1), then Welch mode 1 (order 0),
- * (order 1).  Overwrites out and workspace. */
+ * (order 1); grid 3, the default, has no entry.  Overwrites out and workspace. */
 gw_status gw_ragged_autotune(gw_ragged* r, const float* const* bg, const int64_t* L_bg,
                              float* out, void* workspace, int64_t workspace_bytes,
                              int32_t reps, double* report);

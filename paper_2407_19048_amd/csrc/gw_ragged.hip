@@ -867,9 +867,11 @@ gw_status gw_ragged_autotune(gw_ragged* r, const float* const* bg, const int64_t
   if (hipStreamCreateWithFlags(&st, hipStreamNonBlocking) != hipSuccess) return rfail(r, GW_EHIP, "hipStreamCreate");
   hipEvent_t e0 = nullptr, e1 = nullptr;
   const int saved[6] = {r->ord_welch, r->grid_welch, r->ord_win, r->grid_win, r->win_mode, r->welch_mode};
-  const int grids[3] = {1, 2, 4};
-  double ms[12];
-  std::fill(ms, ms + 12, 1e300);  // best of kTuneRounds interleaved rounds
+  // the report's grids, then the default, which has no place in it
+  const int grids[4] = {1, 2, 4, 3};
+  double ms[14];  // [0, 12) the report, [12, 14) grid 3 in both radix orders
+  std::fill(ms, ms + 14, 1e300);  // best of kTuneRounds interleaved rounds
+  auto slot = [](int o, int gi) { return gi < 3 ? o * 3 + gi : 12 + o; };
   auto time_stage = [&](int stage, double* res) {
     for (int k = 0; k < reps && s == GW_OK; ++k)  // untimed: the clock settles
       s = enqueue_ragged(r, 1, 0, false, bg, L_bg, span, out, nullptr, nullptr, workspace, workspace_bytes, stage, st);
@@ -890,10 +892,10 @@ gw_status gw_ragged_autotune(gw_ragged* r, const float* const* bg, const int64_t
     for (int round = 0; round < kTuneRounds && s == GW_OK; ++round) {
       r->welch_mode = 0;
       for (int o = 0; o < 2 && s == GW_OK; ++o)
-        for (int gi = 0; gi < 3 && s == GW_OK; ++gi) {
+        for (int gi = 0; gi < 4 && s == GW_OK; ++gi) {
           r->ord_welch = o;
           r->grid_welch = grids[gi];
-          time_stage(kStageWelch, &ms[o * 3 + gi]);
+          time_stage(kStageWelch, &ms[slot(o, gi)]);
         }
       r->welch_mode = 1;
       for (int o = 0; o < 2 && s == GW_OK; ++o) {
@@ -910,18 +912,19 @@ gw_status gw_ragged_autotune(gw_ragged* r, const float* const* bg, const int64_t
     }
   }
   if (s == GW_OK) {
-    int best = 0;
-    for (int k = 1; k < 6; ++k)
-      if (ms[k] < ms[best]) best = k;
+    int bo = 0, bg_i = 0;
+    for (int o = 0; o < 2; ++o)
+      for (int gi = 0; gi < 4; ++gi)
+        if (ms[slot(o, gi)] < ms[slot(bo, bg_i)]) bo = o, bg_i = gi;
     const int bc = ms[11] < ms[10] ? 11 : 10;
-    if (ms[bc] < ms[best]) {
+    if (ms[bc] < ms[slot(bo, bg_i)]) {
       r->welch_mode = 1;
       r->ord_welch = bc - 10;
       r->grid_welch = saved[1];
     } else {
       r->welch_mode = 0;
-      r->ord_welch = best / 3;
-      r->grid_welch = grids[best % 3];
+      r->ord_welch = bo;
+      r->grid_welch = grids[bg_i];
     }
     int bw = 6;
     for (int k = 7; k < 10; ++k)

@@ -638,7 +638,8 @@ class Ragged:
         return v.value
 
     def autotune(self, bgs, out, workspace, reps=3):
-        """Pick radix orders, the Welch issue mode and grid; returns the timing table [ms]."""
+        """Pick radix orders, the Welch issue mode and grid; returns the timing table [ms] (grid 3, the default, is
+        timed too and has no entry)."""
         nbytes = self._common(out, workspace, None, None)
         ptrs, lens = self._bg_arrays(bgs)
         rep = (ctypes.c_double * 12)()
