@@ -232,7 +232,7 @@ __device__ __forceinline__ cpx<T> burst_bin(const DevCfg& cf, const WfScalars& w
   const double f = double(k) * cf.invT;
   const T xm = T(f - w.sg_f0), xp = T(f + w.sg_f0);
   const T gm = exp(-T(w.sg_pt2) * xm * xm), gp = exp(-T(w.sg_pt2) * xp * xp);
-  const TP base = frac1(TP(k) * TP(pr.tauT));
+  const TP base = frac_product(TP(k), TP(pr.tauT));
   T sm, cm, sp, cp;
   sincos_rev(T(frac1(base - TP(w.sg_rphi))), &sm, &cm);
   sincos_rev(T(frac1(base + TP(w.sg_rphi))), &sp, &cp);

@@ -26,6 +26,11 @@ __device__ __forceinline__ double fma_t(double a, double b, double c) { return _
 // frac(x) in [0, 1)
 __device__ __forceinline__ float frac1(float x) { return __builtin_amdgcn_fractf(x); }
 __device__ __forceinline__ double frac1(double x) { return __builtin_amdgcn_fract(x); }
+// frac(a b), in binary32 of the exact product (within a rounding of [0, 1)):
+// rounded first, a product of some thousand revolutions has lost 12 of its
+// fraction's bits
+__device__ __forceinline__ float frac_product(float a, float b) { return fma_t(a, b, -floorf(a * b)); }
+__device__ __forceinline__ double frac_product(double a, double b) { return frac1(a * b); }
 
 // precision-generic math
 __device__ __forceinline__ void sincospi_t(float x, float* s, float* c) { sincospif(x, s, c); }

@@ -145,7 +145,7 @@ __global__ __launch_bounds__(256) void k_project(ProjArgs a) {
   const float2 hp = reinterpret_cast<const float2*>(a.hp)[b * F + k];
   const float2 hc = reinterpret_cast<const float2*>(a.hc)[b * F + k];
   for (int d = 0; d < D; ++d) {
-    const TP rev = frac1(TP(k) * TP(ds[d].tau * a.cf.invT));
+    const TP rev = frac_product(TP(k), TP(ds[d].tau * a.cf.invT));
     float s, c;
     sincos_rev(float(rev), &s, &c);
     const float fp = float(ds[d].fp), fx = float(ds[d].fx), fs = float(a.cf.fs);
