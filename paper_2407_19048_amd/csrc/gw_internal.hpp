@@ -3,9 +3,9 @@
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <cstring>
 #include <functional>
 #include <string>
-#include <type_traits>
 #include <vector>
 
 #include "gw_fft.hpp"
@@ -60,32 +60,39 @@ gw_status capture_graph(const std::function<gw_status(hipStream_t)>& enqueue, ui
 // Long windows' table entry of a bin: ln(k)/3 and k^(-5/3) (both 0 at k = 0).
 struct alignas(16) BinTab { double lk = 0.0, k53 = 0.0; };
 
-// {c, t} with c (1 + i t) closest to the unit vector at the angle -2 pi num / den,
-// 0 <= num <= den / 2: t the rounded tangent or one of its neighbours, c the
-// rounded best factor to it.  With cosine and tangent rounded by themselves a
-// twiddle's modulus had up to twice the rounding error, which a PSD does not
-// average over its segments: 7.3e-8 of a PSD's norm at 4096 points, 4.7e-8 so.
-// At the quarter turn, where the tangent has no value, c is 2^-28 (binary32) or
-// 2^-56: a quarter of a unit in the last place of the sine, and still far from
-// overflow when a value is multiplied by the tangent.
+// {cosine, tangent} of the angle -2 pi num / den, 0 <= num <= den / 2.  In
+// binary32 they are rounded as a pair, {c, t} with c (1 + i t) closest to the
+// twiddle: t the rounded tangent or one of its neighbours, c the rounded best
+// factor to it.  Rounded by themselves they left a twiddle's modulus up to
+// twice the rounding error, which a PSD does not average over its segments:
+// 7.3e-8 of a PSD's norm at 4096 points, 4.7e-8 so.
+// At the quarter turn, where the tangent has no value, the cosine is set to
+// 2^-28 (binary32) or 2^-56: a quarter of a unit in the last place of the sine,
+// and still far from overflow when a value is multiplied by the tangent.
 template <class T>
 inline cpx<T> tan_twiddle(int64_t num, int64_t den) {
   if (4 * num == den) {
     const T tiny = sizeof(T) == 4 ? T(0x1p-28) : T(0x1p-56);
     return {tiny, T(-1) / tiny};
   }
-  using W = std::conditional_t<sizeof(T) == 4, double, long double>;
-  const W ang = W(-2) * W(3.14159265358979323846264338327950288L) * W(num) / W(den);
-  const W cs = std::cos(ang), sn = std::sin(ang);
-  const T t0 = T(sn / cs);
-  cpx<T> best = {};
-  W least = 4;
-  for (const T t : {t0, std::nextafter(t0, T(-INFINITY)), std::nextafter(t0, T(INFINITY))}) {
-    const T c = T((cs + sn * W(t)) / (W(1) + W(t) * W(t)));
-    const W dx = W(c) - cs, dy = W(c) * W(t) - sn, e = dx * dx + dy * dy;
-    if (e < least) {
-      least = e;
-      best = {c, t};
+  double sn, cs;
+  ::sincos(-2.0 * M_PI * double(num) / double(den), &sn, &cs);
+  const double tn = sn / cs;
+  cpx<T> best = {T(cs), T(tn)};
+  if constexpr (sizeof(T) == 4) {
+    uint32_t bits;
+    std::memcpy(&bits, &best.y, 4);
+    double least = 4.0;
+    for (const uint32_t b : {bits, bits - 1, bits + 1}) {  // (below 0 a NaN, which is no less)
+      float t;
+      std::memcpy(&t, &b, 4);
+      // (cs + sn t) / (1 + t^2), to the first order in t - tn
+      const float c = float(cs - cs * cs * sn * (t - tn));
+      const double dx = c - cs, dy = double(c) * t - sn, e = dx * dx + dy * dy;
+      if (e < least) {
+        least = e;
+        best = {c, t};
+      }
     }
   }
   return best;
