@@ -30,7 +30,9 @@
  *   - Strain is in units of 2^70 x dimensionless strain.  This exact power of
  *     two keeps PSD values inside binary32 range.  The PSD is in
  *     (2^70)^2 / Hz.  The whitened output is dimensionless and does not depend
- *     on the scale.
+ *     on the scale.  Binary32 transforms (precision 0 and 1) stay finite for
+ *     window spectra and whitened spectra up to 2^114 (2e34); Welch's squares
+ *     overflow, and flag the PSD, from spectra of 2^63 on.
  *   - Complex arrays are interleaved (re, im) binary32 pairs.
  */
 #ifndef GWGEN_H

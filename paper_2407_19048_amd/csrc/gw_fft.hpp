@@ -218,9 +218,17 @@ __device__ __forceinline__ void bfly(cpx<T> e, cpx<T> o, cpx<T> w, cpx<T>& s, cp
   }
 }
 
+// The same with w = {cosine, sine}: eight, and no pole at the quarter turn.
+template <int DIR, class T>
+__device__ __forceinline__ void bfly_sine(cpx<T> e, cpx<T> o, cpx<T> w, cpx<T>& s, cpx<T>& d) {
+  const T sn = DIR < 0 ? w.y : -w.y;
+  s = {fma_t(-sn, o.y, fma_t(w.x, o.x, e.x)), fma_t(sn, o.x, fma_t(w.x, o.y, e.y))};
+  d = {fma_t(sn, o.y, fma_t(-w.x, o.x, e.x)), fma_t(-sn, o.x, fma_t(-w.x, o.y, e.y))};
+}
+
 // Stage of DFT length LEN of the radix-R DFT below: butterflies of the pairs
 // (q, q + LEN/2) of every run of LEN elements.
-template <int R, int LEN, int DIR, bool TW, class T>
+template <int R, int LEN, int DIR, bool TW, bool SINE, class T>
 __device__ __forceinline__ void dit_stage(cpx<T>* b, const cpx<T>* w) {
 #pragma unroll
   for (int g = 0; g < R; g += LEN)
@@ -230,7 +238,9 @@ __device__ __forceinline__ void dit_stage(cpx<T>* b, const cpx<T>* w) {
       const int qq = rot ? q - LEN / 4 : q;
       const cpx<T> e = b[g + q], o = b[g + q + LEN / 2];
       cpx<T>&s = b[g + q], &d = b[g + q + LEN / 2];
-      if constexpr (TW) {
+      if constexpr (TW && SINE && LEN == 2) {
+        bfly_sine<DIR>(e, o, w[0], s, d);
+      } else if constexpr (TW) {
         const cpx<T> ww = w[LEN == 2 ? 0 : LEN / 4 + qq];
         if (rot) bfly<DIR, true>(e, o, ww, s, d);
         else bfly<DIR, false>(e, o, ww, s, d);
@@ -257,19 +267,19 @@ template <int R> __host__ __device__ constexpr int bit_reverse(int i) {
 // the stage of length LEN needs the twiddles W^(R/LEN) exp(-2 pi i q / LEN),
 // of which those with q >= LEN/4 are -i times the others, so that a radix-R
 // pass has R/2 distinct ones: w[0] for LEN = 2, w[LEN/4 + q] above, each as
-// {cosine, tangent}.  A radix-16 pass with its twiddles is 192 fused
+// {cosine, tangent} (SINE: w[0] as {cosine, sine}).  A radix-16 pass with its twiddles is 192 fused
 // multiply-adds, against 60 for multiplying 15 inputs by their twiddles plus
 // 160 for a 4 x 4 DFT, and keeps 8 twiddles instead of 15.  A butterfly output
 // takes two roundings instead of three, and the twiddles are rounded as pairs
 // (see tan_twiddle): 1.18e-7 of a spectrum's norm at 4096 points.
-template <int R, int DIR, bool TW, class T> __device__ __forceinline__ void dit_fft(cpx<T>* a, const cpx<T>* w) {
+template <int R, int DIR, bool TW, bool SINE, class T> __device__ __forceinline__ void dit_fft(cpx<T>* a, const cpx<T>* w) {
   cpx<T> b[R];
 #pragma unroll
   for (int i = 0; i < R; ++i) b[i] = a[bit_reverse<R>(i)];
-  dit_stage<R, 2, DIR, TW>(b, w);
-  if constexpr (R >= 4) dit_stage<R, 4, DIR, TW>(b, w);
-  if constexpr (R >= 8) dit_stage<R, 8, DIR, TW>(b, w);
-  if constexpr (R >= 16) dit_stage<R, 16, DIR, TW>(b, w);
+  dit_stage<R, 2, DIR, TW, SINE>(b, w);
+  if constexpr (R >= 4) dit_stage<R, 4, DIR, TW, SINE>(b, w);
+  if constexpr (R >= 8) dit_stage<R, 8, DIR, TW, SINE>(b, w);
+  if constexpr (R >= 16) dit_stage<R, 16, DIR, TW, SINE>(b, w);
 #pragma unroll
   for (int i = 0; i < R; ++i) a[i] = b[i];
 }
@@ -344,9 +354,19 @@ template <int NC, int ORD> struct PlanTw {
   static constexpr int offset = ORD == 0 ? 0 : PlanTw<NC, 0>::size;
 };
 
+// Tables for other transforms than Welch's hold the twiddle of a pass's first
+// stage as {cosine, sine} in binary32.  There the pole's tangent, 2^28, would
+// bound the data at 2^100 (spectra of windows with samples of 1e28 overflowed);
+// now the largest tangent, NC/6, does.  Welch's squares overflow far below
+// that, and binary64 has the range.  Two multiply-adds more in each butterfly
+// of that stage: 2048 samples with a run filter take 280 us, 275 without.
+// (2 e - s as the second output has six and no pole either, but its error is
+// that of the larger output: coloured noise came out 5 % less accurate.)
+template <class T> constexpr bool kSineTable = sizeof(T) == 4;
+
 // The 8 twiddles of a thread's 16/R butterflies in pass PASS.
 template <class T, int NC, int ORD> struct PassTwiddle {
-  static constexpr bool kLate = false;
+  static constexpr bool kLate = false, kSine = kSineTable<T>;
   const cpx<T>* __restrict__ tab;  // tables of both orders
   template <int PASS> struct Regs { cpx<T> w[8]; };
   template <int PASS> __device__ __forceinline__ Regs<PASS> load(int t) const {
@@ -369,9 +389,10 @@ template <class T, int NC, int ORD> struct PassTwiddle {
   }
 };
 
-// All passes' twiddles held in registers (many transforms per thread).
+// All passes' twiddles held in registers (many transforms per thread).  (Welch's,
+// from a table without sines.)
 template <class T, int NC, int ORD> struct HeldTwiddle {
-  static constexpr bool kLate = false;
+  static constexpr bool kLate = false, kSine = false;
   using Src = PassTwiddle<T, NC, ORD>;
   typename Src::template Regs<1> w1;
   typename Src::template Regs<2> w2;
@@ -393,7 +414,7 @@ template <class T, int NC, int ORD> struct HeldTwiddle {
 // of it, when that pass's own are dead (see block_fft): a binary64 transform
 // whose thread also holds sums has no registers for two passes' twiddles.
 template <class T, int NC, int ORD> struct LateTwiddle {
-  static constexpr bool kLate = true;
+  static constexpr bool kLate = true, kSine = false;
   const cpx<T>* tab;
   __device__ __forceinline__ void init(const cpx<T>* tab_, int) { tab = tab_; }
   template <int PASS> __device__ __forceinline__ auto load(int t) const {
@@ -408,7 +429,7 @@ template <class T, int NC, int ORD> struct LateTwiddle {
 // without READing.  w: the pass's 8 twiddles (unused in pass 0).  after() is
 // called between the pass's arithmetic and its writes.
 struct Nothing { __device__ __forceinline__ void operator()() const {} };
-template <class T, int NC, int PASS, int DIR, bool READ, bool WRITE, int ORD, class After = Nothing>
+template <class T, int NC, int PASS, int DIR, bool READ, bool WRITE, int ORD, bool SINE, class After = Nothing>
 __device__ __forceinline__ void fft_pass(cpx<T>* v, T* sre, T* sim, int t, const cpx<T>* w, After after = {}) {
   constexpr int R = PassInfo<NC, PASS, ORD>::R, NS = PassInfo<NC, PASS, ORD>::NS;
   constexpr int NT = NC / 16, NB = 16 / R, STRIDE = NC / R;
@@ -427,7 +448,7 @@ __device__ __forceinline__ void fft_pass(cpx<T>* v, T* sre, T* sim, int t, const
     }
   }
 #pragma unroll
-  for (int m = 0; m < NB; ++m) dit_fft<R, DIR, (NS > 1)>(v + m * R, w + m * (R / 2));
+  for (int m = 0; m < NB; ++m) dit_fft<R, DIR, (NS > 1), SINE>(v + m * R, w + m * (R / 2));
   after();
   if constexpr (WRITE) {
     if constexpr (READ) lds_barrier();
@@ -462,24 +483,24 @@ __device__ __forceinline__ void block_fft(cpx<T>* v, T* sre, T* sim, int t, cons
     using Src = PassTwiddle<T, NC, ORD>;
     typename Src::template Regs<1> w1;
     typename Src::template Regs<2> w2;
-    fft_pass<T, NC, 0, DIR, FIRST_FROM_LDS, true, ORD>(v, sre, sim, t, nullptr,
+    fft_pass<T, NC, 0, DIR, FIRST_FROM_LDS, true, ORD, TW::kSine>(v, sre, sim, t, nullptr,
                                                        [&]() { w1 = tw.template load<1>(t); });
-    fft_pass<T, NC, 1, DIR, true, true, ORD>(v, sre, sim, t, w1.w, [&]() {
+    fft_pass<T, NC, 1, DIR, true, true, ORD, TW::kSine>(v, sre, sim, t, w1.w, [&]() {
       w2 = tw.template load<2>(t);
       ahead();
     });
-    fft_pass<T, NC, 2, DIR, true, false, ORD>(v, sre, sim, t, w2.w);
+    fft_pass<T, NC, 2, DIR, true, false, ORD, TW::kSine>(v, sre, sim, t, w2.w);
   } else {
     const auto w1 = tw.template load<1>(t);
-    fft_pass<T, NC, 0, DIR, FIRST_FROM_LDS, true, ORD>(v, sre, sim, t, w1.w);
+    fft_pass<T, NC, 0, DIR, FIRST_FROM_LDS, true, ORD, TW::kSine>(v, sre, sim, t, w1.w);
     const auto w2 = tw.template load<2>(t);
-    fft_pass<T, NC, 1, DIR, true, true, ORD>(v, sre, sim, t, w1.w);
+    fft_pass<T, NC, 1, DIR, true, true, ORD, TW::kSine>(v, sre, sim, t, w1.w);
     if constexpr (FftPlan<NC>::NPASS == 3) {
-      fft_pass<T, NC, 2, DIR, true, false, ORD>(v, sre, sim, t, w2.w);
+      fft_pass<T, NC, 2, DIR, true, false, ORD, TW::kSine>(v, sre, sim, t, w2.w);
     } else {
       const auto w3 = tw.template load<3>(t);
-      fft_pass<T, NC, 2, DIR, true, true, ORD>(v, sre, sim, t, w2.w);
-      fft_pass<T, NC, 3, DIR, true, false, ORD>(v, sre, sim, t, w3.w);
+      fft_pass<T, NC, 2, DIR, true, true, ORD, TW::kSine>(v, sre, sim, t, w2.w);
+      fft_pass<T, NC, 3, DIR, true, false, ORD, TW::kSine>(v, sre, sim, t, w3.w);
     }
   }
 }

@@ -98,8 +98,14 @@ inline cpx<T> tan_twiddle(int64_t num, int64_t den) {
   return best;
 }
 
+template <class T>
+inline cpx<T> sin_twiddle(int64_t num, int64_t den) {
+  const double ang = -2.0 * M_PI * double(num) / double(den);
+  return {T(std::cos(ang)), T(std::sin(ang))};
+}
+
 template <class T, int NC, int ORD, int PASS>
-inline void append_pass_table(std::vector<cpx<T>>& h) {
+inline void append_pass_table(std::vector<cpx<T>>& h, bool sine) {
   if constexpr (PASS < FftPlan<NC>::NPASS) {
     using P = PassTw<NC, PASS, ORD>;
     const size_t at = h.size();
@@ -109,36 +115,38 @@ inline void append_pass_table(std::vector<cpx<T>>& h) {
         for (int q = 0; q < (len >= 4 ? len / 4 : 1); ++q) {
           // W^(R/len) exp(-2 pi i q / len), W = exp(-2 pi i k / (NS R))
           const int i = len == 2 ? 0 : len / 4 + q;
+          const int64_t num = int64_t(k) + int64_t(q) * P::NS, den = int64_t(P::NS) * len;
           h[at + (size_t(i / P::G) * P::NS + k) * P::G + i % P::G] =
-              tan_twiddle<T>(int64_t(k) + int64_t(q) * P::NS, int64_t(P::NS) * len);
+              sine && len == 2 ? sin_twiddle<T>(num, den) : tan_twiddle<T>(num, den);
         }
-    append_pass_table<T, NC, ORD, PASS + 1>(h);
+    append_pass_table<T, NC, ORD, PASS + 1>(h, sine);
   }
 }
 
-// Pass twiddle tables of an nc-point transform (see PassTw), order 0 then 1.
+// Pass twiddle tables of an nc-point transform (see PassTw), order 0 then 1;
+// sine: the first stages' twiddles as sines (see kSineTable).
 template <class T, int NC>
-inline std::vector<cpx<T>> plan_tables_of() {
+inline std::vector<cpx<T>> plan_tables_of(bool sine) {
   std::vector<cpx<T>> h;
-  append_pass_table<T, NC, 0, 1>(h);
-  append_pass_table<T, NC, 1, 1>(h);
+  append_pass_table<T, NC, 0, 1>(h, sine);
+  append_pass_table<T, NC, 1, 1>(h, sine);
   return h;
 }
 template <class T>
-inline std::vector<cpx<T>> plan_tables(int nc) {
+inline std::vector<cpx<T>> plan_tables(int nc, bool sine = kSineTable<T>) {
   switch (nc) {
-    case 1024: return plan_tables_of<T, 1024>();
-    case 2048: return plan_tables_of<T, 2048>();
-    case 4096: return plan_tables_of<T, 4096>();
-    case 8192: return plan_tables_of<T, 8192>();
-    default: return plan_tables_of<T, 16384>();
+    case 1024: return plan_tables_of<T, 1024>(sine);
+    case 2048: return plan_tables_of<T, 2048>(sine);
+    case 4096: return plan_tables_of<T, 4096>(sine);
+    case 8192: return plan_tables_of<T, 8192>(sine);
+    default: return plan_tables_of<T, 16384>(sine);
   }
 }
 
 // The Welch table of L = l (WelchTab): pass twiddles, the window's first half.
 template <class T>
 inline std::vector<cpx<T>> welch_tables(int l) {
-  std::vector<cpx<T>> h = plan_tables<T>(l);
+  std::vector<cpx<T>> h = plan_tables<T>(l, false);
   auto hann = [&](int n) {
     const double sp = std::sin(M_PI * double(n) / double(l));
     return T(sp * sp);
