@@ -75,8 +75,9 @@ __device__ __forceinline__ void draw_sample(const DevCfg& c, uint64_t seed, uint
 #pragma unroll
   for (int r = 0; r < 11; ++r) p[r] = lane_value(mine, r);
   WfScalars w = {};
+  WfModel model;  // (of no use here)
   SkyAngles sky;
-  wf_setup(p, c, lane, w, sky);
+  wf_setup(p, c, lane, w, model, sky);
   if (lane == 0) {
     o.wf[i] = w;
     if (o.status) {

@@ -106,26 +106,33 @@ __device__ __forceinline__ double philox_uniform(uint64_t seed, uint64_t index, 
 }
 
 // ------------------------------------------------------- waveform constants
+// What a sample's bins need (bin_polar), kept per sample in the workspace.  In
+// terms of x = k^(1/3), l = ln(k)/3, the phase in revolutions is
+// below f_t  pconst + k^(-5/3) (cN + x^2 (c2 + x (c3 + x (c4 + x ((c5 + b5 l) + x ((c6 + b6x l) + x c7)))))),
+// above      mr_p0 + mr_p1 k + atan(X)/(2 pi), X = mr_x0 + mr_x1 k, amplitude Ard / (1 + X^2) beyond f_RD
 struct WfScalars {
-  double v1, lnv1;      // v_k = v1 k^(1/3);  ln v_k = lnv1 + ln(k)/3
-  double a[8];          // phase polynomial in revolutions: sum (a_k + b_k ln v) v^(k-5)
-  double b5, b6;
+  double lnv1;          // ln v at bin 1
+  double cN;            // Newtonian phase in revolutions at bin k: cN k^(-5/3)
+  double c2, c3, c4, c5, b5, c6, b6x, c7;
   double pconst;        // (-phi_c - pi/4) / (2 pi)
   double A0T;           // amplitude A(f_k) = A0T k^(-7/6)
-  double mr_b0, mr_b1;  // merger-ringdown phase in revolutions: b0 + b1 f + atan(x)/(2 pi)
-  double f_rd, inv_fdamp;
-  double At, Ard, ft, fdamp2;
-  double Apl;           // At (f_t T)^(2/3): power-law amplitude Apl k^(-2/3) between f_t and f_RD
-  double cN;            // Newtonian phase in revolutions at bin k: cN k^(-5/3)
+  double mr_p0, mr_p1, mr_x0, mr_x1;
+  double Apl, Ard;      // power-law amplitude Apl k^(-2/3) between f_t and f_RD, amplitude at f_RD
   // sine-Gaussian (approximant 2): G(x) = sg_G0 exp(-sg_pt2 x^2), phase phi0 / (2 pi)
   double sg_f0, sg_pt2, sg_G0, sg_rphi;
+  double cosi, tc;
   int kend, kt, krd;    // band end; first bins with f >= f_t and f >= f_RD
   int cut_nyquist;
-  double cosi, tc, ra, dec, psi;
-  // the same phases in terms of x = k^(1/3), what a bin needs (bin_polar):
-  // below f_t  pconst + k^(-5/3) (c0 + x^2 (c2 + x (c3 + x (c4 + x ((c5 + b5 l) + x ((c6 + b6x l) + x c7)))))), l = ln(k)/3
-  // above      mr_p0 + mr_p1 k + atan(X)/(2 pi), X = mr_x0 + mr_x1 k, amplitude Ard / (1 + X^2) beyond f_RD
-  double c0, c2, c3, c4, c5, c6, b6x, c7, mr_p0, mr_p1, mr_x0, mr_x1;
+};
+// A batch's workspace holds them, and one of the size it had with 280 bytes a
+// sample has to be enough.
+static_assert(sizeof(WfScalars) <= 280, "workspaces of earlier sizes are accepted");
+
+// The same model at any frequency (the surrogate's targets).
+struct WfModel {
+  double a[8], b5, b6;  // phase in revolutions below f_t: sum (a_k + b_k ln v) v^(k-5)
+  double mr_b0, mr_b1;  // above: b0 + b1 f + atan((f - f_rd) / f_damp)/(2 pi)
+  double f_rd, inv_fdamp, fdamp2, ft, At, Ard;
 };
 
 // first bin k in [0, kmax] with k/T >= f (k/T formed by a correctly rounded
@@ -198,17 +205,14 @@ struct SkyAngles { double sr, cr, sd, cd, sp, cp; };
 // Waveform constants of one sample from its parameter rows p[0..10] (held by
 // every lane of the group; lane = this lane's place in it).  All lanes return
 // the same values.
-__device__ __forceinline__ void wf_setup(const double* p, const DevCfg& cf, int lane, WfScalars& w, SkyAngles& sky) {
+__device__ __forceinline__ void wf_setup(const double* p, const DevCfg& cf, int lane, WfScalars& w, WfModel& m,
+                                         SkyAngles& sky) {
   // iota, RA, dec, psi: one sine and cosine per lane
-  const double iota = p[5], ra = p[6], dec = p[7], psi = p[8];
-  const double ang = lane == 0 ? iota : lane == 1 ? ra : lane == 2 ? dec : psi;
+  const double ang = lane == 0 ? p[5] : lane == 1 ? p[6] : lane == 2 ? p[7] : p[8];
   double sn, cs;
   sincos(ang, &sn, &cs);
   w.cosi = lane_value(cs, 0);
   sky = {lane_value(sn, 1), lane_value(cs, 1), lane_value(sn, 2), lane_value(cs, 2), lane_value(sn, 3), lane_value(cs, 3)};
-  w.ra = ra;
-  w.dec = dec;
-  w.psi = psi;
   w.tc = p[10];
   if (cf.approximant == 2) {
     // sine-Gaussian: rows 0 f0, 1 Q, 2 hrss, 5 iota, 9 phi0, 10 t0
@@ -240,9 +244,9 @@ __device__ __forceinline__ void wf_setup(const double* p, const DevCfg& cf, int 
   pn_coefficients(eta, q, chi1, chi2, c, lg);
   const double rev = 3.0 / (128.0 * eta) / (2.0 * kPi);
 #pragma unroll
-  for (int k = 0; k < 8; ++k) w.a[k] = rev * c[k];
-  w.b5 = rev * lg[5];
-  w.b6 = rev * lg[6];
+  for (int k = 0; k < 8; ++k) m.a[k] = rev * c[k];
+  m.b5 = w.b5 = rev * lg[5];
+  m.b6 = rev * lg[6];
   w.pconst = (-phic - 0.25 * kPi) / (2.0 * kPi);
   const double A0 = kStrainScale * sqrt(5.0 / 24.0) * pow(kPi, -2.0 / 3.0) * lane_value(pw, 1) / (dl * kMpcSec);
   w.A0T = A0 * lane_value(pw, 2);
@@ -264,28 +268,26 @@ __device__ __forceinline__ void wf_setup(const double* p, const DevCfg& cf, int 
   // v and ln v at bin 1 (lane 0) and at f_t; the band edges one per lane
   const double v = cbrt(kPi * Ms * (lane == 0 ? cf.invT : f_t)), lnv = log(v);
   const int kb = first_bin_at_or_above(lane == 0 ? f_cut : lane == 1 ? f_t : f_rd, cf.T, knyq);
-  w.v1 = lane_value(v, 0);
+  const double v1 = lane_value(v, 0);
   w.lnv1 = lane_value(lnv, 0);
-  w.cN = w.a[0] / (w.v1 * w.v1 * w.v1 * w.v1 * w.v1);
+  w.cN = m.a[0] / (v1 * v1 * v1 * v1 * v1);
   w.kend = lane_value(kb, 0);
   w.cut_nyquist = f_cut > 0.5 * cf.fs ? 1 : 0;
   {
-    const double iv = 1.0 / w.v1, iv2 = iv * iv;
-    w.c0 = w.cN;
-    w.c2 = w.a[2] * iv2 * iv;
-    w.c3 = w.a[3] * iv2;
-    w.c4 = w.a[4] * iv;
-    w.c5 = w.a[5] + w.b5 * w.lnv1;
-    w.c6 = (w.a[6] + w.b6 * w.lnv1) * w.v1;
-    w.b6x = w.b6 * w.v1;
-    w.c7 = w.a[7] * w.v1 * w.v1;
+    const double iv = 1.0 / v1, iv2 = iv * iv;
+    w.c2 = m.a[2] * iv2 * iv;
+    w.c3 = m.a[3] * iv2;
+    w.c4 = m.a[4] * iv;
+    w.c5 = m.a[5] + w.b5 * w.lnv1;
+    w.c6 = (m.a[6] + m.b6 * w.lnv1) * v1;
+    w.b6x = m.b6 * v1;
+    w.c7 = m.a[7] * v1 * v1;
   }
   if (cf.approximant == 0) {
     w.mr_p0 = w.mr_p1 = w.mr_x0 = w.mr_x1 = 0.0;
     w.kt = w.kend;
     w.krd = w.kend;
-    w.mr_b0 = w.mr_b1 = w.f_rd = w.inv_fdamp = 0.0;
-    w.At = w.Ard = w.ft = w.fdamp2 = w.Apl = 0.0;
+    w.Ard = w.Apl = 0.0;
     return;
   }
   double Pt, dPt;
@@ -293,38 +295,40 @@ __device__ __forceinline__ void wf_setup(const double* p, const DevCfg& cf, int 
   const double x_t = (f_t - f_rd) / f_damp;
   const double b1 = dPt - (1.0 / f_damp) / (1.0 + x_t * x_t);
   const double b0 = Pt - b1 * f_t - atan(x_t);
-  w.mr_b0 = b0 / (2.0 * kPi);
-  w.mr_b1 = b1 / (2.0 * kPi);
-  w.f_rd = f_rd;
-  w.inv_fdamp = 1.0 / f_damp;
-  w.mr_p0 = w.mr_b0 + w.pconst;
-  w.mr_p1 = w.mr_b1 * cf.invT;
-  w.mr_x0 = -f_rd * w.inv_fdamp;
-  w.mr_x1 = cf.invT * w.inv_fdamp;
+  m.mr_b0 = b0 / (2.0 * kPi);
+  m.mr_b1 = b1 / (2.0 * kPi);
+  m.f_rd = f_rd;
+  m.inv_fdamp = 1.0 / f_damp;
+  w.mr_p0 = m.mr_b0 + w.pconst;
+  w.mr_p1 = m.mr_b1 * cf.invT;
+  w.mr_x0 = -f_rd * m.inv_fdamp;
+  w.mr_x1 = cf.invT * m.inv_fdamp;
   const double pw2 = pow(lane == 0 ? f_t : lane == 1 ? f_rd / f_t : f_t * cf.T,
                          lane == 0 ? -7.0 / 6.0 : lane == 1 ? -2.0 / 3.0 : 2.0 / 3.0);
-  const double At = A0 * lane_value(pw2, 0);
-  w.At = At;
-  w.Ard = At * lane_value(pw2, 1);
-  w.ft = f_t;
-  w.fdamp2 = f_damp * f_damp;
-  w.Apl = At * lane_value(pw2, 2);
+  m.At = A0 * lane_value(pw2, 0);
+  m.Ard = w.Ard = m.At * lane_value(pw2, 1);
+  m.ft = f_t;
+  m.fdamp2 = f_damp * f_damp;
+  w.Apl = m.At * lane_value(pw2, 2);
   w.kt = min(lane_value(kb, 1), w.kend);
   w.krd = min(lane_value(kb, 2), w.kend);
 }
 
 // The same for column b of params [11 or 12][B], by the first kSetupLanes
-// threads of a workgroup (thread t of them); lane 0 writes w.
+// threads of a workgroup (thread t of them); lane 0 writes w, or the model m.
 __device__ __forceinline__ void wf_setup_column(const double* __restrict__ params, int64_t B, int64_t b,
-                                                const DevCfg& cf, int t, WfScalars* w) {
+                                                const DevCfg& cf, int t, WfScalars* w, WfModel* m = nullptr) {
   const double mine = params[min(t, 10) * B + b];
   double p[11];
 #pragma unroll
   for (int r = 0; r < 11; ++r) p[r] = lane_value(mine, r);
   WfScalars v = {};
+  WfModel vm = {};
   SkyAngles sky;
-  wf_setup(p, cf, t, v, sky);
-  if (t == 0) *w = v;
+  wf_setup(p, cf, t, v, vm, sky);
+  if (t != 0) return;
+  if (w) *w = v;
+  if (m) *m = vm;
 }
 
 // Powers of a bin number.
@@ -346,7 +350,7 @@ __device__ __forceinline__ void bin_polar(const WfScalars& w, int k, const BinPo
     p = fma_t(x, p, TP(w.c4));
     p = fma_t(x, p, TP(w.c3));
     p = fma_t(x, p, TP(w.c2));
-    p = fma_t(x * x, p, TP(w.c0));
+    p = fma_t(x * x, p, TP(w.cN));
     *rev = fma_t(p, TP(t.k53), TP(w.pconst));
     const T kf = T(k);
     *amp = T(w.A0T) * T(t.k53) * (kf * rsqrt_t(kf));

@@ -89,7 +89,7 @@ struct TargetArgs {
 
 // Plain IMR-form model at an arbitrary frequency: intrinsic phase [rad] and
 // amplitude ratio to the Newtonian amplitude.
-__device__ void model_at(const WfScalars& w, double Ms, double f, double* P, double* ratio) {
+__device__ void model_at(const WfModel& w, double Ms, double f, double* P, double* ratio) {
   const double two_pi = 2.0 * kPi;
   if (f < w.ft || w.f_rd == 0.0) {
     const double v = cbrt(kPi * Ms * f), lnv = log(v);
@@ -113,10 +113,10 @@ __device__ void model_at(const WfScalars& w, double Ms, double f, double* P, dou
 }
 
 __global__ __launch_bounds__(256) void k_targets(TargetArgs a) {
-  __shared__ WfScalars w;
+  __shared__ WfModel w;
   __shared__ double Ms_s, eta_s;
   const int64_t b = blockIdx.x;
-  if (threadIdx.x < kSetupLanes) wf_setup_column(a.params, a.B, b, a.cf, threadIdx.x, &w);
+  if (threadIdx.x < kSetupLanes) wf_setup_column(a.params, a.B, b, a.cf, threadIdx.x, nullptr, &w);
   if (threadIdx.x == 0) {
     const double q = a.params[1 * a.B + b], mc = a.params[0 * a.B + b];
     const double eta = q / ((1.0 + q) * (1.0 + q));
