@@ -228,9 +228,10 @@ gw_status gw_generate_batch(gw_ctx* ctx, uint64_t seed, uint64_t batch_index,
  * harnesses that forbid allocation).  Same arguments and results except the
  * workspace: the call uses the library's static device scratch area of
  * GW_SCRATCH_BYTES on the device the context was created on, held until the
- * process ends, and calls no allocator.  B must satisfy
- * gw_workspace_size(B) <= GW_SCRATCH_BYTES (B <= 2600 at 3 detectors with
- * L = 4096), else GW_EINVAL.  Every call on a device shares that device's
+ * process ends, and calls no allocator.  The batch's arrays, which are
+ * gw_workspace_size(B) without its last part (the sums of divided stretches),
+ * must fit into GW_SCRATCH_BYTES (B <= 2680 at 3 detectors with L = 4096), else
+ * GW_EINVAL; stretches are divided as far as the rest has room.  Every call on a device shares that device's
  * area, which keeps the last call's contents: calls that overlap in time on
  * one device (other streams or host threads) race, so serialise them; the
  * parameters and offsets are not readable by the caller (use params_f32). */

@@ -22,9 +22,9 @@ struct gw_ctx {
   void* twr_win = nullptr;    // cpx<T>[N/4 + 1]
   void* tw_welch = nullptr;   // Welch table of L (WelchTab)
   void* tw_long = nullptr;    // cpx<float>[N2][N1]: W_NC^(m1 k2), windows longer than 32768 samples
-  // windows longer than 32768 samples: k^(1/3), ln(k)/3 (double[N/2] each) and
-  // exp(-2 pi i k / N) (cpx<float>[N/2]) for k < N/2, stored at the position
-  // (k mod N2) N1 + k / N2 of bin k in the transposed four-step spectrum
+  // windows longer than 32768 samples: BinTab[N/2] and exp(-2 pi i k / N)
+  // (cpx<float>[N/2]) for k < N/2, stored at the position (k mod N2) N1 + k / N2
+  // of bin k in the transposed four-step spectrum
   void* long_tabs = nullptr;
   int device = 0;             // HIP device the context was created on
   int n_cu = 256;             // its compute units

@@ -43,9 +43,6 @@ __device__ __forceinline__ void sincos_rev(float x, float* s, float* c) {
 }
 __device__ __forceinline__ void sincos_rev(double x, double* s, double* c) { sincospi(2.0 * x, s, c); }
 __device__ __forceinline__ void sincospi_t(double x, double* s, double* c) { sincospi(x, s, c); }
-__device__ __forceinline__ float sinpi_t(float x) { return sinpif(x); }
-__device__ __forceinline__ double sinpi_t(double x) { return sinpi(x); }
-__device__ __forceinline__ float sqrt_t(float x) { return sqrtf(x); }
 __device__ __forceinline__ float rsqrt_t(float x) { return __builtin_amdgcn_rsqf(x); }
 __device__ __forceinline__ double rsqrt_t(double x) { return 1.0 / sqrt(x); }
 // reciprocals: binary32 hardware approximation (about 1 ulp); binary64
@@ -57,9 +54,6 @@ __device__ __forceinline__ double rcp_t(double x) {
   r = fma(r, fma(-x, r, 1.0), r);
   return r;
 }
-__device__ __forceinline__ double sqrt_t(double x) { return sqrt(x); }
-__device__ __forceinline__ float pow_t(float x, float y) { return powf(x, y); }
-__device__ __forceinline__ double pow_t(double x, double y) { return pow(x, y); }
 
 constexpr double kPi = 3.14159265358979323846;
 constexpr double kMsunSec = 4.925490947641267e-6;                 // G Msun / c^3
