@@ -743,6 +743,12 @@ static WelchCut welch_whole(int64_t items, int64_t K) {
 // than that (300 binary64 items with 7 draw workgroups took 111 us without, 104 with).
 // price: what the cut's sums cost, in pairs.
 constexpr int64_t kCutPrice = 8;
+// workgroups that the chip holds: registers allow 3 waves per SIMD (binary64
+// transforms: 2)
+static int64_t welch_places(const gw_ctx* c) {
+  const int64_t waves = c->dc.precision == 2 ? 2 : 3;
+  return c->n_cu * (waves * 4 / (c->dc.L / 1024));
+}
 // bytes of a workgroup's two slots
 static int64_t welch_slots_bytes(const DevCfg& d) {
   return 2 * d.Fw * int64_t(d.precision == 2 ? sizeof(PairSum) : sizeof(double));
@@ -751,9 +757,7 @@ static WelchCut welch_cut(const gw_ctx* c, int64_t items, int64_t K, int64_t par
                           int64_t price = kCutPrice) {
   const DevCfg& d = c->dc;
   const int64_t np = (K + 1) / 2, total = items * np;
-  // workgroups per CU: registers allow 3 waves per SIMD (binary64 transforms: 2)
-  const int64_t waves = d.precision == 2 ? 2 : 3;
-  const int64_t places = c->n_cu * (waves * 4 / (d.L / 1024));
+  const int64_t places = welch_places(c);
   int64_t slots = std::min(places, part_bytes / welch_slots_bytes(d));
   if (slots + n_draw > places && n_draw < places &&
       double(total) * double(slots + n_draw - places) < 3.0 * double(slots) * double(places - n_draw))
@@ -1458,6 +1462,24 @@ static int64_t run_psd_base(const DevCfg& d, int64_t n_chunks) {
   return align256(n_chunks * 8) + align256(n_chunks * d.n_det * int64_t(d.Fw) * 4);
 }
 
+// Whether a run PSD is made in equal shares of each detector's whole stretch
+// or as the mean of the chunks' PSDs.  With less workspace than named there are
+// fewer shares (the least one holds a quarter of the chunks' number of them);
+// the chunks take whole rounds of the places and their mean a thirteenth of a
+// pair's time each, with two more launches of together three pairs: 4 chunks of
+// 32 pairs 257 us in 3 shares and 73 as chunks, 64 of 4 pairs 35 and 30, 256 of
+// them 37 and 87.
+static bool run_in_shares(const gw_ctx* c, int64_t n_chunks, int64_t workspace_bytes) {
+  const DevCfg& d = c->dc;
+  if (n_chunks * d.K * d.n_det >= (int64_t(1) << 31)) return false;
+  if (workspace_bytes >= ws_cut_bytes(c, d.n_det, n_chunks * d.K, 0, kRunCutPrice)) return true;
+  const int64_t places = welch_places(c), np = (n_chunks * d.K + 1) / 2;
+  const int64_t shares = std::max<int64_t>(1, std::min(places, workspace_bytes / welch_slots_bytes(d)));
+  const int64_t rounds = (n_chunks * d.n_det + places - 1) / places;
+  // a stretch that is not cut takes its pairs' time
+  return std::min(np, (d.n_det * np + shares - 1) / shares + kRunCutPrice) < rounds * ((d.K + 1) / 2) + n_chunks / 13 + 3;
+}
+
 gw_status gw_run_psd_workspace_size(const gw_ctx* c, int64_t n_chunks, int64_t* bytes) {
   if (!c || !bytes || n_chunks < 1) return GW_EINVAL;
   *bytes = std::max(run_psd_base(c->dc, n_chunks), ws_cut_bytes(c, c->dc.n_det, n_chunks * c->dc.K, 0, kRunCutPrice));
@@ -1477,12 +1499,8 @@ gw_status gw_run_psd(gw_ctx* c, const float* bg, int64_t L_bg, int64_t n_chunks,
   // With binary64 sums the chunks are one stretch per detector, cut into equal
   // shares: 600 chunks of 63 segments in whole took 131 us (768 workgroups at
   // once, 168 of them idle) and averaging the chunks' PSDs another 51 us.
-  // Binary32 sums (mode 0) stay within a chunk, and so does a call whose
-  // workspace holds fewer shares than a full set: the least one holds a quarter
-  // of the chunks' number, which took 260 us for 4 chunks of 63 segments (77 as
-  // chunks).
-  if (d.precision != 0 && n_chunks * d.K * d.n_det < (int64_t(1) << 31) &&
-      workspace_bytes >= ws_cut_bytes(c, d.n_det, n_chunks * d.K, 0, kRunCutPrice))
+  // Binary32 sums (mode 0) stay within a chunk.
+  if (d.precision != 0 && run_in_shares(c, n_chunks, workspace_bytes))
     return welch_launch(c, bg, L_bg, nullptr, 1, n_chunks * d.K, psd, workspace, workspace_bytes, nullptr, stream,
                         kRunCutPrice);
   int64_t* off = static_cast<int64_t*>(workspace);
