@@ -202,7 +202,9 @@ struct SkyAngles { double sr, cr, sd, cd, sp, cp; };
 __device__ __forceinline__ void wf_setup(const double* p, const DevCfg& cf, int lane, WfScalars& w, WfModel& m,
                                          SkyAngles& sky) {
   // iota, RA, dec, psi: one sine and cosine per lane
-  const double ang = lane == 0 ? p[5] : lane == 1 ? p[6] : lane == 2 ? p[7] : p[8];
+  // (selected as values: a selected element's address would keep p in memory)
+  const double iota = p[5], ra = p[6], dec = p[7], psi = p[8];
+  const double ang = lane == 0 ? iota : lane == 1 ? ra : lane == 2 ? dec : psi;
   double sn, cs;
   sincos(ang, &sn, &cs);
   w.cosi = lane_value(cs, 0);
