@@ -312,13 +312,15 @@ __device__ __forceinline__ void add_signal_surr(const DevCfg& cf, const WinArgs&
 // inverse one and only the upper half of the spectrum, their partners, goes
 // through LDS, as far as registers allow (SRC 5 has none left): a quarter of
 // the exchanges between the transforms were of bins a thread gave itself.
-// 2048 samples with a run filter 278.9 -> 275.7 us.
+// 2048 samples with a run filter 278.9 -> 275.7 us (280 since the transforms'
+// first stages take sines, see kSineTable).
 // Bound by its vector arithmetic, most of it in the pairs' loop: of 820
 // instructions for two pairs, 120 went with the phase and the amplitude from
 // one table of k^(-5/3), products summed as fused steps, the factors common
 // to all bins moved to the store and each PSD neighbour read once as eight
-// bytes.  2048 samples of 3 detectors, N = 16384: 361 us before, 344 now (SRC
-// 1); view pairs of 301 samples 112 and 105; 32 samples, N = 524288, on the path for
+// bytes.  2048 samples of 3 detectors, N = 16384: 361 us before, 344 then (SRC
+// 1; 347 since the gain's root takes fs S/2 and the first stages take sines);
+// view pairs of 301 samples 112 and 105; 32 samples, N = 524288, on the path for
 // long windows (the pairs of k_long_rowpair) 255 and 248.
 template <class T, class TP, bool FULL, int NC, int SRC, int ORD>
 __device__ __forceinline__ void window_item(const DevCfg& cf, const WinArgs& a, int t, int64_t b, int d,

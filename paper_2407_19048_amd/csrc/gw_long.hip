@@ -329,8 +329,9 @@ __global__ __launch_bounds__(256) void k_long_bins(LongArgs a) {
 // round trips through the buffer to save registers.  96 windows of 2^19
 // samples: 248 us with both of these as they were, 222 now, of which the
 // vector arithmetic takes 120 to 145 and the rows' 400 MB 80 (207 since with
-// k^(-5/3) from a table, see bin_powers).  Rows are left
-// unscaled, as the separate row passes leave them.
+// k^(-5/3) from a table, see bin_powers; 210 with sines in the transforms'
+// first stages, see kSineTable).  Rows are left unscaled, as the separate row
+// passes leave them.
 template <int N1, class TP, int SRC>
 __global__ __launch_bounds__(N1 / 16, kRowWaves) void k_long_rowpair(LongArgs a) {
   static_assert(SRC == 0 || SRC == 1, "whiten or fused");
